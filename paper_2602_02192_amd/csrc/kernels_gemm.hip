@@ -551,54 +551,71 @@ struct GemmWide {
   static constexpr int BYTES = X_BYTES > EPI_BYTES ? X_BYTES : EPI_BYTES;
 };
 
-// ---- 256-row tiles with both operands in an LDS ring: batches of 256 rows and more ------------------------------
+// ---- tiles with both operands in an LDS ring: batches of 256 rows and more ------------------------------
 // What caps a large-tile GEMM here is what a compute unit can take in per cycle through its vector memory path, so a
 // workgroup must fetch every operand byte once: 256 weight columns and 256 batch rows per k-step are 16 KB for 2 MFLOP.
 // (A register-streaming form with two row halves fetched every weight block once per row half, 24 KB per k-step, and
-// measured 12 - 25 % slower at 4096 rows.)  Eight wavefronts, two per SIMD, as two row halves x four column pairs; wavefront w
-// fetches weight block w of the tile's eight and its share of the activation chunk, each as one 1 KB load that lands
-// in LDS without passing through registers (global_load_lds, the data of lane l at 16 l); a stage of the ring is one
-// k-step: [8 blocks x 64 units of A operands][2 k8 groups x 256 rows of B operands], 16 KB, eight stages.  Step c
-// issues the loads of k-step c + LA, reads its two A and four B operands from stage c and runs eight MFMAs; before the
-// barrier that ends the step a wavefront waits until its own loads of k-step c + 1 have landed (loads retire in
-// order: all but the youngest LA - 1 k-steps' worth), so after the barrier the whole stage c + 1 is there.  The stage that
-// step c's loads overwrite held k-step c + LA - 8, whose readers passed the barrier of step c + LA - 8 <= c - 1.
+// measured 12 - 25 % slower at 4096 rows.)  WR x WC wavefronts, each NBW weight blocks (32 NBW columns) x 32 MB rows.
+// The weight blocks and the activation chunk of a k-step are fetched as 1 KB loads that land in LDS without passing
+// through registers (global_load_lds, the data of lane l at 16 l), shared out over the wavefronts; a stage of the ring is one
+// k-step: [NB blocks x 64 units of A operands][2 k8 groups x ROWS rows of B operands], eight stages.
+// Step c issues the loads of k-step c + LA, reads the operands of k-step c + 1 from the ring into the registers that k-step
+// c - 1 has left, and runs the MFMAs of k-step c on the registers that the step before filled.  The scheduling barriers
+// lay one operand read behind every MFMA and the ring's loads behind the last of them: without them the compiler reads all
+// operands and waits, and with two wavefronts per SIMD in step with one another nothing covers that wait (4096 rows, gate/up
+// of the 4B / 8B / 32B shapes: 391 / 715 / 1908 us with operands read where they are used, 371 / 685 / 1780 us so).
+// Every second step ends with a barrier, before which a wavefront waits until its own loads of the next three k-steps
+// have landed (loads retire in order: all but the youngest LA - 3 k-steps' worth), so after the barrier of step c (odd) the
+// stages c + 1 .. c + 3 are there, which are what steps c + 1 and c + 2 read ahead.  The stage that step c's loads overwrite
+// held k-step c + LA - 8 <= c - 2, read in step c + LA - 9 <= c - 3, and a barrier lies between any two steps that far apart.
 // The wait is written by hand, together with the barrier: the compiler's own barrier sequence would wait for every
 // outstanding load and empty the ring.  Sums run in the same order as in the other kernels (k ascending in one
-// accumulator), so results are bit-identical.  With WC = 2 the same kernel runs four wavefronts (two row halves x two
-// column pairs) on a 256 x 128 tile, 12 KB per k-step: batches of a few hundred rows, where 256 x 256 tiles are too few
-// to fill the chip (4 - 15 % faster there than the register-streaming form it replaced).
-template <int WCv> struct GemmRingT {   // WC = 4: 256 x 256 tile, eight wavefronts; WC = 2: 256 x 128 tile, four wavefronts
-  static constexpr int WR = 2, WC = WCv, WN = WR * WC, MB = 4, NBW = 2, ROWS = 256, T = WN * 64;
-  static constexpr int AU = WC * NBW * 64, XU = 2 * ROWS, SU = AU + XU;   // 16-byte units of a stage: A operands, B operands
-  static constexpr int XLW = XU / T, LPS = 1 + XLW;                       // activation loads, all loads per wavefront and k-step
-  static constexpr int NS = 8, LA = 6;                                    // stages, k-steps ahead (< NS)
-  static constexpr int TILE_STRIDE = 33, BYTES = NS * SU * 16;            // 128 KB / 96 KB; the epilogue's WN x 32 x 33 floats reuse it
+// accumulator), so results are bit-identical.
+// Forms: 256 x 256 on eight wavefronts where such tiles fill the chip; 256 x 128 on four (12 KB per k-step) for batches of
+// a few hundred rows.
+template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
+  static constexpr int WR = WRv, WC = WCv, WN = WR * WC, MB = MBv, NBW = NBWv, NB = WC * NBW, ROWS = 32 * WR * MB, T = WN * 64;
+  static constexpr int AU = NB * 64, XU = 2 * ROWS, SU = AU + XU;         // 16-byte units of a stage: A operands, B operands
+  static constexpr int ALW = NB / WN, XLW = XU / T, LPS = ALW + XLW;      // weight, activation, all loads per wavefront and k-step
+  static constexpr int NS = 8, LA = 6;                                    // stages, k-steps ahead
+  static constexpr int TILE_STRIDE = 33, BYTES = NS * SU * 16;            // 128 / 96 KB; the epilogue's WN x 32 x 33 floats reuse it
+  static_assert(NB % WN == 0 && XU % T == 0 && WN * 32 * TILE_STRIDE * 4 <= BYTES, "whole loads per wavefront, room for the epilogue");
 };
+using Ring256x256 = GemmRingT<2, 4, 4, 2>;
+using Ring256x128 = GemmRingT<2, 2, 4, 2>;   // 256 rows, 128 columns
 
 __device__ __forceinline__ void load_to_lds(const void *g, void *l) {   // 16 bytes per lane; l is the wavefront's base, lane l lands at l + 16 l
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g, (__attribute__((address_space(3))) void *)l, 16, 0, 0);
 }
 
-template <int EPI, bool ZFAST, int WCv>
-__global__ __launch_bounds__(GemmRingT<WCv>::T) void gemm_ring_kernel(void *out, const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp,
-                                                                int Np, int Kp, int groups_per_split) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  using L = GemmRingT<WCv>;
-  constexpr int MB = L::MB, NBW = L::NBW, ROWS = L::ROWS, NS = L::NS, LA = L::LA, SU = L::SU, WC = L::WC, AU = L::AU, WN = L::WN, LPS = L::LPS;
-  static_assert((GEMM_K_PAD / 16) % NS == 0 && LA < NS && LA >= 1, "a run of k-steps is a whole number of trips round the ring");
-  u32x4v *ring = (u32x4v *)lds_raw;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nblocks = Np >> 5, nz = Mp / ROWS;
-  const int c_lo = blockIdx.y * groups_per_split * NS;
-  const int nchunks = min(Kp >> 4, c_lo + groups_per_split * NS), last = nchunks - 1;
-  const int plane = blockIdx.y;
-  const int bx = ZFAST ? blockIdx.x / nz : blockIdx.x, bz = ZFAST ? blockIdx.x % nz : blockIdx.z;
-  const int nbw = bx * WC * NBW, nb0 = nbw + (w % WC) * NBW, mrow0 = bz * ROWS, wrow = (w / WC) * 32 * MB;
-  const int64_t a_step = w_kstep_stride(Np);
-  // what this wavefront fetches: weight block nbw + w (past the end: the last one again, never stored) and the
+// Which tile a workgroup takes: column strip bx, row block bz, run of k-steps by.  Workgroup i starts on XCD i % 8, so the
+// tiles, numbered by runs of k-steps, then bands of four row blocks, then strips, are dealt to the XCDs in contiguous eighths: the 32
+// tiles that are resident behind one L2 are four row blocks x eight strips, twelve operand blocks instead of up to 40.
+constexpr int RING_BAND = 4;
+__device__ __forceinline__ void ring_tile(int strips, int nz, int *bx, int *by, int *bz) {
+  const int n = gridDim.x, id = blockIdx.x, x = id & 7;
+  const int l = x * (n >> 3) + min(x, n & 7) + (id >> 3), per = strips * nz;
+  *by = l / per;
+  const int rem = l - *by * per, band = rem / (RING_BAND * strips), z0 = band * RING_BAND, in = rem - z0 * strips, nb = min(RING_BAND, nz - z0);
+  *bx = in / nb;
+  *bz = z0 + in % nb;
+}
+
+// Accumulates k-steps c_lo .. c_hi - 1 (a whole number of trips round the ring) of the tile whose first weight block is nbw
+// and whose first row is mrow0.  Ends with a workgroup barrier, after which the ring is free for the epilogue.
+template <class L>
+__device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[L::NBW][L::MB], u32x4v *ring, const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp,
+                                              int Mp, int Kp, int nblocks, int nbw, int mrow0, int c_lo, int c_hi) {
+  constexpr int MB = L::MB, NBW = L::NBW, ROWS = L::ROWS, NS = L::NS, LA = L::LA, SU = L::SU, AU = L::AU, WN = L::WN, WC = L::WC, LPS = L::LPS;
+  static_assert((GEMM_K_PAD / 16) % NS == 0, "a run of k-steps is a whole number of trips round the ring");
+  static_assert(NS == 8 && LA == 6, "the waits and the reuse of a stage are worked out above for these");
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, last = c_hi - 1;
+  const int wrow = (w / WC) * 32 * MB;
+  // what this wavefront fetches: weight blocks nbw + w, + WN .. (past the end: the last one again, never stored) and the
   // runs of 64 units i WN + w of the activation chunk (unit u: k8 group u / ROWS of the k-step, batch row u % ROWS)
-  const h16x8 *a_src = Wp + w_block_base(min(nbw + w, nblocks - 1), Kp) + (lane >> 5) * 32 + (lane & 31);
+  const h16x8 *a_src[L::ALW];
+#pragma unroll
+  for (int i = 0; i < L::ALW; ++i) a_src[i] = Wp + w_block_base(min(nbw + i * WN + w, nblocks - 1), Kp) + lane;
   const u32x4v *x_src[L::XLW];
 #pragma unroll
   for (int i = 0; i < L::XLW; ++i) {
@@ -608,12 +625,19 @@ __global__ __launch_bounds__(GemmRingT<WCv>::T) void gemm_ring_kernel(void *out,
   auto fetch = [&](int st, int c) {
 #pragma unroll
     for (int i = 0; i < L::XLW; ++i) load_to_lds(x_src[i] + (int64_t)(c * 2) * Mp, ring + st * SU + AU + (i * WN + w) * 64);
-    load_to_lds(a_src + (int64_t)c * a_step, ring + st * SU + w * 64);
+#pragma unroll
+    for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i] + (int64_t)c * w_kstep_stride(0), ring + st * SU + (i * WN + w) * 64);
   };
-  // what it reads: its two weight blocks, and the rows of its row half
+  // what it reads: its NBW weight blocks, and its rows
   const u32x4v *a_lds = ring + (w % WC) * NBW * 64 + lane;
   const u32x4v *b_lds = ring + AU + (lane >> 5) * ROWS + wrow + (lane & 31);
-  f32x16 acc[NBW][MB];
+  u32x4v a[2][NBW], b[2][MB];
+  auto read = [&](int set, int st) {
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) a[set][n] = a_lds[st * SU + n * 64];
+#pragma unroll
+    for (int j = 0; j < MB; ++j) b[set][j] = b_lds[st * SU + j * 32];
+  };
 #pragma unroll
   for (int n = 0; n < NBW; ++n)
 #pragma unroll
@@ -622,32 +646,53 @@ __global__ __launch_bounds__(GemmRingT<WCv>::T) void gemm_ring_kernel(void *out,
       for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
 #pragma unroll
   for (int j = 0; j < LA; ++j) fetch(j, min(c_lo + j, last));   // a run has at least NS k-steps
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS * (LA - 1)) : "memory");
-  __syncthreads();
-  for (int c0 = c_lo; c0 < nchunks; c0 += NS) {
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
+  read(0, 0);
+  for (int c0 = c_lo; c0 < c_hi; c0 += NS) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      fetch((s + LA) % NS, min(c0 + s + LA, last));   // past the end: the last k-step again, never read
-      u32x4v a[NBW], b[MB];
-#pragma unroll
-      for (int n = 0; n < NBW; ++n) a[n] = a_lds[s * SU + n * 64];
-#pragma unroll
-      for (int j = 0; j < MB; ++j) b[j] = b_lds[s * SU + j * 32];
+      read((s + 1) & 1, (s + 1) % NS);
+      fetch((s + LA) % NS, min(c0 + s + LA, last));   // past the end: the last k-step again, never used
 #pragma unroll
       for (int j = 0; j < MB; ++j)
 #pragma unroll
-        for (int n = 0; n < NBW; ++n) acc[n][j] = mfma_h16(__builtin_bit_cast(h16x8, a[n]), __builtin_bit_cast(h16x8, b[j]), acc[n][j]);
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPS * (LA - 1)) : "memory");
+        for (int n = 0; n < NBW; ++n)
+          acc[n][j] = mfma_h16(__builtin_bit_cast(h16x8, a[s & 1][n]), __builtin_bit_cast(h16x8, b[s & 1][j]), acc[n][j]);
+#pragma unroll
+      for (int q = 0; q < NBW + MB; ++q) {   // MFMA, LDS read, MFMA, LDS read, ...
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, LPS, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, NBW * MB, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (s & 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the end have landed before the ring is reused
   __syncthreads();
+}
+
+// grid strips * (Mp / ROWS) * runs of k-steps, see ring_tile; groups_per_split groups of eight k-steps per run.
+template <class L, int EPI>
+__global__ __launch_bounds__(L::T) void gemm_ring_kernel(void *out, const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np, int Kp,
+                                                         int groups_per_split, int strips) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  constexpr int MB = L::MB, NBW = L::NBW;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, nblocks = Np >> 5;
+  int bx, by, bz;
+  ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
+  const int c_lo = by * groups_per_split * L::NS, c_hi = min(Kp >> 4, c_lo + groups_per_split * L::NS);
+  const int nbw = bx * L::NB, nb0 = nbw + (w % L::WC) * NBW, mrow0 = bz * L::ROWS, wrow = (w / L::WC) * 32 * MB;
+  f32x16 acc[NBW][MB];
+  ring_mainloop<L>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, nbw, mrow0, c_lo, c_hi);
   const int half = lane >> 5, col = lane & 31;
   if (EPI == EPI_PARTIAL) {   // 32 x 32 tiles transposed through LDS so that every store is a whole 128-byte row segment
     float *tile = (float *)lds_raw + (size_t)w * 32 * L::TILE_STRIDE;
 #pragma unroll
     for (int n = 0; n < NBW; ++n) {
-      float *P = (float *)out + ((int64_t)plane * Mp + mrow0 + wrow) * Np + (nb0 + n) * 32;
+      float *P = (float *)out + ((int64_t)by * Mp + mrow0 + wrow) * Np + (nb0 + n) * 32;
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
 #pragma unroll
@@ -691,18 +736,16 @@ __global__ __launch_bounds__(GemmRingT<WCv>::T) void gemm_ring_kernel(void *out,
   }
 }
 
-template <int EPI, bool ZFAST, int WC = 4>
-static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, hipStream_t st, int nsplit = 1) {
-  using L = GemmRingT<WC>;
+template <class L, int EPI>
+static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int nsplit, hipStream_t st) {
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void *)gemm_ring_kernel<EPI, ZFAST, WC>, hipFuncAttributeMaxDynamicSharedMemorySize, L::BYTES);
+    (void)hipFuncSetAttribute((const void *)gemm_ring_kernel<L, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, L::BYTES);
     attr_set = true;
   }
-  int nblocks = Np / 32, per_wg = L::WC * L::NBW, strips = (nblocks + per_wg - 1) / per_wg, nz = Mp / L::ROWS;
-  int groups = (Kp / 16) / L::NS, gps = (groups + nsplit - 1) / nsplit, ny = (groups + gps - 1) / gps;
-  dim3 grid = ZFAST ? dim3(strips * nz, ny, 1) : dim3(strips, ny, nz);
-  hipLaunchKernelGGL((gemm_ring_kernel<EPI, ZFAST, WC>), grid, dim3(L::T), L::BYTES, st, out, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp, Np, Kp, gps);
+  int strips = (Np / 32 + L::NB - 1) / L::NB, groups = (Kp / 16) / L::NS, gps = (groups + nsplit - 1) / nsplit, ny = (groups + gps - 1) / gps;
+  hipLaunchKernelGGL((gemm_ring_kernel<L, EPI>), dim3(strips * (Mp / L::ROWS) * ny), dim3(L::T), L::BYTES, st, out, (const u32x4v *)Xp,
+                     (const h16x8 *)Wp, Mp, Np, Kp, gps, strips);
 }
 
 // Launch shape.  Up to 128 batch rows the LDS-staged kernel runs: three or four weight blocks per workgroup, and a
@@ -728,7 +771,7 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
   int zblocks = Mp / (32 * mb);
   g->lds = 0; g->stages = 0;
   if (Kp % GEMM_K_PAD == 0 && Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {   // 256 x 256 tiles fill the chip
-    g->lds = 2; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = 1;
+    g->lds = GEMM_RING_256X256; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = 1;
     // One tile per compute unit at a time, so a tile count just above a multiple of 256 leaves most of the chip idle in
     // the last round (320 tiles take two rounds).  Splitting K in two runs makes the units of work half as long and the
     // rounds fill up (320 tiles: 1.5 rounds' worth), at the price of a second plane of fp32 partials written and read
@@ -748,7 +791,7 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     if (ns > groups / 4) ns = groups / 4;
     if (ns > 12) ns = 12;
     if (ns < 1) ns = 1;
-    g->lds = 3; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = fast_gemm_even_split(Kp, ns);
+    g->lds = GEMM_RING_256X128; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = fast_gemm_even_split(Kp, ns);
     return;
   }
   if (Kp % (16 * GEMM_KC_SMALL) == 0 && (Mp <= 128 || Mp % 256 == 0)) {
@@ -853,12 +896,11 @@ static void gemm_lds_dispatch(void *out, const void *Xp, const void *Wp, int Mp,
 
 template <int EPI>
 static void gemm_dispatch(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, hipStream_t st) {
-  if (g.lds == 2) {   // row blocks fastest once the weights are far larger than the last-level cache
-    if ((size_t)Np * Kp * 2 >= ((size_t)256 << 20)) gemm_ring_launch<EPI, true>(out, Xp, Wp, Mp, Np, Kp, st, g.nsplit);
-    else gemm_ring_launch<EPI, false>(out, Xp, Wp, Mp, Np, Kp, st, g.nsplit);
-    return;
+  switch (g.lds) {
+    case GEMM_RING_256X256: gemm_ring_launch<Ring256x256, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
+    case GEMM_RING_256X128: gemm_ring_launch<Ring256x128, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
+    default: break;
   }
-  if (g.lds == 3) { gemm_ring_launch<EPI, false, 2>(out, Xp, Wp, Mp, Np, Kp, st, g.nsplit); return; }
   if (g.lds) { gemm_lds_dispatch<EPI>(out, Xp, Wp, Mp, Np, Kp, g, st); return; }
   int mbt = Mp / 32;
   int MB = mbt >= 8 ? 8 : mbt;
