@@ -165,7 +165,7 @@ constexpr int ATT_PREFILL_WAVES = 8;    // wavefronts of a workgroup, which shar
 void fast_attention_prefill(void *Xp_out, const void *q_h16, const PrefillBlock *blocks, int nblocks, KvGeom kv, int layer,
                             int Mp, int Hq, int Hkv, hipStream_t st);
 // lm_head with the sampler fused into the epilogue (partials per workgroup) + the combine kernel.  With `target` set
-// (scoring) only target_lp is meaningful: no noise is drawn and tok / lp describe the plain argmax.
+// (scoring) only target_lp is meaningful: no noise is drawn, tok and lp are left alone or describe the plain argmax.
 void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *Xp, const void *Wp, int Mp, int M,
                         int V, int Np, int Kp, float temperature, uint64_t seed, DrawIds ids,
                         const int32_t *row_active, const int32_t *target, float *partials, hipStream_t st);

@@ -1089,13 +1089,8 @@ struct LmWideLds {
   static constexpr int BYTES = LM_WN * DUMP_PER_WAVE + LM_WN * 8 * 32 * (int)sizeof(SampleAcc);
 };
 
-// SCORE (teacher-forced scoring, target set): only the log-sum-exp of the row and the target's z are wanted, so a
-// lane takes the 16 logits of an accumulator tile at once -- their maximum, then 16 hardware exp2 of the differences
-// -- instead of the sampler's per-logit running update (which costs more than the main loop at this tile size).
-template <bool SCORE>
 __global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np,
-                                                          int Kp, int V, float temperature, uint64_t seed, DrawIds ids,
-                                                          const int32_t *target, float *target_z, float *part, int n_wg) {
+                                                          int Kp, int V, float temperature, uint64_t seed, DrawIds ids, float *part, int n_wg) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   using L = GemmWide;
   constexpr int MB = L::MB, NBW = L::NBW, T = L::T, XU = L::CHUNK_UNITS, XL = L::XL, ROWS = L::ROWS, NSTAGE = L::NSTAGE;
@@ -1158,17 +1153,15 @@ __global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restri
     }
   }
   // ---- sampler epilogue
-  auto fold4 = [&](SampleAcc &sa, f32x4 av, int v0, int m, int tgt, uint32_t stream, uint32_t step) {
-    u32x4 r = {0u, 0u, 0u, 0u};
-    if (!target) r = draw4(seed, stream, step, (uint32_t)(v0 >> 2));
+  auto fold4 = [&](SampleAcc &sa, f32x4 av, int v0, uint32_t stream, uint32_t step) {
+    u32x4 r = draw4(seed, stream, step, (uint32_t)(v0 >> 2));
     const uint32_t bits[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       int v = v0 + i;
       if (v < V) {
         float z = av[i] * W_UNSCALE / temperature;
-        sample_acc_add(sa, z, target ? z : z + gumbel_from_bits(bits[i]), v);   // scoring draws no noise
-        if (v == tgt) target_z[m] = z;
+        sample_acc_add(sa, z, z + gumbel_from_bits(bits[i]), v);
       }
     }
   };
@@ -1186,33 +1179,10 @@ __global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restri
     for (int j = 0; j < MB; ++j) {
       SampleAcc sa = sample_acc_init();
       if (nb < nblocks) {
-        int m = mrow0 + j * 32 + col, tgt = target ? target[m] : -1;
-        if (SCORE) {
-          const float c2 = W_UNSCALE / temperature * 1.44269504088896341f;   // logits in log2 units
-          float z2[16], bm = -INFINITY;
+        int m = mrow0 + j * 32 + col;
+        const uint32_t stream = draw_stream(ids, m), step = draw_step(ids, m);
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            f32x4 av = dump[(j * 4 + g) * 64];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              int v = nb * 32 + 8 * g + 4 * half + i;
-              z2[4 * g + i] = v < V ? av[i] * c2 : -INFINITY;
-              bm = fmaxf(bm, z2[4 * g + i]);
-              if (v == tgt) target_z[m] = av[i] * W_UNSCALE / temperature;
-            }
-          }
-          if (bm > -INFINITY) {
-            float sum = 0.f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(z2[i] - bm);
-            sa.zmax = bm * 0.693147180559945309f;   // back to natural units: exp(z - zmax) = exp2(z2 - bm)
-            sa.zsum = sum;
-          }
-        } else {
-          const uint32_t stream = draw_stream(ids, m), step = target ? 0u : draw_step(ids, m);
-#pragma unroll
-          for (int g = 0; g < 4; ++g) fold4(sa, dump[(j * 4 + g) * 64], nb * 32 + 8 * g + 4 * half, m, tgt, stream, step);
-        }
+        for (int g = 0; g < 4; ++g) fold4(sa, dump[(j * 4 + g) * 64], nb * 32 + 8 * g + 4 * half, stream, step);
       }
       SampleAcc o = sample_acc_shfl_xor(sa, 32);
       sample_acc_merge(sa, o);
@@ -1239,12 +1209,79 @@ __global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restri
   }
 }
 
+// Teacher-forced scoring (target set) on the 256 x 256 tiles of the LDS ring: only the log-sum-exp of the row and the
+// target's z are wanted, so a lane takes the 32 logits that it holds of a batch row straight from its accumulators -- their
+// maximum, then 32 hardware exp2 of the differences.  The main loop is bound by the matrix cores; the register-streaming form
+// that this replaced fetched 24 KB per k-step and parked its accumulators in LDS for the epilogue.  4096 rows, vocabulary
+// 151936: 3.91 -> 2.75 ms at hidden 2560 (1.16 PFLOP/s), 6.83 -> 5.17 ms at 5120 (1.23).  One partial per (row, strip of 256 entries): plane 0 the maximum z, plane 1 the sum.
+__global__ __launch_bounds__(Ring256x256::T) void lmhead_score_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np,
+                                                                      int Kp, int V, float temperature, const int32_t *__restrict__ target,
+                                                                      float *__restrict__ target_z, float *__restrict__ part, int strips) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  using L = Ring256x256;
+  constexpr int MB = L::MB, NBW = L::NBW;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, nblocks = Np >> 5;
+  int bx, by, bz;
+  ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
+  const int nb0 = bx * L::NB + (w % L::WC) * NBW, mrow0 = bz * L::ROWS, wrow = (w / L::WC) * 32 * MB;
+  f32x16 acc[NBW][MB];
+  ring_mainloop<L>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, mrow0, 0, Kp >> 4);
+  const float c2 = W_UNSCALE / temperature * 1.44269504088896341f;   // logits in log2 units
+  const int v0 = nb0 * 32 + 4 * half;                                 // register 4g + i of block n: entry v0 + 32 n + 8 g + i
+  const bool cut = nb0 * 32 + 32 * NBW > V;                           // the wavefront's entries reach past the vocabulary
+  float2 (*sh)[L::ROWS] = (float2 (*)[L::ROWS])lds_raw;               // [WC][ROWS]; the ring is free
+#pragma unroll
+  for (int j = 0; j < MB; ++j) {
+    const int m = mrow0 + wrow + j * 32 + col, tgt = target[m] - v0;
+    float bm = -INFINITY, sum = 0.f;
+    if (cut) {
+#pragma unroll
+      for (int n = 0; n < NBW; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (v0 + 32 * n + 8 * (r >> 2) + (r & 3) >= V) acc[n][j][r] = -INFINITY;
+    }
+    if (__any(tgt >= 0 && tgt < 32 * NBW)) {
+#pragma unroll
+      for (int n = 0; n < NBW; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (tgt == 32 * n + 8 * (r >> 2) + (r & 3)) target_z[m] = acc[n][j][r] * W_UNSCALE / temperature;
+    }
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc[n][j][r] *= c2; bm = fmaxf(bm, acc[n][j][r]); }
+    bm = fmaxf(bm, __shfl_xor(bm, 32, 64));   // lanes l and l^32 hold the same batch row
+    if (bm > -INFINITY) {
+#pragma unroll
+      for (int n = 0; n < NBW; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(acc[n][j][r] - bm);
+    }
+    sum += __shfl_xor(sum, 32, 64);
+    if (half == 0) sh[w % L::WC][wrow + j * 32 + col] = make_float2(bm, sum);
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < L::ROWS; r += L::T) {   // the four column pairs of a row, in order
+    float bm = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int c = 0; c < L::WC; ++c) bm = fmaxf(bm, sh[c][r].x);
+#pragma unroll
+    for (int c = 0; c < L::WC; ++c) sum += sh[c][r].x > -INFINITY ? sh[c][r].y * __builtin_amdgcn_exp2f(sh[c][r].x - bm) : 0.f;
+    const int64_t o = (int64_t)bx * Mp + mrow0 + r, plane = (int64_t)strips * Mp;
+    part[o] = bm * 0.693147180559945309f;   // back to natural units: exp(z - zmax) = exp2(z2 - bm)
+    part[plane + o] = sum;
+  }
+}
+
 static int lm_wide_wgs(int Np) { return (Np / 32 + 7) / 8; }
 static bool lm_use_wide(int Mp, int Kp) { return Mp % 256 == 0 && Kp % GEMM_K_PAD == 0; }
 
-// grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.
+// grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: the partials are those of
+// lmhead_score_kernel, only target_lp is written.
 __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp, const float *part, int n_wg, int Mp,
-                                      const int32_t *row_active, const int32_t *target, const float *target_z) {
+                                      const int32_t *row_active, const int32_t *target, const float *target_z, int sums_only) {
   __shared__ SampleAcc sh[4];
   int m = blockIdx.x;
   if (row_active && !row_active[m]) return;
@@ -1252,7 +1289,9 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
   SampleAcc a = sample_acc_init();
   for (int g = threadIdx.x; g < n_wg; g += blockDim.x) {
     int64_t o = (int64_t)g * Mp + m;
-    SampleAcc b = {part[o], part[plane + o], part[2 * plane + o], part[3 * plane + o], __float_as_int(part[4 * plane + o])};
+    SampleAcc b = sample_acc_init();
+    b.zmax = part[o]; b.zsum = part[plane + o];
+    if (!sums_only) { b.best = part[2 * plane + o]; b.zbest = part[3 * plane + o]; b.idx = __float_as_int(part[4 * plane + o]); }
     sample_acc_merge(a, b);
   }
   for (int o = 32; o > 0; o >>= 1) { SampleAcc b = sample_acc_shfl_xor(a, o); sample_acc_merge(a, b); }
@@ -1261,8 +1300,7 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) sample_acc_merge(a, sh[w]);
     float lse = a.zmax + logf(a.zsum);
-    tok[m] = a.idx;
-    lp[m] = a.zbest - lse;
+    if (!sums_only) { tok[m] = a.idx; lp[m] = a.zbest - lse; }
     if (target_lp) target_lp[m] = (target && target[m] >= 0) ? target_z[m] - lse : 0.f;
   }
 }
@@ -1307,30 +1345,33 @@ void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *X
   const bool wide = lm_use_wide(Mp, Kp);
   int n_wg = wide ? lm_wide_wgs(Np) : lm_wgs(Np);
   float *target_z = partials + (size_t)5 * lm_wgs(Np) * Mp;   // behind the partials of either form
-  if (wide) {
+  if (wide && target) {
+    static bool attr_set = false;
+    if (!attr_set) {
+      (void)hipFuncSetAttribute((const void *)lmhead_score_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, Ring256x256::BYTES);
+      attr_set = true;
+    }
+    hipLaunchKernelGGL(lmhead_score_kernel, dim3(n_wg * (Mp / 256)), dim3(Ring256x256::T), Ring256x256::BYTES, st, (const u32x4v *)Xp,
+                       (const h16x8 *)Wp, Mp, Np, Kp, V, temperature, target, target_z, partials, n_wg);
+  } else if (wide) {
     static bool attr_set = false;
     constexpr int BYTES = LmWideLds::BYTES > GemmWide::BYTES ? LmWideLds::BYTES : GemmWide::BYTES;
     if (!attr_set) {
-      (void)hipFuncSetAttribute((const void *)lmhead_wide_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
-      (void)hipFuncSetAttribute((const void *)lmhead_wide_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
+      (void)hipFuncSetAttribute((const void *)lmhead_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
       attr_set = true;
     }
-    if (target)
-      hipLaunchKernelGGL(lmhead_wide_kernel<true>, dim3(n_wg * (Mp / 256)), dim3(256), BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp,
-                         Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg);
-    else
-      hipLaunchKernelGGL(lmhead_wide_kernel<false>, dim3(n_wg * (Mp / 256)), dim3(256), BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp,
-                         Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg);
+    hipLaunchKernelGGL(lmhead_wide_kernel, dim3(n_wg * (Mp / 256)), dim3(256), BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp,
+                       Np, Kp, V, temperature, seed, ids, partials, n_wg);
   } else {
     lmhead_dispatch<false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, nullptr, 0, st);
   }
   hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, target_lp, partials, n_wg, Mp, row_active,
-                     target, target_z);
+                     target, target_z, wide && target ? 1 : 0);
 }
 
 void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st) {
   hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, (float *)nullptr, part, n_parts, Mp, row_active,
-                     (const int32_t *)nullptr, (const float *)nullptr);
+                     (const int32_t *)nullptr, (const float *)nullptr, 0);
 }
 
 void fast_lmhead_logits(float *logits, int64_t ld, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V,
