@@ -538,19 +538,6 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
   }
 }
 
-// ---- the 256 x 256 register-streaming tile of the wide lm_head kernel ----------------------------------------------
-// Four wavefronts in a row; every wavefront owns two weight blocks (64 output columns), streamed from global memory
-// straight into A-operand registers, against eight blocks of 32 batch rows whose operands come through LDS; every
-// activation operand read from LDS feeds two MFMAs.  (The projections used this form too, also as two row halves x two
-// column pairs on a 256 x 128 tile, until gemm_ring_kernel below replaced it there.)
-struct GemmWide {
-  static constexpr int MB = 8, WN = 4, NBW = 2, ROWS = 256, T = WN * 64;
-  static constexpr int CK = 1, NSTAGE = 8 / CK;   // k-steps per chunk (one barrier each), chunks in flight; CK = 2 measured 1-2 % slower
-  static constexpr int CHUNK_UNITS = CK * 2 * ROWS, XL = CHUNK_UNITS / T;
-  static constexpr int X_BYTES = 2 * CHUNK_UNITS * 16, TILE_STRIDE = 33, EPI_BYTES = WN * 32 * TILE_STRIDE * 4;
-  static constexpr int BYTES = X_BYTES > EPI_BYTES ? X_BYTES : EPI_BYTES;
-};
-
 // ---- tiles with both operands in an LDS ring: batches of 256 rows and more ------------------------------
 // What caps a large-tile GEMM here is what a compute unit can take in per cycle through its vector memory path, so a
 // workgroup must fetch every operand byte once: 256 weight columns and 256 batch rows per k-step are 16 KB for 2 MFLOP.
@@ -578,11 +565,12 @@ template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
   static constexpr int AU = NB * 64, XU = 2 * ROWS, SU = AU + XU;         // 16-byte units of a stage: A operands, B operands
   static constexpr int ALW = NB / WN, XLW = XU / T, LPS = ALW + XLW;      // weight, activation, all loads per wavefront and k-step
   static constexpr int NS = 8, LA = 6;                                    // stages, k-steps ahead
-  static constexpr int TILE_STRIDE = 33, BYTES = NS * SU * 16;            // 128 / 96 KB; the epilogue's WN x 32 x 33 floats reuse it
+  static constexpr int TILE_STRIDE = 33, BYTES = NS * SU * 16;            // 128 / 96 / 64 KB; the epilogue's WN x 32 x 33 floats reuse it
   static_assert(NB % WN == 0 && XU % T == 0 && WN * 32 * TILE_STRIDE * 4 <= BYTES, "whole loads per wavefront, room for the epilogue");
 };
 using Ring256x256 = GemmRingT<2, 4, 4, 2>;
 using Ring256x128 = GemmRingT<2, 2, 4, 2>;   // 256 rows, 128 columns
+using Ring128x128 = GemmRingT<2, 2, 2, 2>;   // two workgroups fit a compute unit; the lm_head only
 
 __device__ __forceinline__ void load_to_lds(const void *g, void *l) {   // 16 bytes per lane; l is the wavefront's base, lane l lands at l + 16 l
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g, (__attribute__((address_space(3))) void *)l, 16, 0, 0);
@@ -935,25 +923,135 @@ void fast_gemm(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp
 }
 
 // ---- lm_head ---------------------------------------------------------------------------------------------
+// What a lane does with the logits it holds of one batch row: register 4g + i of accumulator x[n] is (times W_UNSCALE) the
+// logit of vocabulary entry v0 + 32n + 8g + i, v0 = 32 * (first weight block) + 4 * (lane / 32).  Entries past V do not count.
+constexpr float LOG2_E = 1.44269504088896341f;
+template <int NBW>
+__device__ __forceinline__ void mask_past_vocab(f32x16 (&x)[NBW], int v0, int V) {
+  if (__any(v0 + 32 * NBW > V)) {
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (v0 + 32 * n + 8 * (r >> 2) + (r & 3) >= V) x[n][r] = -INFINITY;
+  }
+}
+
+// Sum of exp(z - max z) from the lane's largest accumulator value xm: the difference first, so that the sum is as exact at
+// scores of thousands (low temperatures) as at small ones, then hardware exp2.
+template <int NBW>
+__device__ __forceinline__ float sum_exp_lane(const f32x16 (&x)[NBW], float c2, float xm) {
+  float sum = 0.f;
+  if (xm > -INFINITY) {
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f((x[n][r] - xm) * c2);
+  }
+  return sum;
+}
+
+// Scoring: (max z, sum of exp(z - max z)); the target's z goes to *target_z if the lane holds it.
+template <int NBW>
+__device__ __forceinline__ SampleAcc score_lane(f32x16 (&x)[NBW], int v0, int V, float temperature, int target, float *target_z) {
+  const float c2 = W_UNSCALE / temperature * LOG2_E;
+  mask_past_vocab<NBW>(x, v0, V);
+  if (__any(target >= v0 && target < v0 + 32 * NBW)) {
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (target == v0 + 32 * n + 8 * (r >> 2) + (r & 3)) *target_z = x[n][r] * W_UNSCALE / temperature;
+  }
+  SampleAcc sa = sample_acc_init();
+  float xm = -INFINITY;
+#pragma unroll
+  for (int n = 0; n < NBW; ++n)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) xm = fmaxf(xm, x[n][r]);
+  sa.zsum = sum_exp_lane<NBW>(x, c2, xm);
+  sa.zmax = xm * W_UNSCALE / temperature;
+  return sa;
+}
+
+// Sampling: the same, and the best perturbed score z + g of the lane's entries (lowest index on exact ties).  The score that
+// decides is the fp32 one (division by T, two logf), but it costs some sixty instructions per entry in a serial chain, more
+// than the main loop at 256 rows.  So the entries are first compared by z/ln2 - log2(-log2 u), which orders them the same way up
+// to the rounding of two hardware logarithms (relative 2^-22 each) and of z, and only the winner is evaluated in full.  The
+// two orders can differ only where the lane's best two are closer than those errors: below 1e-5 plus 1e-6 of the score's
+// magnitude together; within ten times that the lane's wavefront evaluates all entries in full, in index order (a percent of
+// the wavefronts; through `dump`, 4 KB of LDS of its own, because a rolled loop cannot index registers).
+template <int NBW>
+__device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, int v0, int V, float temperature, uint64_t seed, uint32_t stream,
+                                                 uint32_t step) {
+  const float c2 = W_UNSCALE / temperature * LOG2_E;
+  mask_past_vocab<NBW>(x, v0, V);
+  SampleAcc sa = sample_acc_init();
+  float xm = -INFINITY, best = -INFINITY, second = -INFINITY, xbest = 0.f;
+  uint32_t wbest = 0;
+  int kbest = -1;
+#pragma unroll
+  for (int n = 0; n < NBW; ++n)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const u32x4 d = draw4(seed, stream, step, (uint32_t)(v0 >> 2) + 8 * n + 2 * g);
+      const uint32_t w[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float u = fmaf((float)(w[i] >> 9), 0x1p-23f, 0x1p-24f);   // exact: (2k + 1) 2^-24
+        const float f = fmaf(x[n][4 * g + i], c2, -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)));
+        xm = fmaxf(xm, x[n][4 * g + i]);
+        const bool better = f > best;
+        second = fmaxf(second, fminf(f, best));
+        best = better ? f : best;
+        xbest = better ? x[n][4 * g + i] : xbest;
+        wbest = better ? w[i] : wbest;
+        kbest = better ? 32 * n + 8 * g + i : kbest;
+      }
+    }
+  sa.zsum = sum_exp_lane<NBW>(x, c2, xm);
+  sa.zmax = xm * W_UNSCALE / temperature;
+  if (__any(second > best - (1e-4f + 1e-5f * (fabsf(best) + 32.f)))) {
+    float *mine = dump + (threadIdx.x & 63);
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mine[r * 64] = x[n][r];
+#pragma unroll 1
+      for (int g = 0; g < 4; ++g) {
+        const u32x4 d = draw4(seed, stream, step, (uint32_t)(v0 >> 2) + 8 * n + 2 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int v = v0 + 32 * n + 8 * g + i;
+          const float z = mine[(4 * g + i) * 64] * W_UNSCALE / temperature, score = z + gumbel_from_bits(i == 0 ? d.x : i == 1 ? d.y : i == 2 ? d.z : d.w);
+          if (v < V && score > sa.best) { sa.best = score; sa.zbest = z; sa.idx = v; }
+        }
+      }
+    }
+  } else if (kbest >= 0) {
+    sa.zbest = xbest * W_UNSCALE / temperature;
+    sa.best = sa.zbest + gumbel_from_bits(wbest);
+    sa.idx = v0 + kbest;
+  }
+  return sa;
+}
+
 // grid (ceil(Np/32 / 4), 1, Mp/(32*MB)); block 256.  The GEMM main loop over the full K (four weight blocks per
-// workgroup), then every logit is folded into a running (max, sum-exp, best perturbed score, its index, its z) per
+// workgroup), then every lane's logits are folded into a running (max, sum-exp, best perturbed score, its index, its z) per
 // batch row: per wavefront, then over the four wavefronts in wavefront order, one partial per workgroup.
 constexpr int LM_WN = 4;
-template <int MB> struct LmLds {   // epilogue of the 256-row kernel: accumulators of four wavefronts + their partial results
-  static constexpr int DUMP_PER_WAVE = MB * 16 * 64 * 4;
-  static constexpr int BYTES = LM_WN * DUMP_PER_WAVE + LM_WN * MB * 32 * (int)sizeof(SampleAcc);
-};
+constexpr int LM_DUMP_FLOATS = 16 * 64;   // sample_lane's LDS, per wavefront
 
 // The vocabulary takes several rounds of workgroups (1187 for 151936 rows on 256 compute units), and a workgroup's
 // sampler epilogue moves no weights.  With two workgroups resident per compute unit one's epilogue and first loads run
-// under the other's weight stream: 64 rows 199 -> 146 us, 32 rows 158 -> 133 us, 128 rows (sampler) 306 -> 280 us.  That
-// needs the kernel inside 256 registers per lane, which a two-chunk weight pipeline allows (three chunks in flight
-// fit only at 32 rows; the 128-row forms spill a little, and the 128-row logits form, which has no long epilogue to
-// hide, is faster alone on the unit with its three-chunk pipeline).
-template <int MB, bool LOGITS> constexpr int lm_wgs_per_cu() { return MB <= 2 || (MB == 4 && !LOGITS) ? 2 : 1; }
+// under the other's weight stream: 64 rows 199 -> 146 us, 32 rows 158 -> 133 us.  That needs the kernel inside 256 registers
+// per lane, which a two-chunk weight pipeline allows (three chunks in flight fit only at 32 rows).  With only the winner
+// of a lane's entries evaluated in full (sample_lane): 64 rows 137 -> 125 us, 32 rows 120.7 -> 117.5 us.  The logits forms of 128
+// and 256 rows have no long epilogue to hide and are faster alone on the unit with deeper pipelines.
+template <int MB> constexpr int lm_wgs_per_cu() { return MB <= 2 ? 2 : 1; }
 
 template <int MB, int NSTAGE, bool LOGITS>
-__global__ __launch_bounds__(256, (lm_wgs_per_cu<MB, LOGITS>())) void lmhead_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp,
+__global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp,
                                                      int Np, int Kp, int V, float temperature, uint64_t seed,
                                                      DrawIds ids, const int32_t *target, float *target_z,
                                                      float *part, int n_wg, float *logits, int64_t ld) {
@@ -964,31 +1062,6 @@ __global__ __launch_bounds__(256, (lm_wgs_per_cu<MB, LOGITS>())) void lmhead_ker
   const int nb_own = blockIdx.x * LM_WN + w, nb = min(nb_own, nblocks - 1);
   f32x16 acc[MB];
   gemm_lds_mainloop<MB, LM_WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC, mrow0);
-  // One logit: temperature, running (max, sum-exp), perturbed-score argmax, the target's z.
-  auto fold = [&](SampleAcc &sa, float a, uint32_t bits, int v, int m, int tgt) {
-    if (v < V) {
-      float z = a * W_UNSCALE / temperature;
-      sample_acc_add(sa, z, z + gumbel_from_bits(bits), v);
-      if (v == tgt) target_z[m] = z;
-    }
-  };
-  auto fold_plain = [&](SampleAcc &sa, float a, int v, int m, int tgt) {
-    if (v < V) {
-      float z = a * W_UNSCALE / temperature;
-      sample_acc_add(sa, z, z, v);
-      if (v == tgt) target_z[m] = z;
-    }
-  };
-  auto fold4 = [&](SampleAcc &sa, f32x4 a, int v0, int m, int tgt, uint32_t stream, uint32_t step) {
-    if (target) {   // scoring: only the target's log-prob is wanted, so no noise is drawn (the token output is the plain argmax)
-      fold_plain(sa, a[0], v0, m, tgt); fold_plain(sa, a[1], v0 + 1, m, tgt);
-      fold_plain(sa, a[2], v0 + 2, m, tgt); fold_plain(sa, a[3], v0 + 3, m, tgt);
-    } else {
-      u32x4 r = draw4(seed, stream, step, (uint32_t)(v0 >> 2));
-      fold(sa, a[0], r.x, v0, m, tgt); fold(sa, a[1], r.y, v0 + 1, m, tgt);
-      fold(sa, a[2], r.z, v0 + 2, m, tgt); fold(sa, a[3], r.w, v0 + 3, m, tgt);
-    }
-  };
   auto write_partial = [&](const SampleAcc &sa, int m) {
     int64_t o = (int64_t)blockIdx.x * Mp + m, plane = (int64_t)n_wg * Mp;
     part[o] = sa.zmax;
@@ -1010,60 +1083,20 @@ __global__ __launch_bounds__(256, (lm_wgs_per_cu<MB, LOGITS>())) void lmhead_ker
         }
       }
     }
-  } else if constexpr (MB >= 8) {
-    // Unrolling the sampler over eight row tiles is more code than the compiler will unroll, and a rolled loop over
-    // the accumulator array would move it out of the registers for the whole kernel.  So the accumulators are parked
-    // in LDS with static indices (each lane reads back only what it wrote) and the row tiles are folded in a loop.
-    using LM = LmLds<MB>;
-    __syncthreads();   // the main loop's buffers are free once every wavefront has left it
-    f32x4 *dump = (f32x4 *)(lds_raw + w * LM::DUMP_PER_WAVE) + lane;
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) dump[(j * 4 + g) * 64] = f32x4{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]};
-    SampleAcc (*sh)[MB][32] = (SampleAcc (*)[MB][32])(lds_raw + LM_WN * LM::DUMP_PER_WAVE);   // [4][MB][32]
-#pragma unroll 1
-    for (int j = 0; j < MB; ++j) {
-      SampleAcc sa = sample_acc_init();
-      if (nb_own < nblocks) {
-        int m = mrow0 + j * 32 + col, tgt = target ? target[m] : -1;
-        const uint32_t stream = draw_stream(ids, m), step = target ? 0u : draw_step(ids, m);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) fold4(sa, dump[(j * 4 + g) * 64], nb * 32 + 8 * g + 4 * half, m, tgt, stream, step);
-      }
-      SampleAcc o = sample_acc_shfl_xor(sa, 32);
-      sample_acc_merge(sa, o);
-      if (half == 0) sh[w][j][col] = sa;
-    }
-    __syncthreads();
-    if (w == 0 && half == 0) {
-#pragma unroll 1
-      for (int j = 0; j < MB; ++j) {
-        SampleAcc sa = sh[0][j][col];
-        for (int ww = 1; ww < LM_WN; ++ww) sample_acc_merge(sa, sh[ww][j][col]);
-        write_partial(sa, mrow0 + j * 32 + col);
-      }
-    }
   } else {
     SampleAcc sa[MB];
+    const int v0 = nb_own * 32 + 4 * half;
 #pragma unroll
-    for (int j = 0; j < MB; ++j) sa[j] = sample_acc_init();
-    if (nb_own < nblocks) {
-#pragma unroll
-      for (int j = 0; j < MB; ++j) {
-        int m = mrow0 + j * 32 + col, tgt = target ? target[m] : -1;
-        const uint32_t stream = draw_stream(ids, m), step = target ? 0u : draw_step(ids, m);
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          fold4(sa[j], f32x4{acc[j][4 * g], acc[j][4 * g + 1], acc[j][4 * g + 2], acc[j][4 * g + 3]}, nb * 32 + 8 * g + 4 * half, m, tgt,
-                stream, step);
-      }
+    for (int j = 0; j < MB; ++j) {
+      const int m = mrow0 + j * 32 + col;
+      f32x16 x[1] = {acc[j]};
+      if (target) sa[j] = score_lane<1>(x, v0, V, temperature, target[m], target_z + m);
+      else sa[j] = sample_lane<1>(x, (float *)lds_raw + w * LM_DUMP_FLOATS, v0, V, temperature, seed, draw_stream(ids, m), draw_step(ids, m));
     }
     // lanes l and l^32 hold the same batch row; then fold the four wavefronts in wavefront order
-    SampleAcc (*sh)[MB][32] = (SampleAcc (*)[MB][32])lds_raw;   // [3][MB][32]; the main loop's buffers are free by now
+    SampleAcc (*sh)[MB][32] = (SampleAcc (*)[MB][32])(lds_raw + LM_WN * LM_DUMP_FLOATS * 4);   // [3][MB][32]; the main loop's buffers are free by now
 #pragma unroll
     for (int j = 0; j < MB; ++j) { SampleAcc b = sample_acc_shfl_xor(sa[j], 32); sample_acc_merge(sa[j], b); }
-    __syncthreads();   // every wavefront has left the main loop before its buffers are overwritten
     if (w > 0 && half == 0)
 #pragma unroll
       for (int j = 0; j < MB; ++j) sh[w - 1][j][col] = sa[j];
@@ -1078,130 +1111,52 @@ __global__ __launch_bounds__(256, (lm_wgs_per_cu<MB, LOGITS>())) void lmhead_ker
   }
 }
 
-// ---- lm_head on 256 x 256 tiles (batches of 256 rows and more: scoring passes, wide decode batches) -----------------
-// A register-streaming main loop (four wavefronts, two weight blocks each, 256 rows, operands eight k-steps ahead),
-// then the sampler of the kernel above over the 2 x 8 accumulator tiles of a wavefront: parked in LDS one weight block
-// at a time (static indices, so the accumulators stay registers during the main loop) and folded in a rolled loop.
-// grid: ceil(Np/256) column strips x Mp/256 row blocks, the row blocks of a strip neighbours in launch order (the
-// vocabulary matrix is far larger than the caches); one partial per (row, strip).
-struct LmWideLds {
-  static constexpr int DUMP_PER_WAVE = 8 * 16 * 64 * 4;   // one weight block's eight accumulator tiles
-  static constexpr int BYTES = LM_WN * DUMP_PER_WAVE + LM_WN * 8 * 32 * (int)sizeof(SampleAcc);
-};
-
-__global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np,
-                                                          int Kp, int V, float temperature, uint64_t seed, DrawIds ids, float *part, int n_wg) {
+// ---- lm_head on the tiles of the LDS ring (128 rows and more) ----------------------------------------------------------------
+// A wavefront holds 64 vocabulary entries of 32 MB batch rows; lanes l and l^32 hold the same rows.  One partial per (row, strip
+// of 32 NB entries): planes max z, sum exp, best score, its z, its index; scoring (SCORE) writes the first two and target_z.
+// Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.75 ms at hidden 2560 (1.16
+// PFLOP/s), 5.17 ms at 5120 (1.23), where the register-streaming tile it replaced (24 KB per k-step, accumulators parked in
+// LDS for the epilogue) took 3.91 and 6.83.  Sampling takes 128 x 128 tiles: its epilogue keeps the vector unit busy for as long
+// as the main loop keeps the loads and the matrix cores, and two workgroups per compute unit let one's epilogue run under the
+// other's main loop: 256 rows 275 us (256 x 256 tiles, one workgroup per unit: 344; 256 x 128: 336; the register-streaming tile
+// with the full evaluation of every entry: 517), 128 rows 181 us (280).
+template <class L, bool SCORE>
+__global__ __launch_bounds__(L::T) void lmhead_ring_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np, int Kp, int V,
+                                                           float temperature, uint64_t seed, DrawIds ids, const int32_t *__restrict__ target,
+                                                           float *__restrict__ target_z, float *__restrict__ part, int strips) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  using L = GemmWide;
-  constexpr int MB = L::MB, NBW = L::NBW, T = L::T, XU = L::CHUNK_UNITS, XL = L::XL, ROWS = L::ROWS, NSTAGE = L::NSTAGE;
-  u32x4v *xs = (u32x4v *)lds_raw;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x, half = lane >> 5, col = lane & 31;
-  const int nblocks = Np >> 5, nchunks = Kp >> 4, nz = Mp / ROWS;
-  const int bx = blockIdx.x / nz, bz = blockIdx.x % nz;
-  const int nb0 = (bx * L::WN + w) * NBW, mrow0 = bz * ROWS;
-  const int64_t a_step = w_kstep_stride(Np);
-  const h16x8 *a_ptr[NBW];
-#pragma unroll
-  for (int n = 0; n < NBW; ++n) a_ptr[n] = Wp + w_block_base(min(nb0 + n, nblocks - 1), Kp) + (lane >> 5) * 32 + (lane & 31);
+  constexpr int MB = L::MB, NBW = L::NBW;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, nblocks = Np >> 5;
+  int bx, by, bz;
+  ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
+  const int nb0 = bx * L::NB + (w % L::WC) * NBW, mrow0 = bz * L::ROWS, wrow = (w / L::WC) * 32 * MB, v0 = nb0 * 32 + 4 * half;
   f32x16 acc[NBW][MB];
+  ring_mainloop<L>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, mrow0, 0, Kp >> 4);
+  float *dump = (float *)lds_raw + w * LM_DUMP_FLOATS;   // the ring is free
+  SampleAcc (*sh)[L::ROWS] = (SampleAcc (*)[L::ROWS])(lds_raw + L::WN * LM_DUMP_FLOATS * 4);   // [WC][ROWS]
+  static_assert(L::WN * LM_DUMP_FLOATS * 4 + L::WC * L::ROWS * (int)sizeof(SampleAcc) <= L::BYTES, "the epilogue fits the ring");
 #pragma unroll
-  for (int n = 0; n < NBW; ++n)
+  for (int j = 0; j < MB; ++j) {
+    const int row = wrow + j * 32 + col, m = mrow0 + row;
+    f32x16 x[NBW];
 #pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
-  h16x8 a[NSTAGE][NBW];
-  u32x4v xr[NSTAGE][XL];
-  auto load_a = [&](int st, int c) {
-#pragma unroll
-    for (int n = 0; n < NBW; ++n) a[st][n] = __builtin_nontemporal_load(a_ptr[n] + (int64_t)c * a_step);
-  };
-  auto load_x = [&](int st, int c) {
-#pragma unroll
-    for (int i = 0; i < XL; ++i) {
-      int idx = i * T + tid;
-      xr[st][i] = Xp[(int64_t)(c * 2 + idx / ROWS) * Mp + mrow0 + idx % ROWS];
-    }
-  };
-  auto store_x = [&](int st, int buf) {
-#pragma unroll
-    for (int i = 0; i < XL; ++i) xs[buf * XU + i * T + tid] = xr[st][i];
-  };
-  auto compute = [&](int st, int buf) {
-    const u32x4v *bp = xs + buf * XU + (lane >> 5) * ROWS + (lane & 31);
-    u32x4v b[MB];
-#pragma unroll
-    for (int j = 0; j < MB; ++j) b[j] = bp[j * 32];
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int n = 0; n < NBW; ++n) acc[n][j] = mfma_h16(a[st][n], __builtin_bit_cast(h16x8, b[j]), acc[n][j]);
-  };
-#pragma unroll
-  for (int s = 0; s < NSTAGE - 1; ++s) { load_x(s, s); load_a(s, s); }
-  store_x(0, 0);
-  __syncthreads();
-  for (int c0 = 0; c0 < nchunks; c0 += NSTAGE) {
-#pragma unroll
-    for (int s = 0; s < NSTAGE; ++s) {
-      const int c = c0 + s, cn = min(c + NSTAGE - 1, nchunks - 1);
-      load_x((s + NSTAGE - 1) % NSTAGE, cn);
-      load_a((s + NSTAGE - 1) % NSTAGE, cn);
-      compute(s, s & 1);
-      store_x((s + 1) % NSTAGE, (s + 1) & 1);
-      __syncthreads();
-    }
-  }
-  // ---- sampler epilogue
-  auto fold4 = [&](SampleAcc &sa, f32x4 av, int v0, uint32_t stream, uint32_t step) {
-    u32x4 r = draw4(seed, stream, step, (uint32_t)(v0 >> 2));
-    const uint32_t bits[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int v = v0 + i;
-      if (v < V) {
-        float z = av[i] * W_UNSCALE / temperature;
-        sample_acc_add(sa, z, z + gumbel_from_bits(bits[i]), v);
-      }
-    }
-  };
-  f32x4 *dump = (f32x4 *)(lds_raw + w * LmWideLds::DUMP_PER_WAVE) + lane;
-  SampleAcc (*sh)[MB][32] = (SampleAcc (*)[MB][32])(lds_raw + LM_WN * LmWideLds::DUMP_PER_WAVE);   // [4][MB][32]
-#pragma unroll
-  for (int n = 0; n < NBW; ++n) {
-    // (the loop above ended with a barrier: its buffers are free; between the two blocks each lane re-reads only its own dump)
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) dump[(j * 4 + g) * 64] = f32x4{acc[n][j][4 * g], acc[n][j][4 * g + 1], acc[n][j][4 * g + 2], acc[n][j][4 * g + 3]};
-    const int nb = nb0 + n;
-#pragma unroll 1
-    for (int j = 0; j < MB; ++j) {
-      SampleAcc sa = sample_acc_init();
-      if (nb < nblocks) {
-        int m = mrow0 + j * 32 + col;
-        const uint32_t stream = draw_stream(ids, m), step = draw_step(ids, m);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) fold4(sa, dump[(j * 4 + g) * 64], nb * 32 + 8 * g + 4 * half, stream, step);
-      }
-      SampleAcc o = sample_acc_shfl_xor(sa, 32);
-      sample_acc_merge(sa, o);
-      if (half == 0) {
-        if (n > 0) { SampleAcc prev = sh[w][j][col]; sample_acc_merge(prev, sa); sa = prev; }   // block order: lower indices first
-        sh[w][j][col] = sa;
-      }
-    }
+    for (int n = 0; n < NBW; ++n) x[n] = acc[n][j];
+    SampleAcc sa;
+    if (SCORE) sa = score_lane<NBW>(x, v0, V, temperature, target[m], target_z + m);
+    else sa = sample_lane<NBW>(x, dump, v0, V, temperature, seed, draw_stream(ids, m), draw_step(ids, m));
+    SampleAcc o = sample_acc_shfl_xor(sa, 32);
+    sample_acc_merge(sa, o);
+    if (half == 0) sh[w % L::WC][row] = sa;
   }
   __syncthreads();
-  if (w == 0 && half == 0) {
-#pragma unroll 1
-    for (int j = 0; j < MB; ++j) {
-      SampleAcc sa = sh[0][j][col];
-      for (int ww = 1; ww < LM_WN; ++ww) sample_acc_merge(sa, sh[ww][j][col]);
-      int m = mrow0 + j * 32 + col;
-      int64_t o = (int64_t)bx * Mp + m, plane = (int64_t)n_wg * Mp;
-      part[o] = sa.zmax;
-      part[plane + o] = sa.zsum;
+  for (int r = threadIdx.x; r < L::ROWS; r += L::T) {   // the four column pairs of a row, lower indices first
+    SampleAcc sa = sh[0][r];
+#pragma unroll
+    for (int c = 1; c < L::WC; ++c) sample_acc_merge(sa, sh[c][r]);
+    const int64_t o = (int64_t)bx * Mp + mrow0 + r, plane = (int64_t)strips * Mp;
+    part[o] = sa.zmax;
+    part[plane + o] = sa.zsum;
+    if (!SCORE) {
       part[2 * plane + o] = sa.best;
       part[3 * plane + o] = sa.zbest;
       part[4 * plane + o] = __int_as_float(sa.idx);
@@ -1209,77 +1164,20 @@ __global__ __launch_bounds__(256) void lmhead_wide_kernel(const u32x4v *__restri
   }
 }
 
-// Teacher-forced scoring (target set) on the 256 x 256 tiles of the LDS ring: only the log-sum-exp of the row and the
-// target's z are wanted, so a lane takes the 32 logits that it holds of a batch row straight from its accumulators -- their
-// maximum, then 32 hardware exp2 of the differences.  The main loop is bound by the matrix cores; the register-streaming form
-// that this replaced fetched 24 KB per k-step and parked its accumulators in LDS for the epilogue.  4096 rows, vocabulary
-// 151936: 3.91 -> 2.75 ms at hidden 2560 (1.16 PFLOP/s), 6.83 -> 5.17 ms at 5120 (1.23).  One partial per (row, strip of 256 entries): plane 0 the maximum z, plane 1 the sum.
-__global__ __launch_bounds__(Ring256x256::T) void lmhead_score_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np,
-                                                                      int Kp, int V, float temperature, const int32_t *__restrict__ target,
-                                                                      float *__restrict__ target_z, float *__restrict__ part, int strips) {
-  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  using L = Ring256x256;
-  constexpr int MB = L::MB, NBW = L::NBW;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, nblocks = Np >> 5;
-  int bx, by, bz;
-  ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
-  const int nb0 = bx * L::NB + (w % L::WC) * NBW, mrow0 = bz * L::ROWS, wrow = (w / L::WC) * 32 * MB;
-  f32x16 acc[NBW][MB];
-  ring_mainloop<L>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, mrow0, 0, Kp >> 4);
-  const float c2 = W_UNSCALE / temperature * 1.44269504088896341f;   // logits in log2 units
-  const int v0 = nb0 * 32 + 4 * half;                                 // register 4g + i of block n: entry v0 + 32 n + 8 g + i
-  const bool cut = nb0 * 32 + 32 * NBW > V;                           // the wavefront's entries reach past the vocabulary
-  float2 (*sh)[L::ROWS] = (float2 (*)[L::ROWS])lds_raw;               // [WC][ROWS]; the ring is free
-#pragma unroll
-  for (int j = 0; j < MB; ++j) {
-    const int m = mrow0 + wrow + j * 32 + col, tgt = target[m] - v0;
-    float bm = -INFINITY, sum = 0.f;
-    if (cut) {
-#pragma unroll
-      for (int n = 0; n < NBW; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (v0 + 32 * n + 8 * (r >> 2) + (r & 3) >= V) acc[n][j][r] = -INFINITY;
-    }
-    if (__any(tgt >= 0 && tgt < 32 * NBW)) {
-#pragma unroll
-      for (int n = 0; n < NBW; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (tgt == 32 * n + 8 * (r >> 2) + (r & 3)) target_z[m] = acc[n][j][r] * W_UNSCALE / temperature;
-    }
-#pragma unroll
-    for (int n = 0; n < NBW; ++n)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { acc[n][j][r] *= c2; bm = fmaxf(bm, acc[n][j][r]); }
-    bm = fmaxf(bm, __shfl_xor(bm, 32, 64));   // lanes l and l^32 hold the same batch row
-    if (bm > -INFINITY) {
-#pragma unroll
-      for (int n = 0; n < NBW; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(acc[n][j][r] - bm);
-    }
-    sum += __shfl_xor(sum, 32, 64);
-    if (half == 0) sh[w % L::WC][wrow + j * 32 + col] = make_float2(bm, sum);
+template <class L, bool SCORE>
+static void lmhead_ring_launch(const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, float temperature, uint64_t seed, DrawIds ids,
+                               const int32_t *target, float *target_z, float *part, int strips, hipStream_t st) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void *)lmhead_ring_kernel<L, SCORE>, hipFuncAttributeMaxDynamicSharedMemorySize, L::BYTES);
+    attr_set = true;
   }
-  __syncthreads();
-  for (int r = threadIdx.x; r < L::ROWS; r += L::T) {   // the four column pairs of a row, in order
-    float bm = -INFINITY, sum = 0.f;
-#pragma unroll
-    for (int c = 0; c < L::WC; ++c) bm = fmaxf(bm, sh[c][r].x);
-#pragma unroll
-    for (int c = 0; c < L::WC; ++c) sum += sh[c][r].x > -INFINITY ? sh[c][r].y * __builtin_amdgcn_exp2f(sh[c][r].x - bm) : 0.f;
-    const int64_t o = (int64_t)bx * Mp + mrow0 + r, plane = (int64_t)strips * Mp;
-    part[o] = bm * 0.693147180559945309f;   // back to natural units: exp(z - zmax) = exp2(z2 - bm)
-    part[plane + o] = sum;
-  }
+  hipLaunchKernelGGL((lmhead_ring_kernel<L, SCORE>), dim3(strips * (Mp / L::ROWS)), dim3(L::T), L::BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp,
+                     Mp, Np, Kp, V, temperature, seed, ids, target, target_z, part, strips);
 }
 
-static int lm_wide_wgs(int Np) { return (Np / 32 + 7) / 8; }
-static bool lm_use_wide(int Mp, int Kp) { return Mp % 256 == 0 && Kp % GEMM_K_PAD == 0; }
-
 // grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: the partials are those of
-// lmhead_score_kernel, only target_lp is written.
+// lmhead_ring_kernel<true>, only target_lp is written.
 __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp, const float *part, int n_wg, int Mp,
                                       const int32_t *row_active, const int32_t *target, const float *target_z, int sums_only) {
   __shared__ SampleAcc sh[4];
@@ -1313,7 +1211,7 @@ static void lmhead_launch(const void *Xp, const void *Wp, int Mp, int Np, int Kp
                           DrawIds ids, const int32_t *target, float *target_z, float *part, float *logits, int64_t ld,
                           hipStream_t st) {
   using L = GemmLds<MB, LM_WN>;
-  constexpr int SH = (MB >= 8 && !LOGITS) ? LmLds<MB>::BYTES : 3 * MB * 32 * (int)sizeof(SampleAcc);
+  constexpr int SH = LOGITS ? 0 : LM_WN * LM_DUMP_FLOATS * 4 + 3 * MB * 32 * (int)sizeof(SampleAcc);
   constexpr int BYTES = L::X_BYTES > SH ? L::X_BYTES : SH;
   static bool attr_set = false;
   if (!attr_set) {
@@ -1332,9 +1230,11 @@ static void lmhead_dispatch(const void *Xp, const void *Wp, int Mp, int Np, int 
                             int64_t ld, hipStream_t st) {
   int mbt = Mp / 32;
 #define LM_ARGS Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, part, logits, ld, st
-  if (mbt >= 8) lmhead_launch<8, 2, LOGITS>(LM_ARGS);
-  else if (mbt == 4) lmhead_launch<4, LOGITS ? 3 : 2, LOGITS>(LM_ARGS);
-  else if (mbt == 2) lmhead_launch<2, 2, LOGITS>(LM_ARGS);
+  if constexpr (LOGITS) {
+    if (mbt >= 8) { lmhead_launch<8, 2, LOGITS>(LM_ARGS); return; }
+    if (mbt == 4) { lmhead_launch<4, 3, LOGITS>(LM_ARGS); return; }
+  }
+  if (mbt == 2) lmhead_launch<2, 2, LOGITS>(LM_ARGS);
   else lmhead_launch<1, 3, LOGITS>(LM_ARGS);
 #undef LM_ARGS
 }
@@ -1342,31 +1242,15 @@ static void lmhead_dispatch(const void *Xp, const void *Wp, int Mp, int Np, int 
 void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *Xp, const void *Wp, int Mp, int M, int V,
                         int Np, int Kp, float temperature, uint64_t seed, DrawIds ids, const int32_t *row_active,
                         const int32_t *target, float *partials, hipStream_t st) {
-  const bool wide = lm_use_wide(Mp, Kp);
-  int n_wg = wide ? lm_wide_wgs(Np) : lm_wgs(Np);
+  const bool ring = Mp % 128 == 0, big = ring && target && Mp % 256 == 0;   // see lmhead_ring_kernel
+  int n_wg = big ? (Np / 32 + Ring256x256::NB - 1) / Ring256x256::NB : lm_wgs(Np);
   float *target_z = partials + (size_t)5 * lm_wgs(Np) * Mp;   // behind the partials of either form
-  if (wide && target) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      (void)hipFuncSetAttribute((const void *)lmhead_score_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, Ring256x256::BYTES);
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(lmhead_score_kernel, dim3(n_wg * (Mp / 256)), dim3(Ring256x256::T), Ring256x256::BYTES, st, (const u32x4v *)Xp,
-                       (const h16x8 *)Wp, Mp, Np, Kp, V, temperature, target, target_z, partials, n_wg);
-  } else if (wide) {
-    static bool attr_set = false;
-    constexpr int BYTES = LmWideLds::BYTES > GemmWide::BYTES ? LmWideLds::BYTES : GemmWide::BYTES;
-    if (!attr_set) {
-      (void)hipFuncSetAttribute((const void *)lmhead_wide_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
-      attr_set = true;
-    }
-    hipLaunchKernelGGL(lmhead_wide_kernel, dim3(n_wg * (Mp / 256)), dim3(256), BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp,
-                       Np, Kp, V, temperature, seed, ids, partials, n_wg);
-  } else {
-    lmhead_dispatch<false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, nullptr, 0, st);
-  }
+  if (big) lmhead_ring_launch<Ring256x256, true>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
+  else if (ring && target) lmhead_ring_launch<Ring128x128, true>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
+  else if (ring) lmhead_ring_launch<Ring128x128, false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
+  else lmhead_dispatch<false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, nullptr, 0, st);
   hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, target_lp, partials, n_wg, Mp, row_active,
-                     target, target_z, wide && target ? 1 : 0);
+                     target, target_z, ring && target ? 1 : 0);
 }
 
 void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st) {
