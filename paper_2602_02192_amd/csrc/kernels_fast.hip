@@ -1,44 +1,76 @@
 // MFMA path, everything that is not a dense contraction: residual + RMSNorm (with the split-K
 // reduction folded in), QKV post-processing (reduction, per-head norm, rotary embedding, KV append).
+#include <type_traits>
+
 #include "echo_device.h"
 #include "echo_kernels.h"
 
 namespace echo {
 
-// grid M rows, block <= 1024 (a multiple of 64 covering d/4 or d/8 lanes).  h[m] = embed[token[m]]            (embed != null)
-//                           h[m] += sum_s partials[s][..][m]  (nsplit <= REDUCE_MAX_SPLIT, summed in split order)
+// Calls f(std::integral_constant<int, n>) for a split count n in 0 .. REDUCE_MAX_SPLIT that is known only at run time: the
+// reducing kernels take it as a template parameter, because loads behind run-time conditions made the compiler wait for the
+// first of them before it issued the rest.
+template <int N = REDUCE_MAX_SPLIT, typename F>
+static void with_split_count(int n, F f) {
+  if constexpr (N >= 0) {
+    if (n == N) f(std::integral_constant<int, N>{});
+    else with_split_count<N - 1>(n, f);
+  }
+}
+
+// The row that workgroup blockIdx.x of n takes.  Workgroup i starts on XCD i % 8; the rows are dealt to the XCDs in contiguous
+// eighths, because a 128-byte line of the K8 activation layout, or of a key or value tile, holds 16 bytes or less of each of
+// several neighbouring rows: written from one XCD its pieces meet in that XCD's L2, written from eight they reach memory one by
+// one (4096 rows: residual + norm 35.7 -> 29.4 us, qkv_post_wide_kernel 47.6 -> 44.4 at the 4B width).
+__device__ __forceinline__ int xcd_row(int n) {
+  const int id = blockIdx.x, x = id & 7;
+  return x * (n >> 3) + min(x, n & 7) + (id >> 3);
+}
+
+// grid M rows, block <= 1024 (a multiple of 64 covering d/4 (CH = 1) or d/8 (CH = 2) lanes).
+//   EMBED: h[m] = embed[token[m]];  else h[m] += sum_s partials[s][..][m]  (NS partials, summed in split order)
 // then Xp[m] = half(h[m] * rsqrt(mean(h[m]^2) + eps) * gain).  d % 8 == 0, d <= 8192.
-// Every load of a thread (residual, all partials) is issued before the first use, so the kernel costs
-// one memory round trip whatever the split count.
+// A decode step's launch is bound by latency (kilobytes per workgroup, partials that other XCDs wrote): every load of a thread --
+// residual, all partials, the gain -- is issued before the first use, so the kernel costs one memory round trip whatever the
+// split count: 64 rows of 2560, 8 or 9 partials, 4.87 -> 4.80 us (an empty launch takes 3).  Long passes are bound by HBM: 4096 rows
+// of 2560 37.8 -> 29.4 us (14 bytes per element, 5.0 TB/s), of 5120 with two planes 86 -> 77.5 (4.9), for most part by xcd_row.
 constexpr int RN_THREADS = 1024;
-__global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *h, const uint16_t *embed, const int32_t *token,
-                                                                const f32x4 *partials, int nsplit, int Np, uint16_t *Xp,
-                                                                const uint16_t *gain, int Mp, int d, float eps) {
+template <int NS, int CH, bool EMBED>
+__global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restrict__ h, const uint16_t *__restrict__ embed, const int32_t *__restrict__ token,
+                                                                const f32x4 *__restrict__ partials, int Np, uint16_t *__restrict__ Xp,
+                                                                const uint16_t *__restrict__ gain, int Mp, int d, float eps) {
   __shared__ float sh[RN_THREADS / 64];
-  int m = blockIdx.x, d4 = d >> 2;
-  f32x4 v[2];
+  const int m = xcd_row(gridDim.x), d4 = d >> 2;
+  f32x4 v[CH], pp[CH][NS > 0 ? NS : 1];
+  uint2 gn[CH], em[CH];
+  const int tok = EMBED ? token[m] : 0;
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int n4 = min((int)threadIdx.x + c * (int)blockDim.x, d4 - 1);   // lanes past the row repeat its last unit and store nothing
+    if (EMBED) em[c] = *(const uint2 *)(embed + (int64_t)max(tok, 0) * d + n4 * 4);
+    else v[c] = *(const f32x4 *)(h + (int64_t)m * d + n4 * 4);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) pp[c][s] = partials[((int64_t)s * Mp + m) * (Np >> 2) + n4];
+    gn[c] = *(const uint2 *)(gain + n4 * 4);
+  }
+  __builtin_amdgcn_sched_barrier(0);   // the loads above stay ahead of everything below
   float ss = 0.f;
-  int tok = embed ? token[m] : 0;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    int n4 = threadIdx.x + c * (int)blockDim.x;
-    if (n4 >= d4) break;
-    f32x4 a, pp[REDUCE_MAX_SPLIT];
+  for (int c = 0; c < CH; ++c) {
+    const int n4 = threadIdx.x + c * (int)blockDim.x;
+    f32x4 a = v[c];
+    if (EMBED) {
+      const uint2 e = em[c];
+      a = {__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16), __uint_as_float(e.y & 0xffff0000u)};
+      if (tok < 0) a = {0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
-    for (int s = 0; s < REDUCE_MAX_SPLIT; ++s)
-      pp[s] = s < nsplit ? partials[((int64_t)s * Mp + m) * (Np >> 2) + n4] : f32x4{0.f, 0.f, 0.f, 0.f};
-    if (embed) {
-      if (tok >= 0) {
-        uint2 e = *(const uint2 *)(embed + (int64_t)tok * d + n4 * 4);
-        a = {__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
-             __uint_as_float(e.y & 0xffff0000u)};
-      } else a = {0.f, 0.f, 0.f, 0.f};
-    } else a = *(const f32x4 *)(h + (int64_t)m * d + n4 * 4);
-#pragma unroll
-    for (int s = 0; s < REDUCE_MAX_SPLIT; ++s) a += pp[s];
-    *(f32x4 *)(h + (int64_t)m * d + n4 * 4) = a;
+    for (int s = 0; s < NS; ++s) a += pp[c][s];
     v[c] = a;
-    ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
+    if (n4 < d4) {
+      if (EMBED || NS > 0) *(f32x4 *)(h + (int64_t)m * d + n4 * 4) = a;
+      ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
+    }
   }
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
@@ -47,60 +79,74 @@ __global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *h, const 
   for (int i = 0; i < (int)blockDim.x / 64; ++i) ss += sh[i];
   float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    int n4 = threadIdx.x + c * (int)blockDim.x;
-    if (n4 >= d4) break;
-    int n = n4 * 4;
-    uint2 g = *(const uint2 *)(gain + n);
+  for (int c = 0; c < CH; ++c) {
+    const int n4 = threadIdx.x + c * (int)blockDim.x, n = n4 * 4;
+    const uint2 g = gn[c];
     float g0 = __uint_as_float(g.x << 16), g1 = __uint_as_float(g.x & 0xffff0000u);
     float g2 = __uint_as_float(g.y << 16), g3 = __uint_as_float(g.y & 0xffff0000u);
     uint2 o;
     o.x = (uint32_t)f32_to_h16_bits(v[c][0] * inv * g0) | ((uint32_t)f32_to_h16_bits(v[c][1] * inv * g1) << 16);
     o.y = (uint32_t)f32_to_h16_bits(v[c][2] * inv * g2) | ((uint32_t)f32_to_h16_bits(v[c][3] * inv * g3) << 16);
-    *(uint2 *)(Xp + ((int64_t)(n >> 3) * Mp + m) * 8 + (n & 7)) = o;
+    if (n4 < d4) *(uint2 *)(Xp + ((int64_t)(n >> 3) * Mp + m) * 8 + (n & 7)) = o;
   }
 }
 
 void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, const float *partials, int nsplit, int Np,
                      void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, hipStream_t st) {
   if (M <= 0) return;
-  int threads = ((d >> 2) + 63) / 64 * 64;   // one float4 per thread when the row fits, else two
-  if (threads > RN_THREADS) threads = ((d >> 3) + 63) / 64 * 64;
-  hipLaunchKernelGGL(resid_norm_kernel, dim3(M), dim3(threads), 0, st, h, (const uint16_t *)embed_bf16, token,
-                     (const f32x4 *)partials, nsplit, Np, (uint16_t *)Xp, (const uint16_t *)gain_bf16, Mp, d, eps);
+  const int wide = ((d >> 2) + 63) / 64 * 64 <= RN_THREADS ? 1 : 2;   // one float4 per thread when the row fits, else two
+  const int threads = ((d >> (wide + 1)) + 63) / 64 * 64;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(M), dim3(threads), 0, st, h, (const uint16_t *)embed_bf16, token, (const f32x4 *)partials, Np, (uint16_t *)Xp,
+                       (const uint16_t *)gain_bf16, Mp, d, eps);
+  };
+  if (embed_bf16) { if (wide == 1) launch(resid_norm_kernel<0, 1, true>); else launch(resid_norm_kernel<0, 2, true>); return; }
+  with_split_count(nsplit, [&](auto n) {
+    if (wide == 1) launch(resid_norm_kernel<decltype(n)::value, 1, false>);
+    else launch(resid_norm_kernel<decltype(n)::value, 2, false>);
+  });
 }
 
 // grid (M, ceil((Hq + 2*Hkv) / QP_HEADS)), block QP_HEADS * hd/2 with hd/2 <= 64: each group of hd/2 lanes sums the
 // split-K partials of one head of one row, applies the optional per-head RMSNorm and the rotary embedding, and writes
-// q (half [M][Hq][hd]) or appends k / v to the half-precision cache.
+// q (half [M][Hq][hd]) or appends k / v to the half-precision cache.  Bound by latency like resid_norm_kernel: the row's
+// state, the partials, the rotation and the gains are all requested before the first sum, and a row that is not generating
+// only drops its stores.  64 rows, 5 partials of 6144: 5.41 -> 5.19 us.
 constexpr int QP_HEADS = 8;
-__global__ void qkv_post_kernel(const float *partials, int nsplit, int Np, int Mp, uint16_t *q_out, const uint16_t *q_gain,
-                                const uint16_t *k_gain, int qk_norm, float eps, const float2 *rope_cs, RowState rows,
+template <int NS, bool NORM>
+__global__ void qkv_post_kernel(const float *__restrict__ partials, int Np, int Mp, uint16_t *__restrict__ q_out, const uint16_t *__restrict__ q_gain,
+                                const uint16_t *__restrict__ k_gain, float eps, const float2 *__restrict__ rope_cs, RowState rows,
                                 KvGeom kv, int layer, int Hq, int Hkv) {
   int hd = kv.head_dim, half = hd / 2;
   int m = blockIdx.x, j = blockIdx.y * QP_HEADS + threadIdx.x / half, i = threadIdx.x % half;
   if (j >= Hq + 2 * Hkv) return;
   bool is_q = j < Hq, is_k = !is_q && j < Hq + Hkv;
-  if (!is_q && !rows.active[m]) return;
+  int act = rows.active[m], pos = rows.pos[m], slot = rows.slot[m];
   int n0 = j * hd + i, n1 = n0 + half;
-  float a = 0.f, b = 0.f, pa[REDUCE_MAX_SPLIT], pb[REDUCE_MAX_SPLIT];
+  float a = 0.f, b = 0.f, pa[NS], pb[NS];
 #pragma unroll
-  for (int s = 0; s < REDUCE_MAX_SPLIT; ++s) {   // all loads issued before the sums
-    pa[s] = s < nsplit ? partials[((int64_t)s * Mp + m) * Np + n0] : 0.f;
-    pb[s] = s < nsplit ? partials[((int64_t)s * Mp + m) * Np + n1] : 0.f;
+  for (int s = 0; s < NS; ++s) {
+    pa[s] = partials[((int64_t)s * Mp + m) * Np + n0];
+    pb[s] = partials[((int64_t)s * Mp + m) * Np + n1];
   }
+  const float2 cs = rope_cs[(int64_t)m * half + i];
+  uint16_t w0 = 0, w1 = 0;
+  if (NORM) {
+    const uint16_t *g = is_q ? q_gain : k_gain;   // (loaded and not used for a value head)
+    w0 = g[i]; w1 = g[i + half];
+  }
+  __builtin_amdgcn_sched_barrier(0);   // all loads issued before the sums, the row's state among them
+  asm volatile("" : "+s"(act), "+s"(pos), "+s"(slot));
 #pragma unroll
-  for (int s = 0; s < REDUCE_MAX_SPLIT; ++s) { a += pa[s]; b += pb[s]; }
+  for (int s = 0; s < NS; ++s) { a += pa[s]; b += pb[s]; }
   if (is_q || is_k) {
-    if (qk_norm) {
+    if (NORM) {
       float ss = a * a + b * b;   // the head's lanes are an aligned power-of-two group within the wave
       for (int off = half >> 1; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
       float inv = 1.0f / sqrtf(ss / (float)hd + eps);
-      const uint16_t *g = is_q ? q_gain : k_gain;
-      a = a * inv * bf16_bits_to_f32(g[i]);
-      b = b * inv * bf16_bits_to_f32(g[i + half]);
+      a = a * inv * bf16_bits_to_f32(w0);
+      b = b * inv * bf16_bits_to_f32(w1);
     }
-    float2 cs = rope_cs[(int64_t)m * half + i];
     float ra = a * cs.x - b * cs.y, rb = a * cs.y + b * cs.x;
     a = ra; b = rb;
   }
@@ -108,9 +154,9 @@ __global__ void qkv_post_kernel(const float *partials, int nsplit, int Np, int M
     uint16_t *dst = q_out + ((int64_t)m * Hq + j) * hd;
     dst[i] = f32_to_h16_bits(a);
     dst[i + half] = f32_to_h16_bits(b);
-  } else {   // append to the tiled cache
-    int kvh = is_k ? j - Hq : j - Hq - Hkv, pos = rows.pos[m];
-    uint16_t *head = (uint16_t *)kv.base + kv.tiled_head_off(rows.slot[m], layer, kvh);
+  } else if (act) {   // append to the tiled cache
+    int kvh = is_k ? j - Hq : j - Hq - Hkv;
+    uint16_t *head = (uint16_t *)kv.base + kv.tiled_head_off(slot, layer, kvh);
     if (is_k) { head[kv.tiled_k_off(pos, i)] = f32_to_h16_bits(a); head[kv.tiled_k_off(pos, i + half)] = f32_to_h16_bits(b); }
     else { head[kv.tiled_v_off(pos, i)] = f32_to_h16_bits(a); head[kv.tiled_v_off(pos, i + half)] = f32_to_h16_bits(b); }
   }
@@ -122,26 +168,31 @@ __global__ void qkv_post_kernel(const float *partials, int nsplit, int Np, int M
 // of the key tile (a value tile holds eight keys of one dim per unit, so values still leave as single halves).  Same sums in
 // the same order: bit-identical to the kernel above.  grid (M, ceil((Hq + 2*Hkv) / QPW_HEADS)), block QPW_HEADS * hd/8.
 constexpr int QPW_HEADS = 16;
-__global__ void qkv_post_wide_kernel(const float *partials, int nsplit, int Np, int Mp, uint16_t *q_out, const uint16_t *q_gain,
-                                     const uint16_t *k_gain, int qk_norm, float eps, const float2 *rope_cs, RowState rows,
+template <int NS, bool NORM>
+__global__ void qkv_post_wide_kernel(const float *__restrict__ partials, int Np, int Mp, uint16_t *__restrict__ q_out, const uint16_t *__restrict__ q_gain,
+                                     const uint16_t *__restrict__ k_gain, float eps, const float2 *__restrict__ rope_cs, RowState rows,
                                      KvGeom kv, int layer, int Hq, int Hkv) {
   const int hd = kv.head_dim, half = hd / 2, per_head = half / 4;
-  const int m = blockIdx.x, j = blockIdx.y * QPW_HEADS + threadIdx.x / per_head, i = (threadIdx.x % per_head) * 4;
+  const int m = xcd_row(gridDim.x), j = blockIdx.y * QPW_HEADS + threadIdx.x / per_head, i = (threadIdx.x % per_head) * 4;
   if (j >= Hq + 2 * Hkv) return;
   const bool is_q = j < Hq, is_k = !is_q && j < Hq + Hkv;
-  if (!is_q && !rows.active[m]) return;
+  int act = rows.active[m], pos = rows.pos[m], slot = rows.slot[m];
   const int n0 = j * hd + i, n1 = n0 + half;
-  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f}, pa[REDUCE_MAX_SPLIT], pb[REDUCE_MAX_SPLIT];
+  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f}, pa[NS], pb[NS];
 #pragma unroll
-  for (int s = 0; s < REDUCE_MAX_SPLIT; ++s) {   // all loads issued before the sums
+  for (int s = 0; s < NS; ++s) {
     const float *row = partials + ((int64_t)s * Mp + m) * Np;
-    pa[s] = s < nsplit ? *(const f32x4 *)(row + n0) : f32x4{0.f, 0.f, 0.f, 0.f};
-    pb[s] = s < nsplit ? *(const f32x4 *)(row + n1) : f32x4{0.f, 0.f, 0.f, 0.f};
+    pa[s] = *(const f32x4 *)(row + n0);
+    pb[s] = *(const f32x4 *)(row + n1);
   }
+  const f32x4 *cs = (const f32x4 *)(rope_cs + (int64_t)m * half + i);
+  const f32x4 c01 = cs[0], c23 = cs[1];
+  __builtin_amdgcn_sched_barrier(0);   // all loads issued before the sums
+  asm volatile("" : "+s"(act), "+s"(pos), "+s"(slot));
 #pragma unroll
-  for (int s = 0; s < REDUCE_MAX_SPLIT; ++s) { a += pa[s]; b += pb[s]; }
+  for (int s = 0; s < NS; ++s) { a += pa[s]; b += pb[s]; }
   if (is_q || is_k) {
-    if (qk_norm) {
+    if (NORM) {
       // Summed in the order of the one-pair-per-lane kernel, whose tree adds lane i ^ off to lane i for off = half/2 .. 1:
       // its lanes 4q .. 4q+3 sit in this thread, so its offsets >= 4 are shuffles over the head's threads, element by
       // element, and its offsets 2 and 1 are the local sums at the end.
@@ -158,8 +209,6 @@ __global__ void qkv_post_wide_kernel(const float *partials, int nsplit, int Np, 
 #pragma unroll
       for (int e = 0; e < 4; ++e) { a[e] = a[e] * inv * bf16_bits_to_f32(g[i + e]); b[e] = b[e] * inv * bf16_bits_to_f32(g[i + e + half]); }
     }
-    const f32x4 *cs = (const f32x4 *)(rope_cs + (int64_t)m * half + i);
-    const f32x4 c01 = cs[0], c23 = cs[1];
     const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, sy[4] = {c01[1], c01[3], c23[1], c23[3]};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -176,9 +225,9 @@ __global__ void qkv_post_wide_kernel(const float *partials, int nsplit, int Np, 
     uint16_t *dst = q_out + ((int64_t)m * Hq + j) * hd;
     *(uint2 *)(dst + i) = ha;
     *(uint2 *)(dst + i + half) = hb;
-  } else {
-    const int kvh = is_k ? j - Hq : j - Hq - Hkv, pos = rows.pos[m];
-    uint16_t *head = (uint16_t *)kv.base + kv.tiled_head_off(rows.slot[m], layer, kvh);
+  } else if (act) {
+    const int kvh = is_k ? j - Hq : j - Hq - Hkv;
+    uint16_t *head = (uint16_t *)kv.base + kv.tiled_head_off(slot, layer, kvh);
     if (is_k) {   // four dims of one 8-dim unit of the key
       *(uint2 *)(head + kv.tiled_k_off(pos, i)) = ha;
       *(uint2 *)(head + kv.tiled_k_off(pos, i + half)) = hb;
@@ -195,15 +244,21 @@ __global__ void qkv_post_wide_kernel(const float *partials, int nsplit, int Np, 
 void fast_qkv_post(const float *partials, int nsplit, int Np, int Mp, void *q_h16, const void *q_gain, const void *k_gain,
                    int qk_norm, float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv,
                    hipStream_t st) {
-  if (M >= 256) {
-    hipLaunchKernelGGL(qkv_post_wide_kernel, dim3(M, (Hq + 2 * Hkv + QPW_HEADS - 1) / QPW_HEADS), dim3(QPW_HEADS * kv.head_dim / 8), 0, st, partials,
-                       nsplit, Np, Mp, (uint16_t *)q_h16, (const uint16_t *)q_gain, (const uint16_t *)k_gain, qk_norm, eps,
-                       (const float2 *)rope_cs, rows, kv, layer, Hq, Hkv);
-    return;
-  }
-  hipLaunchKernelGGL(qkv_post_kernel, dim3(M, (Hq + 2 * Hkv + QP_HEADS - 1) / QP_HEADS), dim3(QP_HEADS * kv.head_dim / 2), 0, st, partials, nsplit, Np, Mp,
-                     (uint16_t *)q_h16, (const uint16_t *)q_gain, (const uint16_t *)k_gain, qk_norm, eps,
-                     (const float2 *)rope_cs, rows, kv, layer, Hq, Hkv);
+  const int heads = Hq + 2 * Hkv, hd = kv.head_dim;
+  auto launch = [&](auto kernel, int per_wg, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(M, (heads + per_wg - 1) / per_wg), dim3(threads), 0, st, partials, Np, Mp, (uint16_t *)q_h16,
+                       (const uint16_t *)q_gain, (const uint16_t *)k_gain, eps, (const float2 *)rope_cs, rows, kv, layer, Hq, Hkv);
+  };
+  with_split_count(nsplit, [&](auto n) {
+    constexpr int NS = decltype(n)::value > 0 ? decltype(n)::value : 1;   // (a projection leaves at least one plane)
+    if (M >= 256) {
+      if (qk_norm) launch(qkv_post_wide_kernel<NS, true>, QPW_HEADS, QPW_HEADS * hd / 8);
+      else launch(qkv_post_wide_kernel<NS, false>, QPW_HEADS, QPW_HEADS * hd / 8);
+    } else {
+      if (qk_norm) launch(qkv_post_kernel<NS, true>, QP_HEADS, QP_HEADS * hd / 2);
+      else launch(qkv_post_kernel<NS, false>, QP_HEADS, QP_HEADS * hd / 2);
+    }
+  });
 }
 
 // ---- nucleus (top-p) sampling over materialised logits ---------------------------------------------------------
