@@ -57,7 +57,8 @@ void launch_bookkeeping(int N, int max_new, int per_row /*1: a row's step is its
                         const int32_t *forced, const int32_t *limit, int eos, int64_t version,
                         const int32_t *prompt_len, int32_t *gen_len, RowState rows, int32_t *out_tok,
                         float *out_lp, int64_t *out_ver, int32_t *n_active, hipStream_t st);
-void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len /*[P]*/, int P, int G, hipStream_t st);
+// cut_only (tiled cache): only the tile that a prompt fills in part; for batches whose rows read the whole prompt tiles from slot p*G.
+void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len /*[P]*/, int P, int G, int cut_only, hipStream_t st);
 void launch_draw_bits(uint32_t *out, uint64_t seed, uint32_t n, uint32_t s, uint32_t i0, int count, hipStream_t st);
 // quads: device [n_quads][4] = (src slot, dst slot, begin, end); copies keys [begin, end) (plain cache) or whole tiles
 // of 32 keys [begin, end) (tiled cache) of every layer and head from the source slot to the destination slot.

@@ -67,23 +67,24 @@ void launch_bookkeeping(int N, int max_new, int per_row, int32_t *d_step, const 
 
 // Copy the prompt part of slot p*G into slots p*G+1 .. p*G+G-1.  grid = (chunks, regions per slot, P*(G-1)).
 // Plain form: a region is one head's K or V plane and the prompt is its first prompt_len rows.  Tiled form: a region
-// is one head's K and V tiles and the prompt is its first ceil(prompt_len/32) tiles.
-__global__ void kv_replicate_kernel(KvGeom kv, const int32_t *prompt_len, int G) {
+// is one head's K and V tiles and the prompt is its first ceil(prompt_len/32) tiles; with cut_only just the tile that the
+// prompt fills in part, which every sequence goes on writing in its own slot -- the whole ones are read from slot p*G.
+__global__ void kv_replicate_kernel(KvGeom kv, const int32_t *prompt_len, int G, int cut_only) {
   int p = blockIdx.z / (G - 1), g = blockIdx.z % (G - 1) + 1;
-  int64_t region_bytes = kv.head_stride() * kv.elt_bytes * (kv.tiled ? 2 : 1);
-  int64_t bytes = kv.tiled ? (int64_t)((prompt_len[p] + 31) / 32) * 64 * kv.head_dim * kv.elt_bytes
-                           : (int64_t)prompt_len[p] * kv.head_dim * kv.elt_bytes;
-  const char *src = (const char *)kv.base + ((int64_t)p * G) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes;
-  char *dst = (char *)kv.base + ((int64_t)p * G + g) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes;
-  int64_t n16 = bytes / 16;  // head_dim * elt_bytes is a multiple of 16
+  int64_t region_bytes = kv.head_stride() * kv.elt_bytes * (kv.tiled ? 2 : 1), tile_bytes = (int64_t)64 * kv.head_dim * kv.elt_bytes;
+  int64_t bytes = kv.tiled ? (prompt_len[p] + 31) / 32 * tile_bytes : (int64_t)prompt_len[p] * kv.head_dim * kv.elt_bytes;
+  int64_t skip = cut_only ? prompt_len[p] / 32 * tile_bytes : 0;
+  const char *src = (const char *)kv.base + ((int64_t)p * G) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + skip;
+  char *dst = (char *)kv.base + ((int64_t)p * G + g) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + skip;
+  int64_t n16 = (bytes - skip) / 16;  // head_dim * elt_bytes is a multiple of 16
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
     ((uint4 *)dst)[i] = ((const uint4 *)src)[i];
 }
 
-void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len, int P, int G, hipStream_t st) {
+void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len, int P, int G, int cut_only, hipStream_t st) {
   if (G <= 1 || P <= 0) return;
-  int regions = kv.n_layers * kv.n_kv_heads * (kv.tiled ? 1 : 2);
-  hipLaunchKernelGGL(kv_replicate_kernel, dim3(8, regions, P * (G - 1)), dim3(256), 0, st, kv, prompt_len, G);
+  int regions = kv.n_layers * kv.n_kv_heads * (kv.tiled ? 1 : 2), chunks = cut_only ? kv.head_dim / 32 : 8;   // cut_only: one tile, four units per thread
+  hipLaunchKernelGGL(kv_replicate_kernel, dim3(chunks, regions, P * (G - 1)), dim3(256), 0, st, kv, prompt_len, G, cut_only);
 }
 
 // Copy part of one cache slot's prompt into another slot, for a list of (src slot, dst slot, begin, end) quadruples.
