@@ -411,9 +411,10 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
   if (!p.fast) {
     int bf = d.dtype == ECHO_BF16;
     dbg_gemm(logits, at<float>(c, p.o_x), S.lm_head, bf, M, d.vocab, d.hidden, 0, st);
-    if (top_p < 1.0f) nucleus(c, logits, d.vocab, M, temperature, top_p, seed);
-    else dbg_sample(c->d_samp_tok, c->d_samp_lp, logits, d.vocab, M, d.vocab, temperature, seed, c->ids, nullptr, st);
+    // (a scoring pass may have more rows than the sampler's scratch holds; it wants no token)
     if (target) dbg_target_logprob(c->d_target_lp, logits, d.vocab, M, d.vocab, temperature, target, st);
+    else if (top_p < 1.0f) nucleus(c, logits, d.vocab, M, temperature, top_p, seed);
+    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), pad_rows(M), logits, d.vocab, M, d.vocab, temperature, seed, c->ids, nullptr, st);
     return;
   }
   int Mp = pad_rows(M);
@@ -422,9 +423,9 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
       TimerScope t(c, &c->ev_gemm);
       fast_lmhead_logits(logits, p.Np_v, at<void>(c, p.o_xa), S.lm_head, Mp, p.Np_v, p.Kp_d, d.vocab, st);
     }
-    if (top_p < 1.0f) nucleus(c, logits, p.Np_v, M, temperature, top_p, seed);
-    else dbg_sample(c->d_samp_tok, c->d_samp_lp, logits, p.Np_v, M, d.vocab, temperature, seed, c->ids, nullptr, st);
     if (target) dbg_target_logprob(c->d_target_lp, logits, p.Np_v, M, d.vocab, temperature, target, st);
+    else if (top_p < 1.0f) nucleus(c, logits, p.Np_v, M, temperature, top_p, seed);
+    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), Mp, logits, p.Np_v, M, d.vocab, temperature, seed, c->ids, nullptr, st);
   } else {
     TimerScope t(c, &c->ev_gemm);
     fast_lmhead_sample(c->d_samp_tok, c->d_samp_lp, c->d_target_lp, at<void>(c, p.o_xa), S.lm_head, Mp, M, d.vocab, p.Np_v, p.Kp_d,

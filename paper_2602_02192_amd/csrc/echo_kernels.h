@@ -90,8 +90,9 @@ void dbg_qkv_post(float *qkv /*[M][(Hq+2Hkv)*hd], q rotated in place*/, const vo
 void dbg_attention(float *out /*[M][Hq*hd]*/, const float *qkv, RowState rows, KvGeom kv, int layer, int M, int Hq,
                    int Hkv, hipStream_t st);
 void dbg_swiglu(float *ff /*[M][F]*/, const float *gu /*[M][2F] = gate | up*/, int M, int F, hipStream_t st);
-// Unfused sampler over materialised logits [M][ld]: Gumbel-max token and its log-softmax, in fp32.
-void dbg_sample(int32_t *tok, float *lp, const float *logits, int64_t ld, int M, int V, float temperature,
+// Unfused sampler over materialised logits [M][ld]: Gumbel-max token and its log-softmax, in fp32.  scratch: the buffer of
+// fast_topp_cut_and_draw (fast_topp_scratch_floats(Mp) floats).
+void dbg_sample(int32_t *tok, float *lp, float *scratch, int Mp, const float *logits, int64_t ld, int M, int V, float temperature,
                 uint64_t seed, DrawIds ids, const int32_t *row_active, hipStream_t st);
 // log softmax(logits/T)[target[m]] per row (teacher-forced scoring).
 void dbg_target_logprob(float *lp, const float *logits, int64_t ld, int M, int V, float temperature,

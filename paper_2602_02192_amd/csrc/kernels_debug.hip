@@ -160,16 +160,20 @@ void dbg_swiglu(float *ff, const float *gu, int M, int F, hipStream_t st) {
   hipLaunchKernelGGL(dbg_swiglu_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ff, gu, M, F);
 }
 
-// One block of 256 threads per row: Gumbel-max token and log softmax(z)[token] from materialised logits.
-__global__ void dbg_sample_kernel(int32_t *tok, float *lp, const float *logits, int64_t ld, int V, float temperature,
+// grid (slices, M), block 256: Gumbel-max token and log softmax(z)[token] from materialised logits, every entry evaluated in
+// full.  One slice per row: the token and its log-prob; more: the slice's running state, in the partial layout of the fused
+// sampler.  The serial chain of a thread (two logf, an expf and a division per entry) bounds it, so a large vocabulary is cut into
+// slices: 151936 entries, 6 rows: 245 -> 21 us, and 4 us for the merge.
+__global__ void dbg_sample_kernel(int32_t *tok, float *lp, float *part, int Mp, const float *logits, int64_t ld, int V, float temperature,
                                   uint64_t seed, DrawIds ids, const int32_t *row_active) {
   __shared__ SampleAcc sh[4];
-  int m = blockIdx.x;
+  const int c = blockIdx.x, slices = gridDim.x, m = blockIdx.y;
   if (row_active && !row_active[m]) return;
   const uint32_t s = draw_step(ids, m), stream = draw_stream(ids, m);
+  const int v4 = (V + 3) / 4, per = (v4 + slices - 1) / slices, e4 = min(v4, (c + 1) * per);
   SampleAcc a = sample_acc_init();
   const float *lg = logits + (int64_t)m * ld;
-  for (int i4 = threadIdx.x; i4 * 4 < V; i4 += blockDim.x) {
+  for (int i4 = c * per + threadIdx.x; i4 < e4; i4 += blockDim.x) {
     u32x4 r = draw4(seed, stream, s, (uint32_t)i4);
     uint32_t w[4] = {r.x, r.y, r.z, r.w};
     for (int e = 0; e < 4; ++e) {
@@ -184,15 +188,26 @@ __global__ void dbg_sample_kernel(int32_t *tok, float *lp, const float *logits, 
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) sample_acc_merge(a, sh[w]);
-    tok[m] = a.idx;
-    lp[m] = a.zbest - (a.zmax + logf(a.zsum));
+    if (slices == 1) {
+      tok[m] = a.idx;
+      lp[m] = a.zbest - (a.zmax + logf(a.zsum));
+    } else {
+      const int64_t o = (int64_t)c * Mp + m, plane = (int64_t)slices * Mp;
+      part[o] = a.zmax;
+      part[plane + o] = a.zsum;
+      part[2 * plane + o] = a.best;
+      part[3 * plane + o] = a.zbest;
+      part[4 * plane + o] = __int_as_float(a.idx);
+    }
   }
 }
 
-void dbg_sample(int32_t *tok, float *lp, const float *logits, int64_t ld, int M, int V, float temperature, uint64_t seed,
+void dbg_sample(int32_t *tok, float *lp, float *scratch, int Mp, const float *logits, int64_t ld, int M, int V, float temperature, uint64_t seed,
                 DrawIds ids, const int32_t *row_active, hipStream_t st) {
-  hipLaunchKernelGGL(dbg_sample_kernel, dim3(M), dim3(256), 0, st, tok, lp, logits, ld, V, temperature, seed, ids,
-                     row_active);
+  // a second launch (about 5 us) pays once a thread has more than a few entries (of 4) to itself
+  const int slices = V > 8192 ? TOPP_CHUNKS_PER_ROW : 1;
+  hipLaunchKernelGGL(dbg_sample_kernel, dim3(slices, M), dim3(256), 0, st, tok, lp, scratch, Mp, logits, ld, V, temperature, seed, ids, row_active);
+  if (slices > 1) fast_sample_combine(tok, lp, scratch, slices, M, Mp, row_active, st);
 }
 
 __global__ void dbg_target_logprob_kernel(float *lp, const float *logits, int64_t ld, int V, float temperature,

@@ -141,13 +141,13 @@ __global__ void qkv_post_kernel(const float *__restrict__ partials, int Np, int 
   for (int s = 0; s < NS; ++s) { a += pa[s]; b += pb[s]; }
   if (is_q || is_k) {
     if (NORM) {
-      float ss = a * a + b * b;   // the head's lanes are an aligned power-of-two group within the wave
+      float ss = fmaf(a, a, b * b);   // (written out here and in the wide kernel, which must round alike) the head's lanes are an aligned power-of-two group within the wave
       for (int off = half >> 1; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
       float inv = 1.0f / sqrtf(ss / (float)hd + eps);
       a = a * inv * bf16_bits_to_f32(w0);
       b = b * inv * bf16_bits_to_f32(w1);
     }
-    float ra = a * cs.x - b * cs.y, rb = a * cs.y + b * cs.x;
+    float ra = fmaf(a, cs.x, -(b * cs.y)), rb = fmaf(a, cs.y, b * cs.x);
     a = ra; b = rb;
   }
   if (is_q) {
@@ -198,7 +198,7 @@ __global__ void qkv_post_wide_kernel(const float *__restrict__ partials, int Np,
       // element, and its offsets 2 and 1 are the local sums at the end.
       float t[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] = a[e] * a[e] + b[e] * b[e];
+      for (int e = 0; e < 4; ++e) t[e] = fmaf(a[e], a[e], b[e] * b[e]);
       for (int off = per_head >> 1; off > 0; off >>= 1) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) t[e] += __shfl_xor(t[e], off);
@@ -212,7 +212,7 @@ __global__ void qkv_post_wide_kernel(const float *__restrict__ partials, int Np,
     const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, sy[4] = {c01[1], c01[3], c23[1], c23[3]};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float ra = a[e] * cx[e] - b[e] * sy[e], rb = a[e] * sy[e] + b[e] * cx[e];
+      float ra = fmaf(a[e], cx[e], -(b[e] * sy[e])), rb = fmaf(a[e], sy[e], b[e] * cx[e]);
       a[e] = ra; b[e] = rb;
     }
   }

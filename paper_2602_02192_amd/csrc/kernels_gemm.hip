@@ -1046,8 +1046,8 @@ constexpr int LM_DUMP_FLOATS = 16 * 64;   // sample_lane's LDS, per wavefront
 // sampler epilogue moves no weights.  With two workgroups resident per compute unit one's epilogue and first loads run
 // under the other's weight stream: 64 rows 199 -> 146 us, 32 rows 158 -> 133 us.  That needs the kernel inside 256 registers
 // per lane, which a two-chunk weight pipeline allows (three chunks in flight fit only at 32 rows).  With only the winner
-// of a lane's entries evaluated in full (sample_lane): 64 rows 137 -> 125 us, 32 rows 120.7 -> 117.5 us.  The logits forms of 128
-// and 256 rows have no long epilogue to hide and are faster alone on the unit with deeper pipelines.
+// of a lane's entries evaluated in full (sample_lane): 64 rows 137 -> 125 us, 32 rows 120.7 -> 117.5 us.  The logits form of 128
+// rows has no long epilogue to hide and is faster alone on the unit with a deeper pipeline.
 template <int MB> constexpr int lm_wgs_per_cu() { return MB <= 2 ? 2 : 1; }
 
 template <int MB, int NSTAGE, bool LOGITS>
@@ -1231,7 +1231,6 @@ static void lmhead_dispatch(const void *Xp, const void *Wp, int Mp, int Np, int 
   int mbt = Mp / 32;
 #define LM_ARGS Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, part, logits, ld, st
   if constexpr (LOGITS) {
-    if (mbt >= 8) { lmhead_launch<8, 2, LOGITS>(LM_ARGS); return; }
     if (mbt == 4) { lmhead_launch<4, 3, LOGITS>(LM_ARGS); return; }
   }
   if (mbt == 2) lmhead_launch<2, 2, LOGITS>(LM_ARGS);
@@ -1260,6 +1259,9 @@ void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts
 
 void fast_lmhead_logits(float *logits, int64_t ld, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V,
                         hipStream_t st) {
+  // 256 rows, vocabulary 151936, hidden 2560: 236 us on 256 x 256 ring tiles (128 x 128: 278, the LDS-staged kernel: 296); 128 rows are
+  // level (186 us either way).
+  if (Mp % 256 == 0 && ld == Np) { gemm_ring_launch<Ring256x256, EPI_PARTIAL>(logits, Xp, Wp, Mp, Np, Kp, 1, st); return; }
   lmhead_dispatch<true>(Xp, Wp, Mp, Np, Kp, V, 1.0f, 0, DrawIds{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, logits, ld, st);
 }
 
