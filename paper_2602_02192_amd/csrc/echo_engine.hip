@@ -197,6 +197,7 @@ void echo_destroy(echo_ctx *c) {
   for (hipGraphExec_t g : c->retired_graphs) hipGraphExecDestroy(g);
   if (c->staged_ev) hipEventDestroy(c->staged_ev);
   for (int s = 0; s < 2; ++s) if (c->vacated_ev[s]) hipEventDestroy(c->vacated_ev[s]);
+  if (c->pin) hipHostFree(c->pin);
   if (c->own_cs) hipStreamDestroy(c->cs);
   if (c->own_ks) hipStreamDestroy(c->ks);
   delete c;

@@ -221,6 +221,12 @@ struct echo_ctx {
   PrefixPlan px{nullptr, 0, 0, 1};       // shared-prompt attention jobs of the running rollout (n_jobs = 0: none)
   hipGraphExec_t graph = nullptr;
   std::vector<hipGraphExec_t> retired_graphs;   // replaced while replays of them may still be queued; destroyed once the stream is idle
+  // pinned host memory of a continuous rollout: row state in, row state out, slot lists, records (allocated by the first one,
+  // freed with the context)
+  char *pin = nullptr;
+  int32_t *pin_in = nullptr, *pin_out = nullptr, *pin_list = nullptr;
+  char *pin_rec = nullptr;
+  size_t pin_rec_bytes = 0;
   // kernel timing (time_kernels)
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_attn, ev_gemm;
   bool timing = false;

@@ -59,6 +59,16 @@ void launch_bookkeeping(int N, int max_new, int per_row /*1: a row's step is its
                         float *out_lp, int64_t *out_ver, int32_t *n_active, hipStream_t st);
 // cut_only (tiled cache): only the tile that a prompt fills in part; for batches whose rows read the whole prompt tiles from slot p*G.
 void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len /*[P]*/, int P, int G, int cut_only, hipStream_t st);
+// Row state and records of a continuous rollout between the device and pinned host memory (host pointers below are pinned and
+// read or written by the kernel itself: valid, or free again, once the stream has been waited for).
+struct SeqState { int32_t *prompt_len, *gen_len, *limit, *stream; };   // device arrays, one entry per row
+void launch_rows_to_host(int32_t *host /*[4][n]: token, pos, active, gen_len*/, RowState rows, const int32_t *gen_len, int n, hipStream_t st);
+void launch_rows_from_host(const int32_t *host /*[10][n]: token, pos, active, slot, pslot, ptiles, prompt_len, gen_len, limit, stream*/, RowState rows,
+                           SeqState seq, int n, hipStream_t st);
+void launch_records_to_host(char *host /*[n][16 * max_new] bytes: versions, tokens, log-probs*/, const int32_t *slots /*host [n]*/, int n, int max_new,
+                            const int32_t *tok, const float *lp, const int64_t *ver, hipStream_t st);
+void launch_records_begin(const int32_t *slots /*host [n]*/, int n, int max_new, int32_t *tok, float *lp, int64_t *ver, int32_t *forced_dst,
+                          const int32_t *forced /*host [n][max_new] or null*/, hipStream_t st);
 void launch_draw_bits(uint32_t *out, uint64_t seed, uint32_t n, uint32_t s, uint32_t i0, int count, hipStream_t st);
 // quads: device [n_quads][4] = (src slot, dst slot, begin, end); copies keys [begin, end) (plain cache) or whole tiles
 // of 32 keys [begin, end) (tiled cache) of every layer and head from the source slot to the destination slot.

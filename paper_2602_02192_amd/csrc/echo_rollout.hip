@@ -125,6 +125,16 @@ int check_rollout_args(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt
   return ECHO_OK;
 }
 
+// The pinned host memory of continuous rollouts (call with the rollout marked as running: one at a time per context).
+int ensure_pinned(echo_ctx *c) {
+  if (c->pin) return 0;
+  const size_t n = (size_t)round_up(c->d.max_seqs, 64);
+  c->pin_rec_bytes = std::max((size_t)4 << 20, (size_t)16 * c->d.max_ctx);   // at least one record of the longest kind
+  HIPCHK(c, hipHostMalloc((void **)&c->pin, (4 + 10 + 1) * n * 4 + c->pin_rec_bytes, hipHostMallocDefault));
+  c->pin_in = (int32_t *)c->pin; c->pin_out = c->pin_in + 4 * n; c->pin_list = c->pin_out + 10 * n; c->pin_rec = (char *)(c->pin_list + n);
+  return 0;
+}
+
 // Marks the context as running a rollout for the lifetime of the object; begin() fails when it cannot start.  When the
 // rollout ends a staged snapshot becomes the active one and the samplers' draw ids return to their default.
 struct RolloutGuard {
@@ -457,6 +467,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   if ((rc = guard.begin())) return rc;
 
   HIPCHK(c, hipSetDevice(c->device));
+  if ((rc = ensure_pinned(c))) return rc;
   const Plan &p = c->p;
   hipStream_t st = c->cs;
   auto t0 = std::chrono::steady_clock::now();
@@ -481,13 +492,16 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   int32_t *d_out_tok = at<int32_t>(c, p.o_out_tok);
   float *d_out_lp = at<float>(c, p.o_out_lp);
   int64_t *d_out_ver = at<int64_t>(c, p.o_out_ver);
+  const SeqState seq_state{c->d_prompt_len_seq, c->d_gen_len, c->d_limit, c->d_stream};
+  // (the pinned buffer is free to rewrite: the stream is waited for between any two uploads)
   auto upload_rows = [&]() -> int {
-    struct { int32_t *dst; std::vector<int32_t> *src; } cp[] = {
-        {c->rows.token, &tok}, {c->rows.pos, &pos}, {c->rows.active, &act}, {c->rows.slot, &slot}, {c->rows.pslot, &pslot},
-        {c->rows.ptiles, &ptiles}, {c->d_prompt_len_seq, &plen}, {c->d_gen_len, &gen}, {c->d_limit, &lim}, {c->d_stream, &stream}};
-    for (auto &x : cp) HIPCHK(c, hipMemcpyAsync(x.dst, x.src->data(), (size_t)R * 4, hipMemcpyHostToDevice, st));   // R: also the rows given up
+    const std::vector<int32_t> *src[10] = {&tok, &pos, &act, &slot, &pslot, &ptiles, &plen, &gen, &lim, &stream};
+    for (int a = 0; a < 10; ++a) memcpy(c->pin_out + (size_t)a * R, src[a]->data(), (size_t)R * 4);   // R: also the rows given up
+    launch_rows_from_host(c->pin_out, c->rows, seq_state, R, st);
+    HIPCHK(c, hipGetLastError());
     return 0;
   };
+  const int rec_cap = std::max(1, (int)std::min<size_t>(R, c->pin_rec_bytes / ((size_t)16 * max_new)));   // records that fit the pinned buffer
   auto limit_of = [&](int n) { return o.stop_lens ? std::max(1, std::min(max_new, o.stop_lens[n])) : max_new; };
   launch_fill_i32(c->d_step, 0, 1, st);
   c->ids = DrawIds{c->d_step, c->d_gen_len, c->d_stream};
@@ -501,25 +515,35 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   for (;;) {
     if (until_check <= 0) {
       if (!first) {
-        HIPCHK(c, hipMemcpyAsync(tok.data(), c->rows.token, (size_t)Rc * 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipMemcpyAsync(pos.data(), c->rows.pos, (size_t)Rc * 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipMemcpyAsync(act.data(), c->rows.active, (size_t)Rc * 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipMemcpyAsync(gen.data(), c->d_gen_len, (size_t)Rc * 4, hipMemcpyDeviceToHost, st));
+        launch_rows_to_host(c->pin_in, c->rows, c->d_gen_len, Rc, st);
         HIPCHK(c, hipStreamSynchronize(st));
+        memcpy(tok.data(), c->pin_in, (size_t)Rc * 4);
+        memcpy(pos.data(), c->pin_in + Rc, (size_t)Rc * 4);
+        memcpy(act.data(), c->pin_in + 2 * (size_t)Rc, (size_t)Rc * 4);
+        memcpy(gen.data(), c->pin_in + 3 * (size_t)Rc, (size_t)Rc * 4);
       }
       first = false;
       // a sequence that has ended hands its record over
-      for (int r = 0; r < Rc; ++r) {
-        int n = row_seq[r];
-        if (n < 0 || act[r]) continue;
-        int64_t r0 = (int64_t)slot[r] * max_new, n0 = (int64_t)n * max_new;
-        HIPCHK(c, hipMemcpyAsync(out_tokens + n0, d_out_tok + r0, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipMemcpyAsync(out_logprobs + n0, d_out_lp + r0, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
-        if (out_versions) HIPCHK(c, hipMemcpyAsync(out_versions + n0, d_out_ver + r0, (size_t)max_new * 8, hipMemcpyDeviceToHost, st));
-        out_lens[n] = gen[r];
-        row_seq[r] = -1;
-        --group_left[n / G];
-        ++done_seqs;
+      std::vector<int> ended;
+      for (int r = 0; r < Rc; ++r)
+        if (row_seq[r] >= 0 && !act[r]) ended.push_back(r);
+      for (size_t e0 = 0; e0 < ended.size(); e0 += rec_cap) {
+        const int ne = (int)std::min<size_t>(rec_cap, ended.size() - e0);
+        for (int q = 0; q < ne; ++q) c->pin_list[q] = slot[ended[e0 + q]];
+        launch_records_to_host(c->pin_rec, c->pin_list, ne, max_new, d_out_tok, d_out_lp, d_out_ver, st);
+        HIPCHK(c, hipStreamSynchronize(st));
+        for (int q = 0; q < ne; ++q) {
+          const int r = ended[e0 + q], n = row_seq[r];
+          const int64_t n0 = (int64_t)n * max_new;
+          const char *rec = c->pin_rec + (size_t)q * 16 * max_new;
+          if (out_versions) memcpy(out_versions + n0, rec, (size_t)max_new * 8);
+          memcpy(out_tokens + n0, rec + (size_t)8 * max_new, (size_t)max_new * 4);
+          memcpy(out_logprobs + n0, rec + (size_t)12 * max_new, (size_t)max_new * 4);
+          out_lens[n] = gen[r];
+          row_seq[r] = -1;
+          --group_left[n / G];
+          ++done_seqs;
+        }
       }
       if (done_seqs == N) break;
       // its row is free again, unless the cache slot still holds the prompt tiles that running siblings read
@@ -572,16 +596,20 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
           launch_kv_copy_ranges(c->kv, c->d_map_a, nq, st);
           HIPCHK(c, hipStreamSynchronize(st));   // the list is rewritten by the next round
         }
+        // the new sequences' records start empty (the pinned buffer holds as many forced token strings as records)
+        std::vector<std::pair<int, int>> fresh;   // cache slot, sequence
         for (Admit &ad : admitted)
-          for (int g = 0; g < G; ++g) {
-            int64_t r0 = (int64_t)slot[ad.rows[g]] * max_new;
-            launch_fill_i32(d_out_tok + r0, -1, max_new, st);
-            launch_fill_i32((int32_t *)(d_out_lp + r0), 0, max_new, st);
-            launch_fill_i32((int32_t *)(d_out_ver + r0), -1, (int64_t)max_new * 2, st);
-            if (d_forced)
-              HIPCHK(c, hipMemcpyAsync(d_forced + r0, o.forced_tokens + (int64_t)(ad.prompt * G + g) * max_new, (size_t)max_new * 4,
-                                       hipMemcpyHostToDevice, st));
+          for (int g = 0; g < G; ++g) fresh.push_back({slot[ad.rows[g]], ad.prompt * G + g});
+        for (size_t f0 = 0; f0 < fresh.size(); f0 += rec_cap) {
+          const int nf = (int)std::min<size_t>(rec_cap, fresh.size() - f0);
+          int32_t *forced_in = d_forced ? (int32_t *)c->pin_rec : nullptr;
+          for (int q = 0; q < nf; ++q) {
+            c->pin_list[q] = fresh[f0 + q].first;
+            if (d_forced) memcpy(forced_in + (size_t)q * max_new, o.forced_tokens + (int64_t)fresh[f0 + q].second * max_new, (size_t)max_new * 4);
           }
+          launch_records_begin(c->pin_list, nf, max_new, d_out_tok, d_out_lp, d_out_ver, d_forced, forced_in, st);
+          HIPCHK(c, hipStreamSynchronize(st));   // the list and the strings are rewritten
+        }
         dirty = true;   // the upload below also restores the rows the prefill pass used as its own
         admit_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - a0).count();
       }
@@ -619,7 +647,6 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
         if ((rc = plan_prefix_jobs(c, ptiles, pslot, live, Rc, share_prefix ? (max_pl - 1) / 32 : 0, Rc / 2 + 1, o.prefix_kernel))) return rc;
         if (was.n_jobs != c->px.n_jobs || was.np != c->px.np || was.tiles_per_chunk != c->px.tiles_per_chunk) have_graph = false;
         if ((rc = upload_rows())) return rc;
-        HIPCHK(c, hipStreamSynchronize(st));
         dirty = false;
       }
       // the next event: with stop lengths only, the step at which the next sequence ends is known

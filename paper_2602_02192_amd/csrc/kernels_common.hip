@@ -1,5 +1,7 @@
 // Small kernels used by both the debug (fp32) and the MFMA (bf16) path: rotary table, per-step
 // bookkeeping, KV replication across a group, generator read-out, fills and row gathers.
+#include <algorithm>
+
 #include "echo_device.h"
 #include "echo_kernels.h"
 
@@ -107,6 +109,68 @@ void launch_kv_copy_ranges(KvGeom kv, const int32_t *quads, int n_quads, hipStre
   if (n_quads <= 0) return;
   int regions = kv.n_layers * kv.n_kv_heads * (kv.tiled ? 1 : 2);
   hipLaunchKernelGGL(kv_copy_range_kernel, dim3(8, regions, n_quads), dim3(256), 0, st, kv, quads);
+}
+
+// ---- row state and records between the device and pinned host memory ----------------------------------------------
+// A continuous rollout reads the row state back, hands finished records over, opens new ones and uploads the row state at almost
+// every step: each of these is one kernel that reads or writes pinned host memory itself, where a copy per array and per record
+// cost the stream some 10 us each (4 + 3 per record + 4 per new sequence + 10 copies or fills).
+// host [4][n]: token, position, active, generated length.
+__global__ void rows_to_host_kernel(int32_t *host, RowState rows, const int32_t *gen_len, int n) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= n) return;
+  host[r] = rows.token[r]; host[n + r] = rows.pos[r]; host[2 * n + r] = rows.active[r]; host[3 * n + r] = gen_len[r];
+}
+
+void launch_rows_to_host(int32_t *host, RowState rows, const int32_t *gen_len, int n, hipStream_t st) {
+  if (n > 0) hipLaunchKernelGGL(rows_to_host_kernel, dim3((n + 255) / 256), dim3(256), 0, st, host, rows, gen_len, n);
+}
+
+// host [10][n], in the order of the argument list.
+__global__ void rows_from_host_kernel(const int32_t *host, RowState rows, SeqState seq, int n) {
+  const int r = blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= n) return;
+  int32_t *dst[10] = {rows.token, rows.pos, rows.active, rows.slot, rows.pslot, rows.ptiles, seq.prompt_len, seq.gen_len, seq.limit, seq.stream};
+  int32_t v[10];
+#pragma unroll
+  for (int a = 0; a < 10; ++a) v[a] = host[(int64_t)a * n + r];   // all reads across the bus in flight together
+#pragma unroll
+  for (int a = 0; a < 10; ++a) dst[a][r] = v[a];
+}
+
+void launch_rows_from_host(const int32_t *host, RowState rows, SeqState seq, int n, hipStream_t st) {
+  if (n > 0) hipLaunchKernelGGL(rows_from_host_kernel, dim3((n + 255) / 256), dim3(256), 0, st, host, rows, seq, n);
+}
+
+// grid (chunks, records): record q, kept in cache slot slots[q], to host + q * 16 * max_new bytes as versions i64, tokens
+// i32, log-probs f32, [max_new] each.
+__global__ void records_to_host_kernel(char *host, const int32_t *slots, int max_new, const int32_t *tok, const float *lp, const int64_t *ver) {
+  const int64_t r0 = (int64_t)slots[blockIdx.y] * max_new;
+  char *rec = host + (int64_t)blockIdx.y * 16 * max_new;
+  int64_t *hv = (int64_t *)rec;
+  int32_t *ht = (int32_t *)(rec + (int64_t)8 * max_new);
+  float *hl = (float *)(rec + (int64_t)12 * max_new);
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < max_new; t += gridDim.x * blockDim.x) { hv[t] = ver[r0 + t]; ht[t] = tok[r0 + t]; hl[t] = lp[r0 + t]; }
+}
+
+void launch_records_to_host(char *host, const int32_t *slots, int n, int max_new, const int32_t *tok, const float *lp, const int64_t *ver, hipStream_t st) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(records_to_host_kernel, dim3(std::min(16, (max_new + 255) / 256), n), dim3(256), 0, st, host, slots, max_new, tok, lp, ver);
+}
+
+// grid (chunks, records): the record of cache slot slots[q] starts empty; forced: its tokens to feed, host [n][max_new] (or null).
+__global__ void records_begin_kernel(const int32_t *slots, int max_new, int32_t *tok, float *lp, int64_t *ver, int32_t *forced_dst, const int32_t *forced) {
+  const int64_t r0 = (int64_t)slots[blockIdx.y] * max_new;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < max_new; t += gridDim.x * blockDim.x) {
+    tok[r0 + t] = -1; lp[r0 + t] = 0.f; ver[r0 + t] = -1;
+    if (forced) forced_dst[r0 + t] = forced[(int64_t)blockIdx.y * max_new + t];
+  }
+}
+
+void launch_records_begin(const int32_t *slots, int n, int max_new, int32_t *tok, float *lp, int64_t *ver, int32_t *forced_dst, const int32_t *forced,
+                          hipStream_t st) {
+  if (n <= 0) return;
+  hipLaunchKernelGGL(records_begin_kernel, dim3(std::min(16, (max_new + 255) / 256), n), dim3(256), 0, st, slots, max_new, tok, lp, ver, forced_dst, forced);
 }
 
 __global__ void draw_bits_kernel(uint32_t *out, uint64_t seed, uint32_t n, uint32_t s, uint32_t i0, int count) {
