@@ -67,6 +67,16 @@ void launch_bookkeeping(int N, int max_new, int per_row, int32_t *d_step, const 
                      limit, eos, version, prompt_len, gen_len, rows, out_tok, out_lp, out_ver, n_active);
 }
 
+// One key's row of a head is a whole number of 16-byte units, and every region starts on one, unless the all-fp32 path has a
+// head_dim that is no multiple of 4.
+__device__ __forceinline__ void copy_region(char *dst, const char *src, int64_t bytes, const KvGeom &kv) {
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (kv.head_dim * kv.elt_bytes % 16 == 0)
+    for (int64_t i = first; i < bytes / 16; i += step) ((uint4 *)dst)[i] = ((const uint4 *)src)[i];
+  else
+    for (int64_t i = first; i < bytes / 4; i += step) ((uint32_t *)dst)[i] = ((const uint32_t *)src)[i];
+}
+
 // Copy the prompt part of slot p*G into slots p*G+1 .. p*G+G-1.  grid = (chunks, regions per slot, P*(G-1)).
 // Plain form: a region is one head's K or V plane and the prompt is its first prompt_len rows.  Tiled form: a region
 // is one head's K and V tiles and the prompt is its first ceil(prompt_len/32) tiles; with cut_only just the tile that the
@@ -78,9 +88,7 @@ __global__ void kv_replicate_kernel(KvGeom kv, const int32_t *prompt_len, int G,
   int64_t skip = cut_only ? prompt_len[p] / 32 * tile_bytes : 0;
   const char *src = (const char *)kv.base + ((int64_t)p * G) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + skip;
   char *dst = (char *)kv.base + ((int64_t)p * G + g) * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + skip;
-  int64_t n16 = (bytes - skip) / 16;  // head_dim * elt_bytes is a multiple of 16
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
-    ((uint4 *)dst)[i] = ((const uint4 *)src)[i];
+  copy_region(dst, src, bytes - skip, kv);
 }
 
 void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len, int P, int G, int cut_only, hipStream_t st) {
@@ -100,9 +108,7 @@ __global__ void kv_copy_range_kernel(KvGeom kv, const int32_t *quads) {
   if (bytes <= 0) return;
   const char *src = (const char *)kv.base + (int64_t)q[0] * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + off;
   char *dst = (char *)kv.base + (int64_t)q[1] * kv.slot_stride() * kv.elt_bytes + blockIdx.y * region_bytes + off;
-  int64_t n16 = bytes / 16;  // head_dim * elt_bytes is a multiple of 16
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
-    ((uint4 *)dst)[i] = ((const uint4 *)src)[i];
+  copy_region(dst, src, bytes, kv);
 }
 
 void launch_kv_copy_ranges(KvGeom kv, const int32_t *quads, int n_quads, hipStream_t st) {
