@@ -44,29 +44,50 @@ void dbg_rmsnorm(float *x, const float *h, const void *gain, int w_bf16, int M, 
   else hipLaunchKernelGGL(dbg_rmsnorm_kernel<false>, dim3(M), dim3(256), 0, st, x, h, gain, d, eps);
 }
 
-// One wavefront per output element block: lanes stride over k, then a shuffle reduction.
-template <bool BF>
-__global__ void dbg_gemm_kernel(float *Y, const float *X, const void *W, int M, int N, int K, int accumulate) {
+// One wavefront per output element: lanes stride over k, then a shuffle reduction.  VEC (K a multiple of 4, aligned
+// rows): four elements per lane and load.  A product over a few hundred elements is bound by the latency of a lane's loads, one
+// round trip per trip of the loop: MFMA-free and untiled as it is, the tiny model's launches
+// (N 256 .. 1024, K 256 and 704, 8 rows) took 3.2 - 5.1 us and take 2.6 - 3.5, an empty launch 2 - 3.
+template <bool BF, bool VEC>
+__global__ void dbg_gemm_kernel(float *__restrict__ Y, const float *__restrict__ X, const void *__restrict__ W, int M, int N, int K, int accumulate) {
   int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   int m = blockIdx.y, lane = threadIdx.x & 63;
   if (n >= N) return;
+  const int64_t o = (int64_t)m * N + n;
+  const float y = accumulate && lane == 0 ? Y[o] : 0.f;
   float acc = 0.f;
-  for (int k = lane; k < K; k += 64) acc += load_w<BF>(W, (int64_t)n * K + k) * X[(int64_t)m * K + k];
-  acc = wave_sum(acc);
-  if (lane == 0) {
-    int64_t o = (int64_t)m * N + n;
-    Y[o] = accumulate ? Y[o] + acc : acc;
+  if (VEC) {
+    f32x4 a4 = {0.f, 0.f, 0.f, 0.f};
+    const float *x = X + (int64_t)m * K;
+#pragma unroll 4
+    for (int k = lane * 4; k < K; k += 256) {
+      f32x4 w;
+      if (BF) {
+        const uint2 b = *(const uint2 *)((const uint16_t *)W + (int64_t)n * K + k);
+        w = {__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
+      } else {
+        w = *(const f32x4 *)((const float *)W + (int64_t)n * K + k);
+      }
+      a4 += w * *(const f32x4 *)(x + k);
+    }
+    acc = (a4[0] + a4[1]) + (a4[2] + a4[3]);
+  } else {
+    for (int k = lane; k < K; k += 64) acc += load_w<BF>(W, (int64_t)n * K + k) * X[(int64_t)m * K + k];
   }
+  acc = wave_sum(acc);
+  if (lane == 0) Y[o] = y + acc;
 }
 
 void dbg_gemm(float *Y, const float *X, const void *W, int w_bf16, int M, int N, int K, int accumulate, hipStream_t st) {
   dim3 grid((N + 3) / 4, M), block(256);
-  if (w_bf16) hipLaunchKernelGGL(dbg_gemm_kernel<true>, grid, block, 0, st, Y, X, W, M, N, K, accumulate);
-  else hipLaunchKernelGGL(dbg_gemm_kernel<false>, grid, block, 0, st, Y, X, W, M, N, K, accumulate);
+  const bool vec = K % 4 == 0 && (uintptr_t)W % (w_bf16 ? 8 : 16) == 0 && (uintptr_t)X % 16 == 0;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, Y, X, W, M, N, K, accumulate); };
+  if (w_bf16) { if (vec) launch(dbg_gemm_kernel<true, true>); else launch(dbg_gemm_kernel<true, false>); }
+  else { if (vec) launch(dbg_gemm_kernel<false, true>); else launch(dbg_gemm_kernel<false, false>); }
 }
 
-// grid (M, Hq + 2*Hkv), block hd/2 threads (<= 128): optional per-head RMSNorm, rotary embedding on q and k,
-// append k and v to the fp32 cache.
+// grid (M, Hq + 2*Hkv), block hd/2 threads (<= 128) rounded up to whole wavefronts (the norm's sum shuffles over all 64 lanes):
+// optional per-head RMSNorm, rotary embedding on q and k, append k and v to the fp32 cache.
 template <bool BF>
 __global__ void dbg_qkv_post_kernel(float *qkv, const void *q_gain, const void *k_gain, int qk_norm, float eps,
                                     const float2 *rope_cs, RowState rows, KvGeom kv, int layer, int Hq, int Hkv) {
@@ -75,27 +96,30 @@ __global__ void dbg_qkv_post_kernel(float *qkv, const void *q_gain, const void *
   int width = (Hq + 2 * Hkv) * hd;
   float *v = qkv + (int64_t)m * width + (int64_t)j * hd;
   bool is_q = j < Hq, is_k = !is_q && j < Hq + Hkv;
-  float a = v[i], b = v[i + half];
+  const bool on = i < half;
+  float a = on ? v[i] : 0.f, b = on ? v[i + half] : 0.f;
   if (is_q || is_k) {
     if (qk_norm) {
       float ss = a * a + b * b;
       ss = wave_sum(ss);
-      if (blockDim.x > 64) {  // hd = 256: two wavefronts
+      if (blockDim.x > 64) {  // hd > 128: two wavefronts
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = ss;
         __syncthreads();
         ss = sh[0] + sh[1];
       }
       float inv = 1.0f / sqrtf(ss / (float)hd + eps);
+      if (!on) return;
       const void *g = is_q ? q_gain : k_gain;
       a = a * inv * load_w<BF>(g, i);
       b = b * inv * load_w<BF>(g, i + half);
     }
+    if (!on) return;
     float2 cs = rope_cs[(int64_t)m * half + i];
     float ra = a * cs.x - b * cs.y, rb = a * cs.y + b * cs.x;
     a = ra; b = rb;
   }
   if (is_q) { v[i] = a; v[i + half] = b; return; }
-  if (!rows.active[m]) return;
+  if (!on || !rows.active[m]) return;
   int kvh = is_k ? j - Hq : j - Hq - Hkv;
   float *dst = (float *)kv.base + (int64_t)rows.slot[m] * kv.slot_stride() + (int64_t)layer * kv.layer_stride() +
                (is_k ? 0 : kv.kv_stride()) + (int64_t)kvh * kv.head_stride() + (int64_t)rows.pos[m] * hd;
@@ -104,7 +128,7 @@ __global__ void dbg_qkv_post_kernel(float *qkv, const void *q_gain, const void *
 
 void dbg_qkv_post(float *qkv, const void *q_gain, const void *k_gain, int w_bf16, int qk_norm, float eps,
                   const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv, hipStream_t st) {
-  dim3 grid(M, Hq + 2 * Hkv), block(kv.head_dim / 2);
+  dim3 grid(M, Hq + 2 * Hkv), block((kv.head_dim / 2 + 63) / 64 * 64);
   if (w_bf16) hipLaunchKernelGGL(dbg_qkv_post_kernel<true>, grid, block, 0, st, qkv, q_gain, k_gain, qk_norm, eps,
                                  (const float2 *)rope_cs, rows, kv, layer, Hq, Hkv);
   else hipLaunchKernelGGL(dbg_qkv_post_kernel<false>, grid, block, 0, st, qkv, q_gain, k_gain, qk_norm, eps,
@@ -125,7 +149,15 @@ __global__ void dbg_attention_kernel(float *out, const float *qkv, RowState rows
   float scale = 1.0f / sqrtf((float)hd), mx = -INFINITY;
   for (int t = lane; t < n_keys; t += 64) {
     float s = 0.f;
-    for (int i = 0; i < hd; ++i) s += q[i] * K[(int64_t)t * hd + i];
+    if (hd % 4 == 0) {   // a key's dims four at a time, several loads in flight (the sum keeps its order)
+#pragma unroll 8
+      for (int i = 0; i < hd; i += 4) {
+        const f32x4 k4 = *(const f32x4 *)(K + (int64_t)t * hd + i), q4 = *(const f32x4 *)(q + i);
+        s += q4[0] * k4[0]; s += q4[1] * k4[1]; s += q4[2] * k4[2]; s += q4[3] * k4[3];
+      }
+    } else {
+      for (int i = 0; i < hd; ++i) s += q[i] * K[(int64_t)t * hd + i];
+    }
     s *= scale;
     sc[t] = s;
     mx = fmaxf(mx, s);
@@ -137,6 +169,7 @@ __global__ void dbg_attention_kernel(float *out, const float *qkv, RowState rows
   __syncthreads();
   for (int i = lane; i < hd; i += 64) {
     float acc = 0.f;
+#pragma unroll 16
     for (int t = 0; t < n_keys; ++t) acc += sc[t] * V[(int64_t)t * hd + i];
     o[i] = acc / den;
   }
