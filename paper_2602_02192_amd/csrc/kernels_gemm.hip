@@ -980,7 +980,8 @@ __device__ __forceinline__ SampleAcc score_lane(f32x16 (&x)[NBW], int v0, int V,
 // to the rounding of two hardware logarithms (relative 2^-22 each) and of z, and only the winner is evaluated in full.  The
 // two orders can differ only where the lane's best two are closer than those errors: below 1e-5 plus 1e-6 of the score's
 // magnitude together; within ten times that the lane's wavefront evaluates all entries in full, in index order (a percent of
-// the wavefronts; through `dump`, 4 KB of LDS of its own, because a rolled loop cannot index registers).
+// the wavefronts; through `dump`, 4 KB of LDS of its own, because a rolled loop cannot index registers).  So it does where a lane
+// has entries but no score above -inf (logits of -inf): the lowest index among equals is an entry of the vocabulary there too.
 template <int NBW>
 __device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, int v0, int V, float temperature, uint64_t seed, uint32_t stream,
                                                  uint32_t step) {
@@ -1011,7 +1012,7 @@ __device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, 
     }
   sa.zsum = sum_exp_lane<NBW>(x, c2, xm);
   sa.zmax = xm * W_UNSCALE / temperature;
-  if (__any(second > best - (1e-4f + 1e-5f * (fabsf(best) + 32.f)))) {
+  if (__any(second > best - (1e-4f + 1e-5f * (fabsf(best) + 32.f)) || (kbest < 0 && v0 < V))) {
     float *mine = dump + (threadIdx.x & 63);
 #pragma unroll
     for (int n = 0; n < NBW; ++n) {
@@ -1024,7 +1025,7 @@ __device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, 
         for (int i = 0; i < 4; ++i) {
           const int v = v0 + 32 * n + 8 * g + i;
           const float z = mine[(4 * g + i) * 64] * W_UNSCALE / temperature, score = z + gumbel_from_bits(i == 0 ? d.x : i == 1 ? d.y : i == 2 ? d.z : d.w);
-          if (v < V && score > sa.best) { sa.best = score; sa.zbest = z; sa.idx = v; }
+          if (v < V && (score > sa.best || (score == sa.best && v < sa.idx))) { sa.best = score; sa.zbest = z; sa.idx = v; }
         }
       }
     }
