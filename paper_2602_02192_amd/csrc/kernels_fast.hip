@@ -265,15 +265,18 @@ void fast_qkv_post(const float *partials, int nsplit, int Np, int Mp, void *q_h1
 // With p = softmax(logits / T): keep the shortest prefix of the tokens in descending order of p (lower index first
 // among equals) whose probabilities reach top_p, draw by Gumbel-max over the kept set with the usual per-index noise,
 // return the log-prob renormalised over the kept set (Sec. 5.1 runs rollouts at top-p 0.95).  Three launches:
-// 1. topp_cut_kernel, one workgroup per row, finds the cut without sorting: a radix select over the order-preserving
-//    integer image of the logit, most significant byte first; each round histograms the probability mass of the
-//    candidates by their next byte and walks the 256 bins from the top until the running mass reaches the target.
-//    Mass is summed in integers, q_i = floor(exp(z_i - max) * 2^40), so the sums do not depend on the order of the
-//    additions and the kept set is the same on every run.  Equal keys have equal mass; of the keys equal
-//    to the cut the lowest indices are kept until the target is met, so the kernel also returns the last kept index
-//    among them.  Seven passes over the row, which stays in L2.
-// 2. topp_draw_kernel, TOPP_CHUNKS workgroups per row: the sampler's running (max, sum-exp, best perturbed score) over
-//    the kept tokens of one slice of the vocabulary, in the partial layout of the fused sampler;
+// 1. topp_cut_kernel, one workgroup per row, finds the cut without sorting.  A histogram of the probability mass over 4096
+//    bins of z = logit / T, 1/128 wide from the row's maximum down, names the bin that the cut lies in; the keys of that bin
+//    (a few hundred of 150 thousand N(0, 1)-like logits) go to a list, and a radix select over the order-preserving integer
+//    image of the logit, most significant byte first, finds the cut among them.  Mass is summed in integers,
+//    q_i = floor(exp(z_i - max) * 2^40), so the sums do not depend on the order of the additions and the kept set is the
+//    same on every run.  Equal keys have equal mass; of the keys equal to the cut the lowest indices are kept until the
+//    target is met, so the kernel also returns the last kept index among them.  What bounds it is the vector unit of one
+//    compute unit per row, so it counts what a logit costs: three passes (maximum; histogram; list) with one exponential,
+//    where a byte-wise select over the whole row took four with an exponential each.  128 rows of 151936
+//    logits, 8 bits at a time from the top: 102 us, now 60.
+// 2. topp_draw_kernel, TOPP_CHUNKS workgroups per row: (max, sum-exp, best perturbed score) over the kept tokens of one
+//    slice of the vocabulary, in the partial layout of the fused sampler;
 // 3. sample_combine_kernel merges the slices.
 constexpr int TOPP_THREADS = 1024, TOPP_CHUNKS = TOPP_CHUNKS_PER_ROW;
 __device__ __forceinline__ uint32_t float_order_key(float f) {   // a < b  <=>  key(a) < key(b)
@@ -283,25 +286,29 @@ __device__ __forceinline__ uint32_t float_order_key(float f) {   // a < b  <=>  
 __device__ __forceinline__ float order_key_float(uint32_t key) {   // the float whose key this is
   return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
-constexpr int TOPP_CAND = 1024;   // keys the last round can take from the list (more: it walks the row like the others)
+constexpr int TOPP_CAND = 1024;   // keys that the select can take from the list (more: it walks the row in each round)
+// LDS: the histogram, lanes that meet in one bin spread over TOPP_COPIES copies of it; the radix rounds reuse it.
+constexpr int TOPP_BINS = 4096, TOPP_COPIES = 4, TOPP_RADIX_COPIES = 16, TOPP_LDS = TOPP_BINS * TOPP_COPIES * 8;
+static_assert(TOPP_RADIX_COPIES * 256 <= TOPP_BINS * TOPP_COPIES && TOPP_BINS == 4 * TOPP_THREADS, "the rounds fit; four bins per thread");
 __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_key, int32_t *cut_last, const float *logits, int64_t ld,
                                                                  int V, float temperature, float top_p, const int32_t *row_active) {
-  __shared__ unsigned long long hist[4];        // mass of the bins of each of the first four wavefronts
-  __shared__ unsigned long long sub[16][256];   // lanes that meet in one bin are spread over 16 copies of it
+  extern __shared__ unsigned long long topp_hist[];
   __shared__ unsigned long long sh_u64[TOPP_THREADS / 64];
   __shared__ float sh_f[TOPP_THREADS / 64];
   __shared__ int sh_i[TOPP_THREADS / 64];
+  __shared__ uint32_t cand[TOPP_CAND];
   __shared__ unsigned long long sel_above, sel_mass;
   __shared__ uint32_t sel_digit;
+  __shared__ int cand_n;
   const int m = blockIdx.x, tid = threadIdx.x, wv = tid >> 6;
   if (row_active && !row_active[m]) return;
   const float *lg = logits + (int64_t)m * ld;
-  // Every pass visits the row with a stride of the block, two 16-byte loads in flight per thread (a plain loop waits out
+  // Every pass visits the row with a stride of the block, four 16-byte loads in flight per thread (a plain loop waits out
   // one memory latency per element); an index past the end yields -inf: mass 0, no maximum, never above a cut.
   const int n4 = (ld & 3) == 0 ? V >> 2 : 0;   // 16-byte loads need aligned rows
   auto visit = [&](auto &&f) {
     const f32x4 *lg4 = (const f32x4 *)lg;
-    constexpr int B = 2;   // more copies of the body than this and the kernel outgrows the instruction cache
+    constexpr int B = 4;
     for (int i = tid; i < n4; i += B * TOPP_THREADS) {
       f32x4 v[B];
 #pragma unroll
@@ -311,85 +318,99 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
     }
     for (int i = n4 * 4 + tid; i < V; i += TOPP_THREADS) f(lg[i]);
   };
-  // max of z and sum of exp(z - max), one pass (running maximum, the sum rescaled whenever it moves); 1/T instead of the
-  // division: nothing here is returned, the kept set only needs the same arithmetic in every pass
+  for (int j = tid; j < TOPP_BINS * TOPP_COPIES; j += TOPP_THREADS) topp_hist[j] = 0;
+  if (tid == 0) cand_n = 0;
+  // 1/T instead of the division: nothing here is returned, the kept set only needs the same arithmetic in every pass
   const float inv_t = 1.0f / temperature;
-  float mx = -INFINITY, zs = 0.f;
-  visit([&](float v) {
-    float z = v * inv_t;
-    if (z > mx) { zs = zs * __expf(mx - z) + 1.f; mx = z; }
-    else zs += __expf(z - mx);
-  });
-  for (int o = 32; o > 0; o >>= 1) {
-    float om = __shfl_xor(mx, o, 64), os = __shfl_xor(zs, o, 64), nm = fmaxf(mx, om);
-    zs = (mx > -INFINITY ? zs * __expf(mx - nm) : 0.f) + (om > -INFINITY ? os * __expf(om - nm) : 0.f);
-    mx = nm;
-  }
-  if ((tid & 63) == 0) { sh_f[wv] = mx; sh_u64[wv] = (unsigned long long)__float_as_uint(zs); }
+  float mx = -INFINITY;
+  visit([&](float v) { mx = fmaxf(mx, v); });
+  mx = wave_max(mx);
+  if ((tid & 63) == 0) sh_f[wv] = mx;
   __syncthreads();
-  mx = sh_f[0];
-  for (int w = 1; w < TOPP_THREADS / 64; ++w) mx = fmaxf(mx, sh_f[w]);
-  zs = 0.f;
-  for (int w = 0; w < TOPP_THREADS / 64; ++w) zs += __uint_as_float((uint32_t)sh_u64[w]) * __expf(sh_f[w] - mx);
+  for (int w = 0; w < TOPP_THREADS / 64; ++w) mx = fmaxf(mx, sh_f[w]);
+  const float zmax = mx * inv_t;
   // probability mass in units of 2^-40 of the largest one, as an integer: sums of it do not depend on the order of the
   // additions.  (Two 32-bit conversions; a float -> 64-bit integer conversion is a long instruction sequence.)
   auto mass = [&](float logit) {
-    float e = __expf(logit * inv_t - mx) * 256.0f;          // <= 256
+    float e = __expf(fmaf(logit, inv_t, -zmax)) * 256.0f;   // <= 256
     uint32_t hi = (uint32_t)e;
     uint32_t lo = (uint32_t)((e - (float)hi) * 4294967296.0f);
     return ((unsigned long long)hi << 32) | lo;
   };
-  unsigned long long target = (unsigned long long)ceil((double)zs * 1099511627776.0 * (double)top_p);
+  // Bin of a logit, falling in it: 128 to a unit of z.  Beyond 32 units below the maximum, where the mass is zero, the last
+  // one takes all.  Clamped before the conversion, so that any value at all names a bin.
+  auto bin = [&](float logit) { return (int)fminf(fmaxf(fmaf(logit, inv_t, -zmax) * -128.0f, 0.0f), (float)(TOPP_BINS - 1)); };
+  visit([&](float v) {
+    const unsigned long long q = mass(v);
+    if (q) atomicAdd(&topp_hist[bin(v) * TOPP_COPIES + (tid & (TOPP_COPIES - 1))], q);
+  });
+  __syncthreads();
+  // Walk the bins from the top: thread t owns bins 4t .. 4t+3; an inclusive prefix sum over t is the mass at or above them.
+  unsigned long long h4[4], incl = 0, total = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    h4[k] = 0;
+    for (int j = 0; j < TOPP_COPIES; ++j) h4[k] += topp_hist[(4 * tid + k) * TOPP_COPIES + j];
+    incl += h4[k];
+  }
+  const unsigned long long mine4 = incl;
+  for (int o = 1; o < 64; o <<= 1) { unsigned long long v = __shfl_up(incl, o, 64); if ((tid & 63) >= o) incl += v; }
+  if ((tid & 63) == 63) sh_u64[wv] = incl;
+  __syncthreads();
+  for (int w = 0; w < TOPP_THREADS / 64; ++w) { if (w < wv) incl += sh_u64[w]; total += sh_u64[w]; }
+  if (total == 0) {   // no finite maximum: every token is kept
+    if (tid == 0) { cut_key[m] = 0; cut_last[m] = V; }
+    return;
+  }
+  unsigned long long target = (unsigned long long)ceil((double)total * (double)top_p);
   if (target < 1) target = 1;
+  if (target > total) target = total;
+  if (incl >= target && incl - mine4 < target) {   // exactly one thread
+    unsigned long long at = incl - mine4;
+    int k = 0;
+    while (k < 3 && at + h4[k] < target) at += h4[k++];
+    sel_digit = (uint32_t)(4 * tid + k);
+    sel_above = at;
+  }
+  __syncthreads();
+  const int cut_bin = (int)sel_digit;
+  unsigned long long above = sel_above;   // mass of the keys above the range that the cut is known to lie in
+  visit([&](float v) {
+    if (bin(v) == cut_bin) {
+      const int k = atomicAdd(&cand_n, 1);
+      if (k < TOPP_CAND) cand[k] = float_order_key(v);
+    }
+  });
   // radix select of the cut key: the largest key K with mass{key >= K} >= target
   uint32_t prefix = 0;
-  unsigned long long above = 0;   // mass of the keys above the current prefix range
-  // The third round notes the keys it histograms (those that share the cut's upper 16 bits: a few hundred of a row of
-  // N(0, 1)-like logits); if they fit the list the last round walks the list instead of the row.
-  __shared__ uint32_t cand[TOPP_CAND];
-  __shared__ int cand_n;
-  if (tid == 0) cand_n = 0;
   for (int round = 0; round < 4; ++round) {
     const int shift = 24 - 8 * round;
     __syncthreads();
-    for (int j = tid; j < 16 * 256; j += TOPP_THREADS) (&sub[0][0])[j] = 0;
+    for (int j = tid; j < TOPP_RADIX_COPIES * 256; j += TOPP_THREADS) topp_hist[j] = 0;
     __syncthreads();
-    if (round == 3 && cand_n <= TOPP_CAND) {
-      for (int j = tid; j < cand_n; j += TOPP_THREADS) {
-        const uint32_t key = cand[j];
-        if ((key >> 8) == prefix) {
-          unsigned long long q = mass(order_key_float(key));
-          if (q) atomicAdd(&sub[tid & 15][key & 255u], q);
-        }
+    auto count = [&](uint32_t key) {
+      if (round == 0 || (key >> (shift + 8)) == prefix) {
+        const unsigned long long q = mass(order_key_float(key));
+        if (q) atomicAdd(&topp_hist[(tid & (TOPP_RADIX_COPIES - 1)) * 256 + ((key >> shift) & 255u)], q);
       }
-    } else {
-      visit([&](float v) {
-        uint32_t key = float_order_key(v);
-        if (round == 0 || (key >> (shift + 8)) == prefix) {
-          unsigned long long q = mass(v);
-          if (q) atomicAdd(&sub[tid & 15][(key >> shift) & 255u], q);
-          if (round == 2) {
-            const int k = atomicAdd(&cand_n, 1);
-            if (k < TOPP_CAND) cand[k] = key;
-          }
-        }
-      });
-    }
+    };
+    if (cand_n <= TOPP_CAND) { for (int j = tid; j < cand_n; j += TOPP_THREADS) count(cand[j]); }
+    else visit([&](float v) { if (bin(v) == cut_bin) count(float_order_key(v)); });
     __syncthreads();
-    // walk the bins from the top: thread t of the first four wavefronts owns bin 255 - t, so an inclusive prefix sum
-    // over t is the mass of the bins at or above its own; exactly one bin takes the running mass across the target
-    unsigned long long h = 0, incl = 0;
+    // thread t of the first four wavefronts owns digit 255 - t; exactly one digit takes the running mass across the target
+    unsigned long long h = 0;
+    incl = 0;
     if (tid < 256) {
-      for (int j = 0; j < 16; ++j) h += sub[j][255 - tid];
+      for (int j = 0; j < TOPP_RADIX_COPIES; ++j) h += topp_hist[j * 256 + 255 - tid];
       incl = h;
       for (int o = 1; o < 64; o <<= 1) { unsigned long long v = __shfl_up(incl, o, 64); if ((tid & 63) >= o) incl += v; }
-      if ((tid & 63) == 63) hist[wv] = incl;
+      if ((tid & 63) == 63) sh_u64[wv] = incl;
     }
     __syncthreads();
     if (tid < 256) {
-      for (int w = 0; w < wv; ++w) incl += hist[w];
+      for (int w = 0; w < wv; ++w) incl += sh_u64[w];
       const unsigned long long at = above + incl, before = at - h;
-      if ((at >= target && before < target) || (tid == 255 && at < target)) { sel_digit = (uint32_t)(255 - tid); sel_above = before; sel_mass = h; }
+      if (at >= target && before < target) { sel_digit = (uint32_t)(255 - tid); sel_above = before; sel_mass = h; }
     }
     __syncthreads();
     prefix = (prefix << 8) | sel_digit;
@@ -426,12 +447,12 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
   const int chunk = (V + TOPP_THREADS - 1) / TOPP_THREADS, i0 = tid * chunk, i1 = min(V, i0 + chunk);
   int mine = 0;
   for (int i = i0; i < i1; ++i) mine += float_order_key(lg[i]) == cut;
-  int incl = mine;
-  for (int o = 1; o < 64; o <<= 1) { int v = __shfl_up(incl, o, 64); if ((tid & 63) >= o) incl += v; }
+  int upto = mine;
+  for (int o = 1; o < 64; o <<= 1) { int v = __shfl_up(upto, o, 64); if ((tid & 63) >= o) upto += v; }
   __syncthreads();
-  if ((tid & 63) == 63) sh_i[wv] = incl;
+  if ((tid & 63) == 63) sh_i[wv] = upto;
   __syncthreads();
-  int rank = incl - mine;   // ties before this thread's run
+  int rank = upto - mine;   // ties before this thread's run
   for (int w = 0; w < wv; ++w) rank += sh_i[w];
   if (rank < take && take <= rank + mine) {   // the take-th tie lies in this thread's run
     for (int i = i0; i < i1; ++i)
@@ -439,7 +460,12 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
   }
 }
 
-// grid (TOPP_CHUNKS, M), block 256: slice c of row m.
+// grid (TOPP_CHUNKS, M), block 256: slice c of row m.  The score that decides is the fp32 one (division by T, two logf), some
+// sixty instructions per token in a kernel that the vector unit bounds; so, as in the lm_head's sampler, a thread compares its
+// kept tokens by z/ln2 - log2(-log2 u) and evaluates the winner in full.  Both orders agree unless its best two are closer than
+// the roundings of two hardware logarithms and of z: below 1e-5 plus 1e-6 of the score's magnitude; within ten times that
+// the wavefront evaluates all its kept tokens in full.  Four tokens of which none is kept draw no numbers.  128 rows of 151936
+// logits, three quarters of them kept: 62 -> 52 us, of which the ten rounds of the generator are some 35.
 __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, const int32_t *cut_last, const float *logits, int64_t ld,
                                  int V, float temperature, uint64_t seed, DrawIds ids, const int32_t *row_active) {
   __shared__ SampleAcc sh[4];
@@ -449,22 +475,65 @@ __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, c
   const int last = cut_last[m];
   const int v4 = (V + 3) / 4, per = (v4 + TOPP_CHUNKS - 1) / TOPP_CHUNKS, b4 = c * per, e4 = min(v4, b4 + per);
   const float *lg = logits + (int64_t)m * ld;
-  SampleAcc a = sample_acc_init();
-  for (int i4 = b4 + threadIdx.x; i4 < e4; i4 += blockDim.x) {
-    u32x4 r = draw4(seed, stream, step, (uint32_t)i4);
-    uint32_t w[4] = {r.x, r.y, r.z, r.w};
+  const bool aligned = (ld & 3) == 0;
+  // the four logits of a group, -inf for those that are not kept (a kept -inf has no mass and no score either)
+  auto group = [&](int i4) {
+    f32x4 x;
+    if (aligned && 4 * i4 + 4 <= V) x = ((const f32x4 *)lg)[i4];
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = 4 * i4 + e < V ? lg[4 * i4 + e] : -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      int i = i4 * 4 + e;
-      if (i < V) {
-        float v = lg[i];
-        uint32_t key = float_order_key(v);
-        if (key > cut || (key == cut && i <= last)) {
-          float z = v / temperature;
-          sample_acc_add(a, z, z + gumbel_from_bits(w[e]), i);
-        }
+      const uint32_t key = float_order_key(x[e]);
+      if (!(key > cut || (key == cut && 4 * i4 + e <= last))) x[e] = -INFINITY;
+    }
+    return x;
+  };
+  const float c2 = 1.44269504088896341f / temperature;
+  float xm = -INFINITY, sum = 0.f, best = -INFINITY, second = -INFINITY, xbest = 0.f;
+  uint32_t wbest = 0;
+  int ibest = 0x7fffffff;
+  for (int i4 = b4 + threadIdx.x; i4 < e4; i4 += blockDim.x) {
+    const f32x4 x = group(i4);
+    const float x4 = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    if (!(x4 > -INFINITY)) continue;
+    if (x4 > xm) { sum *= __builtin_amdgcn_exp2f((xm - x4) * c2); xm = x4; }
+    const u32x4 r = draw4(seed, stream, step, (uint32_t)i4);
+    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum += __builtin_amdgcn_exp2f((x[e] - xm) * c2);   // the difference first: as exact at scores of thousands
+      const float u = fmaf((float)(w[e] >> 9), 0x1p-23f, 0x1p-24f);   // exact: (2k + 1) 2^-24
+      const float f = fmaf(x[e], c2, -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)));
+      const bool better = f > best;
+      second = fmaxf(second, fminf(f, best));
+      best = better ? f : best;
+      xbest = better ? x[e] : xbest;
+      wbest = better ? w[e] : wbest;
+      ibest = better ? 4 * i4 + e : ibest;
+    }
+  }
+  SampleAcc a = sample_acc_init();
+  if (xm > -INFINITY) { a.zmax = xm / temperature; a.zsum = sum; }
+  // (everything kept and no score above -inf: no finite logit here, the lowest index among equals as everywhere)
+  if (__any(second > best - (1e-4f + 1e-5f * (fabsf(best) + 32.f)) || (cut == 0 && ibest == 0x7fffffff && b4 + (int)threadIdx.x < e4))) {
+#pragma unroll 1
+    for (int i4 = b4 + threadIdx.x; i4 < e4; i4 += blockDim.x) {
+      const f32x4 x = group(i4);
+      const u32x4 r = draw4(seed, stream, step, (uint32_t)i4);
+#pragma unroll 1
+      for (int e = 0; e < 4; ++e) {
+        const float z = (e == 0 ? x[0] : e == 1 ? x[1] : e == 2 ? x[2] : x[3]) / temperature;
+        const float score = z + gumbel_from_bits(e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w);
+        const int i = 4 * i4 + e;
+        if (i < V && (score > a.best || (score == a.best && i < a.idx))) { a.best = score; a.zbest = z; a.idx = i; }
       }
     }
+  } else if (ibest != 0x7fffffff) {
+    a.zbest = xbest / temperature;
+    a.best = a.zbest + gumbel_from_bits(wbest);
+    a.idx = ibest;
   }
   for (int o = 32; o > 0; o >>= 1) { SampleAcc b = sample_acc_shfl_xor(a, o); sample_acc_merge(a, b); }
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
@@ -487,7 +556,12 @@ void fast_topp_cut_and_draw(float *scratch, const float *logits, int64_t ld, int
   if (M <= 0) return;
   uint32_t *cut_key = (uint32_t *)(scratch + (size_t)5 * TOPP_CHUNKS * Mp);
   int32_t *cut_last = (int32_t *)cut_key + Mp;
-  hipLaunchKernelGGL(topp_cut_kernel, dim3(M), dim3(TOPP_THREADS), 0, st, cut_key, cut_last, logits, ld, V, temperature, top_p, row_active);
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void *)topp_cut_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TOPP_LDS);
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(topp_cut_kernel, dim3(M), dim3(TOPP_THREADS), TOPP_LDS, st, cut_key, cut_last, logits, ld, V, temperature, top_p, row_active);
   hipLaunchKernelGGL(topp_draw_kernel, dim3(TOPP_CHUNKS, M), dim3(256), 0, st, scratch, Mp, cut_key, cut_last, logits, ld, V, temperature,
                      seed, ids, row_active);
 }

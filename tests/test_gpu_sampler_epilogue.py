@@ -30,3 +30,34 @@ def test_fused_sampler_takes_the_tokens_of_the_fp32_sampler(rows, vocab):
         z = np.abs(b["logprobs"]).max() + 0.1 / temperature
         assert np.abs(a["logprobs"] - b["logprobs"]).max() < 2e-6 * max(8.0, z), temperature
     ctx.close()
+
+
+@pytest.mark.parametrize("vocab,dtype", [(1001, "fp32"), (4099, "bf16"), (9002, "fp32"), (9002, "bf16")])
+def test_nucleus_draws_the_tokens_of_the_oracle_over_the_same_logits(orc, vocab, dtype):
+    """Vocabularies whose rows are not aligned and end inside a group of four draws; a temperature at which nearly all mass is
+    one token's, one at which the cut's bin holds a few keys and one at which every key shares a few bins (more of them than
+    the candidate list holds)."""
+    shape = synth.ModelShape(1, 256, 4, 2, 64, 512, vocab, dtype=dtype)
+    blob = synth.make_weights(shape, 6)
+    prompts, lens = synth.make_prompts(vocab, 3, 5, seed=vocab)
+    ctx = make_ctx(shape, 3, 9, blob)
+    forced = np.random.default_rng(vocab).integers(0, vocab, size=(3, 4)).astype(np.int32)
+    checked = 0
+    for temperature in (0.02, 1.0, 60.0):
+        for top_p in (0.05, 0.95):
+            got = ctx.rollout(prompts, lens, 1, 4, temperature, 17, top_p=top_p, forced=forced, want_logits=True)
+            for n in range(3):
+                for s in range(4):
+                    z = got["logits"][n, s].astype(np.float64)
+                    tok, lp, gap, kept, margin = orc.sample_top_p(z, temperature, top_p, 17, n, s)
+                    # the kernel's masses carry the hardware exponential's error, relative 1e-6; its scores are fp32
+                    size = max(8.0, np.abs(z).max() / temperature)
+                    if margin < 4e-6 or gap < 1e-6 * size:
+                        continue
+                    checked += 1
+                    assert got["tokens"][n, s] == tok, (temperature, top_p, n, s, kept)
+                    assert abs(got["logprobs"][n, s] - lp) < 2e-6 * size, (temperature, top_p, n, s, kept)
+    # of 72 draws; a row's 9002 masses are nearly equal at T = 60, so all rows' cuts lie as close to the 0.95 as the nearest
+    # multiple of 1 / 9002 does (5e-6), and up to half a dozen of those 12 are left out
+    assert checked >= 54
+    ctx.close()
