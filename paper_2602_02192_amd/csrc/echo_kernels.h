@@ -124,9 +124,9 @@ void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, con
 enum GemmEpilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1 };
 // out = Xp[Mp x Kp] * Wp[Np x Kp]^T.  EPI_PARTIAL: fp32 partials [nsplit][Mp][Np];
 // EPI_SWIGLU (rows alternate gate_f, up_f): silu(gate)*up -> half K8 [Mp][Np/2]; nsplit must be 1.
-struct GemmShape { int nsplit, waves_k, waves_n, nbw, lds, stages; };   // launch shape, see fast_gemm_pick
-// GemmShape.lds: 0 = operands straight into registers, 1 = activations staged through LDS, else the LDS ring, by its tile
-enum { GEMM_RING_256X256 = 2, GEMM_RING_256X128 = 3 };   // rows x columns
+struct GemmShape { int nsplit, waves_n, form, stages; };   // launch shape, see fast_gemm_pick
+// GemmShape.form: weights streamed into registers with the activations staged through LDS, or the LDS ring by its tile (rows x columns)
+enum { GEMM_STREAM = 1, GEMM_RING_256X256 = 2, GEMM_RING_256X128 = 3 };
 constexpr int REDUCE_MAX_SPLIT = 12;   // most grid splits over K whose partials the reducing kernels sum
 constexpr int GEMM_K_PAD = 128;   // packed weights and K8 activations pad K to this (whole LDS chunks of 8 k-steps)
 void fast_gemm(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, GemmEpilogue epi,

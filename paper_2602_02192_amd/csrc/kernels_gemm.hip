@@ -84,151 +84,7 @@ void fast_dequant_q8(void *out_bf16, const void *codes, const void *scales, int6
                      (const float *)scales, n, K);
 }
 
-// ---- the MFMA inner loop -------------------------------------------------------------------------------
-// A wavefront owns NBW consecutive 32-row weight blocks and all MB 32-row batch blocks of its launch slice:
-// per k-step it reads NBW KiB of weights and MB KiB of activations, so activation traffic from L2 per weight
-// byte falls with NBW.  Loads run two groups of U k-steps ahead of the MFMAs (register double buffer).
-template <int MB, int NBW, int U>
-struct KGroup {
-  h16x8 a[U][NBW];
-  h16x8 b[U][MB];
-};
-
-template <int MB, int NBW, int U>
-__device__ __forceinline__ void load_group(KGroup<MB, NBW, U> &g, const h16x8 *__restrict__ a_ptr, int64_t a_blk,
-                                           const h16x8 *__restrict__ b_ptr, int Mp, int ks, int64_t a_step) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-#pragma unroll
-    for (int n = 0; n < NBW; ++n) g.a[u][n] = __builtin_nontemporal_load(a_ptr + n * a_blk + (int64_t)(ks + u) * a_step);
-    const h16x8 *bp = b_ptr + (int64_t)(ks + u) * 2 * Mp;
-#pragma unroll
-    for (int j = 0; j < MB; ++j) g.b[u][j] = bp[j * 32];
-  }
-}
-
-template <int MB, int NBW, int U>
-__device__ __forceinline__ void mma_group(f32x16 (&acc)[NBW][MB], const KGroup<MB, NBW, U> &g) {
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-#pragma unroll
-    for (int n = 0; n < NBW; ++n)
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-        acc[n][j] = mfma_h16(g.a[u][n], g.b[u][j], acc[n][j]);
-}
-
-// Wnb: first weight block of the wavefront; a_blk: distance between consecutive weight blocks (16-byte units).
-template <int MB, int NBW>
-__device__ __forceinline__ void mma_range(f32x16 (&acc)[NBW][MB], const h16x8 *__restrict__ Wnb, int64_t a_blk,
-                                          const h16x8 *__restrict__ Xp, int Mp, int ks0, int ks1, int lane,
-                                          int64_t a_step) {
-  constexpr int U0 = 12 / (MB + NBW), U = U0 < 1 ? 1 : (U0 > 4 ? 4 : U0);
-  const h16x8 *a_ptr = Wnb + (lane >> 5) * 32 + (lane & 31);
-  const h16x8 *b_ptr = Xp + (int64_t)(lane >> 5) * Mp + (lane & 31);
-  int ng = (ks1 - ks0) / U;
-  KGroup<MB, NBW, U> g0, g1;
-  if (ng > 0) load_group<MB, NBW, U>(g0, a_ptr, a_blk, b_ptr, Mp, ks0, a_step);
-  for (int g = 0; g < ng; g += 2) {
-    if (g + 1 < ng) load_group<MB, NBW, U>(g1, a_ptr, a_blk, b_ptr, Mp, ks0 + (g + 1) * U, a_step);
-    mma_group<MB, NBW, U>(acc, g0);
-    if (g + 2 < ng) load_group<MB, NBW, U>(g0, a_ptr, a_blk, b_ptr, Mp, ks0 + (g + 2) * U, a_step);
-    if (g + 1 < ng) mma_group<MB, NBW, U>(acc, g1);
-  }
-  for (int ks = ks0 + ng * U; ks < ks1; ++ks) {   // remainder
-    KGroup<MB, NBW, 1> r;
-    load_group<MB, NBW, 1>(r, a_ptr, a_blk, b_ptr, Mp, ks, a_step);
-    mma_group<MB, NBW, 1>(acc, r);
-  }
-}
-
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
-
-// grid (ceil(Np/32 / (NBW*waves_n)), nsplit, Mp/(32*MB)); block 64 * waves_n * waves_k.
-// Wavefront w = wk*waves_n + wn: the waves_n wavefronts of one wk share a k-range (their activation reads hit
-// L1 together) and own different weight blocks; the waves_k k-ranges of a grid split are summed in LDS in wk order.
-template <int MB, int NBW, int EPI>
-__global__ __launch_bounds__(512) void gemm_kernel(void *out, const h16x8 *__restrict__ Xp, const h16x8 *__restrict__ Wp,
-                                                   int Mp, int Np, int Kp, int ksteps_per_split, int waves_n) {
-  extern __shared__ float red[];
-  const int waves = blockDim.x >> 6, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wn = w % waves_n, wk = w / waves_n, nwk = waves / waves_n;
-  const int nblocks = Np >> 5, split = blockIdx.y, mblk0 = blockIdx.z * MB;
-  const int nb0 = (blockIdx.x * waves_n + wn) * NBW;
-  const int ksteps = Kp >> 4;
-  const int s0 = split * ksteps_per_split, s1 = min(ksteps, s0 + ksteps_per_split);
-  const int per_wave = (s1 - s0 + nwk - 1) / nwk;
-  const int k0 = min(s1, s0 + wk * per_wave), k1 = min(s1, k0 + per_wave);
-  f32x16 acc[NBW][MB];
-#pragma unroll
-  for (int n = 0; n < NBW; ++n)
-#pragma unroll
-    for (int j = 0; j < MB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
-  // blocks past the end re-read the last block (their results are dropped)
-  const int nb_ld = min(nb0, nblocks - NBW);
-  if (nb0 < nblocks)
-    mma_range<MB, NBW>(acc, Wp + w_block_base(nb_ld, Kp), w_block_base(1, Kp), Xp + mblk0 * 32, Mp, k0, k1, lane,
-                       w_kstep_stride(Np));
-  if (nwk > 1) {
-    float *mine = red + (int64_t)((wk - 1) * waves_n + wn) * (NBW * MB * 16 * 64);
-    if (wk > 0) {
-#pragma unroll
-      for (int n = 0; n < NBW; ++n)
-#pragma unroll
-        for (int j = 0; j < MB; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mine[((n * MB + j) * 16 + r) * 64 + lane] = acc[n][j][r];
-    }
-    __syncthreads();
-    if (wk == 0) {
-      for (int ww = 1; ww < nwk; ++ww) {
-        const float *src = red + (int64_t)((ww - 1) * waves_n + wn) * (NBW * MB * 16 * 64);
-#pragma unroll
-        for (int n = 0; n < NBW; ++n)
-#pragma unroll
-          for (int j = 0; j < MB; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[n][j][r] += src[((n * MB + j) * 16 + r) * 64 + lane];
-      }
-    }
-  }
-  if (wk != 0) return;
-  const int half = lane >> 5, col = lane & 31;
-#pragma unroll
-  for (int n = 0; n < NBW; ++n) {
-    const int nb = nb0 + n;
-    if (nb >= nblocks) continue;
-    if (EPI == EPI_PARTIAL) {
-      f32x4 *P = (f32x4 *)out;
-#pragma unroll
-      for (int j = 0; j < MB; ++j) {
-        int m = (mblk0 + j) * 32 + col;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          int n4 = nb * 8 + half + 2 * g;
-          f32x4 v = {acc[n][j][4 * g], acc[n][j][4 * g + 1], acc[n][j][4 * g + 2], acc[n][j][4 * g + 3]};
-          P[((int64_t)split * Mp + m) * (Np >> 2) + n4] = v * W_UNSCALE;
-        }
-      }
-    } else {  // EPI_SWIGLU: rows alternate gate_f, up_f
-      uint32_t *O = (uint32_t *)out;
-#pragma unroll
-      for (int j = 0; j < MB; ++j) {
-        int m = (mblk0 + j) * 32 + col;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          int f = nb * 16 + half * 2 + 4 * g;
-          float v0 = silu_f(acc[n][j][4 * g] * W_UNSCALE) * (acc[n][j][4 * g + 1] * W_UNSCALE);
-          float v1 = silu_f(acc[n][j][4 * g + 2] * W_UNSCALE) * (acc[n][j][4 * g + 3] * W_UNSCALE);
-          uint32_t pk = (uint32_t)f32_to_h16_bits(v0) | ((uint32_t)f32_to_h16_bits(v1) << 16);
-          O[(((int64_t)(f >> 3) * Mp + m) * 8 + (f & 7)) >> 1] = pk;
-        }
-      }
-    }
-  }
-}
 
 // ---- weight-streaming GEMM with the activations staged through LDS -----------------------------------------
 // Measured on MI355X: a compute unit sustains about 48 GB/s of vector-memory reads whether they come from HBM
@@ -238,12 +94,12 @@ __global__ __launch_bounds__(512) void gemm_kernel(void *out, const h16x8 *__res
 // the activation traffic per weight byte to MB/WN.  Weight loads run NSTAGE-1 chunks ahead in registers.  The
 // activation loads of a chunk are issued before the weight loads of the same chunk: the memory counter retires in
 // order, so waiting for them (to copy them into LDS) leaves every younger weight load in flight.
-// grid (ceil(Np/32 / WN), nsplit, Mp/(32*MB)); block 64*WN; chunks_per_split chunks of KC k-steps per grid split.
+// grid (ceil(Np/32 / WN), nsplit); 32*MB batch rows, up to 128; block 64*WN; chunks_per_split chunks of KC k-steps per grid split.
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 
-constexpr int GEMM_KC_SMALL = 8, GEMM_KC_WIDE = 4;   // k-steps per chunk for up to 128 / for 256 batch rows per workgroup
+constexpr int GEMM_KC = 8;   // k-steps per chunk
 template <int MB, int WN> struct GemmLds {
-  static constexpr int KC = MB >= 8 ? GEMM_KC_WIDE : GEMM_KC_SMALL;
+  static constexpr int KC = GEMM_KC;
   static constexpr int CHUNK_UNITS = KC * 2 * 32 * MB;                  // 16-byte units of one activation chunk
   static constexpr int X_BYTES = 2 * CHUNK_UNITS * 16;                   // double buffer
   static constexpr int TILE_STRIDE = 33;                                 // floats per row of the transposed output tile
@@ -290,7 +146,7 @@ __device__ __forceinline__ void gemm_lds_mainloop(f32x16 (&acc)[MB], char *lds_r
   // The B operands of GU k-steps are read from LDS in one batch ahead of their MFMAs: with one wavefront per SIMD
   // nothing else hides the LDS latency, and a read issued right before each MFMA would expose it every time.
   auto compute = [&](int st, int buf) {
-    constexpr int GU = MB >= 8 ? 2 : (MB == 4 ? 4 : KC);
+    constexpr int GU = MB == 4 ? 4 : KC;
     const u32x4v *bp = xs + buf * XU + (lane >> 5) * ROWS + (lane & 31);
 #pragma unroll
     for (int u0 = 0; u0 < KC; u0 += GU) {
@@ -415,7 +271,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
   // The B operands of GU k-steps are read from LDS in one batch ahead of their MFMAs: with one wavefront per SIMD
   // nothing else hides the LDS latency, and a read issued right before each MFMA would expose it every time.
   auto compute = [&](int st, int buf) {
-    constexpr int GU = MB >= 8 ? 2 : (MB == 4 ? 4 : KC);
+    constexpr int GU = MB == 4 ? 4 : KC;
     const u32x4v *bp = xs + buf * XU + (lane >> 5) * ROWS + (lane & 31);
 #pragma unroll
     for (int u0 = 0; u0 < KC; u0 += GU) {
@@ -740,9 +596,8 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
 // grid split over K that brings the launch to about one workgroup per compute unit (partials cost HBM writes, so
 // no more than that); a GEMM whose epilogue needs the whole K (SwiGLU) is not split and takes the workgroup width
 // (three to eight blocks) that needs the fewest rounds of the chip.  Batches that are a multiple of 256 rows take the
-// LDS-ring kernel (256 x 256 tiles when those fill the chip, 256 x 128 tiles with a split over K otherwise).  Shapes
-// that fit neither (K not padded, odd row counts) keep the plain register-streaming kernel: waves_k wavefronts of a
-// workgroup share a block's k-steps and are summed in LDS.
+// LDS-ring kernel (256 x 256 tiles when those fill the chip, 256 x 128 tiles with a split over K otherwise).  K is padded to
+// GEMM_K_PAD and the rows to 32, 64, 128 or a multiple of 256, so there are no other shapes.
 // The largest split count <= nsplit that the 256 x 128-tile kernel realises exactly: it cuts K into runs of
 // ceil(groups / nsplit) groups of eight k-steps, which may come to fewer runs than asked for.
 int fast_gemm_even_split(int Kp, int nsplit) {
@@ -755,11 +610,9 @@ int fast_gemm_even_split(int Kp, int nsplit) {
 }
 
 void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
-  int nblocks = Np / 32, ksteps = Kp / 16, mb = Mp / 32 > 8 ? 8 : Mp / 32;
-  int zblocks = Mp / (32 * mb);
-  g->lds = 0; g->stages = 0;
-  if (Kp % GEMM_K_PAD == 0 && Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {   // 256 x 256 tiles fill the chip
-    g->lds = GEMM_RING_256X256; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = 1;
+  const int nblocks = Np / 32, ksteps = Kp / 16;
+  if (Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {   // 256 x 256 tiles fill the chip
+    g->form = GEMM_RING_256X256; g->waves_n = 4; g->stages = 8; g->nsplit = 1;
     // One tile per compute unit at a time, so a tile count just above a multiple of 256 leaves most of the chip idle in
     // the last round (320 tiles take two rounds).  Splitting K in two runs makes the units of work half as long and the
     // rounds fill up (320 tiles: 1.5 rounds' worth), at the price of a second plane of fp32 partials written and read
@@ -771,7 +624,7 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     }
     return;
   }
-  if (Kp % GEMM_K_PAD == 0 && Mp % 256 == 0) {
+  if (Mp % 256 == 0) {
     // 256 x 128 tiles (two row halves x two column pairs of wavefronts), K split until the launch has about one
     // workgroup per compute unit; a split keeps at least four groups of eight k-steps
     int strips = (nblocks + 3) / 4 * (Mp / 256), groups = ksteps / 8;
@@ -779,66 +632,49 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     if (ns > groups / 4) ns = groups / 4;
     if (ns > 12) ns = 12;
     if (ns < 1) ns = 1;
-    g->lds = GEMM_RING_256X128; g->nbw = 2; g->waves_k = 1; g->waves_n = 4; g->stages = 8; g->nsplit = fast_gemm_even_split(Kp, ns);
+    g->form = GEMM_RING_256X128; g->waves_n = 4; g->stages = 8; g->nsplit = fast_gemm_even_split(Kp, ns);
     return;
   }
-  if (Kp % (16 * GEMM_KC_SMALL) == 0 && (Mp <= 128 || Mp % 256 == 0)) {
-    const bool wide = Mp > 128;   // 256 batch rows per workgroup, Mp/256 workgroups per weight strip
-    int total_chunks = ksteps / (wide ? GEMM_KC_WIDE : GEMM_KC_SMALL);
-    g->lds = 1; g->nbw = 1; g->waves_k = 1;
-    if (full_k && !wide) {
-      // No split over K (the SwiGLU epilogue needs whole sums), one workgroup per compute unit at a time: the launch takes
-      // rounds x width, rounds = ceil(workgroups / 256).  The width with the smallest product wins, the wider one on a
-      // tie (fewer rounds, fewer re-reads of the activations).  Measured at 64 rows: 608 blocks (4B) width 3, 203
-      // workgroups, 21 us (width 4: 23); 768 blocks (8B) width 3, 256 workgroups, 34 us; 1600 blocks (32B) width 7,
-      // 229 workgroups, 81 us -- width 3 (534 workgroups, three rounds) took 109 us there, width 4 (two rounds) 90.
-      int best = 3, best_cost = 1 << 30;
-      const int wn_max = Mp <= 64 ? 8 : 4;   // 128 rows: more than four wavefronts would not fit their registers
-      for (int wn = 3; wn <= wn_max; ++wn) {
-        int wgs = (nblocks + wn - 1) / wn, cost = (wgs + 255) / 256 * wn;
-        if (cost <= best_cost) { best = wn; best_cost = cost; }
-      }
-      g->waves_n = best; g->stages = best == 3 && Mp != 64 ? 3 : 2; g->nsplit = 1;   // 64 rows: see gemm_lds_min_wgs
-      return;
+  const int total_chunks = ksteps / GEMM_KC;
+  g->form = GEMM_STREAM;
+  if (full_k) {
+    // No split over K (the SwiGLU epilogue needs whole sums), one workgroup per compute unit at a time: the launch takes
+    // rounds x width, rounds = ceil(workgroups / 256).  The width with the smallest product wins, the wider one on a
+    // tie (fewer rounds, fewer re-reads of the activations).  Measured at 64 rows: 608 blocks (4B) width 3, 203
+    // workgroups, 21 us (width 4: 23); 768 blocks (8B) width 3, 256 workgroups, 34 us; 1600 blocks (32B) width 7,
+    // 229 workgroups, 81 us -- width 3 (534 workgroups, three rounds) took 109 us there, width 4 (two rounds) 90.
+    int best = 3, best_cost = 1 << 30;
+    const int wn_max = Mp <= 64 ? 8 : 4;   // 128 rows: more than four wavefronts would not fit their registers
+    for (int wn = 3; wn <= wn_max; ++wn) {
+      int wgs = (nblocks + wn - 1) / wn, cost = (wgs + 255) / 256 * wn;
+      if (cost <= best_cost) { best = wn; best_cost = cost; }
     }
-    g->stages = 2;   // deeper register pipelines measured no faster once the wait counts are exact
-    // workgroups of a launch with wn weight blocks per workgroup once K is split to about one workgroup per compute unit
-    auto split_for = [&](int wn, int *wgs) {
-      int strips = (nblocks + wn - 1) / wn * (wide ? Mp / 256 : 1);
-      int ns = full_k ? 1 : (240 + strips / 2) / strips;
-      if (ns > total_chunks / 2) ns = total_chunks / 2;
-      if (ns > 10) ns = 10;
-      if (ns < 1) ns = 1;
-      int cps = (total_chunks + ns - 1) / ns;
-      ns = (total_chunks + cps - 1) / cps;
-      *wgs = strips * ns;
-      return ns;
-    };
-    g->waves_n = wide || nblocks % 4 == 0 || nblocks > 96 ? 4 : 3;
-    int wgs = 0;
-    g->nsplit = split_for(g->waves_n, &wgs);
-    // A narrow output with four blocks per workgroup can leave a third of the chip without a workgroup however K is split
-    // (2560 columns: 20 strips x 8 runs = 160); three blocks give 27 strips and 216 workgroups (measured at 64 rows on the
-    // 4B shape, output and down projection together: decode step 3.764 -> 3.741 ms; where the gain in workgroups is small --
-    // 6144 columns, 240 -> 256 -- nothing moves).  Never past one workgroup per compute unit.
-    if (!full_k && !wide && Mp <= 64 && g->waves_n == 4) {
-      int wgs3 = 0, ns3 = split_for(3, &wgs3);
-      if (wgs3 <= 256 && wgs3 * 20 >= wgs * 23) { g->waves_n = 3; g->nsplit = ns3; }
-    }
+    g->waves_n = best; g->stages = best == 3 && Mp != 64 ? 3 : 2; g->nsplit = 1;   // 64 rows: see gemm_lds_min_wgs
     return;
   }
-  g->nbw = 1;
-  g->waves_n = 1;
-  int tiles = nblocks / g->nbw * zblocks;
-  int wk = 2;
-  while (wk > 1 && (ksteps / wk < 8 || (size_t)(wk - 1) * g->nbw * mb * 4096 > 65536)) --wk;
-  if (full_k && tiles >= 256) wk = tiles >= 512 ? 1 : 2;
-  int ns = full_k ? 1 : (1536 + tiles * wk / 2) / (tiles * wk);
-  if (ns > 8) ns = 8;
-  while (ns > 1 && ksteps / (ns * wk) < 8) --ns;
-  if (ns < 1) ns = 1;
-  g->nsplit = ns;
-  g->waves_k = wk;
+  g->stages = 2;   // deeper register pipelines measured no faster once the wait counts are exact
+  // workgroups of a launch with wn weight blocks per workgroup once K is split to about one workgroup per compute unit
+  auto split_for = [&](int wn, int *wgs) {
+    int strips = (nblocks + wn - 1) / wn, ns = (240 + strips / 2) / strips;
+    if (ns > total_chunks / 2) ns = total_chunks / 2;
+    if (ns > 10) ns = 10;
+    if (ns < 1) ns = 1;
+    int cps = (total_chunks + ns - 1) / ns;
+    ns = (total_chunks + cps - 1) / cps;
+    *wgs = strips * ns;
+    return ns;
+  };
+  g->waves_n = nblocks % 4 == 0 || nblocks > 96 ? 4 : 3;
+  int wgs = 0;
+  g->nsplit = split_for(g->waves_n, &wgs);
+  // A narrow output with four blocks per workgroup can leave a third of the chip without a workgroup however K is split
+  // (2560 columns: 20 strips x 8 runs = 160); three blocks give 27 strips and 216 workgroups (measured at 64 rows on the
+  // 4B shape, output and down projection together: decode step 3.764 -> 3.741 ms; where the gain in workgroups is small --
+  // 6144 columns, 240 -> 256 -- nothing moves).  Never past one workgroup per compute unit.
+  if (Mp <= 64 && g->waves_n == 4) {
+    int wgs3 = 0, ns3 = split_for(3, &wgs3);
+    if (wgs3 <= 256 && wgs3 * 20 >= wgs * 23) { g->waves_n = 3; g->nsplit = ns3; }
+  }
 }
 
 template <int MB, int WN, int NSTAGE, int EPI>
@@ -850,7 +686,7 @@ static void gemm_lds_launch(void *out, const void *Xp, const void *Wp, int Mp, i
     attr_set = true;
   }
   int nblocks = Np / 32, total_chunks = (Kp / 16) / L::KC, cps = (total_chunks + nsplit - 1) / nsplit;
-  dim3 grid((nblocks + WN - 1) / WN, nsplit, Mp / (32 * MB)), block(64 * WN);
+  dim3 grid((nblocks + WN - 1) / WN, nsplit), block(64 * WN);
   hipLaunchKernelGGL((gemm_lds_kernel<MB, WN, NSTAGE, EPI>), grid, block, L::BYTES, st, out, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp,
                      Np, Kp, cps);
 }
@@ -875,45 +711,19 @@ static void gemm_lds_dispatch_rows(void *out, const void *Xp, const void *Wp, in
 
 template <int EPI>
 static void gemm_lds_dispatch(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, hipStream_t st) {
-  int mb = Mp / 32;   // 1, 2, 4 or a multiple of 8
-  if (mb >= 8) gemm_lds_launch<8, 4, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st);
-  else if (mb == 1) gemm_lds_dispatch_rows<1, EPI>(out, Xp, Wp, Mp, Np, Kp, g, st);
+  const int mb = Mp / 32;   // 1, 2 or 4
+  if (mb == 1) gemm_lds_dispatch_rows<1, EPI>(out, Xp, Wp, Mp, Np, Kp, g, st);
   else if (mb == 2) gemm_lds_dispatch_rows<2, EPI>(out, Xp, Wp, Mp, Np, Kp, g, st);
   else gemm_lds_dispatch_rows<4, EPI>(out, Xp, Wp, Mp, Np, Kp, g, st);
 }
 
 template <int EPI>
 static void gemm_dispatch(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, hipStream_t st) {
-  switch (g.lds) {
+  switch (g.form) {
     case GEMM_RING_256X256: gemm_ring_launch<Ring256x256, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
     case GEMM_RING_256X128: gemm_ring_launch<Ring256x128, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
-    default: break;
+    default: gemm_lds_dispatch<EPI>(out, Xp, Wp, Mp, Np, Kp, g, st);
   }
-  if (g.lds) { gemm_lds_dispatch<EPI>(out, Xp, Wp, Mp, Np, Kp, g, st); return; }
-  int mbt = Mp / 32;
-  int MB = mbt >= 8 ? 8 : mbt;
-  int ksteps = Kp / 16, kps = (ksteps + g.nsplit - 1) / g.nsplit;
-  int per_wg = g.nbw * g.waves_n, nblocks = Np / 32;
-  dim3 grid((nblocks + per_wg - 1) / per_wg, g.nsplit, mbt / MB), block(64 * g.waves_n * g.waves_k);
-  size_t lds = (size_t)(g.waves_k - 1) * g.waves_n * g.nbw * MB * 16 * 64 * sizeof(float);
-  const h16x8 *X = (const h16x8 *)Xp, *W = (const h16x8 *)Wp;
-#define GEMM_LAUNCH(MBV, NBWV) \
-  hipLaunchKernelGGL((gemm_kernel<MBV, NBWV, EPI>), grid, block, lds, st, out, X, W, Mp, Np, Kp, kps, g.waves_n)
-  if (g.nbw == 2) {
-    switch (MB) {
-      case 1: GEMM_LAUNCH(1, 2); break;
-      case 2: GEMM_LAUNCH(2, 2); break;
-      default: GEMM_LAUNCH(4, 2); break;
-    }
-  } else {
-    switch (MB) {
-      case 1: GEMM_LAUNCH(1, 1); break;
-      case 2: GEMM_LAUNCH(2, 1); break;
-      case 4: GEMM_LAUNCH(4, 1); break;
-      default: GEMM_LAUNCH(8, 1); break;
-    }
-  }
-#undef GEMM_LAUNCH
 }
 
 void fast_gemm(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, GemmEpilogue epi,
