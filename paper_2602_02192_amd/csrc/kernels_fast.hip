@@ -465,7 +465,7 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
 // kept tokens by z/ln2 - log2(-log2 u) and evaluates the winner in full.  Both orders agree unless its best two are closer than
 // the roundings of two hardware logarithms and of z: below 1e-5 plus 1e-6 of the score's magnitude; within ten times that
 // the wavefront evaluates all its kept tokens in full.  Four tokens of which none is kept draw no numbers.  128 rows of 151936
-// logits, three quarters of them kept: 62 -> 52 us, of which the ten rounds of the generator are some 35.
+// logits, three quarters of them kept: 62 -> 52 us, of which the ten rounds of the generator are some 30 by instruction count.
 __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, const int32_t *cut_last, const float *logits, int64_t ld,
                                  int V, float temperature, uint64_t seed, DrawIds ids, const int32_t *row_active) {
   __shared__ SampleAcc sh[4];
