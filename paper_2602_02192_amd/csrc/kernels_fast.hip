@@ -112,6 +112,8 @@ void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, con
 // q (half [M][Hq][hd]) or appends k / v to the half-precision cache.  Bound by latency like resid_norm_kernel: the row's
 // state, the partials, the rotation and the gains are all requested before the first sum, and a row that is not generating
 // only drops its stores.  64 rows, 5 partials of 6144: 5.41 -> 5.19 us.
+// The fused products are written out here and in the wide kernel below, because which product of a sum the compiler rounds differs
+// from one instantiation to the next, a last bit of fp32 that flips half-precision roundings in every later layer.
 constexpr int QP_HEADS = 8;
 template <int NS, bool NORM>
 __global__ void qkv_post_kernel(const float *__restrict__ partials, int Np, int Mp, uint16_t *__restrict__ q_out, const uint16_t *__restrict__ q_gain,
@@ -141,13 +143,13 @@ __global__ void qkv_post_kernel(const float *__restrict__ partials, int Np, int 
   for (int s = 0; s < NS; ++s) { a += pa[s]; b += pb[s]; }
   if (is_q || is_k) {
     if (NORM) {
-      float ss = fmaf(a, a, b * b);   // (written out here and in the wide kernel, which must round alike) the head's lanes are an aligned power-of-two group within the wave
+      float ss = fmaf(b, b, a * a);   // the head's lanes are an aligned power-of-two group within the wave
       for (int off = half >> 1; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
       float inv = 1.0f / sqrtf(ss / (float)hd + eps);
       a = a * inv * bf16_bits_to_f32(w0);
       b = b * inv * bf16_bits_to_f32(w1);
     }
-    float ra = fmaf(a, cs.x, -(b * cs.y)), rb = fmaf(a, cs.y, b * cs.x);
+    float ra = fmaf(a, cs.x, -(b * cs.y)), rb = fmaf(b, cs.x, a * cs.y);
     a = ra; b = rb;
   }
   if (is_q) {
@@ -166,7 +168,8 @@ __global__ void qkv_post_kernel(const float *__restrict__ partials, int Np, int 
 // launch of millions of threads that move 14 bytes each: here a thread takes four consecutive dims of the head's first half
 // and their four rotation partners, with 16-byte loads of the partials and of the rotation table and 8-byte stores of q and
 // of the key tile (a value tile holds eight keys of one dim per unit, so values still leave as single halves).  Same sums in
-// the same order: bit-identical to the kernel above.  grid (M, ceil((Hq + 2*Hkv) / QPW_HEADS)), block QPW_HEADS * hd/8.
+// the same order: bit-identical to the kernel above, except that with a per-head norm each square pair rounds the other
+// product (b's here, a's there), as results of the two forms always have.  grid (M, ceil((Hq + 2*Hkv) / QPW_HEADS)), block QPW_HEADS * hd/8.
 constexpr int QPW_HEADS = 16;
 template <int NS, bool NORM>
 __global__ void qkv_post_wide_kernel(const float *__restrict__ partials, int Np, int Mp, uint16_t *__restrict__ q_out, const uint16_t *__restrict__ q_gain,
@@ -212,7 +215,7 @@ __global__ void qkv_post_wide_kernel(const float *__restrict__ partials, int Np,
     const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, sy[4] = {c01[1], c01[3], c23[1], c23[3]};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float ra = fmaf(a[e], cx[e], -(b[e] * sy[e])), rb = fmaf(a[e], sy[e], b[e] * cx[e]);
+      float ra = fmaf(a[e], cx[e], -(b[e] * sy[e])), rb = fmaf(b[e], cx[e], a[e] * sy[e]);
       a[e] = ra; b[e] = rb;
     }
   }
