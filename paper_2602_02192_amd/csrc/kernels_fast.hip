@@ -268,16 +268,20 @@ void fast_qkv_post(const float *partials, int nsplit, int Np, int Mp, void *q_h1
 // With p = softmax(logits / T): keep the shortest prefix of the tokens in descending order of p (lower index first
 // among equals) whose probabilities reach top_p, draw by Gumbel-max over the kept set with the usual per-index noise,
 // return the log-prob renormalised over the kept set (Sec. 5.1 runs rollouts at top-p 0.95).  Three launches:
-// 1. topp_cut_kernel, one workgroup per row, finds the cut without sorting.  A histogram of the probability mass over 4096
-//    bins of z = logit / T, 1/128 wide from the row's maximum down, names the bin that the cut lies in; the keys of that bin
-//    (a few hundred of 150 thousand N(0, 1)-like logits) go to a list, and a radix select over the order-preserving integer
-//    image of the logit, most significant byte first, finds the cut among them.  Mass is summed in integers,
-//    q_i = floor(exp(z_i - max) * 2^40), so the sums do not depend on the order of the additions and the kept set is the
+// 1. topp_cut_kernel, one workgroup per row, finds the cut without sorting.  A histogram of the probability mass over bins of
+//    z = logit / T that divide the row's own spread evenly, from its maximum down, names the bin that the cut lies in; if that bin
+//    must hold more keys than the list, a second histogram divides it.  The keys of the bin (a few hundred of 150 thousand) go to a
+//    list, and a radix select over the order-preserving integer image of the logit finds the cut among them.  Mass is summed in
+//    integers, q_i = floor(exp(z_i - max) * 2^40), so the sums do not depend on the order of the additions and the kept set is the
 //    same on every run.  Equal keys have equal mass; of the keys equal to the cut the lowest indices are kept until the
 //    target is met, so the kernel also returns the last kept index among them.  What bounds it is the vector unit of one
-//    compute unit per row, so it counts what a logit costs: three passes (maximum; histogram; list) with one exponential,
-//    where a byte-wise select over the whole row took four with an exponential each.  128 rows of 151936
-//    logits, 8 bits at a time from the top: 102 us, now 60.
+//    compute unit per row, so it counts what a logit costs: three passes (extremes; histogram; list) with one exponential, one
+//    pass more for rows that are flat but for a few large scores.  128 rows of 151936 logits, against a byte-wise select over the
+//    whole row (five passes, an exponential each): N(0, 1) 99 -> 62 us, the same at T = 1000 98 -> 65 us, one score that weighs
+//    as much as all others, which are equal to 1e-4, 103 -> 105 us, two values 357 -> 221 us, all equal 467 -> 131 us; 8 rows of
+//    2000 logits, with the draw and the merge, 18.2 -> 17.7 us.  (Bins of a fixed width, 1/128 of z, put a whole flat row in one: 185 us
+//    at T = 1000.  More copies or bins cost more to clear and walk than they save; fewer than four copies queue up at equal
+//    logits: a third of the row equal 113 -> 123 us with the draw.)
 // 2. topp_draw_kernel, TOPP_CHUNKS workgroups per row: (max, sum-exp, best perturbed score) over the kept tokens of one
 //    slice of the vocabulary, in the partial layout of the fused sampler;
 // 3. sample_combine_kernel merges the slices.
@@ -289,15 +293,20 @@ __device__ __forceinline__ uint32_t float_order_key(float f) {   // a < b  <=>  
 __device__ __forceinline__ float order_key_float(uint32_t key) {   // the float whose key this is
   return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
-constexpr int TOPP_CAND = 1024;   // keys that the select can take from the list (more: it walks the row in each round)
+constexpr int TOPP_CAND = 1024;   // keys that the select can take from the list (more, not all equal: it walks the row in each round)
 // LDS: the histogram, lanes that meet in one bin spread over TOPP_COPIES copies of it; the radix rounds reuse it.
-constexpr int TOPP_BINS = 4096, TOPP_COPIES = 4, TOPP_RADIX_COPIES = 16, TOPP_LDS = TOPP_BINS * TOPP_COPIES * 8;
-static_assert(TOPP_RADIX_COPIES * 256 <= TOPP_BINS * TOPP_COPIES && TOPP_BINS == 4 * TOPP_THREADS, "the rounds fit; four bins per thread");
+constexpr int TOPP_BINS = 2048, TOPP_COPIES = 4, TOPP_RADIX_COPIES = 16, TOPP_PER_THREAD = TOPP_BINS / TOPP_THREADS, TOPP_LDS = TOPP_BINS * TOPP_COPIES * 8;
+constexpr int TOPP_LOADS = 4;   // 16-byte loads of a thread in flight
+// keys that are summed up pair by pair (8 rows of 32000 logits, some 50 keys: 30.6 us so, 28.1 by the radix rounds; of 2000, a few keys: 17.7, 20.0)
+constexpr int TOPP_FEW = 32;
+constexpr float TOPP_SPAN = 32.0f;   // units of z below the maximum that matter: beyond 27.8 the mass is zero
+static_assert(TOPP_RADIX_COPIES * 256 <= TOPP_BINS * TOPP_COPIES && TOPP_BINS % TOPP_THREADS == 0, "the rounds fit; whole bins per thread");
 __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_key, int32_t *cut_last, const float *logits, int64_t ld,
                                                                  int V, float temperature, float top_p, const int32_t *row_active) {
   extern __shared__ unsigned long long topp_hist[];
   __shared__ unsigned long long sh_u64[TOPP_THREADS / 64];
-  __shared__ float sh_f[TOPP_THREADS / 64];
+  __shared__ float sh_f[2][TOPP_THREADS / 64];
+  __shared__ uint32_t sh_k[2][TOPP_THREADS / 64];
   __shared__ int sh_i[TOPP_THREADS / 64];
   __shared__ uint32_t cand[TOPP_CAND];
   __shared__ unsigned long long sel_above, sel_mass;
@@ -306,31 +315,41 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
   const int m = blockIdx.x, tid = threadIdx.x, wv = tid >> 6;
   if (row_active && !row_active[m]) return;
   const float *lg = logits + (int64_t)m * ld;
-  // Every pass visits the row with a stride of the block, four 16-byte loads in flight per thread (a plain loop waits out
-  // one memory latency per element); an index past the end yields -inf: mass 0, no maximum, never above a cut.
+  // Every pass visits the row, four logits at a time, with a stride of the block, TOPP_LOADS loads in flight per thread (a plain loop
+  // waits out one memory latency per element); an index past the end yields `past`.
   const int n4 = (ld & 3) == 0 ? V >> 2 : 0;   // 16-byte loads need aligned rows
-  auto visit = [&](auto &&f) {
+  auto visit = [&](float past, auto &&f) {
     const f32x4 *lg4 = (const f32x4 *)lg;
-    constexpr int B = 4;
-    for (int i = tid; i < n4; i += B * TOPP_THREADS) {
-      f32x4 v[B];
+    for (int i = tid; i < n4; i += TOPP_LOADS * TOPP_THREADS) {
+      f32x4 v[TOPP_LOADS];
 #pragma unroll
-      for (int u = 0; u < B; ++u) { int j = i + u * TOPP_THREADS; v[u] = j < n4 ? lg4[j] : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY}; }
+      for (int u = 0; u < TOPP_LOADS; ++u) { int j = i + u * TOPP_THREADS; v[u] = j < n4 ? lg4[j] : f32x4{past, past, past, past}; }
 #pragma unroll
-      for (int u = 0; u < B; ++u) { f(v[u][0]); f(v[u][1]); f(v[u][2]); f(v[u][3]); }
+      for (int u = 0; u < TOPP_LOADS; ++u) f(v[u]);
     }
-    for (int i = n4 * 4 + tid; i < V; i += TOPP_THREADS) f(lg[i]);
+    auto at = [&](int i) { return i < V ? lg[i] : past; };
+    for (int i = n4 * 4 + tid; i < V; i += 4 * TOPP_THREADS) f(f32x4{lg[i], at(i + TOPP_THREADS), at(i + 2 * TOPP_THREADS), at(i + 3 * TOPP_THREADS)});
   };
-  for (int j = tid; j < TOPP_BINS * TOPP_COPIES; j += TOPP_THREADS) topp_hist[j] = 0;
+  const float nan = __uint_as_float(0x7fc00000u);
   if (tid == 0) cand_n = 0;
   // 1/T instead of the division: nothing here is returned, the kept set only needs the same arithmetic in every pass
   const float inv_t = 1.0f / temperature;
-  float mx = -INFINITY;
-  visit([&](float v) { mx = fmaxf(mx, v); });
+  float mx = -INFINITY, mn = INFINITY;
+  visit(nan, [&](f32x4 v) {   // (a NaN counts for neither)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { mx = fmaxf(mx, v[e]); mn = fminf(mn, v[e]); }
+  });
   mx = wave_max(mx);
-  if ((tid & 63) == 0) sh_f[wv] = mx;
+  mn = -wave_max(-mn);
+  if ((tid & 63) == 0) { sh_f[0][wv] = mx; sh_f[1][wv] = mn; }
   __syncthreads();
-  for (int w = 0; w < TOPP_THREADS / 64; ++w) mx = fmaxf(mx, sh_f[w]);
+  float bulk_hi = INFINITY, bulk_lo = -INFINITY;
+  for (int w = 0; w < TOPP_THREADS / 64; ++w) {
+    mx = fmaxf(mx, sh_f[0][w]); mn = fminf(mn, sh_f[1][w]);
+    bulk_hi = fminf(bulk_hi, sh_f[0][w]); bulk_lo = fmaxf(bulk_lo, sh_f[1][w]);
+  }
+  // most logits within an eighth of the row's spread, by what the sixteen wavefronts saw
+  const bool flat = bulk_hi > bulk_lo && (bulk_hi - bulk_lo) * 8.0f < mx - mn;
   const float zmax = mx * inv_t;
   // probability mass in units of 2^-40 of the largest one, as an integer: sums of it do not depend on the order of the
   // additions.  (Two 32-bit conversions; a float -> 64-bit integer conversion is a long instruction sequence.)
@@ -340,69 +359,187 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
     uint32_t lo = (uint32_t)((e - (float)hi) * 4294967296.0f);
     return ((unsigned long long)hi << 32) | lo;
   };
-  // Bin of a logit, falling in it: 128 to a unit of z.  Beyond 32 units below the maximum, where the mass is zero, the last
-  // one takes all.  Clamped before the conversion, so that any value at all names a bin.
-  auto bin = [&](float logit) { return (int)fminf(fmaxf(fmaf(logit, inv_t, -zmax) * -128.0f, 0.0f), (float)(TOPP_BINS - 1)); };
-  visit([&](float v) {
-    const unsigned long long q = mass(v);
-    if (q) atomicAdd(&topp_hist[bin(v) * TOPP_COPIES + (tid & (TOPP_COPIES - 1))], q);
-  });
-  __syncthreads();
-  // Walk the bins from the top: thread t owns bins 4t .. 4t+3; an inclusive prefix sum over t is the mass at or above them.
-  unsigned long long h4[4], incl = 0, total = 0;
+  // Place of a logit on the scale of the bins, falling in it: 0 at the maximum, near TOPP_BINS at the row's minimum or TOPP_SPAN units
+  // below, where the mass is zero and the last bin takes all.  Clamped before any conversion, so that any value at all names a bin.
+  const float scale = fminf(((float)TOPP_BINS - 0.5f) / fminf(zmax - mn * inv_t, TOPP_SPAN), 1e30f);
+  auto place = [&](float logit) { return fminf(fmaxf(fmaf(logit, inv_t, -zmax) * -scale, 0.0f), (float)TOPP_BINS - 0.25f); };
+  auto bin = [&](float logit) { return (int)place(logit); };
+  int cut_bin = -1, cut_sub = -1;   // the bin that the cut lies in, and, where that bin is divided, its part
+  auto sub = [&](float logit) { return (int)fminf((place(logit) - (float)cut_bin) * (float)TOPP_BINS, (float)(TOPP_BINS - 1)); };
+  auto member = [&](float logit) { return bin(logit) == cut_bin && (cut_sub < 0 || sub(logit) == cut_sub); };
+  unsigned long long target = 0, above = 0;   // mass to reach; mass of the keys above the range that the cut is known to lie in
+  // Clears the histogram, has `fill` add to it, and walks it from the top: exactly one bin takes the running mass across the target.
+  // A sum over the whole row (target 0) first says what the target is.  Returns false if there is no mass at all.
+  auto histogram = [&](auto &&fill) {
+    __syncthreads();
+    for (int j = tid; j < TOPP_BINS * TOPP_COPIES; j += TOPP_THREADS) topp_hist[j] = 0;
+    __syncthreads();
+    fill();
+    __syncthreads();
+    unsigned long long h[TOPP_PER_THREAD], incl = 0, total = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    h4[k] = 0;
-    for (int j = 0; j < TOPP_COPIES; ++j) h4[k] += topp_hist[(4 * tid + k) * TOPP_COPIES + j];
-    incl += h4[k];
-  }
-  const unsigned long long mine4 = incl;
-  for (int o = 1; o < 64; o <<= 1) { unsigned long long v = __shfl_up(incl, o, 64); if ((tid & 63) >= o) incl += v; }
-  if ((tid & 63) == 63) sh_u64[wv] = incl;
-  __syncthreads();
-  for (int w = 0; w < TOPP_THREADS / 64; ++w) { if (w < wv) incl += sh_u64[w]; total += sh_u64[w]; }
-  if (total == 0) {   // no finite maximum: every token is kept
+    for (int k = 0; k < TOPP_PER_THREAD; ++k) {   // the copies of bin k * TOPP_THREADS + tid, then (from LDS) consecutive bins per thread
+      h[k] = 0;
+#pragma unroll
+      for (int j = 0; j < TOPP_COPIES; ++j) h[k] += topp_hist[(k * TOPP_THREADS + tid) * TOPP_COPIES + j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TOPP_PER_THREAD; ++k) topp_hist[k * TOPP_THREADS + tid] = h[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TOPP_PER_THREAD; ++k) { h[k] = topp_hist[TOPP_PER_THREAD * tid + k]; incl += h[k]; }
+    const unsigned long long mine = incl;
+    for (int o = 1; o < 64; o <<= 1) { unsigned long long v = __shfl_up(incl, o, 64); if ((tid & 63) >= o) incl += v; }
+    if ((tid & 63) == 63) sh_u64[wv] = incl;
+    __syncthreads();
+    for (int w = 0; w < TOPP_THREADS / 64; ++w) { if (w < wv) incl += sh_u64[w]; total += sh_u64[w]; }
+    if (total == 0) return false;
+    if (target == 0) {
+      target = (unsigned long long)ceil((double)total * (double)top_p);
+      if (target < 1) target = 1;
+      if (target > total) target = total;
+    }
+    unsigned long long at = above + incl - mine;
+    if (at < target && at + mine >= target) {
+      int k = 0;
+      while (k < TOPP_PER_THREAD - 1 && at + h[k] < target) at += h[k++];
+      sel_digit = (uint32_t)(TOPP_PER_THREAD * tid + k);
+      sel_above = at;
+      sel_mass = h[k];
+    }
+    __syncthreads();
+    above = sel_above;
+    return true;
+  };
+  // Four masses to four places of the histogram; neighbours that share one -- flat or equal scores, which would otherwise queue up at one
+  // address -- go there as one sum.
+  auto add4 = [&](const int (&at)[4], const unsigned long long (&q)[4]) {
+    if (at[0] == at[1] && at[0] == at[2] && at[0] == at[3]) {
+      const unsigned long long sum = (q[0] + q[1]) + (q[2] + q[3]);
+      if (sum) atomicAdd(&topp_hist[at[0]], sum);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (q[e]) atomicAdd(&topp_hist[at[e]], q[e]);
+    }
+  };
+  const int copy = tid & (TOPP_COPIES - 1);
+  uint32_t kmin = 0xffffffffu, kmax = 0;
+  const bool one_value = mn == mx;   // (zeros may differ in sign)
+  if (!histogram([&] {
+        if (one_value) {
+          int n = 0;
+          visit(nan, [&](f32x4 v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (v[e] == mx) { ++n; kmin = min(kmin, float_order_key(v[e])); kmax = max(kmax, float_order_key(v[e])); }
+          });
+          if (n) atomicAdd(&topp_hist[bin(mx) * TOPP_COPIES + copy], mass(mx) * (unsigned long long)n);
+          if (tid == 0) cand_n = TOPP_CAND + 1;   // no list
+        } else if (flat) {
+          visit(-INFINITY, [&](f32x4 v) {
+            int at[4];
+            unsigned long long q[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { at[e] = bin(v[e]) * TOPP_COPIES + copy; q[e] = mass(v[e]); }
+            add4(at, q);
+          });
+        } else {
+          visit(-INFINITY, [&](f32x4 v) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const unsigned long long q = mass(v[e]);
+              if (q) atomicAdd(&topp_hist[bin(v[e]) * TOPP_COPIES + copy], q);
+            }
+          });
+        }
+      })) {   // no finite maximum: every token is kept
     if (tid == 0) { cut_key[m] = 0; cut_last[m] = V; }
     return;
   }
-  unsigned long long target = (unsigned long long)ceil((double)total * (double)top_p);
-  if (target < 1) target = 1;
-  if (target > total) target = total;
-  if (incl >= target && incl - mine4 < target) {   // exactly one thread
-    unsigned long long at = incl - mine4;
-    int k = 0;
-    while (k < 3 && at + h4[k] < target) at += h4[k++];
-    sel_digit = (uint32_t)(4 * tid + k);
-    sel_above = at;
+  cut_bin = (int)sel_digit;
+  // The bin's keys have at most the mass at its upper edge each.  If it holds more of them than the list for certain, it is
+  // divided (flat scores below a few large ones; equal ones stay together however it is divided).
+  if (!one_value && (float)sel_mass > (float)TOPP_CAND * 1.0995116e12f * __expf(-(float)cut_bin / scale)) {
+    histogram([&] {
+      visit(-INFINITY, [&](f32x4 v) {
+        int at[4];
+        unsigned long long q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool in = bin(v[e]) == cut_bin;
+          at[e] = (in ? sub(v[e]) : 0) * TOPP_COPIES + copy;
+          q[e] = in ? mass(v[e]) : 0;
+        }
+        add4(at, q);
+      });
+    });
+    cut_sub = (int)sel_digit;
   }
+  if (!one_value)
+    visit(nan, [&](f32x4 v) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (member(v[e]) && v[e] == v[e]) {
+          const int k = cand_n > TOPP_CAND ? TOPP_CAND : atomicAdd(&cand_n, 1);
+          const uint32_t key = float_order_key(v[e]);
+          if (k < TOPP_CAND) cand[k] = key;
+          kmin = min(kmin, key);
+          kmax = max(kmax, key);
+        }
+    });
+  for (int o = 32; o > 0; o >>= 1) { kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, 64)); kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, 64)); }
+  if ((tid & 63) == 0) { sh_k[0][wv] = kmin; sh_k[1][wv] = kmax; }
   __syncthreads();
-  const int cut_bin = (int)sel_digit;
-  unsigned long long above = sel_above;   // mass of the keys above the range that the cut is known to lie in
-  visit([&](float v) {
-    if (bin(v) == cut_bin) {
-      const int k = atomicAdd(&cand_n, 1);
-      if (k < TOPP_CAND) cand[k] = float_order_key(v);
+  for (int w = 0; w < TOPP_THREADS / 64; ++w) { kmin = min(kmin, sh_k[0][w]); kmax = max(kmax, sh_k[1][w]); }
+  if (cand_n <= TOPP_FEW && kmin != kmax) {   // few keys: each thread sums over all of them what its own one has above and beside it
+    __syncthreads();
+    const uint32_t key = tid < cand_n ? cand[tid] : 0;
+    if (tid < cand_n) topp_hist[tid] = mass(order_key_float(key));
+    __syncthreads();
+    if (tid < cand_n) {
+      unsigned long long over = above, equal = 0;
+      for (int j = 0; j < cand_n; ++j) {
+        if (cand[j] > key) over += topp_hist[j];
+        if (cand[j] == key) equal += topp_hist[j];
+      }
+      if (over < target && over + equal >= target) { sel_digit = key; sel_above = over; sel_mass = equal; }   // (the same from equal keys)
     }
-  });
-  // radix select of the cut key: the largest key K with mass{key >= K} >= target
-  uint32_t prefix = 0;
-  for (int round = 0; round < 4; ++round) {
+    __syncthreads();
+    kmin = kmax = sel_digit;
+    above = sel_above;
+  }
+  // Radix select of the cut key among the members: the largest key K with mass{key >= K} >= target.  The leading bytes that all of them
+  // share are known already, all four where they are equal.
+  const int shared_bytes = kmin == kmax ? 4 : __clz((int)(kmin ^ kmax)) >> 3;
+  uint32_t prefix = shared_bytes ? kmin >> (32 - 8 * shared_bytes) : 0;
+  for (int round = shared_bytes; round < 4; ++round) {
     const int shift = 24 - 8 * round;
     __syncthreads();
     for (int j = tid; j < TOPP_RADIX_COPIES * 256; j += TOPP_THREADS) topp_hist[j] = 0;
     __syncthreads();
-    auto count = [&](uint32_t key) {
-      if (round == 0 || (key >> (shift + 8)) == prefix) {
-        const unsigned long long q = mass(order_key_float(key));
-        if (q) atomicAdd(&topp_hist[(tid & (TOPP_RADIX_COPIES - 1)) * 256 + ((key >> shift) & 255u)], q);
+    // (a key outside the prefix adds nothing, anywhere)
+    const int rcopy = (tid & (TOPP_RADIX_COPIES - 1)) * 256;
+    auto digit = [&](uint32_t key) { return rcopy + (int)((key >> shift) & 255u); };
+    auto weight = [&](uint32_t key) { return round == 0 || (key >> (shift + 8)) == prefix ? mass(order_key_float(key)) : 0; };
+    if (cand_n <= TOPP_CAND) {
+      for (int j = tid; j < cand_n; j += TOPP_THREADS) {
+        const unsigned long long q = weight(cand[j]);
+        if (q) atomicAdd(&topp_hist[digit(cand[j])], q);
       }
-    };
-    if (cand_n <= TOPP_CAND) { for (int j = tid; j < cand_n; j += TOPP_THREADS) count(cand[j]); }
-    else visit([&](float v) { if (bin(v) == cut_bin) count(float_order_key(v)); });
+    } else {
+      visit(-INFINITY, [&](f32x4 v) {
+        int at[4];
+        unsigned long long q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { at[e] = digit(float_order_key(v[e])); q[e] = member(v[e]) ? weight(float_order_key(v[e])) : 0; }
+        add4(at, q);
+      });
+    }
     __syncthreads();
     // thread t of the first four wavefronts owns digit 255 - t; exactly one digit takes the running mass across the target
-    unsigned long long h = 0;
-    incl = 0;
+    unsigned long long h = 0, incl = 0;
     if (tid < 256) {
       for (int j = 0; j < TOPP_RADIX_COPIES; ++j) h += topp_hist[j * 256 + 255 - tid];
       incl = h;
@@ -447,19 +584,19 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
     }
     return;
   }
-  const int chunk = (V + TOPP_THREADS - 1) / TOPP_THREADS, i0 = tid * chunk, i1 = min(V, i0 + chunk);
-  int mine = 0;
-  for (int i = i0; i < i1; ++i) mine += float_order_key(lg[i]) == cut;
-  int upto = mine;
-  for (int o = 1; o < 64; o <<= 1) { int v = __shfl_up(upto, o, 64); if ((tid & 63) >= o) upto += v; }
+  // each wavefront counts its share of the row, then the one whose share holds the take-th looks for it
+  const int share = (V + TOPP_THREADS - 1) / TOPP_THREADS * 64, i0 = wv * share, i1 = min(V, i0 + share), lane = tid & 63;
+  auto tie = [&](int i) { return __ballot(i < i1 && float_order_key(lg[min(i, V - 1)]) == cut); };
+  int mine = 0, rank = 0;
+  for (int i = i0; i < i1; i += 64) mine += __popcll(tie(i + lane));
+  if (lane == 0) sh_i[wv] = mine;
   __syncthreads();
-  if ((tid & 63) == 63) sh_i[wv] = upto;
-  __syncthreads();
-  int rank = upto - mine;   // ties before this thread's run
-  for (int w = 0; w < wv; ++w) rank += sh_i[w];
-  if (rank < take && take <= rank + mine) {   // the take-th tie lies in this thread's run
-    for (int i = i0; i < i1; ++i)
-      if (float_order_key(lg[i]) == cut && ++rank == take) cut_last[m] = i;
+  for (int w = 0; w < wv; ++w) rank += sh_i[w];   // ties before this share
+  if (rank >= take || take > rank + mine) return;
+  for (int i = i0; i < i1; i += 64) {
+    const unsigned long long b = tie(i + lane);
+    if (rank < take && take <= rank + __popcll(b) && (b >> lane & 1) && rank + __popcll(b & ((1ull << lane) - 1)) == take - 1) cut_last[m] = i + lane;
+    rank += __popcll(b);
   }
 }
 

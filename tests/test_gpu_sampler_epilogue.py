@@ -4,6 +4,7 @@ Vocabularies that end inside a weight block, inside a wavefront's share and on t
 batch size; temperatures at which the scores span thousands and at which they are nearly all noise."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2602_02192_amd import synth
 
@@ -60,4 +61,58 @@ def test_nucleus_draws_the_tokens_of_the_oracle_over_the_same_logits(orc, vocab,
     # of 72 draws; a row's 9002 masses are nearly equal at T = 60, so all rows' cuts lie as close to the 0.95 as the nearest
     # multiple of 1 / 9002 does (5e-6), and up to half a dozen of those 12 are left out
     assert checked >= 54
+    ctx.close()
+
+
+def _row(kind, vocab, r):
+    z = r.standard_normal(vocab)
+    if kind == "flat":
+        z *= 1e-3
+    elif kind == "spike over flat":      # half of the mass on one token, the cut among the others
+        z *= 1e-4
+        z[7] = np.log(vocab)
+    elif kind == "a third equal":        # more equal logits than any list holds, in the middle of the others
+        z[vocab // 3:2 * vocab // 3] = 0.25
+    elif kind == "two values":
+        z = np.where(z > 0, 1.0, 0.0)
+    elif kind == "spike over equal":
+        z[:] = 0.0
+        z[vocab - 1] = np.log(vocab)
+    return z
+
+
+@pytest.mark.parametrize("kind", ["normal", "flat", "spike over flat", "a third equal", "two values", "spike over equal"])
+@pytest.mark.parametrize("vocab", [1500, 32001, 151936])
+def test_nucleus_of_rows_of_any_shape(orc, kind, vocab):
+    """Rows whose scores spread over ten units, over a few thousandths, over thousandths below one large score, or fall on few
+    values: the cut's bin then holds a few keys, has to be divided, or holds nothing but equal keys.  The model passes one vector
+    on to the lm_head, whatever the token: 16 (1, 1/256, 0 ...), so two columns of lm_head are the row, in some 16 bits."""
+    r = np.random.default_rng(vocab)
+    shape = synth.ModelShape(1, 256, 4, 2, 64, 64, vocab)
+    blob = synth.make_weights(shape, 1)
+    off = synth.blob_offsets(shape)
+
+    def tensor(name):
+        at, dims = off[name]
+        return blob[at:at + int(np.prod(dims))].view(*dims)
+    for name in ("embed", "layers.0.wo", "layers.0.w_down", "lm_head"):
+        tensor(name).zero_()
+    tensor("embed")[:, 0], tensor("embed")[:, 1] = 1.0, 2.0 ** -8
+    z = torch.from_numpy(_row(kind, vocab, r) / 16)
+    head = tensor("lm_head")
+    head[:, 0] = z
+    head[:, 1] = (z - head[:, 0].double()) * 256
+    ctx = make_ctx(shape, 2, 6, blob)
+    prompts, lens = synth.make_prompts(vocab, 2, 3, seed=1)
+    for top_p in (0.95, 0.6):
+        got = ctx.rollout(prompts, lens, 1, 2, 1.0, 23, top_p=top_p, forced=np.zeros((2, 2), np.int32), want_logits=True)
+        for n in range(2):
+            for s in range(2):
+                zz = got["logits"][n, s].astype(np.float64)
+                tok, lp, gap, kept, _ = orc.sample_top_p(zz, 1.0, top_p, 23, n, s)
+                # where the cut falls between nearly equal masses it may be one entry off: that entry's mass, 1 / (top_p vocab) at most
+                # unless the spike is kept alone, goes to the log-sum-exp; its own draw is as unlikely as its mass
+                assert gap < 1e-5 or got["tokens"][n, s] == tok, (top_p, n, s, kept)
+                if got["tokens"][n, s] == tok:
+                    assert abs(got["logprobs"][n, s] - lp) < 2.4e-5 + 2 / (top_p * kept), (top_p, n, s, kept)
     ctx.close()
