@@ -516,6 +516,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
     if (until_check <= 0) {
       if (!first) {
         launch_rows_to_host(c->pin_in, c->rows, c->d_gen_len, Rc, st);
+        HIPCHK(c, hipGetLastError());   // (a launch that was refused would leave the bytes of the last hand-over there)
         HIPCHK(c, hipStreamSynchronize(st));
         memcpy(tok.data(), c->pin_in, (size_t)Rc * 4);
         memcpy(pos.data(), c->pin_in + Rc, (size_t)Rc * 4);
@@ -531,6 +532,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
         const int ne = (int)std::min<size_t>(rec_cap, ended.size() - e0);
         for (int q = 0; q < ne; ++q) c->pin_list[q] = slot[ended[e0 + q]];
         launch_records_to_host(c->pin_rec, c->pin_list, ne, max_new, d_out_tok, d_out_lp, d_out_ver, st);
+        HIPCHK(c, hipGetLastError());
         HIPCHK(c, hipStreamSynchronize(st));
         for (int q = 0; q < ne; ++q) {
           const int r = ended[e0 + q], n = row_seq[r];
@@ -608,6 +610,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
             if (d_forced) memcpy(forced_in + (size_t)q * max_new, o.forced_tokens + (int64_t)fresh[f0 + q].second * max_new, (size_t)max_new * 4);
           }
           launch_records_begin(c->pin_list, nf, max_new, d_out_tok, d_out_lp, d_out_ver, d_forced, forced_in, st);
+          HIPCHK(c, hipGetLastError());
           HIPCHK(c, hipStreamSynchronize(st));   // the list and the strings are rewritten
         }
         dirty = true;   // the upload below also restores the rows the prefill pass used as its own

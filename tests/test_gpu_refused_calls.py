@@ -1,0 +1,63 @@
+"""What the host does when the HIP runtime refuses a call in the middle of a continuous rollout: a refused launch of one of its
+hand-over kernels is an error of the call (it would otherwise return the bytes of an earlier hand-over).  Each case is a process of
+its own, whose calls of the runtime go through hip_refusals.c; nothing that is refused reaches the GPU."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+CHILD = r"""
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path[:0] = [sys.argv[2], sys.argv[2] + "/tests"]
+import numpy as np
+from paper_2602_02192_amd import echo, synth
+from gpu_util import make_ctx
+
+shape, P, G, new = synth.TINY, 6, 2, 7
+blob = synth.make_weights(shape, 0)
+prompts, lens = synth.make_prompts(shape.vocab, P, 9, seed=1)
+forced = np.random.default_rng(2).integers(0, shape.vocab, size=(P * G, new)).astype(np.int32)
+stop = np.random.default_rng(3).integers(1, new + 1, P * G).astype(np.int32)
+
+def run(ctx):
+    return ctx.rollout(prompts, lens, G, new, 1.0, 4, stop_lens=stop, forced=forced, continuous=True)
+
+ref_ctx = make_ctx(shape, 4, 9 + new, blob)
+ref = run(ref_ctx)
+"""
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("shim") / "hip_refusals.so")
+    subprocess.check_call(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-o", lib, os.path.join(HERE, "hip_refusals.c"), "-ldl"])
+
+    def run(body):
+        r = subprocess.run([sys.executable, "-c", CHILD + body, lib, os.path.dirname(HERE)], capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0 and r.stdout.strip().endswith("as expected"), r.stdout[-2000:] + r.stderr[-2000:]
+    return run
+
+
+@pytest.mark.parametrize("kernel", ["rows_to_host_kernel", "rows_from_host_kernel", "records_to_host_kernel", "records_begin_kernel"])
+@pytest.mark.parametrize("after", [0, 1])
+def test_a_refused_hand_over_is_an_error(child, kernel, after):
+    child(f"""
+ctx = make_ctx(shape, 4, 9 + new, blob)
+shim.hip_refuse(b"{kernel}", {after})
+try:
+    run(ctx)
+except echo.EchoError as e:
+    assert e.code == echo.ECHO_EHIP, e
+    assert shim.hip_refused()
+else:
+    raise SystemExit("the call succeeded")
+again = run(ctx)    # and the context is as good as before
+assert all(np.array_equal(again[k], ref[k]) for k in ("tokens", "logprobs", "lens", "versions"))
+print("as expected")
+""")
