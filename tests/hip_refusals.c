@@ -9,7 +9,7 @@
 
 typedef struct { unsigned x, y, z; } dim3;
 static char what[128];
-static int left, pending;
+static int left, seen, pending;
 
 static int find(struct dl_phdr_info *i, size_t n, void *out) {
   (void)n;
@@ -23,13 +23,16 @@ static void *runtime(const char *sym) {
   return dlsym(lib, sym);
 }
 static int refuse(const char *name, int error) {
-  if (!what[0] || !name || !strstr(name, what) || left-- > 0) return 0;
+  if (!what[0] || !name || !strstr(name, what)) return 0;
+  ++seen;
+  if (left-- > 0) return 0;
   what[0] = 0;
   return pending = error;
 }
 
-void hip_refuse(const char *name, int after) { strncpy(what, name, sizeof what - 1); left = after; }
+void hip_refuse(const char *name, int after) { strncpy(what, name, sizeof what - 1); left = after; seen = 0; }
 int hip_refused(void) { return what[0] == 0; }
+int hip_seen(void) { return seen; }   /* such calls since hip_refuse */
 
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
   static int (*next)(const void *, dim3, dim3, void **, size_t, void *);
