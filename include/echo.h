@@ -214,7 +214,10 @@ int echo_rollout(echo_ctx *ctx, const int32_t *prompt_tokens, int32_t prompt_str
  *   - a snapshot staged by echo_load_policy / _commit while the call runs is switched in between two decode
  *     steps as soon as it is there (out_versions tags every token); pinned swaps (n_swaps), debug_logits and
  *     time_kernels are refused with ECHO_EINVAL;
- *   - echo_stats: prefill_ms is the time spent admitting prompts, decode_ms the rest. */
+ *   - echo_stats: prefill_ms is the time spent admitting prompts, decode_ms the rest.
+ * The first call on a context allocates pinned host memory for what it exchanges with the GPU between steps (60 bytes per
+ * sequence of max_seqs and the larger of 4 MiB and 16 * max_ctx bytes), which echo_destroy frees; where the system gives none the call
+ * does without and copies piece by piece. */
 int echo_rollout_continuous(echo_ctx *ctx, const int32_t *prompt_tokens, int32_t prompt_stride,
                             const int32_t *prompt_lens, int32_t n_prompts, int32_t G, int32_t max_new,
                             float temperature, uint64_t seed, const echo_rollout_opts *opts, int32_t *out_tokens,

@@ -125,12 +125,20 @@ int check_rollout_args(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt
   return ECHO_OK;
 }
 
-// The pinned host memory of continuous rollouts (call with the rollout marked as running: one at a time per context).
+// The pinned host memory of continuous rollouts (call with the rollout marked as running: one at a time per context).  Without it
+// (c->pin null: the system gives none) a continuous rollout copies array by array and record by record.
 int ensure_pinned(echo_ctx *c) {
-  if (c->pin) return 0;
+  if (c->pin) {   // a call that failed half-way may have left work queued that reads it
+    HIPCHK(c, hipStreamSynchronize(c->cs));
+    return 0;
+  }
   const size_t n = (size_t)round_up(c->d.max_seqs, 64);
   c->pin_rec_bytes = std::max((size_t)4 << 20, (size_t)16 * c->d.max_ctx);   // at least one record of the longest kind
-  HIPCHK(c, hipHostMalloc((void **)&c->pin, (4 + 10 + 1) * n * 4 + c->pin_rec_bytes, hipHostMallocDefault));
+  if (hipHostMalloc((void **)&c->pin, (4 + 10 + 1) * n * 4 + c->pin_rec_bytes, hipHostMallocDefault) != hipSuccess) {
+    c->pin = nullptr;
+    (void)hipGetLastError();
+    return 0;
+  }
   c->pin_in = (int32_t *)c->pin; c->pin_out = c->pin_in + 4 * n; c->pin_list = c->pin_out + 10 * n; c->pin_rec = (char *)(c->pin_list + n);
   return 0;
 }
@@ -496,12 +504,88 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   // (the pinned buffer is free to rewrite: the stream is waited for between any two uploads)
   auto upload_rows = [&]() -> int {
     const std::vector<int32_t> *src[10] = {&tok, &pos, &act, &slot, &pslot, &ptiles, &plen, &gen, &lim, &stream};
+    if (!c->pin) {
+      int32_t *dst[10] = {c->rows.token, c->rows.pos, c->rows.active, c->rows.slot, c->rows.pslot, c->rows.ptiles, seq_state.prompt_len, seq_state.gen_len,
+                          seq_state.limit, seq_state.stream};
+      for (int a = 0; a < 10; ++a) HIPCHK(c, hipMemcpyAsync(dst[a], src[a]->data(), (size_t)R * 4, hipMemcpyHostToDevice, st));
+      HIPCHK(c, hipStreamSynchronize(st));
+      return 0;
+    }
     for (int a = 0; a < 10; ++a) memcpy(c->pin_out + (size_t)a * R, src[a]->data(), (size_t)R * 4);   // R: also the rows given up
     launch_rows_from_host(c->pin_out, c->rows, seq_state, R, st);
     HIPCHK(c, hipGetLastError());
     return 0;
   };
+  auto read_rows = [&]() -> int {
+    std::vector<int32_t> *dst[4] = {&tok, &pos, &act, &gen};
+    if (!c->pin) {
+      const int32_t *src[4] = {c->rows.token, c->rows.pos, c->rows.active, c->d_gen_len};
+      for (int a = 0; a < 4; ++a) HIPCHK(c, hipMemcpyAsync(dst[a]->data(), src[a], (size_t)Rc * 4, hipMemcpyDeviceToHost, st));
+      HIPCHK(c, hipStreamSynchronize(st));
+      return 0;
+    }
+    launch_rows_to_host(c->pin_in, c->rows, c->d_gen_len, Rc, st);
+    HIPCHK(c, hipGetLastError());   // (a launch that was refused would leave the bytes of the last hand-over there)
+    HIPCHK(c, hipStreamSynchronize(st));
+    for (int a = 0; a < 4; ++a) memcpy(dst[a]->data(), c->pin_in + (size_t)a * Rc, (size_t)Rc * 4);
+    return 0;
+  };
   const int rec_cap = std::max(1, (int)std::min<size_t>(R, c->pin_rec_bytes / ((size_t)16 * max_new)));   // records that fit the pinned buffer
+  // The records in cache slots slots[i] go to the caller's arrays as sequences seqs[i].
+  auto hand_over = [&](const std::vector<int> &slots, const std::vector<int> &seqs) -> int {
+    if (!c->pin) {
+      for (size_t i = 0; i < slots.size(); ++i) {
+        const int64_t r0 = (int64_t)slots[i] * max_new, n0 = (int64_t)seqs[i] * max_new;
+        HIPCHK(c, hipMemcpyAsync(out_tokens + n0, d_out_tok + r0, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
+        HIPCHK(c, hipMemcpyAsync(out_logprobs + n0, d_out_lp + r0, (size_t)max_new * 4, hipMemcpyDeviceToHost, st));
+        if (out_versions) HIPCHK(c, hipMemcpyAsync(out_versions + n0, d_out_ver + r0, (size_t)max_new * 8, hipMemcpyDeviceToHost, st));
+      }
+      HIPCHK(c, hipStreamSynchronize(st));
+      return 0;
+    }
+    for (size_t e0 = 0; e0 < slots.size(); e0 += rec_cap) {
+      const int ne = (int)std::min<size_t>(rec_cap, slots.size() - e0);
+      for (int q = 0; q < ne; ++q) c->pin_list[q] = slots[e0 + q];
+      launch_records_to_host(c->pin_rec, c->pin_list, ne, max_new, d_out_tok, d_out_lp, d_out_ver, st);
+      HIPCHK(c, hipGetLastError());
+      HIPCHK(c, hipStreamSynchronize(st));
+      for (int q = 0; q < ne; ++q) {
+        const int64_t n0 = (int64_t)seqs[e0 + q] * max_new;
+        const char *rec = c->pin_rec + (size_t)q * 16 * max_new;
+        if (out_versions) memcpy(out_versions + n0, rec, (size_t)max_new * 8);
+        memcpy(out_tokens + n0, rec + (size_t)8 * max_new, (size_t)max_new * 4);
+        memcpy(out_logprobs + n0, rec + (size_t)12 * max_new, (size_t)max_new * 4);
+      }
+    }
+    return 0;
+  };
+  // The records of cache slots slots[i] start empty, for sequences seqs[i] (the pinned buffer holds as many forced token strings as records).
+  auto begin_records = [&](const std::vector<int> &slots, const std::vector<int> &seqs) -> int {
+    if (!c->pin) {
+      for (size_t i = 0; i < slots.size(); ++i) {
+        const int64_t r0 = (int64_t)slots[i] * max_new;
+        launch_fill_i32(d_out_tok + r0, -1, max_new, st);
+        launch_fill_i32((int32_t *)(d_out_lp + r0), 0, max_new, st);
+        launch_fill_i32((int32_t *)(d_out_ver + r0), -1, (int64_t)max_new * 2, st);
+        if (d_forced)
+          HIPCHK(c, hipMemcpyAsync(d_forced + r0, o.forced_tokens + (int64_t)seqs[i] * max_new, (size_t)max_new * 4, hipMemcpyHostToDevice, st));
+      }
+      HIPCHK(c, hipGetLastError());
+      return 0;
+    }
+    for (size_t f0 = 0; f0 < slots.size(); f0 += rec_cap) {
+      const int nf = (int)std::min<size_t>(rec_cap, slots.size() - f0);
+      int32_t *forced_in = d_forced ? (int32_t *)c->pin_rec : nullptr;
+      for (int q = 0; q < nf; ++q) {
+        c->pin_list[q] = slots[f0 + q];
+        if (d_forced) memcpy(forced_in + (size_t)q * max_new, o.forced_tokens + (int64_t)seqs[f0 + q] * max_new, (size_t)max_new * 4);
+      }
+      launch_records_begin(c->pin_list, nf, max_new, d_out_tok, d_out_lp, d_out_ver, d_forced, forced_in, st);
+      HIPCHK(c, hipGetLastError());
+      HIPCHK(c, hipStreamSynchronize(st));   // the list and the strings are rewritten
+    }
+    return 0;
+  };
   auto limit_of = [&](int n) { return o.stop_lens ? std::max(1, std::min(max_new, o.stop_lens[n])) : max_new; };
   launch_fill_i32(c->d_step, 0, 1, st);
   c->ids = DrawIds{c->d_step, c->d_gen_len, c->d_stream};
@@ -514,39 +598,21 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   const int max_quads = 2 * c->p.Mcap / 4;   // the two row maps serve as the copy list
   for (;;) {
     if (until_check <= 0) {
-      if (!first) {
-        launch_rows_to_host(c->pin_in, c->rows, c->d_gen_len, Rc, st);
-        HIPCHK(c, hipGetLastError());   // (a launch that was refused would leave the bytes of the last hand-over there)
-        HIPCHK(c, hipStreamSynchronize(st));
-        memcpy(tok.data(), c->pin_in, (size_t)Rc * 4);
-        memcpy(pos.data(), c->pin_in + Rc, (size_t)Rc * 4);
-        memcpy(act.data(), c->pin_in + 2 * (size_t)Rc, (size_t)Rc * 4);
-        memcpy(gen.data(), c->pin_in + 3 * (size_t)Rc, (size_t)Rc * 4);
-      }
+      if (!first && (rc = read_rows())) return rc;
       first = false;
       // a sequence that has ended hands its record over
-      std::vector<int> ended;
-      for (int r = 0; r < Rc; ++r)
-        if (row_seq[r] >= 0 && !act[r]) ended.push_back(r);
-      for (size_t e0 = 0; e0 < ended.size(); e0 += rec_cap) {
-        const int ne = (int)std::min<size_t>(rec_cap, ended.size() - e0);
-        for (int q = 0; q < ne; ++q) c->pin_list[q] = slot[ended[e0 + q]];
-        launch_records_to_host(c->pin_rec, c->pin_list, ne, max_new, d_out_tok, d_out_lp, d_out_ver, st);
-        HIPCHK(c, hipGetLastError());
-        HIPCHK(c, hipStreamSynchronize(st));
-        for (int q = 0; q < ne; ++q) {
-          const int r = ended[e0 + q], n = row_seq[r];
-          const int64_t n0 = (int64_t)n * max_new;
-          const char *rec = c->pin_rec + (size_t)q * 16 * max_new;
-          if (out_versions) memcpy(out_versions + n0, rec, (size_t)max_new * 8);
-          memcpy(out_tokens + n0, rec + (size_t)8 * max_new, (size_t)max_new * 4);
-          memcpy(out_logprobs + n0, rec + (size_t)12 * max_new, (size_t)max_new * 4);
-          out_lens[n] = gen[r];
-          row_seq[r] = -1;
-          --group_left[n / G];
-          ++done_seqs;
-        }
+      std::vector<int> from, ended;   // cache slot, sequence
+      for (int r = 0; r < Rc; ++r) {
+        const int n = row_seq[r];
+        if (n < 0 || act[r]) continue;
+        from.push_back(slot[r]);
+        ended.push_back(n);
+        out_lens[n] = gen[r];
+        row_seq[r] = -1;
+        --group_left[n / G];
+        ++done_seqs;
       }
+      if (!ended.empty() && (rc = hand_over(from, ended))) return rc;
       if (done_seqs == N) break;
       // its row is free again, unless the cache slot still holds the prompt tiles that running siblings read
       free_rows.clear();
@@ -598,21 +664,10 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
           launch_kv_copy_ranges(c->kv, c->d_map_a, nq, st);
           HIPCHK(c, hipStreamSynchronize(st));   // the list is rewritten by the next round
         }
-        // the new sequences' records start empty (the pinned buffer holds as many forced token strings as records)
-        std::vector<std::pair<int, int>> fresh;   // cache slot, sequence
+        std::vector<int> into, fresh;   // cache slot, sequence
         for (Admit &ad : admitted)
-          for (int g = 0; g < G; ++g) fresh.push_back({slot[ad.rows[g]], ad.prompt * G + g});
-        for (size_t f0 = 0; f0 < fresh.size(); f0 += rec_cap) {
-          const int nf = (int)std::min<size_t>(rec_cap, fresh.size() - f0);
-          int32_t *forced_in = d_forced ? (int32_t *)c->pin_rec : nullptr;
-          for (int q = 0; q < nf; ++q) {
-            c->pin_list[q] = fresh[f0 + q].first;
-            if (d_forced) memcpy(forced_in + (size_t)q * max_new, o.forced_tokens + (int64_t)fresh[f0 + q].second * max_new, (size_t)max_new * 4);
-          }
-          launch_records_begin(c->pin_list, nf, max_new, d_out_tok, d_out_lp, d_out_ver, d_forced, forced_in, st);
-          HIPCHK(c, hipGetLastError());
-          HIPCHK(c, hipStreamSynchronize(st));   // the list and the strings are rewritten
-        }
+          for (int g = 0; g < G; ++g) { into.push_back(slot[ad.rows[g]]); fresh.push_back(ad.prompt * G + g); }
+        if ((rc = begin_records(into, fresh))) return rc;
         dirty = true;   // the upload below also restores the rows the prefill pass used as its own
         admit_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - a0).count();
       }

@@ -1,5 +1,6 @@
 """What the host does when the HIP runtime refuses a call in the middle of a continuous rollout: a refused launch of one of its
-hand-over kernels is an error of the call (it would otherwise return the bytes of an earlier hand-over).  Each case is a process of
+hand-over kernels is an error of the call (it would otherwise return the bytes of an earlier hand-over); where there is no pinned
+memory the call does without.  Each case is a process of
 its own, whose calls of the runtime go through hip_refusals.c; nothing that is refused reaches the GPU."""
 import os
 import subprocess
@@ -63,5 +64,25 @@ for after in (0, 1, n - 1):
         raise SystemExit(f"succeeded with launch {{after}} of {{n}} refused")
     again = run(ctx)    # and the context is as good as before
     assert all(np.array_equal(again[k], ref[k]) for k in ("tokens", "logprobs", "lens", "versions"))
+print("as expected")
+""")
+
+
+def test_without_pinned_memory(child):
+    """The same records, with forced tokens and free running; a later call finds pinned memory again and keeps it."""
+    child("""
+ctx = make_ctx(shape, 4, 9 + new, blob)
+for k in range(2):
+    shim.hip_refuse(b"hipHostMalloc", 0)
+    got = run(ctx)
+    assert shim.hip_refused()
+    assert all(np.array_equal(got[k], ref[k]) for k in ("tokens", "logprobs", "lens", "versions"))
+got = run(ctx)
+assert all(np.array_equal(got[k], ref[k]) for k in ("tokens", "logprobs", "lens", "versions"))
+shim.hip_refuse(b"hipHostMalloc", 0)
+free = ctx.rollout(prompts, lens, G, new, 1.0, 4, eos_id=int(ref["tokens"][0, 0]), continuous=True)
+assert not shim.hip_refused()      # (it has its memory by now)
+want = ref_ctx.rollout(prompts, lens, G, new, 1.0, 4, eos_id=int(ref["tokens"][0, 0]), continuous=True)
+assert all(np.array_equal(free[k], want[k]) for k in ("tokens", "logprobs", "lens", "versions"))
 print("as expected")
 """)
