@@ -1001,7 +1001,8 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
     SampleAcc b = sample_acc_init();
     b.zmax = part[o]; b.zsum = part[plane + o];
     if (!sums_only) { b.best = part[2 * plane + o]; b.zbest = part[3 * plane + o]; b.idx = __float_as_int(part[4 * plane + o]); }
-    sample_acc_merge(a, b);
+    if (g == (int)threadIdx.x) a = b;   // (as it is: a row of NaN has no maximum, and a merge would drop its sum)
+    else sample_acc_merge(a, b);
   }
   for (int o = 32; o > 0; o >>= 1) { SampleAcc b = sample_acc_shfl_xor(a, o); sample_acc_merge(a, b); }
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;

@@ -116,3 +116,18 @@ def test_nucleus_of_rows_of_any_shape(orc, kind, vocab):
                 if got["tokens"][n, s] == tok:
                     assert abs(got["logprobs"][n, s] - lp) < 2.4e-5 + 2 / (top_p * kept), (top_p, n, s, kept)
     ctx.close()
+
+
+@pytest.mark.parametrize("vocab", [1000, 9002])
+def test_logits_of_nan_give_nan(vocab):
+    """A snapshot with a NaN: the all-fp32 path, whose log-probs say so, whether a row is sampled whole or in slices.  One token, so
+    that none is fed back."""
+    shape = synth.ModelShape(1, 256, 4, 2, 64, 512, vocab, dtype="fp32")
+    blob = synth.make_weights(shape, 5).clone()
+    at, _ = synth.blob_offsets(shape)["final_norm"]
+    blob[at + 3] = float("nan")
+    prompts, lens = synth.make_prompts(vocab, 3, 5, seed=1)
+    ctx = make_ctx(shape, 3, 6, blob)
+    got = ctx.rollout(prompts, lens, 1, 1, 1.0, 9)
+    assert np.isnan(got["logprobs"]).all()
+    ctx.close()
