@@ -45,7 +45,7 @@ __global__ void bookkeeping_kernel(int N, int max_new, int per_row, int32_t *d_s
     out_tok[o] = tok;
     out_lp[o] = samp_lp[n];
     out_ver[o] = version;
-    int fed = forced ? forced[o] : tok;
+    int fed = forced ? forced[o] : tok == 0x7fffffff ? 0 : tok;   // (logits of NaN yield no entry of the vocabulary, and none to read an embedding at)
     int len = s + 1;
     gen_len[n] = len;
     bool done = (len >= limit[n]) || (eos >= 0 && fed == eos);

@@ -120,14 +120,14 @@ def test_nucleus_of_rows_of_any_shape(orc, kind, vocab):
 
 @pytest.mark.parametrize("vocab", [1000, 9002])
 def test_logits_of_nan_give_nan(vocab):
-    """A snapshot with a NaN: the all-fp32 path, whose log-probs say so, whether a row is sampled whole or in slices.  One token, so
-    that none is fed back."""
+    """A snapshot with a NaN: the all-fp32 path, whose log-probs say so at every step, whether a row is sampled whole or in slices."""
     shape = synth.ModelShape(1, 256, 4, 2, 64, 512, vocab, dtype="fp32")
     blob = synth.make_weights(shape, 5).clone()
     at, _ = synth.blob_offsets(shape)["final_norm"]
     blob[at + 3] = float("nan")
     prompts, lens = synth.make_prompts(vocab, 3, 5, seed=1)
-    ctx = make_ctx(shape, 3, 6, blob)
-    got = ctx.rollout(prompts, lens, 1, 1, 1.0, 9)
-    assert np.isnan(got["logprobs"]).all()
+    ctx = make_ctx(shape, 3, 9, blob)
+    for continuous in (False, True):
+        got = ctx.rollout(prompts, lens, 1, 4, 1.0, 9, continuous=continuous)
+        assert np.isnan(got["logprobs"]).all() and (got["lens"] == 4).all()
     ctx.close()
