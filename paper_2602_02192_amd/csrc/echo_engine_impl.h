@@ -427,7 +427,7 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
   if (unfused) {
     {
       TimerScope t(c, &c->ev_gemm);
-      fast_lmhead_logits(logits, p.Np_v, at<void>(c, p.o_xa), S.lm_head, Mp, p.Np_v, p.Kp_d, d.vocab, st);
+      fast_lmhead_logits(logits, at<void>(c, p.o_xa), S.lm_head, Mp, p.Np_v, p.Kp_d, d.vocab, st);
     }
     if (target) dbg_target_logprob(c->d_target_lp, logits, p.Np_v, M, d.vocab, temperature, target, st);
     else if (top_p < 1.0f) nucleus(c, logits, p.Np_v, M, temperature, top_p, seed);

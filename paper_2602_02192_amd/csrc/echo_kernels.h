@@ -124,7 +124,7 @@ void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, con
 enum GemmEpilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1 };
 // out = Xp[Mp x Kp] * Wp[Np x Kp]^T.  EPI_PARTIAL: fp32 partials [nsplit][Mp][Np];
 // EPI_SWIGLU (rows alternate gate_f, up_f): silu(gate)*up -> half K8 [Mp][Np/2]; nsplit must be 1.
-struct GemmShape { int nsplit, waves_n, form, stages; };   // launch shape, see fast_gemm_pick
+struct GemmShape { int nsplit, waves_n /* weight blocks of a workgroup, GEMM_STREAM only */, form; };   // launch shape, see fast_gemm_pick
 // GemmShape.form: weights streamed into registers with the activations staged through LDS, or the LDS ring by its tile (rows x columns)
 enum { GEMM_STREAM = 1, GEMM_RING_256X256 = 2, GEMM_RING_256X128 = 3 };
 constexpr int REDUCE_MAX_SPLIT = 12;   // most grid splits over K whose partials the reducing kernels sum
@@ -177,7 +177,7 @@ constexpr int ATT_PREFILL_WAVES = 8;    // wavefronts of a workgroup, which shar
 void fast_attention_prefill(void *Xp_out, const void *q_h16, const PrefillBlock *blocks, int nblocks, KvGeom kv, int layer,
                             int Mp, int Hq, int Hkv, hipStream_t st);
 // lm_head with the sampler fused into the epilogue (partials per workgroup) + the combine kernel.  With `target` set
-// (scoring) only target_lp is meaningful: no noise is drawn, tok and lp are left alone or describe the plain argmax.
+// (scoring) only target_lp is written: no noise is drawn, tok and lp are left alone.
 void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *Xp, const void *Wp, int Mp, int M,
                         int V, int Np, int Kp, float temperature, uint64_t seed, DrawIds ids,
                         const int32_t *row_active, const int32_t *target, float *partials, hipStream_t st);
@@ -190,8 +190,7 @@ size_t fast_topp_scratch_floats(int Mp);
 void fast_topp_cut_and_draw(float *scratch, const float *logits, int64_t ld, int M, int Mp, int V, float temperature, float top_p,
                             uint64_t seed, DrawIds ids, const int32_t *row_active, hipStream_t st);
 void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st);
-// lm_head writing fp32 logits [Mp][ld] row-major (debug / unfused sampler).
-void fast_lmhead_logits(float *logits, int64_t ld, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V,
-                        hipStream_t st);
+// lm_head writing fp32 logits [Mp][Np] row-major (debug / unfused sampler, nucleus).
+void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st);
 
 }  // namespace echo

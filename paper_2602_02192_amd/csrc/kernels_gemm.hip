@@ -14,7 +14,7 @@ namespace echo {
 
 // Packed weight addressing, in units of 16 bytes (8 halves): one 32-row block is contiguous over K, a k-step of it is 64 units.
 __host__ __device__ __forceinline__ int64_t w_block_base(int nb, int Kp) { return (int64_t)nb * (Kp >> 3) * 32; }
-__host__ __device__ __forceinline__ int64_t w_kstep_stride(int) { return 64; }
+constexpr int64_t W_KSTEP = 64;
 
 // ---- weight repacking --------------------------------------------------------------------------------
 // src: row-major bf16 [n_rows][K]; destination row of source row i is dst_row0 + i*dst_row_stride.
@@ -31,7 +31,7 @@ __global__ void pack_weight_kernel(uint4 *dst, const uint4 *src, int64_t dst_row
   for (int q = 0; q < 4; ++q)   // bf16 pair -> half pair, scaled by W_SCALE (exact)
     o[q] = (uint32_t)f32_to_h16_bits(__uint_as_float(w[q] << 16) * W_SCALE) |
            ((uint32_t)f32_to_h16_bits(__uint_as_float(w[q] & 0xffff0000u) * W_SCALE) << 16);
-  dst[w_block_base((int)(r >> 5), Kp8 * 8) + (k8 >> 1) * w_kstep_stride(Np) + (k8 & 1) * 32 + (r & 31)] = make_uint4(o[0], o[1], o[2], o[3]);
+  dst[w_block_base((int)(r >> 5), Kp8 * 8) + (k8 >> 1) * W_KSTEP + (k8 & 1) * 32 + (r & 31)] = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 void fast_pack_weight(void *dst, const void *src, int64_t dst_row0, int dst_row_stride, int64_t n_rows, int K, int Kp,
@@ -52,7 +52,7 @@ __global__ void pack_span_kernel(uint16_t *dst, const uint16_t *src, int64_t e0,
   const int K8 = K >> 3;
   const int64_t i = u / K8, r = dst_row0 + i * dst_row_stride;
   const int k8 = (int)(u % K8);
-  uint16_t *d = dst + (w_block_base((int)(r >> 5), Kp8 * 8) + (k8 >> 1) * w_kstep_stride(Np) + (k8 & 1) * 32 + (r & 31)) * 8;
+  uint16_t *d = dst + (w_block_base((int)(r >> 5), Kp8 * 8) + (k8 >> 1) * W_KSTEP + (k8 & 1) * 32 + (r & 31)) * 8;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
     const int64_t e = u * 8 + q;
@@ -108,19 +108,19 @@ template <int MB, int WN> struct GemmLds {
 };
 
 // The GEMM kernel's main loop as a function, for the lm_head (the GEMM kernel keeps its own inline copy: hipcc
-// schedules the inlined function measurably worse there): accumulates, for weight block `nb` and the 32*MB batch rows from
-// mrow0, the k-range of `nchunks` chunks starting at chunk c_begin.  Ends with a workgroup barrier, after which the
+// schedules the inlined function measurably worse there): accumulates, for weight block `nb` and the 32*MB batch rows,
+// the k-range of `nchunks` chunks starting at chunk c_begin.  Ends with a workgroup barrier, after which the
 // LDS buffers are free for the epilogue.
 template <int MB, int WN, int NSTAGE>
 __device__ __forceinline__ void gemm_lds_mainloop(f32x16 (&acc)[MB], char *lds_raw, const u32x4v *__restrict__ Xp,
                                                   const h16x8 *__restrict__ Wp, int Mp, int Np, int Kp, int nb, int c_begin,
-                                                  int nchunks, int mrow0) {
+                                                  int nchunks) {
   using L = GemmLds<MB, WN>;
   constexpr int KC = L::KC, T = WN * 64, XU = L::CHUNK_UNITS, XL = (XU + T - 1) / T, ROWS = 32 * MB;
   u32x4v *xs = (u32x4v *)lds_raw;
   const int lane = threadIdx.x & 63, tid = threadIdx.x;
-  const h16x8 *a_ptr = Wp + w_block_base(nb, Kp) + (int64_t)c_begin * KC * w_kstep_stride(Np) + (lane >> 5) * 32 + (lane & 31);
-  const int64_t a_step = w_kstep_stride(Np);
+  const h16x8 *a_ptr = Wp + w_block_base(nb, Kp) + (int64_t)c_begin * KC * W_KSTEP + (lane >> 5) * 32 + (lane & 31);
+  const int64_t a_step = W_KSTEP;
 #pragma unroll
   for (int j = 0; j < MB; ++j)
 #pragma unroll
@@ -136,7 +136,7 @@ __device__ __forceinline__ void gemm_lds_mainloop(f32x16 (&acc)[MB], char *lds_r
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       int idx = min(i * T + tid, XU - 1);   // surplus threads repeat the last unit: no divergent branch around a load
-      xr[st][i] = Xp[(int64_t)((c_begin + c) * KC * 2 + idx / ROWS) * Mp + mrow0 + idx % ROWS];
+      xr[st][i] = Xp[(int64_t)((c_begin + c) * KC * 2 + idx / ROWS) * Mp + idx % ROWS];
     }
   };
   auto store_x = [&](int st, int buf) {
@@ -194,14 +194,12 @@ __device__ __forceinline__ void gemm_lds_mainloop(f32x16 (&acc)[MB], char *lds_r
       }
     }
     // NSTAGE-1 .. 2*NSTAGE-2 chunks are left and c0 is a multiple of NSTAGE, so their register stages are static
-    static_assert(NSTAGE >= 2 && NSTAGE <= 4, "one tail per remaining count");
+    static_assert(NSTAGE == 2 || NSTAGE == 3, "one tail per remaining count");
     switch (nchunks - c0) {
       case 1: if (NSTAGE == 2) tail(std::integral_constant<int, 1>{}); break;
-      case 2: if (NSTAGE <= 3) tail(std::integral_constant<int, 2>{}); break;
-      case 3: if (NSTAGE >= 3) tail(std::integral_constant<int, 3>{}); break;
-      case 4: if (NSTAGE >= 3) tail(std::integral_constant<int, 4>{}); break;
-      case 5: if (NSTAGE == 4) tail(std::integral_constant<int, 5>{}); break;
-      case 6: if (NSTAGE == 4) tail(std::integral_constant<int, 6>{}); break;
+      case 2: tail(std::integral_constant<int, 2>{}); break;
+      case 3: if (NSTAGE == 3) tail(std::integral_constant<int, 3>{}); break;
+      case 4: if (NSTAGE == 3) tail(std::integral_constant<int, 4>{}); break;
       default: break;
     }
   } else if (nchunks > 0) {   // a K range shorter than the pipeline: guarded loads
@@ -242,9 +240,8 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
   const int nblocks = Np >> 5, total_chunks = (Kp >> 4) / KC;
   const int nb_own = blockIdx.x * WN + w, nb = min(nb_own, nblocks - 1);   // wavefronts past the end re-read the last block
   const int c_begin = blockIdx.y * chunks_per_split, nchunks = min(chunks_per_split, total_chunks - c_begin);
-  const int mrow0 = blockIdx.z * ROWS;
-  const h16x8 *a_ptr = Wp + w_block_base(nb, Kp) + (int64_t)c_begin * KC * w_kstep_stride(Np) + (lane >> 5) * 32 + (lane & 31);
-  const int64_t a_step = w_kstep_stride(Np);
+  const h16x8 *a_ptr = Wp + w_block_base(nb, Kp) + (int64_t)c_begin * KC * W_KSTEP + (lane >> 5) * 32 + (lane & 31);
+  const int64_t a_step = W_KSTEP;
   f32x16 acc[MB];
 #pragma unroll
   for (int j = 0; j < MB; ++j)
@@ -261,7 +258,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
 #pragma unroll
     for (int i = 0; i < XL; ++i) {
       int idx = min(i * T + tid, XU - 1);   // surplus threads repeat the last unit: no divergent branch around a load
-      xr[st][i] = Xp[(int64_t)((c_begin + c) * KC * 2 + idx / ROWS) * Mp + mrow0 + idx % ROWS];
+      xr[st][i] = Xp[(int64_t)((c_begin + c) * KC * 2 + idx / ROWS) * Mp + idx % ROWS];
     }
   };
   auto store_x = [&](int st, int buf) {
@@ -319,14 +316,12 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
       }
     }
     // NSTAGE-1 .. 2*NSTAGE-2 chunks are left and c0 is a multiple of NSTAGE, so their register stages are static
-    static_assert(NSTAGE >= 2 && NSTAGE <= 4, "one tail per remaining count");
+    static_assert(NSTAGE == 2 || NSTAGE == 3, "one tail per remaining count");
     switch (nchunks - c0) {
       case 1: if (NSTAGE == 2) tail(std::integral_constant<int, 1>{}); break;
-      case 2: if (NSTAGE <= 3) tail(std::integral_constant<int, 2>{}); break;
-      case 3: if (NSTAGE >= 3) tail(std::integral_constant<int, 3>{}); break;
-      case 4: if (NSTAGE >= 3) tail(std::integral_constant<int, 4>{}); break;
-      case 5: if (NSTAGE == 4) tail(std::integral_constant<int, 5>{}); break;
-      case 6: if (NSTAGE == 4) tail(std::integral_constant<int, 6>{}); break;
+      case 2: tail(std::integral_constant<int, 2>{}); break;
+      case 3: if (NSTAGE == 3) tail(std::integral_constant<int, 3>{}); break;
+      case 4: if (NSTAGE == 3) tail(std::integral_constant<int, 4>{}); break;
       default: break;
     }
   } else if (nchunks > 0) {   // a K range shorter than the pipeline: guarded loads
@@ -353,7 +348,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
     // transpose the wavefront's tile through LDS, 32 batch rows at a time, so that every store is a whole 128-byte
     // row segment (the LDS tile is private to the wavefront: only its own LDS traffic has to be waited for)
     float *tile = (float *)lds_raw + (size_t)w * 32 * L::TILE_STRIDE;
-    float *P = (float *)out + ((int64_t)blockIdx.y * Mp + mrow0) * Np + nb * 32;
+    float *P = (float *)out + (int64_t)blockIdx.y * Mp * Np + nb * 32;
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
 #pragma unroll
@@ -388,7 +383,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
       uint32_t give0 = half ? pk[0] : pk[2], give1 = half ? pk[1] : pk[3];
       uint32_t got0 = __shfl_xor(give0, 32, 64), got1 = __shfl_xor(give1, 32, 64);
       u32x4v o = half ? u32x4v{got0, pk[2], got1, pk[3]} : u32x4v{pk[0], got0, pk[1], got1};
-      int m = mrow0 + j * 32 + col;
+      int m = j * 32 + col;
       *(u32x4v *)(O + (((int64_t)(nb * 2 + half) * Mp + m) * 4)) = o;
     }
   }
@@ -470,7 +465,7 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[L::NBW][L::MB], u32x
 #pragma unroll
     for (int i = 0; i < L::XLW; ++i) load_to_lds(x_src[i] + (int64_t)(c * 2) * Mp, ring + st * SU + AU + (i * WN + w) * 64);
 #pragma unroll
-    for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i] + (int64_t)c * w_kstep_stride(0), ring + st * SU + (i * WN + w) * 64);
+    for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i] + (int64_t)c * W_KSTEP, ring + st * SU + (i * WN + w) * 64);
   };
   // what it reads: its NBW weight blocks, and its rows
   const u32x4v *a_lds = ring + (w % WC) * NBW * 64 + lane;
@@ -592,14 +587,8 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
                      (const h16x8 *)Wp, Mp, Np, Kp, gps, strips);
 }
 
-// Launch shape.  Up to 128 batch rows the LDS-staged kernel runs: three or four weight blocks per workgroup, and a
-// grid split over K that brings the launch to about one workgroup per compute unit (partials cost HBM writes, so
-// no more than that); a GEMM whose epilogue needs the whole K (SwiGLU) is not split and takes the workgroup width
-// (three to eight blocks) that needs the fewest rounds of the chip.  Batches that are a multiple of 256 rows take the
-// LDS-ring kernel (256 x 256 tiles when those fill the chip, 256 x 128 tiles with a split over K otherwise).  K is padded to
-// GEMM_K_PAD and the rows to 32, 64, 128 or a multiple of 256, so there are no other shapes.
-// The largest split count <= nsplit that the 256 x 128-tile kernel realises exactly: it cuts K into runs of
-// ceil(groups / nsplit) groups of eight k-steps, which may come to fewer runs than asked for.
+// The largest split count <= nsplit that a ring kernel realises exactly: it cuts K into runs of ceil(groups / nsplit) groups of
+// eight k-steps, which may come to fewer runs than asked for.
 int fast_gemm_even_split(int Kp, int nsplit) {
   int groups = Kp / 16 / 8;
   for (;;) {
@@ -609,10 +598,16 @@ int fast_gemm_even_split(int Kp, int nsplit) {
   }
 }
 
+// Launch shape.  Up to 128 batch rows the LDS-staged kernel runs: three or four weight blocks per workgroup, and a
+// grid split over K that brings the launch to about one workgroup per compute unit (partials cost HBM writes, so
+// no more than that); a GEMM whose epilogue needs the whole K (SwiGLU) is not split and takes the workgroup width
+// (three to eight blocks) that needs the fewest rounds of the chip.  Batches that are a multiple of 256 rows take the
+// LDS-ring kernel (256 x 256 tiles when those fill the chip, 256 x 128 tiles with a split over K otherwise).  K is padded to
+// GEMM_K_PAD and the rows to 32, 64, 128 or a multiple of 256, so there are no other shapes.
 void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
   const int nblocks = Np / 32, ksteps = Kp / 16;
   if (Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {   // 256 x 256 tiles fill the chip
-    g->form = GEMM_RING_256X256; g->waves_n = 4; g->stages = 8; g->nsplit = 1;
+    g->form = GEMM_RING_256X256; g->waves_n = 0; g->nsplit = 1;
     // One tile per compute unit at a time, so a tile count just above a multiple of 256 leaves most of the chip idle in
     // the last round (320 tiles take two rounds).  Splitting K in two runs makes the units of work half as long and the
     // rounds fill up (320 tiles: 1.5 rounds' worth), at the price of a second plane of fp32 partials written and read
@@ -632,7 +627,7 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     if (ns > groups / 4) ns = groups / 4;
     if (ns > 12) ns = 12;
     if (ns < 1) ns = 1;
-    g->form = GEMM_RING_256X128; g->waves_n = 4; g->stages = 8; g->nsplit = fast_gemm_even_split(Kp, ns);
+    g->form = GEMM_RING_256X128; g->waves_n = 0; g->nsplit = fast_gemm_even_split(Kp, ns);
     return;
   }
   const int total_chunks = ksteps / GEMM_KC;
@@ -649,10 +644,9 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
       int wgs = (nblocks + wn - 1) / wn, cost = (wgs + 255) / 256 * wn;
       if (cost <= best_cost) { best = wn; best_cost = cost; }
     }
-    g->waves_n = best; g->stages = best == 3 && Mp != 64 ? 3 : 2; g->nsplit = 1;   // 64 rows: see gemm_lds_min_wgs
+    g->waves_n = best; g->nsplit = 1;
     return;
   }
-  g->stages = 2;   // deeper register pipelines measured no faster once the wait counts are exact
   // workgroups of a launch with wn weight blocks per workgroup once K is split to about one workgroup per compute unit
   auto split_for = [&](int wn, int *wgs) {
     int strips = (nblocks + wn - 1) / wn, ns = (240 + strips / 2) / strips;
@@ -691,12 +685,16 @@ static void gemm_lds_launch(void *out, const void *Xp, const void *Wp, int Mp, i
                      Np, Kp, cps);
 }
 
-// The instantiated forms: three blocks with the three-chunk weight pipeline (two chunks at 64 rows), four blocks with two
-// chunks, and for the full-K projection at up to 64 rows five to eight blocks with two chunks (see fast_gemm_pick).
+// The instantiated forms: three blocks (the full-K projection at 32 and 128 rows with a three-chunk weight pipeline, all others with
+// two chunks: deeper pipelines measured no faster for the split projections, and for 64 rows see gemm_lds_min_wgs), four blocks with two chunks, and for the full-K projection at up to 64 rows five to eight blocks with two chunks (see
+// fast_gemm_pick).
 template <int MB, int EPI>
 static void gemm_lds_dispatch_rows(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, hipStream_t st) {
-  if (g.waves_n == 3 && g.stages == 2) { gemm_lds_launch<MB, 3, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
-  if (g.waves_n == 3) { gemm_lds_launch<MB, 3, 3, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
+  if constexpr (EPI == EPI_SWIGLU && MB != 2) {
+    if (g.waves_n == 3) { gemm_lds_launch<MB, 3, 3, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
+  } else {
+    if (g.waves_n == 3) { gemm_lds_launch<MB, 3, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
+  }
   if constexpr (EPI == EPI_SWIGLU && MB <= 2) {
     switch (g.waves_n) {
       case 5: gemm_lds_launch<MB, 5, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
@@ -847,7 +845,7 @@ __device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, 
   return sa;
 }
 
-// grid (ceil(Np/32 / 4), 1, Mp/(32*MB)); block 256.  The GEMM main loop over the full K (four weight blocks per
+// grid ceil(Np/32 / 4), block 256; 32*MB batch rows.  The GEMM main loop over the full K (four weight blocks per
 // workgroup), then every lane's logits are folded into a running (max, sum-exp, best perturbed score, its index, its z) per
 // batch row: per wavefront, then over the four wavefronts in wavefront order, one partial per workgroup.
 constexpr int LM_WN = 4;
@@ -869,14 +867,15 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   using L = GemmLds<MB, LM_WN>;
   int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-  const int nblocks = Np >> 5, mrow0 = blockIdx.z * 32 * MB;
+  const int nblocks = Np >> 5;
   const int nb_own = blockIdx.x * LM_WN + w, nb = min(nb_own, nblocks - 1);
   f32x16 acc[MB];
-  gemm_lds_mainloop<MB, LM_WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC, mrow0);
+  gemm_lds_mainloop<MB, LM_WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC);
   auto write_partial = [&](const SampleAcc &sa, int m) {
     int64_t o = (int64_t)blockIdx.x * Mp + m, plane = (int64_t)n_wg * Mp;
     part[o] = sa.zmax;
     part[plane + o] = sa.zsum;
+    if (target) return;
     part[2 * plane + o] = sa.best;
     part[3 * plane + o] = sa.zbest;
     part[4 * plane + o] = __int_as_float(sa.idx);
@@ -885,7 +884,7 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
     if (nb_own < nblocks) {
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
-        int m = mrow0 + j * 32 + col;
+        int m = j * 32 + col;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           int v0 = nb * 32 + 8 * g + 4 * half;
@@ -899,7 +898,7 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
     const int v0 = nb_own * 32 + 4 * half;
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
-      const int m = mrow0 + j * 32 + col;
+      const int m = j * 32 + col;
       f32x16 x[1] = {acc[j]};
       if (target) sa[j] = score_lane<1>(x, v0, V, temperature, target[m], target_z + m);
       else sa[j] = sample_lane<1>(x, (float *)lds_raw + w * LM_DUMP_FLOATS, v0, V, temperature, seed, draw_stream(ids, m), draw_step(ids, m));
@@ -916,7 +915,7 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
         for (int ww = 0; ww < 3; ++ww) sample_acc_merge(sa[j], sh[ww][j][col]);
-        write_partial(sa[j], mrow0 + j * 32 + col);
+        write_partial(sa[j], j * 32 + col);
       }
     }
   }
@@ -987,8 +986,8 @@ static void lmhead_ring_launch(const void *Xp, const void *Wp, int Mp, int Np, i
                      Mp, Np, Kp, V, temperature, seed, ids, target, target_z, part, strips);
 }
 
-// grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: the partials are those of
-// lmhead_ring_kernel<true>, only target_lp is written.
+// grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: a scoring pass, whose partials are
+// the first two planes; only target_lp is written.
 __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp, const float *part, int n_wg, int Mp,
                                       const int32_t *row_active, const int32_t *target, const float *target_z, int sums_only) {
   __shared__ SampleAcc sh[4];
@@ -1031,7 +1030,7 @@ static void lmhead_launch(const void *Xp, const void *Wp, int Mp, int Np, int Kp
     attr_set = true;
   }
   int n_wg = lm_wgs(Np);
-  dim3 grid(n_wg, 1, Mp / (32 * MB)), block(256);
+  dim3 grid(n_wg), block(256);
   hipLaunchKernelGGL((lmhead_kernel<MB, NSTAGE, LOGITS>), grid, block, BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp, Np, Kp, V,
                      temperature, seed, ids, target, target_z, part, n_wg, logits, ld);
 }
@@ -1061,7 +1060,7 @@ void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *X
   else if (ring) lmhead_ring_launch<Ring128x128, false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
   else lmhead_dispatch<false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, nullptr, 0, st);
   hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, target_lp, partials, n_wg, Mp, row_active,
-                     target, target_z, ring && target ? 1 : 0);
+                     target, target_z, target ? 1 : 0);
 }
 
 void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st) {
@@ -1069,12 +1068,11 @@ void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts
                      (const int32_t *)nullptr, (const float *)nullptr, 0);
 }
 
-void fast_lmhead_logits(float *logits, int64_t ld, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V,
-                        hipStream_t st) {
+void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st) {
   // 256 rows, vocabulary 151936, hidden 2560: 236 us on 256 x 256 ring tiles (128 x 128: 278, the LDS-staged kernel: 296); 128 rows are
   // level (186 us either way).
-  if (Mp % 256 == 0 && ld == Np) { gemm_ring_launch<Ring256x256, EPI_PARTIAL>(logits, Xp, Wp, Mp, Np, Kp, 1, st); return; }
-  lmhead_dispatch<true>(Xp, Wp, Mp, Np, Kp, V, 1.0f, 0, DrawIds{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, logits, ld, st);
+  if (Mp % 256 == 0) { gemm_ring_launch<Ring256x256, EPI_PARTIAL>(logits, Xp, Wp, Mp, Np, Kp, 1, st); return; }
+  lmhead_dispatch<true>(Xp, Wp, Mp, Np, Kp, V, 1.0f, 0, DrawIds{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, logits, Np, st);
 }
 
 }  // namespace echo
