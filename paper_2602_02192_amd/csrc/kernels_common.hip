@@ -93,7 +93,7 @@ __global__ void kv_replicate_kernel(KvGeom kv, const int32_t *prompt_len, int G,
 
 void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len, int P, int G, int cut_only, hipStream_t st) {
   if (G <= 1 || P <= 0) return;
-  int regions = kv.n_layers * kv.n_kv_heads * (kv.tiled ? 1 : 2), chunks = cut_only ? kv.head_dim / 32 : 8;   // cut_only: one tile, four units per thread
+  int regions = kv.n_layers * kv.n_kv_heads * (kv.tiled ? 1 : 2), chunks = cut_only ? kv.head_dim / 32 : 8;   // cut_only: one tile, a unit per thread
   hipLaunchKernelGGL(kv_replicate_kernel, dim3(chunks, regions, P * (G - 1)), dim3(256), 0, st, kv, prompt_len, G, cut_only);
 }
 
