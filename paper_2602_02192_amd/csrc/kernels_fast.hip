@@ -277,8 +277,8 @@ void fast_qkv_post(const float *partials, int nsplit, int Np, int Mp, void *q_h1
 //    target is met, so the kernel also returns the last kept index among them.  What bounds it is the vector unit of one
 //    compute unit per row, so it counts what a logit costs: three passes (extremes; histogram; list) with one exponential, one
 //    pass more for rows that are flat but for a few large scores.  128 rows of 151936 logits, against a byte-wise select over the
-//    whole row (five passes, an exponential each): N(0, 1) 99 -> 62 us, the same at T = 1000 98 -> 65 us, one score that weighs
-//    as much as all others, which are equal to 1e-4, 103 -> 105 us, two values 357 -> 221 us, all equal 467 -> 131 us; 8 rows of
+//    whole row (five passes, an exponential each): N(0, 1) 99 -> 61 us, the same at T = 1000 98 -> 59 us, one score that weighs
+//    as much as all others, which are equal to 1e-4, 103 -> 103 us, two values 357 -> 219 us, all equal 467 -> 131 us; 8 rows of
 //    2000 logits, with the draw and the merge, 18.2 -> 17.7 us.  (Bins of a fixed width, 1/128 of z, put a whole flat row in one: 185 us
 //    at T = 1000.  More copies or bins cost more to clear and walk than they save; fewer than four copies queue up at equal
 //    logits: a third of the row equal 113 -> 123 us with the draw.)
