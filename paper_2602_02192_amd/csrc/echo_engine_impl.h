@@ -319,7 +319,7 @@ struct TimerScope {
   ~TimerScope() { if (a && b) { hipEventRecord(b, c->cs); v->push_back({a, b}); } }
 };
 
-void gemm_fast(echo_ctx *c, void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmEpilogue epi, int *nsplit_out) {
+GemmShape gemm_shape(echo_ctx *c, int Mp, int Np, int Kp, GemmEpilogue epi) {
   GemmShape g;
   fast_gemm_pick(Np, Kp, Mp, epi == EPI_SWIGLU, &g);
   if (g.nsplit > MAX_GRID_SPLIT) g.nsplit = MAX_GRID_SPLIT;
@@ -328,6 +328,11 @@ void gemm_fast(echo_ctx *c, void *out, const void *Xp, const void *Wp, int Mp, i
     if (g.nsplit > room) g.nsplit = room;
   }
   if (g.form != GEMM_STREAM) g.nsplit = fast_gemm_even_split(Kp, g.nsplit);
+  return g;
+}
+
+void gemm_fast(echo_ctx *c, void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmEpilogue epi, int *nsplit_out) {
+  const GemmShape g = gemm_shape(c, Mp, Np, Kp, epi);
   {
     TimerScope t(c, &c->ev_gemm);
     fast_gemm(out, Xp, Wp, Mp, Np, Kp, g, epi, c->cs);
@@ -371,10 +376,18 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int
   const int att_rows = n_prefill_blocks == 0 && use_splitk_attn && c->px.n_jobs == 0 ? fast_attention_rows_per_group(M, Hq, Hkv, c->attn_mode) : 1;
   if (n_prefill_blocks == 0 && use_splitk_attn) { c->st.attn_rows_per_workgroup = att_rows; c->st.attn_prefix_jobs = c->px.n_jobs; }
   if (att_rows > 1) fast_attention_rows_plan(at<int32_t>(c, p.o_aplan), c->rows, M, Hq, Hkv, c->attn_mode, st);
+  const GemmShape g_qkv = gemm_shape(c, Mp, p.Np_qkv, p.Kp_d, EPI_PARTIAL);
+  const bool qkv_whole = fast_gemm_qkv_fits(g_qkv);   // (long passes) norm, rotation and KV append in the projection's epilogue
   for (int l = 0; l < d.n_layers; ++l) {
     const LayerW &L = S.layers[l];
-    gemm_fast(c, part, xa, L.wqkv, Mp, p.Np_qkv, p.Kp_d, EPI_PARTIAL, &ns);
-    fast_qkv_post(part, ns, p.Np_qkv, Mp, q16, L.q_norm, L.k_norm, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
+    if (qkv_whole) {
+      TimerScope t(c, &c->ev_gemm);
+      fast_gemm_qkv(q16, xa, L.wqkv, Mp, p.Np_qkv, p.Kp_d, g_qkv, L.q_norm, L.k_norm, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
+      if (c->timing) c->t_gemm_bytes += (double)p.Np_qkv * p.Kp_d * 2;
+    } else {
+      gemm_fast(c, part, xa, L.wqkv, Mp, p.Np_qkv, p.Kp_d, EPI_PARTIAL, &ns);
+      fast_qkv_post(part, ns, p.Np_qkv, Mp, q16, L.q_norm, L.k_norm, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
+    }
     if (n_prefill_blocks == 0 && use_splitk_attn)   // the groups' shared prompt tiles, once per group (outside the timed launch)
       fast_attention_prefix(q16, c->kv, l, Hq, Hkv, at<float>(c, p.o_attn_o), at<float>(c, p.o_attn_ml), c->px, st);
     {

@@ -132,6 +132,11 @@ constexpr int GEMM_K_PAD = 128;   // packed weights and K8 activations pad K to 
 void fast_gemm(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, GemmEpilogue epi,
                hipStream_t st);
 int fast_gemm_even_split(int Kp, int nsplit);
+// The QKV projection with fast_qkv_post's work in its epilogue, for launch shapes that fit (the ring forms without a split over K):
+// q_h16, and keys and values of the rows that are active, are written; there are no partials.
+bool fast_gemm_qkv_fits(GemmShape g);
+void fast_gemm_qkv(void *q_h16, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, const void *q_gain, const void *k_gain, int qk_norm,
+                   float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv, hipStream_t st);
 void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g);
 void fast_qkv_post(const float *partials, int nsplit, int Np, int Mp, void *q_h16 /*[M][Hq][hd]*/,
                    const void *q_gain, const void *k_gain, int qk_norm, float eps, const float *rope_cs,

@@ -102,10 +102,20 @@ template <int MB, int WN> struct GemmLds {
   static constexpr int KC = GEMM_KC;
   static constexpr int CHUNK_UNITS = KC * 2 * 32 * MB;                  // 16-byte units of one activation chunk
   static constexpr int X_BYTES = 2 * CHUNK_UNITS * 16;                   // double buffer
-  static constexpr int TILE_STRIDE = 33;                                 // floats per row of the transposed output tile
+  static constexpr int TILE_STRIDE = 36;                                 // floats per row of the transposed output tile, see transpose_in
   static constexpr int EPI_BYTES = WN * 32 * TILE_STRIDE * 4;            // one 32 x 32 tile per wavefront at a time
   static constexpr int BYTES = X_BYTES > EPI_BYTES ? X_BYTES : EPI_BYTES;
 };
+
+// A 32 x 32 accumulator tile to LDS as [batch row][weight row], scaled back, in 16-byte stores: with 36 floats per row the sixteen-byte
+// slots of eight neighbouring lanes lie on all banks, here and in row-wise 16-byte reads.
+template <int STRIDE> __device__ __forceinline__ void transpose_in(float *tile, const f32x16 &acc, int half, int col) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 v = {acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    *(f32x4 *)(tile + col * STRIDE + 8 * g + 4 * half) = v * W_UNSCALE;
+  }
+}
 
 // The GEMM kernel's main loop as a function, for the lm_head (the GEMM kernel keeps its own inline copy: hipcc
 // schedules the inlined function measurably worse there): accumulates, for weight block `nb` and the 32*MB batch rows,
@@ -351,18 +361,13 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
     float *P = (float *)out + (int64_t)blockIdx.y * Mp * Np + nb * 32;
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tile[col * L::TILE_STRIDE + 8 * g + 4 * half + i] = acc[j][4 * g + i] * W_UNSCALE;
+      transpose_in<L::TILE_STRIDE>(tile, acc[j], half, col);
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if (nb_own < nblocks) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           int r = q * 8 + (lane >> 3), n4 = (lane & 7) * 4;
-          const float *t = tile + r * L::TILE_STRIDE + n4;
-          f32x4 v = {t[0], t[1], t[2], t[3]};
-          *(f32x4 *)(P + (int64_t)(j * 32 + r) * Np + n4) = v;
+          *(f32x4 *)(P + (int64_t)(j * 32 + r) * Np + n4) = *(const f32x4 *)(tile + r * L::TILE_STRIDE + n4);
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the next pass overwrites the tile
@@ -416,7 +421,7 @@ template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
   static constexpr int AU = NB * 64, XU = 2 * ROWS, SU = AU + XU;         // 16-byte units of a stage: A operands, B operands
   static constexpr int ALW = NB / WN, XLW = XU / T, LPS = ALW + XLW;      // weight, activation, all loads per wavefront and k-step
   static constexpr int NS = 8, LA = 6;                                    // stages, k-steps ahead
-  static constexpr int TILE_STRIDE = 33, BYTES = NS * SU * 16;            // 128 / 96 / 64 KB; the epilogue's WN x 32 x 33 floats reuse it
+  static constexpr int TILE_STRIDE = 36, BYTES = NS * SU * 16;            // 128 / 96 / 64 KB; the epilogue's WN x 32 x 36 floats reuse it
   static_assert(NB % WN == 0 && XU % T == 0 && WN * 32 * TILE_STRIDE * 4 <= BYTES, "whole loads per wavefront, room for the epilogue");
 };
 using Ring256x256 = GemmRingT<2, 4, 4, 2>;
@@ -441,8 +446,13 @@ __device__ __forceinline__ void ring_tile(int strips, int nz, int *bx, int *by, 
 }
 
 // Accumulates k-steps c_lo .. c_hi - 1 (a whole number of trips round the ring) of the tile whose first weight block is nbw
-// and whose first row is mrow0.  Ends with a workgroup barrier, after which the ring is free for the epilogue.
-template <class L>
+// and whose first row is mrow0.  Wavefront column wc holds the weight blocks ring_block<L, APART>(wc, 0 .. NBW - 1) of the
+// tile.  Ends with a workgroup barrier, after which the ring is free for the epilogue.
+template <class L, int APART = 1> __device__ __forceinline__ int ring_block(int wc, int n) {
+  return wc / APART * APART * L::NBW + wc % APART + n * APART;
+}
+
+template <class L, int APART = 1>
 __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[L::NBW][L::MB], u32x4v *ring, const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp,
                                               int Mp, int Kp, int nblocks, int nbw, int mrow0, int c_lo, int c_hi) {
   constexpr int MB = L::MB, NBW = L::NBW, ROWS = L::ROWS, NS = L::NS, LA = L::LA, SU = L::SU, AU = L::AU, WN = L::WN, WC = L::WC, LPS = L::LPS;
@@ -468,12 +478,12 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[L::NBW][L::MB], u32x
     for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i] + (int64_t)c * W_KSTEP, ring + st * SU + (i * WN + w) * 64);
   };
   // what it reads: its NBW weight blocks, and its rows
-  const u32x4v *a_lds = ring + (w % WC) * NBW * 64 + lane;
+  const u32x4v *a_lds = ring + ring_block<L, APART>(w % WC, 0) * 64 + lane;
   const u32x4v *b_lds = ring + AU + (lane >> 5) * ROWS + wrow + (lane & 31);
   u32x4v a[2][NBW], b[2][MB];
   auto read = [&](int set, int st) {
 #pragma unroll
-    for (int n = 0; n < NBW; ++n) a[set][n] = a_lds[st * SU + n * 64];
+    for (int n = 0; n < NBW; ++n) a[set][n] = a_lds[st * SU + n * APART * 64];
 #pragma unroll
     for (int j = 0; j < MB; ++j) b[set][j] = b_lds[st * SU + j * 32];
   };
@@ -534,18 +544,13 @@ __global__ __launch_bounds__(L::T) void gemm_ring_kernel(void *out, const u32x4v
       float *P = (float *)out + ((int64_t)by * Mp + mrow0 + wrow) * Np + (nb0 + n) * 32;
 #pragma unroll
       for (int j = 0; j < MB; ++j) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) tile[col * L::TILE_STRIDE + 8 * g + 4 * half + i] = acc[n][j][4 * g + i] * W_UNSCALE;
+        transpose_in<L::TILE_STRIDE>(tile, acc[n][j], half, col);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (nb0 + n < nblocks) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             int r = q * 8 + (lane >> 3), n4 = (lane & 7) * 4;
-            const float *t = tile + r * L::TILE_STRIDE + n4;
-            f32x4 v = {t[0], t[1], t[2], t[3]};
-            *(f32x4 *)(P + (int64_t)(j * 32 + r) * Np + n4) = v;
+            *(f32x4 *)(P + (int64_t)(j * 32 + r) * Np + n4) = *(const f32x4 *)(tile + r * L::TILE_STRIDE + n4);
           }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -585,6 +590,185 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
   int strips = (Np / 32 + L::NB - 1) / L::NB, groups = (Kp / 16) / L::NS, gps = (groups + nsplit - 1) / nsplit, ny = (groups + gps - 1) / gps;
   hipLaunchKernelGGL((gemm_ring_kernel<L, EPI>), dim3(strips * (Mp / L::ROWS) * ny), dim3(L::T), L::BYTES, st, out, (const u32x4v *)Xp,
                      (const h16x8 *)Wp, Mp, Np, Kp, gps, strips);
+}
+
+// ---- QKV projection of long passes: per-head norm, rotary embedding and KV append in the epilogue ---------------------------------
+// The ring tile for a projection that is not split over K (passes of about a thousand rows and more).  A wavefront holds the two
+// weight blocks whose dims are each other's rotation partners -- of a head of 128 blocks 0 and 2 or 1 and 3 (APART = 2), of a head of
+// 64 both.  32 rows at a time it transposes its two 32 x 32 tiles through LDS, rotates four neighbouring dims and their partners per
+// lane and stores q or the key tile; the per-head norm of a head of 128 adds the neighbouring wavefront's squares from its tiles.  A
+// value unit holds eight keys of one dim, so there a lane takes a dim and gathers the eight rows of a unit (rows of a pass are runs of
+// consecutive positions; the ends of a run, and rows in any other order, are stored one by one).
+// What it saves is the fp32 plane of the projection, written and read once: same products, same order, so q and the cache are
+// bit-identical to qkv_post_wide_kernel's.  4096 rows, both kernels before against this one: 4B width 132 + 43 -> 138 us, 8B 208 + 46 ->
+// 215, 32B 383 + 64 -> 404; whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
+struct QkvOut {
+  uint16_t *q;              // half [M][Hq][hd]
+  const float2 *rope;       // [M][hd / 2] (cos, sin)
+  RowState rows;
+  KvGeom kv;
+  int layer, Hq, Hkv, M;
+  const uint16_t *q_gain, *k_gain;   // bf16 [hd], with a per-head norm
+  float eps;
+};
+
+template <class L, int HD, bool NORM>
+__global__ __launch_bounds__(L::T) void gemm_ring_qkv_kernel(QkvOut out, const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np, int Kp,
+                                                             int strips) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  constexpr int MB = L::MB, NBW = L::NBW, APART = HD / 64, HALF = HD / 2, TS = L::TILE_STRIDE;
+  static_assert(NBW == 2 && L::WC % APART == 0 && L::WN * 2 * 32 * TS * 4 <= L::BYTES, "whole heads per tile, room for the transposed tiles");
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31, nblocks = Np >> 5;
+  int bx, by, bz;
+  ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
+  const int nb0 = bx * L::NB + ring_block<L, APART>(w % L::WC, 0), mrow0 = bz * L::ROWS + (w / L::WC) * 32 * MB;
+  int act[MB], pos[MB], slot[MB];   // of batch row mrow0 + 32 j + col
+#pragma unroll
+  for (int j = 0; j < MB; ++j) {
+    const int m = min(mrow0 + j * 32 + col, out.M - 1);
+    act[j] = out.rows.active[m]; pos[j] = out.rows.pos[m]; slot[j] = out.rows.slot[m];
+  }
+  f32x16 acc[NBW][MB];
+  ring_mainloop<L, APART>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, bz * L::ROWS, 0, Kp >> 4);
+  const bool own = nb0 < nblocks;   // (heads are whole: both blocks lie past the end, or neither)
+  if (!NORM && !own) return;
+  const int head = nb0 / (HD / 32), d0 = (nb0 % (HD / 32)) * 32;   // dims d0 .. d0 + 31 and their partners HALF further
+  const bool is_q = head < out.Hq, is_k = !is_q && head < out.Hq + out.Hkv, rotate = own && (is_q || is_k);
+  const int kvh = is_q ? 0 : is_k ? head - out.Hq : head - out.Hq - out.Hkv;
+  float *tile = (float *)lds_raw + (size_t)w * 2 * 32 * TS;   // [block][row][dim]
+  // the rotation of rows 8 s + lane / 8 of 32, dims (lane % 8) * 4 .. + 3; requested 32 rows ahead of its use
+  f32x4 cs[2][4][2];
+  auto load_cs = [&](int j) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const f32x4 *p = (const f32x4 *)(out.rope + (int64_t)min(mrow0 + j * 32 + s * 8 + (lane >> 3), out.M - 1) * HALF + d0 + (lane & 7) * 4);
+      cs[j & 1][s][0] = p[0]; cs[j & 1][s][1] = p[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  float gain[2][4];   // of the lane's dims
+  if (NORM && rotate) {
+    const uint16_t *g = (is_q ? out.q_gain : out.k_gain) + d0 + (lane & 7) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { gain[0][e] = bf16_bits_to_f32(g[e]); gain[1][e] = bf16_bits_to_f32(g[e + HALF]); }
+  }
+  const float *beside = tile + ((w % L::WC) % APART == 0 ? 1 : -1) * (APART - 1) * 2 * 32 * TS;   // the head's other wavefront's tiles, if it has one
+  if (rotate) load_cs(0);
+#pragma unroll
+  for (int j = 0; j < MB; ++j) {
+    const int m0 = mrow0 + j * 32;
+    if (!NORM && m0 >= out.M) break;
+    if (rotate && j + 1 < MB) load_cs(j + 1);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) transpose_in<TS>(tile + n * 32 * TS, acc[n][j], half, col);
+    const int on = m0 + col < out.M && act[j];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (NORM) __syncthreads();
+    if (rotate) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int r = s * 8 + (lane >> 3), i = (lane & 7) * 4, m = m0 + r;
+        const int r_act = __shfl(on, r, 64), r_pos = __shfl(pos[j], r, 64), r_slot = __shfl(slot[j], r, 64);
+        f32x4 a = *(const f32x4 *)(tile + r * TS + i), b = *(const f32x4 *)(tile + (32 + r) * TS + i);
+        if (NORM) {   // summed in the order of qkv_post_wide_kernel: dims 32 apart (a head of 128), then 16, 8, 4, 2 and 1
+          float t[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[e] = fmaf(a[e], a[e], b[e] * b[e]);
+          if (APART == 2) {
+            const f32x4 oa = *(const f32x4 *)(beside + r * TS + i), ob = *(const f32x4 *)(beside + (32 + r) * TS + i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] += fmaf(oa[e], oa[e], ob[e] * ob[e]);
+          }
+#pragma unroll
+          for (int off = 4; off > 0; off >>= 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] += __shfl_xor(t[e], off);
+          const float ss = (t[0] + t[2]) + (t[1] + t[3]), inv = 1.0f / sqrtf(ss / (float)HD + out.eps);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { a[e] = a[e] * inv * gain[0][e]; b[e] = b[e] * inv * gain[1][e]; }
+        }
+        if (m >= out.M) continue;
+        const f32x4 c01 = cs[j & 1][s][0], c23 = cs[j & 1][s][1];
+        const float cx[4] = {c01[0], c01[2], c23[0], c23[2]}, sy[4] = {c01[1], c01[3], c23[1], c23[3]};
+        uint16_t ha[4], hb[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ha[e] = f32_to_h16_bits(fmaf(a[e], cx[e], -(b[e] * sy[e])));
+          hb[e] = f32_to_h16_bits(fmaf(b[e], cx[e], a[e] * sy[e]));
+        }
+        const uint2 pa = {(uint32_t)ha[0] | (uint32_t)ha[1] << 16, (uint32_t)ha[2] | (uint32_t)ha[3] << 16};
+        const uint2 pb = {(uint32_t)hb[0] | (uint32_t)hb[1] << 16, (uint32_t)hb[2] | (uint32_t)hb[3] << 16};
+        if (is_q) {
+          uint16_t *dst = out.q + ((int64_t)m * out.Hq + head) * HD + d0 + i;
+          *(uint2 *)dst = pa;
+          *(uint2 *)(dst + HALF) = pb;
+        } else if (r_act) {
+          uint16_t *dst = (uint16_t *)out.kv.base + out.kv.tiled_head_off(r_slot, out.layer, kvh);
+          *(uint2 *)(dst + out.kv.tiled_k_off(r_pos, d0 + i)) = pa;
+          *(uint2 *)(dst + out.kv.tiled_k_off(r_pos, d0 + HALF + i)) = pb;
+        }
+      }
+    } else if (own) {
+      const int pos0 = __builtin_amdgcn_readfirstlane(pos[j]), slot0 = __builtin_amdgcn_readfirstlane(slot[j]);
+      uint16_t *cache = (uint16_t *)out.kv.base;
+      const int dim = d0 + half * HALF + col;   // the lower half of the wavefront takes the first block's dims, the upper half their partners
+      const float *t = tile + half * 32 * TS + col;
+      if (__all(on && slot[j] == slot0 && pos[j] == pos0 + col)) {   // 32 consecutive keys
+        uint16_t *dst = cache + out.kv.tiled_head_off(slot0, out.layer, kvh);
+        for (int r = -(pos0 & 7); r < 32; r += 8) {
+          uint16_t *unit = dst + out.kv.tiled_v_off(pos0 + r, dim);
+          if (r >= 0 && r + 8 <= 32) {
+            uint32_t p[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = (uint32_t)f32_to_h16_bits(t[(r + 2 * e) * TS]) | (uint32_t)f32_to_h16_bits(t[(r + 2 * e + 1) * TS]) << 16;
+            *(uint4 *)unit = make_uint4(p[0], p[1], p[2], p[3]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (r + e >= 0 && r + e < 32) unit[e] = f32_to_h16_bits(t[(r + e) * TS]);
+          }
+        }
+      } else {
+        const int64_t mine = out.kv.tiled_head_off(slot[j], out.layer, kvh) + out.kv.tiled_v_off(pos[j], 0);   // where the row's dim 0 lies
+        const int lo = (int)mine, hi = (int)(mine >> 32), of_dim = (int)out.kv.tiled_v_off(0, dim) - (int)out.kv.tiled_v_off(0, 0);
+        for (int r = 0; r < 32; ++r) {
+          if (!__builtin_amdgcn_readlane(on, r)) continue;
+          const int64_t at = (int64_t)__builtin_amdgcn_readlane(hi, r) << 32 | (uint32_t)__builtin_amdgcn_readlane(lo, r);
+          cache[at + of_dim] = f32_to_h16_bits(t[r * TS]);
+        }
+      }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the reads are done before the next rows overwrite the tiles
+    if (NORM) __syncthreads();
+  }
+}
+
+template <class L, int HD, bool NORM>
+static void gemm_ring_qkv_launch(const QkvOut &out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, hipStream_t st) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    (void)hipFuncSetAttribute((const void *)gemm_ring_qkv_kernel<L, HD, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, L::BYTES);
+    attr_set = true;
+  }
+  const int strips = (Np / 32 + L::NB - 1) / L::NB;
+  hipLaunchKernelGGL((gemm_ring_qkv_kernel<L, HD, NORM>), dim3(strips * (Mp / L::ROWS)), dim3(L::T), L::BYTES, st, out, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp, Np,
+                     Kp, strips);
+}
+
+bool fast_gemm_qkv_fits(GemmShape g) { return g.form != GEMM_STREAM && g.nsplit == 1; }
+
+void fast_gemm_qkv(void *q_h16, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, const void *q_gain, const void *k_gain, int qk_norm,
+                   float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv, hipStream_t st) {
+  const QkvOut out{(uint16_t *)q_h16, (const float2 *)rope_cs, rows, kv, layer, Hq, Hkv, M, (const uint16_t *)q_gain, (const uint16_t *)k_gain, eps};
+  auto tile = [&](auto l) {
+    using L = decltype(l);
+    if (kv.head_dim == 128) {
+      if (qk_norm) gemm_ring_qkv_launch<L, 128, true>(out, Xp, Wp, Mp, Np, Kp, st); else gemm_ring_qkv_launch<L, 128, false>(out, Xp, Wp, Mp, Np, Kp, st);
+    } else {
+      if (qk_norm) gemm_ring_qkv_launch<L, 64, true>(out, Xp, Wp, Mp, Np, Kp, st); else gemm_ring_qkv_launch<L, 64, false>(out, Xp, Wp, Mp, Np, Kp, st);
+    }
+  };
+  if (g.form == GEMM_RING_256X256) tile(Ring256x256{}); else tile(Ring256x128{});
 }
 
 // The largest split count <= nsplit that a ring kernel realises exactly: it cuts K into runs of ceil(groups / nsplit) groups of
