@@ -108,4 +108,46 @@ __device__ __forceinline__ SampleAcc sample_acc_shfl_xor(const SampleAcc &a, int
   return b;
 }
 
+// Entry idx = m * half + i of the rotary table: cos/sin of pos * base^(-2i/hd), evaluated in double and stored as fp32.
+__device__ __forceinline__ void rope_entry(float2 *cs, const int32_t *pos, int idx, int M, int half, float base) {
+  if (idx >= M * half) return;
+  const int m = idx / half, i = idx % half, p = max(pos[m], 0);
+  const double theta = pow((double)base, -2.0 * (double)i / (double)(2 * half)), ang = (double)p * theta;
+  double s, c;
+  sincos(ang, &s, &c);
+  cs[idx] = make_float2((float)c, (float)s);
+}
+
+// Bookkeeping of a generation step for row n, by one thread of the workgroup that has drawn its token: records the token, chooses
+// the one that is fed back (forced or sampled), applies the stop rules and prepares the row for the next decode pass.  All b.n rows
+// of the batch pass here; the last to arrive closes the step (*d_step, *n_active).  Rows are counted, and the live ones among
+// them, in one atomic, so nothing else has to be visible to that last one; and what a workgroup reads of *d_step has arrived
+// before it counts itself, hence before the last one moves the step on.
+__device__ __forceinline__ void book_row(const StepBook &b, int n, int tok, float lp) {
+  const int s0 = *b.d_step;
+  unsigned long long live = 0;
+  if (b.rows.active[n]) {
+    const int s = b.per_row ? b.gen_len[n] : s0;
+    const int64_t o = (int64_t)b.rows.slot[n] * b.max_new + s;   // records are kept per cache slot (= row unless rows were compacted)
+    b.out_tok[o] = tok;
+    b.out_lp[o] = lp;
+    b.out_ver[o] = b.version;
+    const int fed = b.forced ? b.forced[o] : tok == 0x7fffffff ? 0 : tok;   // (logits of NaN yield no entry of the vocabulary, and none to read an embedding at)
+    const int len = s + 1;
+    b.gen_len[n] = len;
+    const bool done = len >= b.limit[n] || (b.eos >= 0 && fed == b.eos);
+    b.rows.token[n] = fed;
+    b.rows.pos[n] = b.prompt_len[n] + s;
+    b.rows.active[n] = done ? 0 : 1;
+    live = done ? 0 : 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  const unsigned long long before = atomicAdd(b.arrived, live << 32 | 1);
+  if ((int)(uint32_t)before + 1 == b.n) {
+    *b.n_active = (int)(before >> 32) + (int)live;
+    *b.d_step = s0 + 1;
+    atomicExch(b.arrived, 0ull);
+  }
+}
+
 }  // namespace echo

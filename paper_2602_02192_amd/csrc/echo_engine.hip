@@ -56,7 +56,7 @@ int echo_init(const echo_model_desc *desc, int device, void *dev_arena, size_t a
   c->d_samp_tok = sm; c->d_samp_lp = (float *)(sm + M); c->d_target = sm + 2 * M; c->d_target_lp = (float *)(sm + 3 * M);
   int32_t *mp = at<int32_t>(c, p.o_maps);
   c->d_map_a = mp; c->d_map_b = mp + M; c->d_plen_p = mp + 2 * M;
-  c->d_step = at<int32_t>(c, p.o_scal); c->d_n_active = c->d_step + 1;
+  c->d_step = at<int32_t>(c, p.o_scal); c->d_n_active = c->d_step + 1; c->d_arrived = (unsigned long long *)(c->d_step + 2);
   c->ids = DrawIds{c->d_step, nullptr, nullptr};
   // activations, row state and scratch start from zero (padding rows and columns are never written); so does the
   // KV cache: the keys of a sequence's last tile that lie beyond its length get weight zero, which only cancels

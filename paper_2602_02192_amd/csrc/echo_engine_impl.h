@@ -216,6 +216,7 @@ struct echo_ctx {
   KvGeom kv;
   int32_t *d_prompt_len_seq, *d_gen_len, *d_limit, *d_samp_tok, *d_target, *d_step, *d_n_active, *d_map_a, *d_map_b, *d_plen_p;
   float *d_samp_lp, *d_target_lp;
+  unsigned long long *d_arrived;   // StepBook.arrived
   int32_t *d_stream;  // per-row stream ids of a continuous rollout
   DrawIds ids{nullptr, nullptr, nullptr};
   PrefixPlan px{nullptr, 0, 0, 1};       // shared-prompt attention jobs of the running rollout (n_jobs = 0: none)
@@ -347,12 +348,12 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int
   hipStream_t st = c->cs;
   int Hq = d.n_q_heads, Hkv = d.n_kv_heads, hd = d.head_dim, H = d.hidden, F = d.ffn;
   float *h = at<float>(c, p.o_h), *rope = at<float>(c, p.o_rope);
-  launch_rope_table(rope, c->rows.pos, M, hd, d.rope_base, st);
+  const RopeTable table{rope, c->rows.pos, d.rope_base, hd};
   if (!p.fast) {
     int bf = d.dtype == ECHO_BF16;
     float *x = at<float>(c, p.o_x), *qkv = at<float>(c, p.o_qkv), *att = at<float>(c, p.o_att), *gu = at<float>(c, p.o_gu),
           *ff = at<float>(c, p.o_ff);
-    dbg_embed(h, S.embed, bf, c->rows.token, M, H, st);
+    dbg_embed(h, S.embed, bf, c->rows.token, M, H, table, st);
     for (int l = 0; l < d.n_layers; ++l) {
       const LayerW &L = S.layers[l];
       dbg_rmsnorm(x, h, L.attn_norm, bf, M, H, d.rms_eps, st);
@@ -371,11 +372,11 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int
   int Mp = pad_rows(M), ns;
   void *xa = at<void>(c, p.o_xa), *xatt = at<void>(c, p.o_xatt), *xff = at<void>(c, p.o_xff), *q16 = at<void>(c, p.o_q16);
   float *part = at<float>(c, p.o_part);
-  fast_resid_norm(h, S.embed, c->rows.token, nullptr, 0, p.Np_d, xa, S.layers[0].attn_norm, M, Mp, H, d.rms_eps, st);
   // decode attention over several rows per workgroup: the tile lists are the same for every layer
   const int att_rows = n_prefill_blocks == 0 && use_splitk_attn && c->px.n_jobs == 0 ? fast_attention_rows_per_group(M, Hq, Hkv, c->attn_mode) : 1;
   if (n_prefill_blocks == 0 && use_splitk_attn) { c->st.attn_rows_per_workgroup = att_rows; c->st.attn_prefix_jobs = c->px.n_jobs; }
-  if (att_rows > 1) fast_attention_rows_plan(at<int32_t>(c, p.o_aplan), c->rows, M, Hq, Hkv, c->attn_mode, st);
+  const RowsPlan plan = att_rows > 1 ? fast_attention_rows_plan(at<int32_t>(c, p.o_aplan), M, Hq, Hkv, c->attn_mode) : RowsPlan{nullptr, 0, 0};
+  fast_step_begin(h, S.embed, c->rows, xa, S.layers[0].attn_norm, M, Mp, H, d.rms_eps, table, plan, Hq / Hkv, st);
   const GemmShape g_qkv = gemm_shape(c, Mp, p.Np_qkv, p.Kp_d, EPI_PARTIAL);
   const bool qkv_whole = fast_gemm_qkv_fits(g_qkv);   // (long passes) norm, rotation and KV append in the projection's epilogue
   for (int l = 0; l < d.n_layers; ++l) {
@@ -404,25 +405,31 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int
     }
     if (c->timing) c->t_attn_bytes += c->cur_attn_bytes;
     gemm_fast(c, part, xatt, L.wo, Mp, p.Np_d, p.Kp_q, EPI_PARTIAL, &ns);
-    fast_resid_norm(h, nullptr, nullptr, part, ns, p.Np_d, xa, L.ffn_norm, M, Mp, H, d.rms_eps, st);
+    fast_resid_norm(h, part, ns, p.Np_d, xa, L.ffn_norm, M, Mp, H, d.rms_eps, st);
     gemm_fast(c, xff, xa, L.wgu, Mp, p.Np_gu, p.Kp_d, EPI_SWIGLU, nullptr);
     gemm_fast(c, part, xff, L.wdown, Mp, p.Np_d, p.Kp_f, EPI_PARTIAL, &ns);
     const void *next_gain = l + 1 < d.n_layers ? S.layers[l + 1].attn_norm : S.final_norm;
-    fast_resid_norm(h, nullptr, nullptr, part, ns, p.Np_d, xa, next_gain, M, Mp, H, d.rms_eps, st);
+    fast_resid_norm(h, part, ns, p.Np_d, xa, next_gain, M, Mp, H, d.rms_eps, st);
   }
 }
 
-// lm_head + sampler over the normed rows left by forward_layers (or by norm_only).
+// The end of a generation step over n rows: records of max_new tokens, written under the snapshot in S.
+StepBook step_book(echo_ctx *c, const Slot &S, int n, int max_new, int per_row, const int32_t *forced, int eos) {
+  return StepBook{c->d_step, n, max_new, per_row, forced, c->d_limit, eos, S.version, c->d_prompt_len_seq, c->d_gen_len, c->rows,
+                  at<int32_t>(c, c->p.o_out_tok), at<float>(c, c->p.o_out_lp), at<int64_t>(c, c->p.o_out_ver), c->d_n_active, c->d_arrived};
+}
+
+// lm_head + sampler over the normed rows left by forward_layers (or by norm_only), and the step's bookkeeping if `book` has any.
 // top_p < 1: cut, slice partials, combine -> d_samp_tok / d_samp_lp
-void nucleus(echo_ctx *c, const float *logits, int64_t ld, int M, float temperature, float top_p, uint64_t seed) {
+void nucleus(echo_ctx *c, const float *logits, int64_t ld, int M, float temperature, float top_p, uint64_t seed, const StepBook &book) {
   int Mp = pad_rows(M);
   float *scratch = at<float>(c, c->p.o_topp);
-  fast_topp_cut_and_draw(scratch, logits, ld, M, Mp, c->d.vocab, temperature, top_p, seed, c->ids, nullptr, c->cs);
-  fast_sample_combine(c->d_samp_tok, c->d_samp_lp, scratch, TOPP_CHUNKS_PER_ROW, M, Mp, nullptr, c->cs);
+  fast_topp_cut_and_draw(scratch, logits, ld, M, Mp, c->d.vocab, temperature, top_p, seed, c->ids, c->cs);
+  fast_sample_combine(c->d_samp_tok, c->d_samp_lp, scratch, TOPP_CHUNKS_PER_ROW, M, Mp, book, c->cs);
 }
 
 void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t seed, bool unfused, const int32_t *target,
-                 float top_p = 1.0f) {
+                 float top_p = 1.0f, const StepBook &book = StepBook{}) {
   const echo_model_desc &d = c->d;
   const Plan &p = c->p;
   hipStream_t st = c->cs;
@@ -432,8 +439,8 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
     dbg_gemm(logits, at<float>(c, p.o_x), S.lm_head, bf, M, d.vocab, d.hidden, 0, st);
     // (a scoring pass may have more rows than the sampler's scratch holds; it wants no token)
     if (target) dbg_target_logprob(c->d_target_lp, logits, d.vocab, M, d.vocab, temperature, target, st);
-    else if (top_p < 1.0f) nucleus(c, logits, d.vocab, M, temperature, top_p, seed);
-    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), pad_rows(M), logits, d.vocab, M, d.vocab, temperature, seed, c->ids, nullptr, st);
+    else if (top_p < 1.0f) nucleus(c, logits, d.vocab, M, temperature, top_p, seed, book);
+    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), pad_rows(M), logits, d.vocab, M, d.vocab, temperature, seed, c->ids, book, st);
     return;
   }
   int Mp = pad_rows(M);
@@ -443,12 +450,12 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
       fast_lmhead_logits(logits, at<void>(c, p.o_xa), S.lm_head, Mp, p.Np_v, p.Kp_d, d.vocab, st);
     }
     if (target) dbg_target_logprob(c->d_target_lp, logits, p.Np_v, M, d.vocab, temperature, target, st);
-    else if (top_p < 1.0f) nucleus(c, logits, p.Np_v, M, temperature, top_p, seed);
-    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), Mp, logits, p.Np_v, M, d.vocab, temperature, seed, c->ids, nullptr, st);
+    else if (top_p < 1.0f) nucleus(c, logits, p.Np_v, M, temperature, top_p, seed, book);
+    else dbg_sample(c->d_samp_tok, c->d_samp_lp, at<float>(c, p.o_topp), Mp, logits, p.Np_v, M, d.vocab, temperature, seed, c->ids, book, st);
   } else {
     TimerScope t(c, &c->ev_gemm);
     fast_lmhead_sample(c->d_samp_tok, c->d_samp_lp, c->d_target_lp, at<void>(c, p.o_xa), S.lm_head, Mp, M, d.vocab, p.Np_v, p.Kp_d,
-                       temperature, seed, c->ids, nullptr, target, at<float>(c, p.o_lmpart), st);
+                       temperature, seed, c->ids, target, book, at<float>(c, p.o_lmpart), st);
   }
   if (c->timing) c->t_gemm_bytes += (double)p.Np_v * p.Kp_d * 2;
 }
@@ -460,7 +467,7 @@ void norm_only(echo_ctx *c, const Slot &S, int M) {
   const echo_model_desc &d = c->d;
   const Plan &p = c->p;
   if (!p.fast) dbg_rmsnorm(at<float>(c, p.o_x), at<float>(c, p.o_h), S.final_norm, d.dtype == ECHO_BF16, M, d.hidden, d.rms_eps, c->cs);
-  else fast_resid_norm(at<float>(c, p.o_h), nullptr, nullptr, nullptr, 0, p.Np_d, at<void>(c, p.o_xa), S.final_norm, M, pad_rows(M),
+  else fast_resid_norm(at<float>(c, p.o_h), nullptr, 0, p.Np_d, at<void>(c, p.o_xa), S.final_norm, M, pad_rows(M),
                        d.hidden, d.rms_eps, c->cs);
 }
 

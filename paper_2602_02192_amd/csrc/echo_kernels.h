@@ -52,11 +52,26 @@ struct KvGeom {          // KV cache, plain form: [slot][layer][K|V][kv_head][ma
 };
 
 // ---- shared small kernels (both paths) -----------------------------------------------------------
-void launch_rope_table(float *cs /*[M][hd/2][2]*/, const int32_t *pos, int M, int hd, float base, hipStream_t st);
-void launch_bookkeeping(int N, int max_new, int per_row /*1: a row's step is its gen_len*/, int32_t *d_step, const int32_t *samp_tok, const float *samp_lp,
-                        const int32_t *forced, const int32_t *limit, int eos, int64_t version,
-                        const int32_t *prompt_len, int32_t *gen_len, RowState rows, int32_t *out_tok,
-                        float *out_lp, int64_t *out_ver, int32_t *n_active, hipStream_t st);
+// The bookkeeping at the end of a generation step, which the kernel that draws a row's token does (book_row in echo_device.h).
+struct StepBook {
+  int32_t *d_step;              // null: a pass without bookkeeping
+  int32_t n, max_new, per_row;  // rows of the batch; length of a record; 1: a row's generation step is its gen_len (the sequences did not start together)
+  const int32_t *forced, *limit;
+  int32_t eos;
+  int64_t version;
+  const int32_t *prompt_len;
+  int32_t *gen_len;
+  RowState rows;
+  int32_t *out_tok;
+  float *out_lp;
+  int64_t *out_ver;
+  int32_t *n_active;
+  unsigned long long *arrived;  // zero between launches
+};
+// The rotary table of a pass (cs [M][hd/2][2] from pos), written by the kernel that begins it.
+struct RopeTable { float *cs; const int32_t *pos; float base; int32_t hd; };
+// The tile lists of the several-rows decode attention (fast_attention_rows_plan), written by the kernel that begins a decode step; plan null: none.
+struct RowsPlan { int32_t *plan; int32_t sets, rows_per_set; };
 // cut_only (tiled cache): only the tile that a prompt fills in part; for batches whose rows read the whole prompt tiles from slot p*G.
 void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len /*[P]*/, int P, int G, int cut_only, hipStream_t st);
 // Row state and records of a continuous rollout between the device and pinned host memory (host pointers below are pinned and
@@ -90,7 +105,7 @@ void launch_gather_rows_f32(float *dst, const float *src, const int32_t *src_row
                             int n_dst, int width, hipStream_t st);
 
 // ---- debug path: row-major weights (fp32 or bf16), fp32 activations, fp32 KV cache ------------------
-void dbg_embed(float *h, const void *embed, int w_bf16, const int32_t *token, int M, int d, hipStream_t st);
+void dbg_embed(float *h, const void *embed, int w_bf16, const int32_t *token, int M, int d, RopeTable rope, hipStream_t st);
 void dbg_rmsnorm(float *x, const float *h, const void *gain, int w_bf16, int M, int d, float eps, hipStream_t st);
 // Y[m][n] (+)= sum_k X[m][k] * W[n][k]
 void dbg_gemm(float *Y, const float *X, const void *W, int w_bf16, int M, int N, int K, int accumulate, hipStream_t st);
@@ -103,7 +118,7 @@ void dbg_swiglu(float *ff /*[M][F]*/, const float *gu /*[M][2F] = gate | up*/, i
 // Unfused sampler over materialised logits [M][ld]: Gumbel-max token and its log-softmax, in fp32.  scratch: the buffer of
 // fast_topp_cut_and_draw (fast_topp_scratch_floats(Mp) floats).
 void dbg_sample(int32_t *tok, float *lp, float *scratch, int Mp, const float *logits, int64_t ld, int M, int V, float temperature,
-                uint64_t seed, DrawIds ids, const int32_t *row_active, hipStream_t st);
+                uint64_t seed, DrawIds ids, const StepBook &book, hipStream_t st);
 // log softmax(logits/T)[target[m]] per row (teacher-forced scoring).
 void dbg_target_logprob(float *lp, const float *logits, int64_t ld, int M, int V, float temperature,
                         const int32_t *target, hipStream_t st);
@@ -118,9 +133,11 @@ void fast_pack_span(void *dst, const void *src, int64_t e0, int64_t n, int64_t d
                     hipStream_t st);
 // rows x K int8 codes with one fp32 scale per row -> row-major bf16 [rows][K] (any path; out, codes, scales on the device).
 void fast_dequant_q8(void *out_bf16, const void *codes, const void *scales, int64_t rows, int K, hipStream_t st);
-// h = embed[token] (first layer) or h += sum_s P[s] (+0); then x = rmsnorm(h)*gain -> Xp (half K8).
-void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, const float *partials, int nsplit,
-                     int Np, void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, hipStream_t st);
+// Begins a pass: h = embed[token], x = rmsnorm(h)*gain -> Xp (half K8), the rotary table, and a decode step's tile lists.
+void fast_step_begin(float *h, const void *embed_bf16, RowState rows, void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, RopeTable rope,
+                     RowsPlan plan, int grp, hipStream_t st);
+// h += sum_s P[s]; then x = rmsnorm(h)*gain -> Xp (half K8).
+void fast_resid_norm(float *h, const float *partials, int nsplit, int Np, void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, hipStream_t st);
 enum GemmEpilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1 };
 // out = Xp[Mp x Kp] * Wp[Np x Kp]^T.  EPI_PARTIAL: fp32 partials [nsplit][Mp][Np];
 // EPI_SWIGLU (rows alternate gate_f, up_f): silu(gate)*up -> half K8 [Mp][Np/2]; nsplit must be 1.
@@ -163,13 +180,13 @@ int fast_attention_splits(int M, int Hkv, int max_splits);
 // Decode attention with several rows of the batch per workgroup (at most R, R * Hq/Hkv <= 32): the whole prompt tiles
 // that neighbouring rows of one group have in common are loaded and multiplied once per workgroup.  No key splitting and no
 // partial buffers.  fast_attention_rows_per_group gives R (1: use fast_attention) -- mode 0: a workgroup for every compute
-// unit, and at least two rows for each; 1, 2: never; 3: as many rows as the MFMA columns hold.  fast_attention_rows_plan
+// unit, and at least two rows for each; 1, 2: never; 3: as many rows as the MFMA columns hold.  What
 // deals the generating rows to the workgroups and writes every workgroup's tile list (fast_attention_plan_ints(rows of
 // the largest batch) ints) from the row state, once per decode step and before the first fast_attention_rows of that
-// step on the same stream, with the same M and mode.
+// step on the same stream, is fast_step_begin with fast_attention_rows_plan for the same M and mode.
 int fast_attention_rows_per_group(int M, int Hq, int Hkv, int mode);
 size_t fast_attention_plan_ints(int max_rows);
-void fast_attention_rows_plan(int32_t *plan, RowState rows, int M, int Hq, int Hkv, int mode, hipStream_t st);
+RowsPlan fast_attention_rows_plan(int32_t *plan, int M, int Hq, int Hkv, int mode);
 void fast_attention_rows(void *Xp_out, const void *q_h16, const int32_t *plan, RowState rows, KvGeom kv, int layer, int M, int Mp, int Hq,
                          int Hkv, int mode, hipStream_t st);
 // Causal attention for runs of consecutive positions (prefill, teacher-forced scoring).  A block is up to
@@ -185,7 +202,7 @@ void fast_attention_prefill(void *Xp_out, const void *q_h16, const PrefillBlock 
 // (scoring) only target_lp is written: no noise is drawn, tok and lp are left alone.
 void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *Xp, const void *Wp, int Mp, int M,
                         int V, int Np, int Kp, float temperature, uint64_t seed, DrawIds ids,
-                        const int32_t *row_active, const int32_t *target, float *partials, hipStream_t st);
+                        const int32_t *target, const StepBook &book, float *partials, hipStream_t st);
 size_t fast_lmhead_partial_floats(int Np, int Mp);
 // Nucleus sampling over fp32 logits [M][ld] (top_p < 1): finds every row's cut and leaves the sampler's partials of
 // TOPP_CHUNKS vocabulary slices per row in scratch (fast_topp_scratch_floats(Mp) floats), in the layout that
@@ -193,8 +210,8 @@ size_t fast_lmhead_partial_floats(int Np, int Mp);
 constexpr int TOPP_CHUNKS_PER_ROW = 16;
 size_t fast_topp_scratch_floats(int Mp);
 void fast_topp_cut_and_draw(float *scratch, const float *logits, int64_t ld, int M, int Mp, int V, float temperature, float top_p,
-                            uint64_t seed, DrawIds ids, const int32_t *row_active, hipStream_t st);
-void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st);
+                            uint64_t seed, DrawIds ids, hipStream_t st);
+void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const StepBook &book, hipStream_t st);
 // lm_head writing fp32 logits [Mp][Np] row-major (debug / unfused sampler, nucleus).
 void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st);
 

@@ -11,10 +11,7 @@ int capture_step(echo_ctx *c, const Slot &S, int N, int max_new, float temperatu
   hipGraph_t g = nullptr;
   HIPCHK(c, hipStreamBeginCapture(c->cs, hipStreamCaptureModeThreadLocal));
   forward_layers(c, S, N, !c->attn_plain);
-  sample_rows(c, S, N, temperature, seed, unfused, nullptr, top_p);
-  launch_bookkeeping(N, max_new, per_row, c->d_step, c->d_samp_tok, c->d_samp_lp, forced, c->d_limit, eos, S.version, c->d_prompt_len_seq,
-                     c->d_gen_len, c->rows, at<int32_t>(c, c->p.o_out_tok), at<float>(c, c->p.o_out_lp), at<int64_t>(c, c->p.o_out_ver),
-                     c->d_n_active, c->cs);
+  sample_rows(c, S, N, temperature, seed, unfused, nullptr, top_p, step_book(c, S, N, max_new, per_row, forced, eos));
   HIPCHK(c, hipStreamEndCapture(c->cs, &g));
   hipError_t e = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
   hipGraphDestroy(g);
@@ -230,7 +227,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   launch_fill_i32(at<int32_t>(c, p.o_out_lp), 0, outn, st);
   launch_fill_i32(at<int32_t>(c, p.o_out_ver), -1, outn * 2, st);
   launch_fill_i32(c->d_gen_len, 0, N, st);
-  launch_fill_i32(c->d_step, 0, 1, st);
+  launch_fill_i32(c->d_step, 0, 4, st);   // and the counts behind it
   HIPCHK(c, hipStreamSynchronize(st));
 
   int cur = c->active;
@@ -282,7 +279,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   }
   c->ids = DrawIds{c->d_step, nullptr, c->d_stream};   // a row's draws are keyed by its sequence, wherever the row moves
   norm_only(c, c->slots[cur], N);
-  sample_rows(c, c->slots[cur], N, temperature, seed, unfused, nullptr, o.top_p);
+  sample_rows(c, c->slots[cur], N, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], N, max_new, 0, d_forced, o.eos_id));
   auto grab_logits = [&](int s) -> int {
     if (!o.debug_logits) return 0;
     HIPCHK(c, hipMemcpy2DAsync(o.debug_logits + (int64_t)s * c->d.vocab, (size_t)max_new * c->d.vocab * 4, at<float>(c, p.o_logits),
@@ -295,12 +292,6 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   std::vector<int> row_seq(N);
   for (int n = 0; n < N; ++n) row_seq[n] = n;
   std::vector<int32_t> lens_host(N, 0);
-  auto book = [&](int slot) {
-    launch_bookkeeping(Rc, max_new, 0, c->d_step, c->d_samp_tok, c->d_samp_lp, d_forced, c->d_limit, o.eos_id, c->slots[slot].version,
-                       c->d_prompt_len_seq, c->d_gen_len, c->rows, at<int32_t>(c, p.o_out_tok), at<float>(c, p.o_out_lp),
-                       at<int64_t>(c, p.o_out_ver), c->d_n_active, st);
-  };
-  book(cur);
   // Siblings need the prompt's last, partly filled tile only when its whole tiles are read from the group's first slot (all 512
   // tokens of 8 x 8 sequences of the 4B model were 4.2 GB of copies, 1.2 ms).
   bool cut = !share_prefix;
@@ -410,9 +401,8 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
       HIPCHK(c, hipGraphLaunch(c->graph, st));
     } else {
       forward_layers(c, c->slots[cur], Rc, splitk);
-      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p);
+      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 0, d_forced, o.eos_id));
       if ((rc = grab_logits(s))) return rc;
-      book(cur);
     }
     c->timing = time_this;
     ++decode_steps;
@@ -587,7 +577,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
     return 0;
   };
   auto limit_of = [&](int n) { return o.stop_lens ? std::max(1, std::min(max_new, o.stop_lens[n])) : max_new; };
-  launch_fill_i32(c->d_step, 0, 1, st);
+  launch_fill_i32(c->d_step, 0, 4, st);   // and the counts behind it
   c->ids = DrawIds{c->d_step, c->d_gen_len, c->d_stream};
 
   int cur = c->active, next_prompt = 0, done_seqs = 0, decode_steps = 0, until_check = 0;
@@ -737,9 +727,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
       HIPCHK(c, hipGraphLaunch(c->graph, st));
     } else {
       forward_layers(c, c->slots[cur], Rc, splitk);
-      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p);
-      launch_bookkeeping(Rc, max_new, 1, c->d_step, c->d_samp_tok, c->d_samp_lp, d_forced, c->d_limit, o.eos_id, c->slots[cur].version,
-                         c->d_prompt_len_seq, c->d_gen_len, c->rows, d_out_tok, d_out_lp, d_out_ver, c->d_n_active, st);
+      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 1, d_forced, o.eos_id));
     }
     ++decode_steps;
     --until_check;

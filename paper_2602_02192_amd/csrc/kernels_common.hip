@@ -1,71 +1,10 @@
-// Small kernels used by both the debug (fp32) and the MFMA (bf16) path: rotary table, per-step
-// bookkeeping, KV replication across a group, generator read-out, fills and row gathers.
+// Small kernels used by both the debug (fp32) and the MFMA (bf16) path: KV replication across a group, generator read-out, fills and row gathers.
 #include <algorithm>
 
 #include "echo_device.h"
 #include "echo_kernels.h"
 
 namespace echo {
-
-// cos/sin of pos * base^(-2i/hd), evaluated in double and stored as fp32: cs[m][i] = (cos, sin).
-__global__ void rope_table_kernel(float2 *cs, const int32_t *pos, int M, int half, int hd, float base) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= M * half) return;
-  int m = idx / half, i = idx % half;
-  int p = pos[m];
-  if (p < 0) p = 0;
-  double theta = pow((double)base, -2.0 * (double)i / (double)hd);
-  double ang = (double)p * theta, s, c;
-  sincos(ang, &s, &c);
-  cs[idx] = make_float2((float)c, (float)s);
-}
-
-void launch_rope_table(float *cs, const int32_t *pos, int M, int hd, float base, hipStream_t st) {
-  int half = hd / 2, n = M * half;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (float2 *)cs, pos, M, half, hd, base);
-}
-
-// One block.  Records the token sampled at generation step *d_step for every active sequence, chooses the
-// token fed back (forced or sampled), applies the stop rules and prepares the rows of the next decode pass.
-// per_row: the sequences of the batch did not start together, a row's generation step is its gen_len.
-__global__ void bookkeeping_kernel(int N, int max_new, int per_row, int32_t *d_step, const int32_t *samp_tok, const float *samp_lp,
-                                   const int32_t *forced, const int32_t *limit, int eos, int64_t version,
-                                   const int32_t *prompt_len, int32_t *gen_len, RowState rows, int32_t *out_tok,
-                                   float *out_lp, int64_t *out_ver, int32_t *n_active) {
-  __shared__ int cnt;
-  if (threadIdx.x == 0) cnt = 0;
-  __syncthreads();
-  const int s0 = *d_step;
-  int mine = 0;
-  for (int n = threadIdx.x; n < N; n += blockDim.x) {
-    if (!rows.active[n]) continue;
-    const int s = per_row ? gen_len[n] : s0;
-    int tok = samp_tok[n];
-    int64_t o = (int64_t)rows.slot[n] * max_new + s;   // records are kept per cache slot (= row unless rows were compacted)
-    out_tok[o] = tok;
-    out_lp[o] = samp_lp[n];
-    out_ver[o] = version;
-    int fed = forced ? forced[o] : tok == 0x7fffffff ? 0 : tok;   // (logits of NaN yield no entry of the vocabulary, and none to read an embedding at)
-    int len = s + 1;
-    gen_len[n] = len;
-    bool done = (len >= limit[n]) || (eos >= 0 && fed == eos);
-    rows.token[n] = fed;
-    rows.pos[n] = prompt_len[n] + s;
-    rows.active[n] = done ? 0 : 1;
-    mine += done ? 0 : 1;
-  }
-  if (mine) atomicAdd(&cnt, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) { *d_step = s0 + 1; *n_active = cnt; }
-}
-
-void launch_bookkeeping(int N, int max_new, int per_row, int32_t *d_step, const int32_t *samp_tok, const float *samp_lp,
-                        const int32_t *forced, const int32_t *limit, int eos, int64_t version,
-                        const int32_t *prompt_len, int32_t *gen_len, RowState rows, int32_t *out_tok, float *out_lp,
-                        int64_t *out_ver, int32_t *n_active, hipStream_t st) {
-  hipLaunchKernelGGL(bookkeeping_kernel, dim3(1), dim3(256), 0, st, N, max_new, per_row, d_step, samp_tok, samp_lp, forced,
-                     limit, eos, version, prompt_len, gen_len, rows, out_tok, out_lp, out_ver, n_active);
-}
 
 // One key's row of a head is a whole number of 16-byte units, and every region starts on one, unless the all-fp32 path has a
 // head_dim that is no multiple of 4.

@@ -6,15 +6,21 @@
 
 namespace echo {
 
+// Workgroups 0 .. M - 1: a row's embedding; the rest: the rotary table.
 template <bool BF>
-__global__ void dbg_embed_kernel(float *h, const void *embed, const int32_t *token, int d) {
+__global__ void dbg_embed_kernel(float *h, const void *embed, const int32_t *token, int M, int d, RopeTable rope) {
+  if ((int)blockIdx.x >= M) {
+    rope_entry((float2 *)rope.cs, rope.pos, (blockIdx.x - M) * blockDim.x + threadIdx.x, M, rope.hd / 2, rope.base);
+    return;
+  }
   int m = blockIdx.x, t = token[m];
   for (int i = threadIdx.x; i < d; i += blockDim.x) h[(int64_t)m * d + i] = t >= 0 ? load_w<BF>(embed, (int64_t)t * d + i) : 0.f;
 }
 
-void dbg_embed(float *h, const void *embed, int w_bf16, const int32_t *token, int M, int d, hipStream_t st) {
-  if (w_bf16) hipLaunchKernelGGL(dbg_embed_kernel<true>, dim3(M), dim3(256), 0, st, h, embed, token, d);
-  else hipLaunchKernelGGL(dbg_embed_kernel<false>, dim3(M), dim3(256), 0, st, h, embed, token, d);
+void dbg_embed(float *h, const void *embed, int w_bf16, const int32_t *token, int M, int d, RopeTable rope, hipStream_t st) {
+  const dim3 grid(M + (M * (rope.hd / 2) + 255) / 256);
+  if (w_bf16) hipLaunchKernelGGL(dbg_embed_kernel<true>, grid, dim3(256), 0, st, h, embed, token, M, d, rope);
+  else hipLaunchKernelGGL(dbg_embed_kernel<false>, grid, dim3(256), 0, st, h, embed, token, M, d, rope);
 }
 
 __device__ float block_sum_256(float v, float *sh) {
@@ -198,10 +204,9 @@ void dbg_swiglu(float *ff, const float *gu, int M, int F, hipStream_t st) {
 // sampler.  The serial chain of a thread (two logf, an expf and a division per entry) bounds it, so a large vocabulary is cut into
 // slices: 151936 entries, 6 rows: 245 -> 21 us, and 4 us for the merge.
 __global__ void dbg_sample_kernel(int32_t *tok, float *lp, float *part, int Mp, const float *logits, int64_t ld, int V, float temperature,
-                                  uint64_t seed, DrawIds ids, const int32_t *row_active) {
+                                  uint64_t seed, DrawIds ids, StepBook book) {
   __shared__ SampleAcc sh[4];
   const int c = blockIdx.x, slices = gridDim.x, m = blockIdx.y;
-  if (row_active && !row_active[m]) return;
   const uint32_t s = draw_step(ids, m), stream = draw_stream(ids, m);
   const int v4 = (V + 3) / 4, per = (v4 + slices - 1) / slices, e4 = min(v4, (c + 1) * per);
   SampleAcc a = sample_acc_init();
@@ -224,6 +229,7 @@ __global__ void dbg_sample_kernel(int32_t *tok, float *lp, float *part, int Mp, 
     if (slices == 1) {
       tok[m] = a.idx;
       lp[m] = a.zbest - (a.zmax + logf(a.zsum));
+      if (book.d_step) book_row(book, m, a.idx, lp[m]);
     } else {
       const int64_t o = (int64_t)c * Mp + m, plane = (int64_t)slices * Mp;
       part[o] = a.zmax;
@@ -236,11 +242,11 @@ __global__ void dbg_sample_kernel(int32_t *tok, float *lp, float *part, int Mp, 
 }
 
 void dbg_sample(int32_t *tok, float *lp, float *scratch, int Mp, const float *logits, int64_t ld, int M, int V, float temperature, uint64_t seed,
-                DrawIds ids, const int32_t *row_active, hipStream_t st) {
+                DrawIds ids, const StepBook &book, hipStream_t st) {
   // a second launch (about 5 us) pays once a thread has more than a few entries (of 4) to itself
   const int slices = V > 8192 ? TOPP_CHUNKS_PER_ROW : 1;
-  hipLaunchKernelGGL(dbg_sample_kernel, dim3(slices, M), dim3(256), 0, st, tok, lp, scratch, Mp, logits, ld, V, temperature, seed, ids, row_active);
-  if (slices > 1) fast_sample_combine(tok, lp, scratch, slices, M, Mp, row_active, st);
+  hipLaunchKernelGGL(dbg_sample_kernel, dim3(slices, M), dim3(256), 0, st, tok, lp, scratch, Mp, logits, ld, V, temperature, seed, ids, book);
+  if (slices > 1) fast_sample_combine(tok, lp, scratch, slices, M, Mp, book, st);
 }
 
 __global__ void dbg_target_logprob_kernel(float *lp, const float *logits, int64_t ld, int V, float temperature,

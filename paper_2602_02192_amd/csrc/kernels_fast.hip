@@ -2,6 +2,7 @@
 // reduction folded in), QKV post-processing (reduction, per-head norm, rotary embedding, KV append).
 #include <type_traits>
 
+#include "attn_plan.h"
 #include "echo_device.h"
 #include "echo_kernels.h"
 
@@ -22,7 +23,7 @@ static void with_split_count(int n, F f) {
 // eighths, because a 128-byte line of the K8 activation layout, or of a key or value tile, holds 16 bytes or less of each of
 // several neighbouring rows: written from one XCD its pieces meet in that XCD's L2, written from eight they reach memory one by
 // one (4096 rows: residual + norm 35.7 -> 29.4 us, qkv_post_wide_kernel 47.6 -> 44.4 at the 4B width).
-__device__ __forceinline__ int xcd_row(int n) {
+__device__ __forceinline__ int xcd_row(int n) {   // (of workgroups 0 .. n - 1)
   const int id = blockIdx.x, x = id & 7;
   return x * (n >> 3) + min(x, n & 7) + (id >> 3);
 }
@@ -36,17 +37,17 @@ __device__ __forceinline__ int xcd_row(int n) {
 // of 2560 37.8 -> 29.4 us (14 bytes per element, 5.0 TB/s), of 5120 with two planes 86 -> 77.5 (4.9), for most part by xcd_row.
 constexpr int RN_THREADS = 1024;
 template <int NS, int CH, bool EMBED>
-__global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restrict__ h, const uint16_t *__restrict__ embed, const int32_t *__restrict__ token,
-                                                                const f32x4 *__restrict__ partials, int Np, uint16_t *__restrict__ Xp,
-                                                                const uint16_t *__restrict__ gain, int Mp, int d, float eps) {
+__device__ __forceinline__ void resid_norm_row(int m, int lanes, float *__restrict__ h, const uint16_t *__restrict__ embed, const int32_t *__restrict__ token,
+                                               const f32x4 *__restrict__ partials, int Np, uint16_t *__restrict__ Xp,
+                                               const uint16_t *__restrict__ gain, int Mp, int d, float eps) {
   __shared__ float sh[RN_THREADS / 64];
-  const int m = xcd_row(gridDim.x), d4 = d >> 2;
+  const int d4 = d >> 2;
   f32x4 v[CH], pp[CH][NS > 0 ? NS : 1];
   uint2 gn[CH], em[CH];
   const int tok = EMBED ? token[m] : 0;
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int n4 = min((int)threadIdx.x + c * (int)blockDim.x, d4 - 1);   // lanes past the row repeat its last unit and store nothing
+    const int n4 = min((int)threadIdx.x + c * lanes, d4 - 1);   // lanes past the row repeat its last unit and store nothing
     if (EMBED) em[c] = *(const uint2 *)(embed + (int64_t)max(tok, 0) * d + n4 * 4);
     else v[c] = *(const f32x4 *)(h + (int64_t)m * d + n4 * 4);
 #pragma unroll
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restric
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int n4 = threadIdx.x + c * (int)blockDim.x;
+    const int n4 = (int)threadIdx.x + c * lanes;
     f32x4 a = v[c];
     if (EMBED) {
       const uint2 e = em[c];
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restric
 #pragma unroll
     for (int s = 0; s < NS; ++s) a += pp[c][s];
     v[c] = a;
-    if (n4 < d4) {
+    if (n4 < d4 && (int)threadIdx.x < lanes) {
       if (EMBED || NS > 0) *(f32x4 *)(h + (int64_t)m * d + n4 * 4) = a;
       ss += a[0] * a[0] + a[1] * a[1] + a[2] * a[2] + a[3] * a[3];
     }
@@ -80,30 +81,62 @@ __global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restric
   float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    const int n4 = threadIdx.x + c * (int)blockDim.x, n = n4 * 4;
+    const int n4 = (int)threadIdx.x + c * lanes, n = n4 * 4;
     const uint2 g = gn[c];
     float g0 = __uint_as_float(g.x << 16), g1 = __uint_as_float(g.x & 0xffff0000u);
     float g2 = __uint_as_float(g.y << 16), g3 = __uint_as_float(g.y & 0xffff0000u);
     uint2 o;
     o.x = (uint32_t)f32_to_h16_bits(v[c][0] * inv * g0) | ((uint32_t)f32_to_h16_bits(v[c][1] * inv * g1) << 16);
     o.y = (uint32_t)f32_to_h16_bits(v[c][2] * inv * g2) | ((uint32_t)f32_to_h16_bits(v[c][3] * inv * g3) << 16);
-    if (n4 < d4) *(uint2 *)(Xp + ((int64_t)(n >> 3) * Mp + m) * 8 + (n & 7)) = o;
+    if (n4 < d4 && (int)threadIdx.x < lanes) *(uint2 *)(Xp + ((int64_t)(n >> 3) * Mp + m) * 8 + (n & 7)) = o;
   }
 }
 
-void fast_resid_norm(float *h, const void *embed_bf16, const int32_t *token, const float *partials, int nsplit, int Np,
-                     void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, hipStream_t st) {
+template <int NS, int CH>
+__global__ __launch_bounds__(RN_THREADS) void resid_norm_kernel(float *__restrict__ h, const f32x4 *__restrict__ partials, int Np, uint16_t *__restrict__ Xp,
+                                                                const uint16_t *__restrict__ gain, int Mp, int d, float eps) {
+  resid_norm_row<NS, CH, false>(xcd_row(gridDim.x), blockDim.x, h, nullptr, nullptr, partials, Np, Xp, gain, Mp, d, eps);
+}
+
+// Begins a pass in one launch: workgroups 0 .. M - 1 embed and norm a row each, the next one (with a plan; blocks are of
+// ATT_ROWS_BATCH_MAX threads then) writes the tile lists of the decode attention, the rest the rotary table.  None needs another's
+// result, and each is a dependent launch saved per step: 64 rows of the 4B shape 4.7 + 5.4 + 4.9 us apart, 6.6 us together; one
+// row (no plan) 4.5 + 4.4 us, 4.7 us.  `lanes` threads share a row whatever the block, so that its sum keeps its order.
+template <int CH>
+__global__ __launch_bounds__(RN_THREADS) void step_begin_kernel(float *__restrict__ h, const uint16_t *__restrict__ embed, RowState rows, uint16_t *__restrict__ Xp,
+                                                                const uint16_t *__restrict__ gain, int M, int Mp, int d, int lanes, float eps, RopeTable rope,
+                                                                RowsPlan plan, int grp) {
+  const int extra = (int)blockIdx.x - M, planners = plan.plan ? 1 : 0;
+  if (extra < 0) resid_norm_row<0, CH, true>(xcd_row(M), lanes, h, embed, rows.token, nullptr, 0, Xp, gain, Mp, d, eps);
+  else if (extra < planners) attn_rows_plan(plan.plan, rows, M, grp, plan.sets, plan.rows_per_set);
+  else rope_entry((float2 *)rope.cs, rope.pos, (extra - planners) * blockDim.x + threadIdx.x, M, rope.hd / 2, rope.base);
+}
+
+static_assert(RN_THREADS == ATT_ROWS_BATCH_MAX, "a workgroup of the largest size can write the plan");
+// One float4 per thread when a row of d fits a workgroup so, else two.
+static int row_loads(int d) { return ((d >> 2) + 63) / 64 * 64 <= RN_THREADS ? 1 : 2; }
+static int row_threads(int d) { return ((d >> (row_loads(d) + 1)) + 63) / 64 * 64; }
+
+void fast_step_begin(float *h, const void *embed_bf16, RowState rows, void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps, RopeTable rope,
+                     RowsPlan plan, int grp, hipStream_t st) {
   if (M <= 0) return;
-  const int wide = ((d >> 2) + 63) / 64 * 64 <= RN_THREADS ? 1 : 2;   // one float4 per thread when the row fits, else two
-  const int threads = ((d >> (wide + 1)) + 63) / 64 * 64;
+  const int threads = plan.plan ? RN_THREADS : row_threads(d), grid = M + (plan.plan ? 1 : 0) + (M * (rope.hd / 2) + threads - 1) / threads;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(M), dim3(threads), 0, st, h, (const uint16_t *)embed_bf16, token, (const f32x4 *)partials, Np, (uint16_t *)Xp,
-                       (const uint16_t *)gain_bf16, Mp, d, eps);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, h, (const uint16_t *)embed_bf16, rows, (uint16_t *)Xp, (const uint16_t *)gain_bf16, M, Mp, d,
+                       row_threads(d), eps, rope, plan, grp);
   };
-  if (embed_bf16) { if (wide == 1) launch(resid_norm_kernel<0, 1, true>); else launch(resid_norm_kernel<0, 2, true>); return; }
+  if (row_loads(d) == 1) launch(step_begin_kernel<1>); else launch(step_begin_kernel<2>);
+}
+
+void fast_resid_norm(float *h, const float *partials, int nsplit, int Np, void *Xp, const void *gain_bf16, int M, int Mp, int d, float eps,
+                     hipStream_t st) {
+  if (M <= 0) return;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(M), dim3(row_threads(d)), 0, st, h, (const f32x4 *)partials, Np, (uint16_t *)Xp, (const uint16_t *)gain_bf16, Mp, d, eps);
+  };
   with_split_count(nsplit, [&](auto n) {
-    if (wide == 1) launch(resid_norm_kernel<decltype(n)::value, 1, false>);
-    else launch(resid_norm_kernel<decltype(n)::value, 2, false>);
+    if (row_loads(d) == 1) launch(resid_norm_kernel<decltype(n)::value, 1>);
+    else launch(resid_norm_kernel<decltype(n)::value, 2>);
   });
 }
 
@@ -302,7 +335,7 @@ constexpr int TOPP_FEW = 32;
 constexpr float TOPP_SPAN = 32.0f;   // units of z below the maximum that matter: beyond 27.8 the mass is zero
 static_assert(TOPP_RADIX_COPIES * 256 <= TOPP_BINS * TOPP_COPIES && TOPP_BINS % TOPP_THREADS == 0, "the rounds fit; whole bins per thread");
 __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_key, int32_t *cut_last, const float *logits, int64_t ld,
-                                                                 int V, float temperature, float top_p, const int32_t *row_active) {
+                                                                 int V, float temperature, float top_p) {
   extern __shared__ unsigned long long topp_hist[];
   __shared__ unsigned long long sh_u64[TOPP_THREADS / 64];
   __shared__ float sh_f[2][TOPP_THREADS / 64];
@@ -313,7 +346,6 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
   __shared__ uint32_t sel_digit;
   __shared__ int cand_n;
   const int m = blockIdx.x, tid = threadIdx.x, wv = tid >> 6;
-  if (row_active && !row_active[m]) return;
   const float *lg = logits + (int64_t)m * ld;
   // Every pass visits the row, four logits at a time, with a stride of the block, TOPP_LOADS loads in flight per thread (a plain loop
   // waits out one memory latency per element); an index past the end yields `past`.
@@ -607,10 +639,9 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
 // the wavefront evaluates all its kept tokens in full.  Four tokens of which none is kept draw no numbers.  128 rows of 151936
 // logits, three quarters of them kept: 62 -> 52 us, of which the ten rounds of the generator are some 30 by instruction count.
 __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, const int32_t *cut_last, const float *logits, int64_t ld,
-                                 int V, float temperature, uint64_t seed, DrawIds ids, const int32_t *row_active) {
+                                 int V, float temperature, uint64_t seed, DrawIds ids) {
   __shared__ SampleAcc sh[4];
   const int c = blockIdx.x, m = blockIdx.y;
-  if (row_active && !row_active[m]) return;
   const uint32_t step = draw_step(ids, m), stream = draw_stream(ids, m), cut = cut_key[m];
   const int last = cut_last[m];
   const int v4 = (V + 3) / 4, per = (v4 + TOPP_CHUNKS - 1) / TOPP_CHUNKS, b4 = c * per, e4 = min(v4, b4 + per);
@@ -692,7 +723,7 @@ __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, c
 size_t fast_topp_scratch_floats(int Mp) { return (size_t)5 * TOPP_CHUNKS * Mp + 2 * (size_t)Mp; }
 
 void fast_topp_cut_and_draw(float *scratch, const float *logits, int64_t ld, int M, int Mp, int V, float temperature, float top_p,
-                            uint64_t seed, DrawIds ids, const int32_t *row_active, hipStream_t st) {
+                            uint64_t seed, DrawIds ids, hipStream_t st) {
   if (M <= 0) return;
   uint32_t *cut_key = (uint32_t *)(scratch + (size_t)5 * TOPP_CHUNKS * Mp);
   int32_t *cut_last = (int32_t *)cut_key + Mp;
@@ -701,9 +732,9 @@ void fast_topp_cut_and_draw(float *scratch, const float *logits, int64_t ld, int
     (void)hipFuncSetAttribute((const void *)topp_cut_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, TOPP_LDS);
     attr_set = true;
   }
-  hipLaunchKernelGGL(topp_cut_kernel, dim3(M), dim3(TOPP_THREADS), TOPP_LDS, st, cut_key, cut_last, logits, ld, V, temperature, top_p, row_active);
+  hipLaunchKernelGGL(topp_cut_kernel, dim3(M), dim3(TOPP_THREADS), TOPP_LDS, st, cut_key, cut_last, logits, ld, V, temperature, top_p);
   hipLaunchKernelGGL(topp_draw_kernel, dim3(TOPP_CHUNKS, M), dim3(256), 0, st, scratch, Mp, cut_key, cut_last, logits, ld, V, temperature,
-                     seed, ids, row_active);
+                     seed, ids);
 }
 
 }  // namespace echo

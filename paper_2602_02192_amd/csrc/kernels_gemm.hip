@@ -1171,12 +1171,12 @@ static void lmhead_ring_launch(const void *Xp, const void *Wp, int Mp, int Np, i
 }
 
 // grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: a scoring pass, whose partials are
-// the first two planes; only target_lp is written.
+// the first two planes; only target_lp is written.  Otherwise the row's bookkeeping follows, if the pass has
+// any (a launch of its own before: 10.6 + 3.9 us at one row, 10.4 + 4.5 at 64; 12.0 together).
 __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp, const float *part, int n_wg, int Mp,
-                                      const int32_t *row_active, const int32_t *target, const float *target_z, int sums_only) {
+                                      const int32_t *target, const float *target_z, int sums_only, StepBook book) {
   __shared__ SampleAcc sh[4];
   int m = blockIdx.x;
-  if (row_active && !row_active[m]) return;
   int64_t plane = (int64_t)n_wg * Mp;
   SampleAcc a = sample_acc_init();
   for (int g = threadIdx.x; g < n_wg; g += blockDim.x) {
@@ -1193,7 +1193,10 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) sample_acc_merge(a, sh[w]);
     float lse = a.zmax + logf(a.zsum);
-    if (!sums_only) { tok[m] = a.idx; lp[m] = a.zbest - lse; }
+    if (!sums_only) {
+      tok[m] = a.idx; lp[m] = a.zbest - lse;
+      if (book.d_step) book_row(book, m, a.idx, a.zbest - lse);
+    }
     if (target_lp) target_lp[m] = (target && target[m] >= 0) ? target_z[m] - lse : 0.f;
   }
 }
@@ -1234,8 +1237,8 @@ static void lmhead_dispatch(const void *Xp, const void *Wp, int Mp, int Np, int 
 }
 
 void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *Xp, const void *Wp, int Mp, int M, int V,
-                        int Np, int Kp, float temperature, uint64_t seed, DrawIds ids, const int32_t *row_active,
-                        const int32_t *target, float *partials, hipStream_t st) {
+                        int Np, int Kp, float temperature, uint64_t seed, DrawIds ids,
+                        const int32_t *target, const StepBook &book, float *partials, hipStream_t st) {
   const bool ring = Mp % 128 == 0, big = ring && target && Mp % 256 == 0;   // see lmhead_ring_kernel
   int n_wg = big ? (Np / 32 + Ring256x256::NB - 1) / Ring256x256::NB : lm_wgs(Np);
   float *target_z = partials + (size_t)5 * lm_wgs(Np) * Mp;   // behind the partials of either form
@@ -1243,13 +1246,13 @@ void fast_lmhead_sample(int32_t *tok, float *lp, float *target_lp, const void *X
   else if (ring && target) lmhead_ring_launch<Ring128x128, true>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
   else if (ring) lmhead_ring_launch<Ring128x128, false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, n_wg, st);
   else lmhead_dispatch<false>(Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, partials, nullptr, 0, st);
-  hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, target_lp, partials, n_wg, Mp, row_active,
-                     target, target_z, target ? 1 : 0);
+  hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, target_lp, partials, n_wg, Mp, target,
+                     target_z, target ? 1 : 0, book);
 }
 
-void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const int32_t *row_active, hipStream_t st) {
-  hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, (float *)nullptr, part, n_parts, Mp, row_active,
-                     (const int32_t *)nullptr, (const float *)nullptr, 0);
+void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts, int M, int Mp, const StepBook &book, hipStream_t st) {
+  hipLaunchKernelGGL(sample_combine_kernel, dim3(M), dim3(256), 0, st, tok, lp, (float *)nullptr, part, n_parts, Mp, (const int32_t *)nullptr,
+                     (const float *)nullptr, 0, book);
 }
 
 void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st) {
