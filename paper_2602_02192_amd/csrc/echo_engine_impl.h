@@ -342,7 +342,8 @@ void gemm_fast(echo_ctx *c, void *out, const void *Xp, const void *Wp, int Mp, i
   if (nsplit_out) *nsplit_out = g.nsplit;
 }
 
-void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int n_prefill_blocks = 0) {
+// decode: the rows belong to different sequences.  (The fp32 path leaves its last norm to the product behind it where dbg_fuses.)
+void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, bool decode, int n_prefill_blocks = 0) {
   const echo_model_desc &d = c->d;
   const Plan &p = c->p;
   hipStream_t st = c->cs;
@@ -354,19 +355,27 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, int
     float *x = at<float>(c, p.o_x), *qkv = at<float>(c, p.o_qkv), *att = at<float>(c, p.o_att), *gu = at<float>(c, p.o_gu),
           *ff = at<float>(c, p.o_ff);
     dbg_embed(h, S.embed, bf, c->rows.token, M, H, table, st);
+    auto normed_gemm = [&](float *y, const void *gain, const void *w, int N) {
+      if (dbg_fuses(M, N, H)) { dbg_gemm(y, h, w, bf, M, N, H, 0, st, DBG_NORM, gain, d.rms_eps); return; }
+      dbg_rmsnorm(x, h, gain, bf, M, H, d.rms_eps, st);
+      dbg_gemm(y, x, w, bf, M, N, H, 0, st);
+    };
     for (int l = 0; l < d.n_layers; ++l) {
       const LayerW &L = S.layers[l];
-      dbg_rmsnorm(x, h, L.attn_norm, bf, M, H, d.rms_eps, st);
-      dbg_gemm(qkv, x, L.wqkv, bf, M, (Hq + 2 * Hkv) * hd, H, 0, st);
-      dbg_qkv_post(qkv, L.q_norm, L.k_norm, bf, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
-      dbg_attention(att, qkv, c->rows, c->kv, l, M, Hq, Hkv, st);
+      const DbgHeads heads{L.q_norm, L.k_norm, d.qk_norm, d.rms_eps, (const float2 *)rope};
+      normed_gemm(qkv, L.attn_norm, L.wqkv, (Hq + 2 * Hkv) * hd);
+      if (!decode) dbg_qkv_post(qkv, L.q_norm, L.k_norm, bf, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
+      dbg_attention(att, qkv, c->rows, c->kv, l, M, Hq, Hkv, st, decode ? &heads : nullptr, bf);
       dbg_gemm(h, att, L.wo, bf, M, H, Hq * hd, 1, st);
-      dbg_rmsnorm(x, h, L.ffn_norm, bf, M, H, d.rms_eps, st);
-      dbg_gemm(gu, x, L.wgu, bf, M, 2 * F, H, 0, st);
-      dbg_swiglu(ff, gu, M, F, st);
-      dbg_gemm(h, ff, L.wdown, bf, M, H, F, 1, st);
+      normed_gemm(gu, L.ffn_norm, L.wgu, 2 * F);
+      if (dbg_fuses(M, H, F)) {
+        dbg_gemm(h, gu, L.wdown, bf, M, H, F, 1, st, DBG_SWIGLU);
+      } else {
+        dbg_swiglu(ff, gu, M, F, st);
+        dbg_gemm(h, ff, L.wdown, bf, M, H, F, 1, st);
+      }
     }
-    dbg_rmsnorm(x, h, S.final_norm, bf, M, H, d.rms_eps, st);
+    if (!dbg_fuses(M, d.vocab, H)) dbg_rmsnorm(x, h, S.final_norm, bf, M, H, d.rms_eps, st);
     return;
   }
   int Mp = pad_rows(M), ns;
@@ -436,7 +445,8 @@ void sample_rows(echo_ctx *c, const Slot &S, int M, float temperature, uint64_t 
   float *logits = at<float>(c, p.o_logits);
   if (!p.fast) {
     int bf = d.dtype == ECHO_BF16;
-    dbg_gemm(logits, at<float>(c, p.o_x), S.lm_head, bf, M, d.vocab, d.hidden, 0, st);
+    if (dbg_fuses(M, d.vocab, d.hidden)) dbg_gemm(logits, at<float>(c, p.o_h), S.lm_head, bf, M, d.vocab, d.hidden, 0, st, DBG_NORM, S.final_norm, d.rms_eps);
+    else dbg_gemm(logits, at<float>(c, p.o_x), S.lm_head, bf, M, d.vocab, d.hidden, 0, st);
     // (a scoring pass may have more rows than the sampler's scratch holds; it wants no token)
     if (target) dbg_target_logprob(c->d_target_lp, logits, d.vocab, M, d.vocab, temperature, target, st);
     else if (top_p < 1.0f) nucleus(c, logits, d.vocab, M, temperature, top_p, seed, book);
@@ -466,6 +476,7 @@ int64_t logits_ld(echo_ctx *c) { return c->p.fast ? c->p.Np_v : c->d.vocab; }
 void norm_only(echo_ctx *c, const Slot &S, int M) {
   const echo_model_desc &d = c->d;
   const Plan &p = c->p;
+  if (!p.fast && dbg_fuses(M, d.vocab, d.hidden)) return;   // (sample_rows does it)
   if (!p.fast) dbg_rmsnorm(at<float>(c, p.o_x), at<float>(c, p.o_h), S.final_norm, d.dtype == ECHO_BF16, M, d.hidden, d.rms_eps, c->cs);
   else fast_resid_norm(at<float>(c, p.o_h), nullptr, 0, p.Np_d, at<void>(c, p.o_xa), S.final_norm, M, pad_rows(M),
                        d.hidden, d.rms_eps, c->cs);
@@ -506,7 +517,7 @@ int run_chunk_seqs(echo_ctx *c, const Slot &S, const std::vector<ChunkSeq> &seqs
                                hipMemcpyHostToDevice, c->cs));
     }
     HIPCHK(c, hipStreamSynchronize(c->cs));  // the host vectors are reused by the next chunk
-    forward_layers(c, S, M, splitk, (int)blocks.size());
+    forward_layers(c, S, M, splitk, false, (int)blocks.size());
     int rc = after(&all[a], M);
     if (rc) return rc;
   }

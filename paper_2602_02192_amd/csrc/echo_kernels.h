@@ -107,13 +107,22 @@ void launch_gather_rows_f32(float *dst, const float *src, const int32_t *src_row
 // ---- debug path: row-major weights (fp32 or bf16), fp32 activations, fp32 KV cache ------------------
 void dbg_embed(float *h, const void *embed, int w_bf16, const int32_t *token, int M, int d, RopeTable rope, hipStream_t st);
 void dbg_rmsnorm(float *x, const float *h, const void *gain, int w_bf16, int M, int d, float eps, hipStream_t st);
-// Y[m][n] (+)= sum_k X[m][k] * W[n][k]
-void dbg_gemm(float *Y, const float *X, const void *W, int w_bf16, int M, int N, int K, int accumulate, hipStream_t st);
+// Y[m][n] (+)= sum_k x[m][k] * W[n][k], where x is X [M][K], its RMS norm with `gain`, or silu(gate) * up of X [M][2K] = gate | up
+enum DbgOperand { DBG_PLAIN = 0, DBG_NORM = 1, DBG_SWIGLU = 2 };
+void dbg_gemm(float *Y, const float *X, const void *W, int w_bf16, int M, int N, int K, int accumulate, hipStream_t st, DbgOperand pro = DBG_PLAIN,
+              const void *gain = nullptr, float eps = 0.f);
+// Norm and SwiGLU inside the product that reads them: small products, where a launch (about 3 us of a dependent chain) costs more than
+// the work that each of the M * N / 4 workgroups repeats over K.  Step of the tiny model (hidden 256) at 4 / 8 / 16 / 32 rows: 81 / 82 / 88 /
+// 101 us with kernels of their own, 70 / 74 / 84 / 98 us so; above the line it loses (everything fused: 32 rows 106, 64 rows 126 -> 150; hidden
+// 1024: 4 rows 140 -> 153, 8 rows 167 -> 213).
+inline bool dbg_fuses(int M, int N, int K) { return (int64_t)M * N * K <= 4 << 20; }
 void dbg_qkv_post(float *qkv /*[M][(Hq+2Hkv)*hd], q rotated in place*/, const void *q_gain, const void *k_gain,
                   int w_bf16, int qk_norm, float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer,
                   int M, int Hq, int Hkv, hipStream_t st);
+// own: a decode pass (rows are different sequences) over rows that dbg_qkv_post has not seen; its work is done here.
+struct DbgHeads { const void *q_gain, *k_gain; int qk_norm; float eps; const float2 *rope; };
 void dbg_attention(float *out /*[M][Hq*hd]*/, const float *qkv, RowState rows, KvGeom kv, int layer, int M, int Hq,
-                   int Hkv, hipStream_t st);
+                   int Hkv, hipStream_t st, const DbgHeads *own, int w_bf16);
 void dbg_swiglu(float *ff /*[M][F]*/, const float *gu /*[M][2F] = gate | up*/, int M, int F, hipStream_t st);
 // Unfused sampler over materialised logits [M][ld]: Gumbel-max token and its log-softmax, in fp32.  scratch: the buffer of
 // fast_topp_cut_and_draw (fast_topp_scratch_floats(Mp) floats).

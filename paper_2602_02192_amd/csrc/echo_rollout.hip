@@ -10,7 +10,7 @@ int capture_step(echo_ctx *c, const Slot &S, int N, int max_new, float temperatu
   if (c->graph) { c->retired_graphs.push_back(c->graph); c->graph = nullptr; }
   hipGraph_t g = nullptr;
   HIPCHK(c, hipStreamBeginCapture(c->cs, hipStreamCaptureModeThreadLocal));
-  forward_layers(c, S, N, !c->attn_plain);
+  forward_layers(c, S, N, !c->attn_plain, true);
   sample_rows(c, S, N, temperature, seed, unfused, nullptr, top_p, step_book(c, S, N, max_new, per_row, forced, eos));
   HIPCHK(c, hipStreamEndCapture(c->cs, &g));
   hipError_t e = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
@@ -400,7 +400,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
       }
       HIPCHK(c, hipGraphLaunch(c->graph, st));
     } else {
-      forward_layers(c, c->slots[cur], Rc, splitk);
+      forward_layers(c, c->slots[cur], Rc, splitk, true);
       sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 0, d_forced, o.eos_id));
       if ((rc = grab_logits(s))) return rc;
     }
@@ -726,7 +726,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
       }
       HIPCHK(c, hipGraphLaunch(c->graph, st));
     } else {
-      forward_layers(c, c->slots[cur], Rc, splitk);
+      forward_layers(c, c->slots[cur], Rc, splitk, true);
       sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 1, d_forced, o.eos_id));
     }
     ++decode_steps;
