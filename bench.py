@@ -144,7 +144,7 @@ def main():
                     help="run the workload through echo_rollout_continuous (refill does not apply when everything fits the cache; "
                          "the rows of a draining batch are compacted)")
     ap.add_argument("--no-graph", action="store_true",
-                    help="launch decode steps kernel by kernel (counter collection cannot follow graph replays)")
+                    help="without effect: decode steps are launched kernel by kernel either way")
     ap.add_argument("--prefix-kernel", type=int, default=0, choices=[0, 1, 2, 3],
                     help="echo_rollout_opts.prefix_kernel: who attends a group's shared prompt tiles (0 = the planner decides)")
     a = ap.parse_args()
@@ -261,7 +261,7 @@ def main():
         step_frac = bytes_decode / (np.mean(decode_ms) * 1e-3) / (HBM_PEAK_GBS * 1e9)
         step_frac_per_seq = bytes_per_seq / (np.mean(decode_ms) * 1e-3) / (HBM_PEAK_GBS * 1e9)
 
-    # per-step roofline fractions: one more rollout (graph replay as timed above) with a HIP event between every two steps
+    # per-step roofline fractions: one more rollout (launched as timed above) with a HIP event between every two steps
     step_stats = {}
     if not continuous and not swaps and not a.no_step_timing:
         rollout(2 + a.steps - 1, time_steps=True)

@@ -77,11 +77,9 @@ typedef struct {
   float *debug_logits;         /* host [N, max_new, vocab] or NULL: also return the raw logits (uses the
                                   unfused sampler; sizes the caller can afford only) */
   int32_t unfused_sampler;     /* 1: write logits to HBM and sample from them with the fp32 debug sampler */
-  int32_t no_graph;            /* 1: launch decode steps kernel by kernel instead of replaying a HIP graph */
-  int32_t time_kernels;        /* 1: bracket decode-attention and GEMM launches with HIP events (implies
-                                  no_graph); durations are read back with echo_stats */
-  int32_t time_steps;          /* 1 (echo_rollout only): a HIP event between every two decode steps (graph replays
-                                  included); the per-step durations are read back with echo_step_times */
+  int32_t no_graph;            /* without effect: decode steps are launched kernel by kernel either way */
+  int32_t time_kernels;        /* 1: bracket decode-attention and GEMM launches with HIP events ; durations are read back with echo_stats */
+  int32_t time_steps;          /* 1 (echo_rollout only): a HIP event between every two decode steps; the per-step durations are read back with echo_step_times */
   int32_t no_compaction;       /* 1 (echo_rollout only): rows of sequences that have ended stay in the batch as inactive
                                   rows until the call ends, instead of the rows of a drained batch being moved together */
   /* Cross-check switches (0 = the default path; results differ from it by rounding order at most, see each): */

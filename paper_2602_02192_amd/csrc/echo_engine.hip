@@ -35,7 +35,7 @@ int echo_init(const echo_model_desc *desc, int device, void *dev_arena, size_t a
   auto bail = [&](const char *what, hipError_t e) { int rc = fail(nullptr, ECHO_EHIP, "%s: %s", what, hipGetErrorString(e)); delete c; return rc; };
   hipError_t e;
   if ((e = hipSetDevice(device)) != hipSuccess) return bail("hipSetDevice", e);
-  // graph capture is not possible on the null stream, so it is replaced by a stream of the library's own
+  // (the null stream would order the rollout's work against the copies; it is replaced by a stream of the library's own)
   c->cs = (hipStream_t)compute_stream; c->ks = (hipStream_t)copy_stream;
   if (!c->cs) { if ((e = hipStreamCreateWithFlags(&c->cs, hipStreamNonBlocking)) != hipSuccess) return bail("hipStreamCreate", e); c->own_cs = true; }
   if (!c->ks) { if ((e = hipStreamCreateWithFlags(&c->ks, hipStreamNonBlocking)) != hipSuccess) return bail("hipStreamCreate", e); c->own_ks = true; }
@@ -193,8 +193,6 @@ void echo_destroy(echo_ctx *c) {
   hipSetDevice(c->device);
   hipStreamSynchronize(c->cs);
   hipStreamSynchronize(c->ks);
-  if (c->graph) hipGraphExecDestroy(c->graph);
-  for (hipGraphExec_t g : c->retired_graphs) hipGraphExecDestroy(g);
   if (c->staged_ev) hipEventDestroy(c->staged_ev);
   for (int s = 0; s < 2; ++s) if (c->vacated_ev[s]) hipEventDestroy(c->vacated_ev[s]);
   if (c->pin) hipHostFree(c->pin);

@@ -220,8 +220,6 @@ struct echo_ctx {
   int32_t *d_stream;  // per-row stream ids of a continuous rollout
   DrawIds ids{nullptr, nullptr, nullptr};
   PrefixPlan px{nullptr, 0, 0, 1};       // shared-prompt attention jobs of the running rollout (n_jobs = 0: none)
-  hipGraphExec_t graph = nullptr;
-  std::vector<hipGraphExec_t> retired_graphs;   // replaced while replays of them may still be queued; destroyed once the stream is idle
   // pinned host memory of a continuous rollout: row state in, row state out, slot lists, records (allocated by the first one,
   // freed with the context)
   char *pin = nullptr;
@@ -257,11 +255,9 @@ int fail(echo_ctx *c, int code, const char *fmt, ...) {
 
 template <typename T> T *at(echo_ctx *c, size_t off) { return (T *)(c->arena + off); }
 
-// The rollout stops using weight slot `s` (call with c->mu held, outside stream capture): decode steps that read the slot
+// The rollout stops using weight slot `s` (call with c->mu held): decode steps that read the slot
 // may still be queued on the compute stream, so whatever the copy stream does from now on -- the next install writes
-// into this slot -- starts behind them.  The wait is placed here, by the rollout's thread, and not by the installing
-// thread: the runtime refuses a cross-stream wait on an event of a stream that is capturing at that moment, and the
-// rollout captures its next step graph right after a switch.
+// into this slot -- starts behind them.
 hipError_t leave_slot(echo_ctx *c, int s) {
   hipError_t e = hipEventRecord(c->vacated_ev[s], c->cs);
   if (e == hipSuccess) e = hipStreamWaitEvent(c->ks, c->vacated_ev[s], 0);

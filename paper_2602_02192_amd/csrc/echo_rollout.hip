@@ -1,21 +1,18 @@
-// The rollout entry points behind the C ABI: echo_rollout (all sequences start together, one HIP graph per snapshot
-// replayed per generation step) and echo_rollout_continuous (refill, compaction), with the planning of the shared-prompt
+// The rollout entry points behind the C ABI: echo_rollout (all sequences start together) and echo_rollout_continuous (refill, compaction), with the planning of the shared-prompt
 // attention jobs and the argument checks they share.
 #include "echo_engine_impl.h"
 
 namespace {
 
-int capture_step(echo_ctx *c, const Slot &S, int N, int max_new, float temperature, uint64_t seed, bool unfused, const int32_t *forced,
-                 int eos, float top_p, int per_row = 0) {
-  if (c->graph) { c->retired_graphs.push_back(c->graph); c->graph = nullptr; }
-  hipGraph_t g = nullptr;
-  HIPCHK(c, hipStreamBeginCapture(c->cs, hipStreamCaptureModeThreadLocal));
+// One generation step over the N rows of the batch, launched kernel by kernel.  (A captured graph per step, which this was, leaves the GPU
+// idle for some 8 us between two replays, and for the capture, 5 us a launch, wherever the rows or the snapshot change; the host
+// enqueues a step in a quarter to a half of the time that the GPU takes for it.  Tiny fp32 model 2.30 -> 2.10 ms, one row of four 4B layers 18.97 ->
+// 18.50, 32B shape at 64 rows 28.0 -> 27.9.)
+int launch_step(echo_ctx *c, const Slot &S, int N, int max_new, float temperature, uint64_t seed, bool unfused, const int32_t *forced, int eos,
+                float top_p, int per_row) {
   forward_layers(c, S, N, !c->attn_plain, true);
   sample_rows(c, S, N, temperature, seed, unfused, nullptr, top_p, step_book(c, S, N, max_new, per_row, forced, eos));
-  HIPCHK(c, hipStreamEndCapture(c->cs, &g));
-  hipError_t e = hipGraphInstantiate(&c->graph, g, nullptr, nullptr, 0);
-  hipGraphDestroy(g);
-  if (e != hipSuccess) return fail(c, ECHO_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
+  HIPCHK(c, hipGetLastError());   // (a launch that was refused)
   return 0;
 }
 
@@ -34,8 +31,7 @@ double drain_events(std::vector<std::pair<hipEvent_t, hipEvent_t>> &v, int64_t *
 // Plans the shared-prompt attention of a decode batch of R rows.  Rows that read whole prompt tiles from a common cache slot
 // (ptiles >= 1) and are still generating are grouped by that slot; every group of two or more is cut into jobs of up to
 // 32 / grp rows, whose rows get ATT_PREFIX_DONE in ptiles (host copy: the caller uploads it).  max_ptiles fixes the chunking
-// for the whole rollout and grid_jobs the launch's job count (unused job slots are empty), so a captured step stays valid
-// when the list is rebuilt.  Leaves c->px.n_jobs = 0 when there is nothing to share or the decode kernel splits keys.
+// for the whole rollout and grid_jobs the launch's job count (unused job slots are empty).  Leaves c->px.n_jobs = 0 when there is nothing to share or the decode kernel splits keys.
 int plan_prefix_jobs(echo_ctx *c, std::vector<int32_t> &ptiles, const std::vector<int32_t> &pslot, const std::vector<int32_t> &live, int R,
                      int max_ptiles, int grid_jobs, int prefix_kernel /* echo_rollout_opts.prefix_kernel */) {
   const int grp = c->d.n_q_heads / c->d.n_kv_heads, per_job = std::max(1, 32 / grp);
@@ -156,11 +152,6 @@ struct RolloutGuard {
   }
   ~RolloutGuard() {
     if (!held) return;
-    if (!c->retired_graphs.empty()) {   // step graphs replaced at a snapshot switch or a compaction
-      hipStreamSynchronize(c->cs);
-      for (hipGraphExec_t g : c->retired_graphs) hipGraphExecDestroy(g);
-      c->retired_graphs.clear();
-    }
     std::lock_guard<std::mutex> lk(c->mu);
     c->rollout_running = false;
     c->attn_plain = false;
@@ -203,7 +194,6 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   bool unfused = o.unfused_sampler || o.debug_logits || o.top_p < 1.0f;   // the nucleus cut needs the whole row of logits
   bool want_timing = o.time_kernels != 0;
   c->timing = false;
-  bool use_graph = !o.no_graph && !want_timing && !o.debug_logits;
   c->t_attn_bytes = c->t_gemm_bytes = 0;
 
   // per-sequence state
@@ -314,8 +304,6 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   if ((rc = mark_step())) return rc;
   double swap_wait = 0;
   int next_swap = 0, decode_steps = 0;
-  bool have_graph = false;
-  bool splitk = !o.attn_plain;
   const bool may_compact = !o.debug_logits && !o.no_compaction;   // (returned logits are in sequence order)
   for (int s = 1; s < steps; ++s) {
     if (next_swap < o.n_swaps && o.swap_at_step[next_swap] == s) {
@@ -330,7 +318,6 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
       lk.unlock();
       HIPCHK(c, hipStreamWaitEvent(st, c->staged_ev, 0));
       swap_wait += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - w0).count();
-      have_graph = false;
       ++next_swap;
     }
     int live_now = Rc;   // sequences that take part in pass s, as far as the host knows
@@ -347,7 +334,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
       for (int r = 0; r < Rc; ++r) live_now += limit[row_seq[r]] > s;
     }
     // A draining batch: once the sequences still generating fit a smaller padded batch their rows are moved to the
-    // front (cache slots and records stay where they are) and the step is captured again for fewer rows.  With stop
+    // front (cache slots and records stay where they are) and the steps go on with fewer rows.  With stop
     // lengths only, the host knows who is still generating; with an end-of-sequence token it looks every 16 steps.
     if (may_compact && pad_rows(std::max(1, live_now)) < pad_rows(Rc) && live_now > 0) {
       std::vector<int32_t> tok(Rc), pos(Rc), act(Rc), gen(Rc);
@@ -376,7 +363,6 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
         HIPCHK(c, hipStreamSynchronize(st));
         pslot = pslot2; ptiles = ptiles2; row_seq = seq2;
         Rc = w;
-        have_graph = false;
       }
     }
     bool time_this = c->timing;
@@ -393,17 +379,8 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
       }
       c->cur_attn_bytes = keys * 2 * c->d.n_kv_heads * c->d.head_dim * 2;
     }
-    if (use_graph) {
-      if (!have_graph) {
-        if ((rc = capture_step(c, c->slots[cur], Rc, max_new, temperature, seed, unfused, d_forced, o.eos_id, o.top_p))) return rc;
-        have_graph = true;
-      }
-      HIPCHK(c, hipGraphLaunch(c->graph, st));
-    } else {
-      forward_layers(c, c->slots[cur], Rc, splitk, true);
-      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 0, d_forced, o.eos_id));
-      if ((rc = grab_logits(s))) return rc;
-    }
+    if ((rc = launch_step(c, c->slots[cur], Rc, max_new, temperature, seed, unfused, d_forced, o.eos_id, o.top_p, 0))) return rc;
+    if ((rc = grab_logits(s))) return rc;
     c->timing = time_this;
     ++decode_steps;
     if ((rc = mark_step())) return rc;
@@ -470,14 +447,12 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   hipStream_t st = c->cs;
   auto t0 = std::chrono::steady_clock::now();
   const bool unfused = o.unfused_sampler || o.top_p < 1.0f;
-  const bool use_graph = !o.no_graph;
   c->attn_plain = o.attn_plain != 0;
   // rows of unequal lengths: workgroups of several rows, one per compute unit, would finish at very different times
   // (measured 22.7 k tokens/s against 25.5 k with the once-per-group kernel at 256 rows), so unless asked for that form is
   // taken only while the live rows sit at about the same position (decided whenever the rows change, below)
   c->attn_mode = o.prefix_kernel == 0 ? 1 : o.prefix_kernel;
   const bool share_prefix = p.fast && !o.own_prompt_copy && !o.attn_plain;
-  const bool splitk = !o.attn_plain;
   const int R = std::min(N, c->d.max_seqs);   // cache slots in use; rows of the batch until the rows are compacted
   int Rc = R;                                 // rows of the batch now
   // host mirrors of the per-row state; token, pos, active and gen are read back at every check
@@ -581,7 +556,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   c->ids = DrawIds{c->d_step, c->d_gen_len, c->d_stream};
 
   int cur = c->active, next_prompt = 0, done_seqs = 0, decode_steps = 0, until_check = 0;
-  bool have_graph = false, first = true, dirty = false;
+  bool first = true, dirty = false;
   double admit_ms = 0, swap_wait = 0;
   std::vector<int> free_rows;
   std::vector<int32_t> quads;
@@ -662,7 +637,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
         admit_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - a0).count();
       }
       // No prompt is waiting any more: once the live rows fit a smaller padded batch they are moved to the front (their
-      // cache slots and records stay where they are) and the step is captured again for fewer rows.
+      // cache slots and records stay where they are) and the steps go on with fewer rows.
       if (next_prompt == P) {
         int live = 0;
         for (int r = 0; r < Rc; ++r) live += row_seq[r] >= 0;
@@ -677,7 +652,6 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
           for (int r = w; r < Rc; ++r) { act[r] = 0; row_seq[r] = -1; }
           Rc = w;
           dirty = true;
-          have_graph = false;
         }
       }
       if (dirty) {   // the rows changed: plan the shared-prompt attention for them, then put the row state on the device
@@ -689,11 +663,9 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
         }
         if (o.prefix_kernel == 0) {   // several rows per decode-attention workgroup only while their lengths are within an eighth
           const int mode = pos_hi >= pos_lo && (pos_hi - pos_lo) * 8 <= pos_hi ? 0 : 1;
-          if (mode != c->attn_mode) { c->attn_mode = mode; have_graph = false; }
+          c->attn_mode = mode;
         }
-        const PrefixPlan was = c->px;
         if ((rc = plan_prefix_jobs(c, ptiles, pslot, live, Rc, share_prefix ? (max_pl - 1) / 32 : 0, Rc / 2 + 1, o.prefix_kernel))) return rc;
-        if (was.n_jobs != c->px.n_jobs || was.np != c->px.np || was.tiles_per_chunk != c->px.tiles_per_chunk) have_graph = false;
         if ((rc = upload_rows())) return rc;
         dirty = false;
       }
@@ -716,19 +688,9 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
         lk.unlock();
         HIPCHK(c, hipStreamWaitEvent(st, c->staged_ev, 0));
         swap_wait += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - w0).count();
-        have_graph = false;
       }
     }
-    if (use_graph) {
-      if (!have_graph) {
-        if ((rc = capture_step(c, c->slots[cur], Rc, max_new, temperature, seed, unfused, d_forced, o.eos_id, o.top_p, 1))) return rc;
-        have_graph = true;
-      }
-      HIPCHK(c, hipGraphLaunch(c->graph, st));
-    } else {
-      forward_layers(c, c->slots[cur], Rc, splitk, true);
-      sample_rows(c, c->slots[cur], Rc, temperature, seed, unfused, nullptr, o.top_p, step_book(c, c->slots[cur], Rc, max_new, 1, d_forced, o.eos_id));
-    }
+    if ((rc = launch_step(c, c->slots[cur], Rc, max_new, temperature, seed, unfused, d_forced, o.eos_id, o.top_p, 1))) return rc;
     ++decode_steps;
     --until_check;
   }

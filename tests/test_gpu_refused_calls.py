@@ -68,6 +68,31 @@ print("as expected")
 """)
 
 
+@pytest.mark.parametrize("kernel", ["dbg_gemm_kernel", "dbg_attention_kernel", "dbg_sample_kernel"])
+@pytest.mark.parametrize("continuous", [False, True])
+def test_a_refused_launch_of_a_step_is_an_error(child, kernel, continuous):
+    """A launch in the middle of the call and the last one; sequences that all start together, and refilled ones."""
+    child(f"""
+slots = 4 if {continuous} else P * G
+ctx = make_ctx(shape, slots, 9 + new, blob)
+go = lambda: ctx.rollout(prompts, lens, G, new, 1.0, 4, stop_lens=stop, forced=forced, continuous={continuous})
+shim.hip_refuse(b"{kernel}", 1 << 30)
+want = go()
+n = shim.hip_seen()
+for after in (n // 2, n - 1):
+    shim.hip_refuse(b"{kernel}", after)
+    try:
+        go()
+    except echo.EchoError as e:
+        assert e.code == echo.ECHO_EHIP and shim.hip_refused(), e
+    else:
+        raise SystemExit(f"succeeded with launch {{after}} of {{n}} refused")
+    again = go()
+    assert all(np.array_equal(again[k], want[k]) for k in ("tokens", "logprobs", "lens", "versions"))
+print("as expected")
+""")
+
+
 def test_without_pinned_memory(child):
     """The same records, with forced tokens and free running; a later call finds pinned memory again and keeps it."""
     child("""
