@@ -232,6 +232,7 @@ struct echo_ctx {
   std::vector<float> step_ms;   // per-step durations of the last rollout run with time_steps
   bool attn_plain = false;   // cross-check switch of the running rollout (echo_rollout_opts.attn_plain)
   int attn_mode = 0;         // echo_rollout_opts.prefix_kernel of the running rollout
+  int max_keys = 0;          // the most keys that a row of the running rollout can come to (0: no rollout)
   double t_attn_bytes = 0, t_gemm_bytes = 0, cur_attn_bytes = 0;
 };
 
@@ -403,7 +404,7 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, boo
       else if (att_rows > 1)
         fast_attention_rows(xatt, q16, at<int32_t>(c, p.o_aplan), c->rows, c->kv, l, M, Mp, Hq, Hkv, c->attn_mode, st);
       else if (use_splitk_attn)
-        fast_attention(xatt, q16, c->rows, c->kv, l, M, Mp, Hq, Hkv, fast_attention_splits(M, Hkv, p.attn_max_splits),
+        fast_attention(xatt, q16, c->rows, c->kv, l, M, Mp, Hq, Hkv, fast_attention_splits(M, Hkv, p.attn_max_splits, c->max_keys),
                        at<float>(c, p.o_attn_o), at<float>(c, p.o_attn_ml), c->px, st);
       else
         fast_attention_simple(xatt, q16, c->rows, c->kv, l, M, Mp, Hq, Hkv, st);

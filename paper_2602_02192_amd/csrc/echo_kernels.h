@@ -179,13 +179,14 @@ void fast_attention_simple(void *Xp_out, const void *q_h16, RowState rows, KvGeo
 constexpr int ATT_PREFIX_DONE = 0x40000000;
 struct PrefixJob { int32_t pslot, ptiles, nrows; int32_t rows[32]; };
 struct PrefixPlan { const PrefixJob *jobs; int n_jobs, np, tiles_per_chunk; };
-// nsplit = fast_attention_splits(M, Hkv, capacity); partial buffers hold M*Hq*max(nsplit, px.np)*(hd + 2) floats.
+// nsplit = fast_attention_splits(M, Hkv, capacity, bound on the keys of every row); partial buffers hold M*Hq*max(nsplit, px.np)*(hd + 2) floats.
 // With px.n_jobs > 0 and nsplit == 1, fast_attention_prefix must have run first on the same stream, partial buffers and q.
 void fast_attention(void *Xp_out, const void *q_h16, RowState rows, KvGeom kv, int layer, int M, int Mp, int Hq,
                     int Hkv, int nsplit, float *part_o, float *part_ml, PrefixPlan px, hipStream_t st);
 void fast_attention_prefix(const void *q_h16, KvGeom kv, int layer, int Hq, int Hkv, float *part_o, float *part_ml, PrefixPlan px,
                            hipStream_t st);
-int fast_attention_splits(int M, int Hkv, int max_splits);
+int fast_attention_splits(int M, int Hkv, int max_splits, int max_keys);
+bool fast_attention_fills(int M, int Hkv);   // a workgroup per row and KV head fills the chip
 // Decode attention with several rows of the batch per workgroup (at most R, R * Hq/Hkv <= 32): the whole prompt tiles
 // that neighbouring rows of one group have in common are loaded and multiplied once per workgroup.  No key splitting and no
 // partial buffers.  fast_attention_rows_per_group gives R (1: use fast_attention) -- mode 0: a workgroup for every compute

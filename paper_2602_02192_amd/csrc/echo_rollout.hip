@@ -38,7 +38,7 @@ int plan_prefix_jobs(echo_ctx *c, std::vector<int32_t> &ptiles, const std::vecto
   const int cap = pad_rows(c->d.max_seqs) / 2 + 1;
   c->px = PrefixPlan{at<PrefixJob>(c, c->p.o_pjobs), 0, 0, 1};
   for (int r = 0; r < R; ++r) ptiles[r] &= ~ATT_PREFIX_DONE;
-  if (!c->p.fast || max_ptiles < 1 || fast_attention_splits(R, c->d.n_kv_heads, c->p.attn_max_splits) != 1 || prefix_kernel == 1) return 0;
+  if (!c->p.fast || max_ptiles < 1 || !fast_attention_fills(R, c->d.n_kv_heads) || prefix_kernel == 1) return 0;
   if (fast_attention_rows_per_group(R, c->d.n_q_heads, c->d.n_kv_heads, c->attn_mode) > 1) return 0;   // the decode kernel shares the tiles itself
   std::vector<PrefixJob> jobs;
   std::vector<int> order(R);
@@ -156,6 +156,7 @@ struct RolloutGuard {
     c->rollout_running = false;
     c->attn_plain = false;
     c->attn_mode = 0;
+    c->max_keys = 0;
     c->ids = DrawIds{c->d_step, nullptr, nullptr};
     c->px.n_jobs = 0;
     if (c->staged >= 0) {   // (a rollout that failed half-way may have left work queued on the old slot)
@@ -203,6 +204,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
     plen_seq[n] = prompt_lens[n / G];
     limit[n] = o.stop_lens ? std::max(1, std::min(max_new, o.stop_lens[n])) : max_new;
     steps = std::max(steps, limit[n]);
+    c->max_keys = std::max(c->max_keys, plen_seq[n] + limit[n]);
   }
   HIPCHK(c, hipMemcpyAsync(c->d_prompt_len_seq, plen_seq.data(), N * 4, hipMemcpyHostToDevice, st));
   HIPCHK(c, hipMemcpyAsync(c->d_limit, limit.data(), N * 4, hipMemcpyHostToDevice, st));
@@ -440,6 +442,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   for (int p = 0; p < P; ++p) max_pl = std::max(max_pl, prompt_lens[p]);
   RolloutGuard guard(c);
   if ((rc = guard.begin())) return rc;
+  c->max_keys = max_pl + max_new;
 
   HIPCHK(c, hipSetDevice(c->device));
   if ((rc = ensure_pinned(c))) return rc;

@@ -74,10 +74,10 @@ void fast_attention_simple(void *Xp_out, const void *q_h16, RowState rows, KvGeo
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int ATT_WAVES = 4;
 
-template <int HD> struct AttLds {
+template <int HD, int NW> struct AttLds {
   static constexpr int MERGE_PER_WAVE = 8 * HD * 4 + 64;    // O rows of up to 8 query heads + (m, l)
   static constexpr int Q_BYTES = 8 * HD * 2;                // the group's queries (B operands are re-read per tile)
-  static constexpr int TOTAL = ATT_WAVES * MERGE_PER_WAVE + Q_BYTES;
+  static constexpr int TOTAL = NW * MERGE_PER_WAVE + Q_BYTES;
 };
 
 // Keys per split of a row with n_keys keys cut into nsplit equal parts (whole tiles).
@@ -105,20 +105,20 @@ __device__ __forceinline__ void att_issue_v(v4u (&rv)[HD / 16], const v4u *__res
 // (nsplit == 1): the workgroup normalises and writes the half-precision output itself and no partials exist.
 // DIRECT with np > 0: rows whose ptiles carry ATT_PREFIX_DONE skip their group's shared prompt tiles and fold in the
 // partials attn_prefix_kernel left for them (np chunk slots per (row, head), prefix_tpc tiles per chunk).
-template <int HD, bool DIRECT>
-__global__ __launch_bounds__(256, 2) void attn_splitk_kernel(float *__restrict__ part_o, float *__restrict__ part_ml,
+template <int HD, bool DIRECT, int NW>
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_splitk_kernel(float *__restrict__ part_o, float *__restrict__ part_ml,
                                                           uint16_t *__restrict__ Xp, int Mp, const uint16_t *__restrict__ q_h16,
                                                           RowState rows, KvGeom kv, int layer, int Hq, int Hkv, int nsplit,
                                                           int np, int prefix_tpc) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  using L = AttLds<HD>;
+  using L = AttLds<HD, NW>;
   constexpr int KS = HD / 16;          // k-steps of K Q^T; also 1 KiB loads per K (or V) tile
   constexpr int NE = HD / 32;          // 32-dim blocks of the head
   const int c = blockIdx.x, kvh = blockIdx.y, m = blockIdx.z;
   const int grp = Hq / Hkv;
   if (!rows.active[m]) {
     if (DIRECT)
-      for (int idx = threadIdx.x; idx < grp * HD; idx += 256) Xp[k8_index(m, kvh * grp * HD + idx, Mp)] = 0;
+      for (int idx = threadIdx.x; idx < grp * HD; idx += NW * 64) Xp[k8_index(m, kvh * grp * HD + idx, Mp)] = 0;
     return;
   }
   const int n_keys = rows.pos[m] + 1, chunk_keys = att_split_len(n_keys, nsplit), key0 = c * chunk_keys;
@@ -143,8 +143,8 @@ __global__ __launch_bounds__(256, 2) void attn_splitk_kernel(float *__restrict__
   if (tile < ntiles) { issue_k(tile0 + tile); issue_v(tile0 + tile); }
 
   // the group's queries as B operands in LDS: unit (ks*2 + half)*8 + head holds dims ks*16 + half*8 .. +8 of one head
-  v4u *qs = (v4u *)(lds + ATT_WAVES * L::MERGE_PER_WAVE);
-  for (int idx = threadIdx.x; idx < 8 * (HD / 8); idx += 256) {
+  v4u *qs = (v4u *)(lds + NW * L::MERGE_PER_WAVE);
+  for (int idx = threadIdx.x; idx < 8 * (HD / 8); idx += NW * 64) {
     int hq = idx & 7, d8 = idx >> 3;
     v4u v = v4u{0u, 0u, 0u, 0u};
     if (hq < grp) v = *(const v4u *)(q_h16 + ((int64_t)m * Hq + kvh * grp + hq) * HD + d8 * 8);
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void attn_splitk_kernel(float *__restrict__
       s = mfma_h16(__builtin_bit_cast(h16x8, rk[ks]), __builtin_bit_cast(h16x8, qb), s);
     }
     // the MFMAs above read rk when they issue; the loads below write rk when the data arrives, after them
-    if (more) issue_k(tile0 + tile + ATT_WAVES);
+    if (more) issue_k(tile0 + tile + NW);
     // ---- online softmax for head `col` over the tile's keys (register 4g+i: key 8g + 4*half + i)
     const int kbase = key0 + tile * ATT_TILE + 4 * half;
     float tm = -INFINITY;
@@ -219,11 +219,11 @@ __global__ __launch_bounds__(256, 2) void attn_splitk_kernel(float *__restrict__
       for (int e = 0; e < NE; ++e)
         o[e] = mfma_h16(__builtin_bit_cast(h16x8, rv[ks2 * NE + e]), __builtin_bit_cast(h16x8, pb), o[e]);
     }
-    if (more) issue_v(tile0 + tile + ATT_WAVES);
+    if (more) issue_v(tile0 + tile + NW);
   };
   // every tile but the wavefront's last requests its successor unconditionally: a load behind a condition would make
   // the compiler's wait counts assume it was not issued, and the waits that follow would drain the queue
-  for (; tile + ATT_WAVES < ntiles; tile += ATT_WAVES) step(std::true_type{});
+  for (; tile + NW < ntiles; tile += NW) step(std::true_type{});
   if (tile < ntiles) step(std::false_type{});
   // ---- the two lanes of a column add their sums; then the four wavefronts are folded in wavefront order
   l_run += __shfl_xor(l_run, 32, 64);
@@ -240,18 +240,18 @@ __global__ __launch_bounds__(256, 2) void attn_splitk_kernel(float *__restrict__
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < grp * HD; idx += 256) {
+  for (int idx = threadIdx.x; idx < grp * HD; idx += NW * 64) {
     int r = idx / HD, dd = idx % HD;
-    float mw[ATT_WAVES], M = -INFINITY;
+    float mw[NW], M = -INFINITY;
 #pragma unroll
-    for (int ww = 0; ww < ATT_WAVES; ++ww) { mw[ww] = ((float *)(lds + ww * L::MERGE_PER_WAVE))[8 * HD + r]; M = fmaxf(M, mw[ww]); }
+    for (int ww = 0; ww < NW; ++ww) { mw[ww] = ((float *)(lds + ww * L::MERGE_PER_WAVE))[8 * HD + r]; M = fmaxf(M, mw[ww]); }
     // the chunks of the shared prompt, computed once for the whole group
     const int npc = pre ? (ptiles + prefix_tpc - 1) / prefix_tpc : 0;
     const int64_t ppi = ((int64_t)m * Hq + kvh * grp + r) * np;
     for (int pc = 0; pc < npc; ++pc) M = fmaxf(M, part_ml[(ppi + pc) * 2]);
     float acc = 0.f, lsum = 0.f;
 #pragma unroll
-    for (int ww = 0; ww < ATT_WAVES; ++ww) {
+    for (int ww = 0; ww < NW; ++ww) {
       const float *mo = (const float *)(lds + ww * L::MERGE_PER_WAVE);
       float f = __expf(mw[ww] - M);   // a wavefront that saw no tile has max -inf and weight 0
       acc += mo[r * HD + dd] * f;
@@ -422,11 +422,17 @@ __global__ void attn_combine_kernel(uint16_t *Xp, const float *__restrict__ part
   Xp[xi] = f32_to_h16_bits(acc / lsum);
 }
 
+bool fast_attention_fills(int M, int Hkv) { return 640 / (M * Hkv) <= 1; }
+
 // Splits per row: enough workgroups (rows x KV heads x splits) to put two on every compute unit, never more
-// than max_splits (the capacity of the partial buffers).  One split needs no partials and no combine launch.
-int fast_attention_splits(int M, int Hkv, int max_splits) {
+// than max_splits (the capacity of the partial buffers).  One split needs no partials and no combine launch: where the batch alone does
+// not fill the chip, a row's workgroup has eight wavefronts then (instead of two splits of four: the same loads in flight), and rows that are short
+// enough for that (max_keys: a bound on the keys of every row, 0: unknown) are not split further.  A layer of the 4B attention shape, rows x keys, split
+// / alone: 1 x 120 55.9 / 54.1 us, 1 x 1020 63.8 / 61.9, 1 x 2020 64.4 / 71.0; 4 x 500 63.7 / 57.6, 4 x 2020 65.8 / 70.1; 16 x 120
+// 61.3 / 55.7, 16 x 2020 73.0 / 70.8; 31 rows (two splits) x 120 60.8 / 57.5, x 2020 75.1 / 72.2.
+int fast_attention_splits(int M, int Hkv, int max_splits, int max_keys) {
   int ns = 640 / (M * Hkv);
-  if (ns < 1) ns = 1;
+  if (ns <= 2 || (max_keys > 0 && max_keys <= (ns <= 5 ? 2048 : 1024))) ns = 1;
   return ns < max_splits ? ns : max_splits;
 }
 
@@ -436,10 +442,14 @@ static void attention_launch(void *Xp_out, const void *q_h16, RowState rows, KvG
   dim3 grid(nsplit, Hkv, M);
   if (nsplit == 1) {
     const bool pre = px.n_jobs > 0 && px.np > 0;
-    hipLaunchKernelGGL((attn_splitk_kernel<HD, true>), grid, dim3(256), AttLds<HD>::TOTAL, st, part_o, part_ml, (uint16_t *)Xp_out,
-                       Mp, (const uint16_t *)q_h16, rows, kv, layer, Hq, Hkv, nsplit, pre ? px.np : 0, px.tiles_per_chunk);
+    auto launch = [&](auto kernel, int waves, int lds) {
+      hipLaunchKernelGGL(kernel, grid, dim3(waves * 64), lds, st, part_o, part_ml, (uint16_t *)Xp_out, Mp, (const uint16_t *)q_h16, rows, kv, layer, Hq,
+                         Hkv, nsplit, pre ? px.np : 0, px.tiles_per_chunk);
+    };
+    if (!fast_attention_fills(M, Hkv)) launch(attn_splitk_kernel<HD, true, 8>, 8, AttLds<HD, 8>::TOTAL);   // see fast_attention_splits
+    else launch(attn_splitk_kernel<HD, true, ATT_WAVES>, ATT_WAVES, AttLds<HD, ATT_WAVES>::TOTAL);
   } else {
-    hipLaunchKernelGGL((attn_splitk_kernel<HD, false>), grid, dim3(256), AttLds<HD>::TOTAL, st, part_o, part_ml, (uint16_t *)Xp_out,
+    hipLaunchKernelGGL((attn_splitk_kernel<HD, false, ATT_WAVES>), grid, dim3(256), (AttLds<HD, ATT_WAVES>::TOTAL), st, part_o, part_ml, (uint16_t *)Xp_out,
                        Mp, (const uint16_t *)q_h16, rows, kv, layer, Hq, Hkv, nsplit, 0, 1);
     hipLaunchKernelGGL(attn_combine_kernel<HD>, dim3(M, Hq), dim3(HD), 0, st, (uint16_t *)Xp_out, part_o, part_ml, rows, Mp, Hq,
                        nsplit);
