@@ -78,7 +78,7 @@ typedef struct {
                                   unfused sampler; sizes the caller can afford only) */
   int32_t unfused_sampler;     /* 1: write logits to HBM and sample from them with the fp32 debug sampler */
   int32_t no_graph;            /* without effect: decode steps are launched kernel by kernel either way */
-  int32_t time_kernels;        /* 1: bracket decode-attention and GEMM launches with HIP events ; durations are read back with echo_stats */
+  int32_t time_kernels;        /* 1: bracket decode-attention and GEMM launches with HIP events; durations are read back with echo_stats */
   int32_t time_steps;          /* 1 (echo_rollout only): a HIP event between every two decode steps; the per-step durations are read back with echo_step_times */
   int32_t no_compaction;       /* 1 (echo_rollout only): rows of sequences that have ended stay in the batch as inactive
                                   rows until the call ends, instead of the rows of a drained batch being moved together */
@@ -107,7 +107,7 @@ typedef struct {
   int32_t rollout_running;    /* 1 while echo_rollout is inside its loop on another thread (a snapshot installed
                                  now is staged, not activated) */
   int32_t attn_rows_per_workgroup; /* rows of the batch that one workgroup of the decode attention took in the last decode
-                                 step that was launched or captured (1: a workgroup per row and KV head; see prefix_kernel) */
+                                 step that was launched (1: a workgroup per row and KV head; see prefix_kernel) */
   int32_t attn_prefix_jobs;   /* jobs of the once-per-group prompt kernel in that step (0: the kernel did not run) */
 } echo_stats_t;
 

@@ -351,6 +351,7 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, boo
     int bf = d.dtype == ECHO_BF16;
     float *x = at<float>(c, p.o_x), *qkv = at<float>(c, p.o_qkv), *att = at<float>(c, p.o_att), *gu = at<float>(c, p.o_gu),
           *ff = at<float>(c, p.o_ff);
+    const bool own = decode && dbg_attention_owns(c->kv.max_ctx);
     dbg_embed(h, S.embed, bf, c->rows.token, M, H, table, st);
     auto normed_gemm = [&](float *y, const void *gain, const void *w, int N) {
       if (dbg_fuses(M, N, H)) { dbg_gemm(y, h, w, bf, M, N, H, 0, st, DBG_NORM, gain, d.rms_eps); return; }
@@ -361,8 +362,8 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, boo
       const LayerW &L = S.layers[l];
       const DbgHeads heads{L.q_norm, L.k_norm, d.qk_norm, d.rms_eps, (const float2 *)rope};
       normed_gemm(qkv, L.attn_norm, L.wqkv, (Hq + 2 * Hkv) * hd);
-      if (!decode) dbg_qkv_post(qkv, L.q_norm, L.k_norm, bf, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
-      dbg_attention(att, qkv, c->rows, c->kv, l, M, Hq, Hkv, st, decode ? &heads : nullptr, bf);
+      if (!own) dbg_qkv_post(qkv, L.q_norm, L.k_norm, bf, d.qk_norm, d.rms_eps, rope, c->rows, c->kv, l, M, Hq, Hkv, st);
+      dbg_attention(att, qkv, c->rows, c->kv, l, M, Hq, Hkv, st, own ? &heads : nullptr, bf);
       dbg_gemm(h, att, L.wo, bf, M, H, Hq * hd, 1, st);
       normed_gemm(gu, L.ffn_norm, L.wgu, 2 * F);
       if (dbg_fuses(M, H, F)) {

@@ -120,7 +120,10 @@ void dbg_qkv_post(float *qkv /*[M][(Hq+2Hkv)*hd], q rotated in place*/, const vo
                   int w_bf16, int qk_norm, float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer,
                   int M, int Hq, int Hkv, hipStream_t st);
 // own: a decode pass (rows are different sequences) over rows that dbg_qkv_post has not seen; its work is done here.
+// Its query and key take 2 KB of LDS beside the scores (a float per key of max_ctx): only while both fit 64 KB, so that
+// no context that the scores alone fit is refused; where the limit is higher, the launch that it saves no longer shows beside so many keys.
 struct DbgHeads { const void *q_gain, *k_gain; int qk_norm; float eps; const float2 *rope; };
+inline bool dbg_attention_owns(int max_ctx) { return max_ctx <= (64 - 2) * 1024 / 4; }
 void dbg_attention(float *out /*[M][Hq*hd]*/, const float *qkv, RowState rows, KvGeom kv, int layer, int M, int Hq,
                    int Hkv, hipStream_t st, const DbgHeads *own, int w_bf16);
 void dbg_swiglu(float *ff /*[M][F]*/, const float *gu /*[M][2F] = gate | up*/, int M, int F, hipStream_t st);

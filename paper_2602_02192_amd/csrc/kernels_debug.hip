@@ -184,7 +184,7 @@ void dbg_qkv_post(float *qkv, const void *q_gain, const void *k_gain, int w_bf16
 template <bool OWN, bool BF>
 __global__ void dbg_attention_kernel(float *out, const float *qkv, RowState rows, KvGeom kv, int layer, int Hq, int Hkv, DbgHeads hp) {
   extern __shared__ float sc[];
-  __shared__ float own[2][256];   // OWN: the query, the new key
+  __shared__ __attribute__((aligned(16))) float own[2][256];   // OWN: the query, the new key
   int m = blockIdx.x, j = blockIdx.y, lane = threadIdx.x, hd = kv.head_dim;
   float *o = out + ((int64_t)m * Hq + j) * hd;
   if (!rows.active[m]) { for (int i = lane; i < hd; i += 64) o[i] = 0.f; return; }

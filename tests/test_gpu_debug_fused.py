@@ -25,3 +25,21 @@ def test_products_on_either_side_of_the_line(hidden, kv, ffn, vocab):
     if check_tokens_fp32_sampler(out["tokens"], ref, mask) == 0:
         assert np.abs(out["logprobs"] - ref["logprobs"])[mask].max() < F32_LOGPROB_TOL
     ctx.close()
+
+
+@pytest.mark.parametrize("qk_norm", [False, True])
+def test_contexts_on_either_side_of_the_scores_that_fit(qk_norm):
+    """The decode attention makes its own query and key only while they fit beside the scores of a full context: the same results either way."""
+    shape = synth.TINY.replace(qk_norm=qk_norm)
+    blob = synth.make_weights(shape, 3, gain_jitter=0.1)
+    prompts, lens = synth.make_prompts(shape.vocab, 2, 33, seed=9)
+    outs = []
+    for max_ctx in (39, 15872, 15873, 16384):
+        ctx = make_ctx(shape, 4, max_ctx, blob)
+        outs.append(ctx.rollout(prompts, lens, 2, 6, 1.0, 2, want_logits=True))
+        ctx.close()
+    ref = oracle_rollout(shape, synth.widen_to_f32(blob), prompts, lens, G=2, max_new=6, temperature=1.0, seed=2, forced=outs[0]["tokens"], want_logits=True)
+    assert np.abs(outs[0]["logits"] - ref["logits"]).max() < F32_LOGIT_TOL
+    for out in outs[1:]:
+        for k in ("tokens", "logprobs", "logits"):
+            assert np.array_equal(out[k], outs[0][k])
