@@ -42,16 +42,20 @@ __device__ __forceinline__ float load_w(const void *p, int64_t i) {
 }
 
 // Philox-4x32 with 10 rounds (Salmon et al., SC'11): multipliers 0xD2511F53 / 0xCD9E8D57, key
-// increments 0x9E3779B9 / 0xBB67AE85.
+// increments 0x9E3779B9 / 0xBB67AE85.  Both halves of a product come from one v_mad_u64_u32 and the three words that meet are
+// folded by one v_bitop3_b32: 20 multiplications and 20 folds a call, where the compiler makes 40 (a high and a low one each) and 38
+// of the plain form.  128 rows of 151936: topp_draw_kernel, which the vector unit bounds, 52.8 -> 46.0 us; the lm_head's sampler, which
+// hides most of it behind its loads, 254 -> 249 (256 rows) and 134.0 -> 132.6 (64).
 struct u32x4 { uint32_t x, y, z, w; };
 __device__ __forceinline__ u32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                uint32_t k1) {
+  constexpr uint32_t XOR3 = 0x96;   // truth table of a ^ b ^ c
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    c0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, k0, XOR3);
+    c2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c3, k1, XOR3);
+    c1 = (uint32_t)p1; c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
   }
   return {c0, c1, c2, c3};
@@ -66,7 +70,12 @@ __device__ __forceinline__ u32x4 draw4(uint64_t seed, uint32_t n, uint32_t s, ui
 __device__ __forceinline__ uint32_t draw_step(const DrawIds &d, int m) { return (uint32_t)(d.row_step ? d.row_step[m] : *d.d_step); }
 __device__ __forceinline__ uint32_t draw_stream(const DrawIds &d, int m) { return (uint32_t)(d.row_stream ? d.row_stream[m] : m); }
 
-// 23 random bits -> u = (2k+1) 2^-24, then the standard Gumbel variate -log(-log u) in fp32.
+// 23 random bits k -> u = (2k + 1) 2^-24: the bits as the significand of a number from 1 to 2, less what is too much (exact).
+__device__ __forceinline__ float uniform_from_bits(uint32_t bits) {
+  return __uint_as_float(__builtin_amdgcn_alignbit(127u, bits, 9)) - (1.0f - 0x1p-24f);
+}
+
+// The standard Gumbel variate -log(-log u) of the same u in fp32.
 __device__ __forceinline__ float gumbel_from_bits(uint32_t bits) {
   float u = (float)(2u * (bits >> 9) + 1u) * 0x1p-24f;
   return -logf(-logf(u));

@@ -637,7 +637,7 @@ __global__ __launch_bounds__(TOPP_THREADS) void topp_cut_kernel(uint32_t *cut_ke
 // kept tokens by z/ln2 - log2(-log2 u) and evaluates the winner in full.  Both orders agree unless its best two are closer than
 // the roundings of two hardware logarithms and of z: below 1e-5 plus 1e-6 of the score's magnitude; within ten times that
 // the wavefront evaluates all its kept tokens in full.  Four tokens of which none is kept draw no numbers.  128 rows of 151936
-// logits, three quarters of them kept: 62 -> 52 us, of which the ten rounds of the generator are some 30 by instruction count.
+// logits, three quarters of them kept: 62 -> 52 us, 46 with the generator in its present form (philox4x32_10).
 __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, const int32_t *cut_last, const float *logits, int64_t ld,
                                  int V, float temperature, uint64_t seed, DrawIds ids) {
   __shared__ SampleAcc sh[4];
@@ -675,10 +675,10 @@ __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, c
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       sum += __builtin_amdgcn_exp2f((x[e] - xm) * c2);   // the difference first: as exact at scores of thousands
-      const float u = fmaf((float)(w[e] >> 9), 0x1p-23f, 0x1p-24f);   // exact: (2k + 1) 2^-24
+      const float u = uniform_from_bits(w[e]);
       const float f = fmaf(x[e], c2, -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)));
       const bool better = f > best;
-      second = fmaxf(second, fminf(f, best));
+      second = __builtin_amdgcn_fmed3f(f, best, second);   // (the smaller of the two others where f is NaN)
       best = better ? f : best;
       xbest = better ? x[e] : xbest;
       wbest = better ? w[e] : wbest;

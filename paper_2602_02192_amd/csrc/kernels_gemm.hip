@@ -991,11 +991,11 @@ __device__ __forceinline__ SampleAcc sample_lane(f32x16 (&x)[NBW], float *dump, 
       const uint32_t w[4] = {d.x, d.y, d.z, d.w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float u = fmaf((float)(w[i] >> 9), 0x1p-23f, 0x1p-24f);   // exact: (2k + 1) 2^-24
+        const float u = uniform_from_bits(w[i]);
         const float f = fmaf(x[n][4 * g + i], c2, -__builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)));
         xm = fmaxf(xm, x[n][4 * g + i]);
         const bool better = f > best;
-        second = fmaxf(second, fminf(f, best));
+        second = __builtin_amdgcn_fmed3f(f, best, second);   // (the smaller of the two others where f is NaN)
         best = better ? f : best;
         xbest = better ? x[n][4 * g + i] : xbest;
         wbest = better ? w[i] : wbest;
