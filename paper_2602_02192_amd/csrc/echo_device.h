@@ -117,6 +117,18 @@ __device__ __forceinline__ SampleAcc sample_acc_shfl_xor(const SampleAcc &a, int
   return b;
 }
 
+// A workgroup's partial of a row, at o = workgroup * rows + row of a buffer of `plane` partials: (max z, sum, best score, its z) side by
+// side, so that the row's reader fetches one line of them, and the index in a plane of its own.  A scoring pass has the first two only.
+__device__ __forceinline__ void sample_part_store(float *part, int64_t o, int64_t plane, const SampleAcc &a) {
+  *(f32x4 *)(part + 4 * o) = f32x4{a.zmax, a.zsum, a.best, a.zbest};
+  part[4 * plane + o] = __int_as_float(a.idx);
+}
+__device__ __forceinline__ SampleAcc sample_part_load(const float *part, int64_t o, int64_t plane) {
+  const f32x4 v = *(const f32x4 *)(part + 4 * o);
+  return {v[0], v[1], v[2], v[3], __float_as_int(part[4 * plane + o])};
+}
+__device__ __forceinline__ void score_part_store(float *part, int64_t o, const SampleAcc &a) { *(float2 *)(part + 2 * o) = make_float2(a.zmax, a.zsum); }
+
 // Entry idx = m * half + i of the rotary table: cos/sin of pos * base^(-2i/hd), evaluated in double and stored as fp32.
 __device__ __forceinline__ void rope_entry(float2 *cs, const int32_t *pos, int idx, int M, int half, float base) {
   if (idx >= M * half) return;

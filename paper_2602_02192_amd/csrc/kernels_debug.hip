@@ -309,11 +309,7 @@ __global__ void dbg_sample_kernel(int32_t *tok, float *lp, float *part, int Mp, 
       if (book.d_step) book_row(book, m, a.idx, lp[m]);
     } else {
       const int64_t o = (int64_t)c * Mp + m, plane = (int64_t)slices * Mp;
-      part[o] = a.zmax;
-      part[plane + o] = a.zsum;
-      part[2 * plane + o] = a.best;
-      part[3 * plane + o] = a.zbest;
-      part[4 * plane + o] = __int_as_float(a.idx);
+      sample_part_store(part, o, plane, a);
     }
   }
 }

@@ -712,11 +712,7 @@ __global__ void topp_draw_kernel(float *part, int Mp, const uint32_t *cut_key, c
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) sample_acc_merge(a, sh[w]);
     int64_t o = (int64_t)c * Mp + m, plane = (int64_t)TOPP_CHUNKS * Mp;
-    part[o] = a.zmax;
-    part[plane + o] = a.zsum;
-    part[2 * plane + o] = a.best;
-    part[3 * plane + o] = a.zbest;
-    part[4 * plane + o] = __int_as_float(a.idx);
+    sample_part_store(part, o, plane, a);
   }
 }
 

@@ -1057,12 +1057,8 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
   gemm_lds_mainloop<MB, LM_WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC);
   auto write_partial = [&](const SampleAcc &sa, int m) {
     int64_t o = (int64_t)blockIdx.x * Mp + m, plane = (int64_t)n_wg * Mp;
-    part[o] = sa.zmax;
-    part[plane + o] = sa.zsum;
-    if (target) return;
-    part[2 * plane + o] = sa.best;
-    part[3 * plane + o] = sa.zbest;
-    part[4 * plane + o] = __int_as_float(sa.idx);
+    if (target) score_part_store(part, o, sa);
+    else sample_part_store(part, o, plane, sa);
   };
   if constexpr (LOGITS) {
     if (nb_own < nblocks) {
@@ -1107,7 +1103,7 @@ __global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const 
 
 // ---- lm_head on the tiles of the LDS ring (128 rows and more) ----------------------------------------------------------------
 // A wavefront holds 64 vocabulary entries of 32 MB batch rows; lanes l and l^32 hold the same rows.  One partial per (row, strip
-// of 32 NB entries): planes max z, sum exp, best score, its z, its index; scoring (SCORE) writes the first two and target_z.
+// of 32 NB entries): max z, sum exp, best score, its z, its index (sample_part_store); scoring (SCORE) writes the first two and target_z.
 // Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.75 ms at hidden 2560 (1.16
 // PFLOP/s), 5.17 ms at 5120 (1.23), where the register-streaming tile it replaced (24 KB per k-step, accumulators parked in
 // LDS for the epilogue) took 3.91 and 6.83.  Sampling takes 128 x 128 tiles: its epilogue keeps the vector unit busy for as long
@@ -1148,13 +1144,8 @@ __global__ __launch_bounds__(L::T) void lmhead_ring_kernel(const u32x4v *__restr
 #pragma unroll
     for (int c = 1; c < L::WC; ++c) sample_acc_merge(sa, sh[c][r]);
     const int64_t o = (int64_t)bx * Mp + mrow0 + r, plane = (int64_t)strips * Mp;
-    part[o] = sa.zmax;
-    part[plane + o] = sa.zsum;
-    if (!SCORE) {
-      part[2 * plane + o] = sa.best;
-      part[3 * plane + o] = sa.zbest;
-      part[4 * plane + o] = __int_as_float(sa.idx);
-    }
+    if (SCORE) score_part_store(part, o, sa);
+    else sample_part_store(part, o, plane, sa);
   }
 }
 
@@ -1171,8 +1162,11 @@ static void lmhead_ring_launch(const void *Xp, const void *Wp, int Mp, int Np, i
 }
 
 // grid M rows, block 256: fold the per-workgroup partials of one row in workgroup order.  sums_only: a scoring pass, whose partials are
-// the first two planes; only target_lp is written.  Otherwise the row's bookkeeping follows, if the pass has
-// any (a launch of its own before: 10.6 + 3.9 us at one row, 10.4 + 4.5 at 64; 12.0 together).
+// the maximum and the sum only; only target_lp is written.  Otherwise the row's bookkeeping follows, if the pass has any (a launch of its
+// own before: 10.6 + 3.9 us at one row, 10.4 + 4.5 at 64; 12.3 together).  The lines that one compute unit can fetch bound it, 1187
+// workgroups' times five while each value had a plane of its own, two with four of them side by side (sample_part_store): 12.3 -> 8.8 us
+// at one row, 10.2 at 64, 17.2 -> 15.1 at 256, 4096 rows of a scoring pass 33 -> 28.5, and the lm_heads as before.  Requesting a thread's
+// five partials at once changed nothing.
 __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp, const float *part, int n_wg, int Mp,
                                       const int32_t *target, const float *target_z, int sums_only, StepBook book) {
   __shared__ SampleAcc sh[4];
@@ -1181,9 +1175,9 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
   SampleAcc a = sample_acc_init();
   for (int g = threadIdx.x; g < n_wg; g += blockDim.x) {
     int64_t o = (int64_t)g * Mp + m;
-    SampleAcc b = sample_acc_init();
-    b.zmax = part[o]; b.zsum = part[plane + o];
-    if (!sums_only) { b.best = part[2 * plane + o]; b.zbest = part[3 * plane + o]; b.idx = __float_as_int(part[4 * plane + o]); }
+    SampleAcc b;
+    if (sums_only) { b = sample_acc_init(); b.zmax = part[2 * o]; b.zsum = part[2 * o + 1]; }
+    else b = sample_part_load(part, o, plane);
     if (g == (int)threadIdx.x) a = b;   // (as it is: a row of NaN has no maximum, and a merge would drop its sum)
     else sample_acc_merge(a, b);
   }

@@ -33,6 +33,21 @@ def test_fused_sampler_takes_the_tokens_of_the_fp32_sampler(rows, vocab):
     ctx.close()
 
 
+@pytest.mark.parametrize("rows", [3, 130])
+@pytest.mark.parametrize("vocab", [32768, 32769, 163840, 163841])
+def test_partials_of_a_row_at_the_edges_of_the_merge(rows, vocab):
+    """A row's 256 partials of 128 entries, one for each thread of the merge, 1280, and one more than either."""
+    shape = synth.ModelShape(1, 64, 1, 1, 64, 64, vocab)
+    ctx = make_ctx(shape, rows, 8, synth.make_weights(shape, 7))
+    prompts, lens = synth.make_prompts(vocab, rows, 5, seed=2)
+    forced = np.random.default_rng(rows).integers(0, vocab, size=(rows, 3)).astype(np.int32)
+    a = ctx.rollout(prompts, lens, 1, 3, 1.0, 9, forced=forced)
+    b = ctx.rollout(prompts, lens, 1, 3, 1.0, 9, forced=forced, unfused_sampler=True)
+    assert np.array_equal(a["tokens"], b["tokens"])
+    assert np.abs(a["logprobs"] - b["logprobs"]).max() < 2e-6 * max(8.0, np.abs(b["logprobs"]).max() + 0.1)   # as above
+    ctx.close()
+
+
 @pytest.mark.parametrize("vocab,dtype", [(1001, "fp32"), (4099, "bf16"), (9002, "fp32"), (9002, "bf16")])
 def test_nucleus_draws_the_tokens_of_the_oracle_over_the_same_logits(orc, vocab, dtype):
     """Vocabularies whose rows are not aligned and end inside a group of four draws; a temperature at which nearly all mass is
