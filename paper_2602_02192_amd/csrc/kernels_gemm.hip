@@ -156,7 +156,7 @@ __device__ __forceinline__ void gemm_lds_mainloop(f32x16 (&acc)[MB], char *lds_r
   // The B operands of GU k-steps are read from LDS in one batch ahead of their MFMAs: with one wavefront per SIMD
   // nothing else hides the LDS latency, and a read issued right before each MFMA would expose it every time.
   auto compute = [&](int st, int buf) {
-    constexpr int GU = MB == 4 ? 4 : KC;
+    constexpr int GU = MB == 4 ? (WN > 4 ? 2 : 4) : KC;
     const u32x4v *bp = xs + buf * XU + (lane >> 5) * ROWS + (lane & 31);
 #pragma unroll
     for (int u0 = 0; u0 < KC; u0 += GU) {
@@ -1040,21 +1040,22 @@ constexpr int LM_DUMP_FLOATS = 16 * 64;   // sample_lane's LDS, per wavefront
 // under the other's weight stream: 64 rows 199 -> 146 us, 32 rows 158 -> 133 us.  That needs the kernel inside 256 registers
 // per lane, which a two-chunk weight pipeline allows (three chunks in flight fit only at 32 rows).  With only the winner
 // of a lane's entries evaluated in full (sample_lane): 64 rows 137 -> 125 us, 32 rows 120.7 -> 117.5 us.  The logits form of 128
-// rows has no long epilogue to hide and is faster alone on the unit with a deeper pipeline.
+// rows has no long epilogue to hide and is alone on the unit.
 template <int MB> constexpr int lm_wgs_per_cu() { return MB <= 2 ? 2 : 1; }
 
-template <int MB, int NSTAGE, bool LOGITS>
-__global__ __launch_bounds__(256, lm_wgs_per_cu<MB>()) void lmhead_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp,
+template <int MB, int NSTAGE, bool LOGITS, int WN = LM_WN>
+__global__ __launch_bounds__(WN * 64, lm_wgs_per_cu<MB>()) void lmhead_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp,
                                                      int Np, int Kp, int V, float temperature, uint64_t seed,
                                                      DrawIds ids, const int32_t *target, float *target_z,
                                                      float *part, int n_wg, float *logits, int64_t ld) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  using L = GemmLds<MB, LM_WN>;
+  using L = GemmLds<MB, WN>;
+  static_assert(LOGITS || WN == LM_WN, "the sampler's fold is over four wavefronts");
   int w = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int nblocks = Np >> 5;
-  const int nb_own = blockIdx.x * LM_WN + w, nb = min(nb_own, nblocks - 1);
+  const int nb_own = blockIdx.x * WN + w, nb = min(nb_own, nblocks - 1);
   f32x16 acc[MB];
-  gemm_lds_mainloop<MB, LM_WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC);
+  gemm_lds_mainloop<MB, WN, NSTAGE>(acc, lds_raw, Xp, Wp, Mp, Np, Kp, nb, 0, (Kp >> 4) / L::KC);
   auto write_partial = [&](const SampleAcc &sa, int m) {
     int64_t o = (int64_t)blockIdx.x * Mp + m, plane = (int64_t)n_wg * Mp;
     if (target) score_part_store(part, o, sa);
@@ -1198,22 +1199,31 @@ __global__ void sample_combine_kernel(int32_t *tok, float *lp, float *target_lp,
 static int lm_wgs(int Np) { return (Np / 32 + LM_WN - 1) / LM_WN; }
 size_t fast_lmhead_partial_floats(int Np, int Mp) { return (size_t)5 * lm_wgs(Np) * Mp + Mp; }
 
-template <int MB, int NSTAGE, bool LOGITS>
+template <int MB, int NSTAGE, bool LOGITS, int WN = LM_WN>
 static void lmhead_launch(const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, float temperature, uint64_t seed,
                           DrawIds ids, const int32_t *target, float *target_z, float *part, float *logits, int64_t ld,
                           hipStream_t st) {
-  using L = GemmLds<MB, LM_WN>;
+  using L = GemmLds<MB, WN>;
   constexpr int SH = LOGITS ? 0 : LM_WN * LM_DUMP_FLOATS * 4 + 3 * MB * 32 * (int)sizeof(SampleAcc);
   constexpr int BYTES = L::X_BYTES > SH ? L::X_BYTES : SH;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute((const void *)lmhead_kernel<MB, NSTAGE, LOGITS>, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
+    (void)hipFuncSetAttribute((const void *)lmhead_kernel<MB, NSTAGE, LOGITS, WN>, hipFuncAttributeMaxDynamicSharedMemorySize, BYTES);
     attr_set = true;
   }
-  int n_wg = lm_wgs(Np);
-  dim3 grid(n_wg), block(256);
-  hipLaunchKernelGGL((lmhead_kernel<MB, NSTAGE, LOGITS>), grid, block, BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp, Np, Kp, V,
+  const int n_wg = (Np / 32 + WN - 1) / WN;
+  dim3 grid(n_wg), block(WN * 64);
+  hipLaunchKernelGGL((lmhead_kernel<MB, NSTAGE, LOGITS, WN>), grid, block, BYTES, st, (const u32x4v *)Xp, (const h16x8 *)Wp, Mp, Np, Kp, V,
                      temperature, seed, ids, target, target_z, part, n_wg, logits, ld);
+}
+
+// 128 rows of logits: every workgroup reads all activations, 4 of its WN + 4 blocks' worth of loads per k-step, and a compute unit holds
+// one workgroup, so a launch takes rounds x (WN + 4).  Seven wavefronts (two per SIMD, inside 256 registers with two chunks of
+// weights and half as many operands in flight; nothing spilled, where the form of four wavefronts spills 35) where that is less: 151936 entries at hidden 4096
+// 3 x 11 against 5 x 8, 277.7 -> 256.7 us; a vocabulary of 32000 fits one round of four.
+static bool logits128_wide(int Np) {
+  auto cost = [&](int wn) { return ((Np / 32 + wn - 1) / wn + 255) / 256 * (wn + 4); };
+  return cost(7) < cost(LM_WN);
 }
 
 template <bool LOGITS>
@@ -1223,7 +1233,10 @@ static void lmhead_dispatch(const void *Xp, const void *Wp, int Mp, int Np, int 
   int mbt = Mp / 32;
 #define LM_ARGS Xp, Wp, Mp, Np, Kp, V, temperature, seed, ids, target, target_z, part, logits, ld, st
   if constexpr (LOGITS) {
-    if (mbt == 4) { lmhead_launch<4, 3, LOGITS>(LM_ARGS); return; }
+    if (mbt == 4) {
+      if (logits128_wide(Np)) lmhead_launch<4, 2, LOGITS, 7>(LM_ARGS); else lmhead_launch<4, 3, LOGITS>(LM_ARGS);
+      return;
+    }
   }
   if (mbt == 2) lmhead_launch<2, 2, LOGITS>(LM_ARGS);
   else lmhead_launch<1, 3, LOGITS>(LM_ARGS);
@@ -1251,7 +1264,7 @@ void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts
 
 void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st) {
   // 256 rows, vocabulary 151936, hidden 2560: 236 us on 256 x 256 ring tiles (128 x 128: 278, the LDS-staged kernel: 296); 128 rows are
-  // level (186 us either way).
+  // level (186 us on 128 x 128 tiles and by workgroups of four blocks; see logits128_wide for those of seven).
   if (Mp % 256 == 0) { gemm_ring_launch<Ring256x256, EPI_PARTIAL>(logits, Xp, Wp, Mp, Np, Kp, 1, st); return; }
   lmhead_dispatch<true>(Xp, Wp, Mp, Np, Kp, V, 1.0f, 0, DrawIds{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, logits, Np, st);
 }

@@ -33,10 +33,11 @@ def test_fused_sampler_takes_the_tokens_of_the_fp32_sampler(rows, vocab):
     ctx.close()
 
 
-@pytest.mark.parametrize("rows", [3, 130])
+@pytest.mark.parametrize("rows", [3, 100, 130])
 @pytest.mark.parametrize("vocab", [32768, 32769, 163840, 163841])
 def test_partials_of_a_row_at_the_edges_of_the_merge(rows, vocab):
-    """A row's 256 partials of 128 entries, one for each thread of the merge, 1280, and one more than either."""
+    """A row's 256 partials of 128 entries, one for each thread of the merge, 1280, and one more than either; the logits of
+    100 rows by workgroups of four blocks (32768) and of seven."""
     shape = synth.ModelShape(1, 64, 1, 1, 64, 64, vocab)
     ctx = make_ctx(shape, rows, 8, synth.make_weights(shape, 7))
     prompts, lens = synth.make_prompts(vocab, rows, 5, seed=2)
