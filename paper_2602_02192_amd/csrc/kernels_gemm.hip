@@ -278,7 +278,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
   // The B operands of GU k-steps are read from LDS in one batch ahead of their MFMAs: with one wavefront per SIMD
   // nothing else hides the LDS latency, and a read issued right before each MFMA would expose it every time.
   auto compute = [&](int st, int buf) {
-    constexpr int GU = MB == 4 ? 4 : KC;
+    constexpr int GU = MB == 4 ? (WN > 4 ? 2 : 4) : KC;
     const u32x4v *bp = xs + buf * XU + (lane >> 5) * ROWS + (lane & 31);
 #pragma unroll
     for (int u0 = 0; u0 < KC; u0 += GU) {
@@ -822,10 +822,13 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     // tie (fewer rounds, fewer re-reads of the activations).  Measured at 64 rows: 608 blocks (4B) width 3, 203
     // workgroups, 21 us (width 4: 23); 768 blocks (8B) width 3, 256 workgroups, 34 us; 1600 blocks (32B) width 7,
     // 229 workgroups, 81 us -- width 3 (534 workgroups, three rounds) took 109 us there, width 4 (two rounds) 90.
+    // At 128 rows the activations that every workgroup reads, as much as four blocks, are counted, and widths of five and six spill
+    // registers (seven and eight do not, with half as many operands read ahead): 1600 blocks width 7, 92 us (width 4: 121); two layers of the 32B width
+    // with 1100 blocks, 24 steps, width 7 14.1 ms (width 3: 15.7), 2040 blocks width 8 17.6 (width 4: 18.9).
     int best = 3, best_cost = 1 << 30;
-    const int wn_max = Mp <= 64 ? 8 : 4;   // 128 rows: more than four wavefronts would not fit their registers
-    for (int wn = 3; wn <= wn_max; ++wn) {
-      int wgs = (nblocks + wn - 1) / wn, cost = (wgs + 255) / 256 * wn;
+    for (int wn = 3; wn <= 8; ++wn) {
+      if (Mp > 64 && (wn == 5 || wn == 6)) continue;
+      int wgs = (nblocks + wn - 1) / wn, cost = (wgs + 255) / 256 * (Mp <= 64 ? wn : wn + 4);
       if (cost <= best_cost) { best = wn; best_cost = cost; }
     }
     g->waves_n = best; g->nsplit = 1;
@@ -870,7 +873,7 @@ static void gemm_lds_launch(void *out, const void *Xp, const void *Wp, int Mp, i
 }
 
 // The instantiated forms: three blocks (the full-K projection at 32 and 128 rows with a three-chunk weight pipeline, all others with
-// two chunks: deeper pipelines measured no faster for the split projections, and for 64 rows see gemm_lds_min_wgs), four blocks with two chunks, and for the full-K projection at up to 64 rows five to eight blocks with two chunks (see
+// two chunks: deeper pipelines measured no faster for the split projections, and for 64 rows see gemm_lds_min_wgs), four blocks with two chunks, and for the full-K projection five to eight blocks with two chunks, at 128 rows seven or eight (see
 // fast_gemm_pick).
 template <int MB, int EPI>
 static void gemm_lds_dispatch_rows(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, hipStream_t st) {
@@ -880,9 +883,11 @@ static void gemm_lds_dispatch_rows(void *out, const void *Xp, const void *Wp, in
     if (g.waves_n == 3) { gemm_lds_launch<MB, 3, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
   }
   if constexpr (EPI == EPI_SWIGLU && MB <= 2) {
+    if (g.waves_n == 5) { gemm_lds_launch<MB, 5, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
+    if (g.waves_n == 6) { gemm_lds_launch<MB, 6, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return; }
+  }
+  if constexpr (EPI == EPI_SWIGLU) {
     switch (g.waves_n) {
-      case 5: gemm_lds_launch<MB, 5, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
-      case 6: gemm_lds_launch<MB, 6, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
       case 7: gemm_lds_launch<MB, 7, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
       case 8: gemm_lds_launch<MB, 8, 2, EPI>(out, Xp, Wp, Mp, Np, Kp, g.nsplit, st); return;
       default: break;
