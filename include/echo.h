@@ -15,6 +15,7 @@
  * Conventions: all functions return 0 on success or a negative echo_status; they
  * never throw, abort or print.  "host" / "device" in a parameter comment says
  * where the pointer must live.  The caller owns every buffer it passes in.
+ * A call that works on the GPU first drops what the HIP runtime holds as the calling thread's last error.
  */
 #ifndef ECHO_H_
 #define ECHO_H_

@@ -89,7 +89,7 @@ int echo_logprobs(echo_ctx *c, const int32_t *tokens, int32_t stride, const int3
     if (c->load.open && c->load.target == c->active) return fail(c, ECHO_ESTATE, "a snapshot is arriving in the only weight slot");
     if (c->rollout_running) return fail(c, ECHO_ESTATE, "a rollout is running on this context");
   }
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   memset(out, 0, (size_t)n_seqs * stride * sizeof(float));
   hipStream_t st = c->cs;
   launch_fill_i32(c->d_step, 0, 1, st);
@@ -128,7 +128,7 @@ int echo_grpo_tensors(echo_ctx *c, const int32_t *tokens, int32_t stride, const 
   if (need(G) > cap) return fail(c, ECHO_ENOMEM, "one group (%d x %d tokens) needs %zu bytes of staging, the context has %zu", G, stride, need(G), cap);
   size_t groups_per_pass = 1;
   while (need((groups_per_pass * 2) * G) <= cap && groups_per_pass * G < (size_t)n_seqs) groups_per_pass *= 2;
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   hipStream_t st = c->cs;
   char *base = at<char>(c, c->p.o_logits);
   for (int n0 = 0; n0 < n_seqs; n0 += (int)(groups_per_pass * G)) {
@@ -161,7 +161,7 @@ int echo_debug_draw_bits(echo_ctx *c, uint64_t seed, uint32_t n, uint32_t s, uin
     std::lock_guard<std::mutex> lk(c->mu);
     if (c->rollout_running) return fail(c, ECHO_ESTATE, "a rollout is running on this context");
   }
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   uint32_t *buf = at<uint32_t>(c, c->p.o_logits);
   launch_draw_bits(buf, seed, n, s, i0, count, c->cs);
   HIPCHK(c, hipMemcpyAsync(out_bits, buf, (size_t)count * 4, hipMemcpyDeviceToHost, c->cs));

@@ -256,6 +256,14 @@ int fail(echo_ctx *c, int code, const char *fmt, ...) {
 
 template <typename T> T *at(echo_ctx *c, size_t off) { return (T *)(c->arena + off); }
 
+// Work of a call on the context's GPU begins here.  The runtime keeps the last error of a thread until somebody reads it: what the
+// caller's own code has left there is dropped, so that the calls' checks of their launches (hipGetLastError) see their own only.
+hipError_t use_device(const echo_ctx *c) {
+  const hipError_t e = hipSetDevice(c->device);
+  (void)hipGetLastError();
+  return e;
+}
+
 // The rollout stops using weight slot `s` (call with c->mu held): decode steps that read the slot
 // may still be queued on the compute stream, so whatever the copy stream does from now on -- the next install writes
 // into this slot -- starts behind them.

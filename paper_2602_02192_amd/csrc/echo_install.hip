@@ -285,7 +285,7 @@ int echo_load_policy_delta(echo_ctx *c, int64_t base_version, int64_t version, i
     if (target == c->active) { c->active = -1; c->st.active_version = -1; }
     return rc;
   };
-  if (hipSetDevice(c->device) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipSetDevice failed"));
+  if (use_device(c) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipSetDevice failed"));
   if (!running && hipStreamSynchronize(c->cs) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipStreamSynchronize failed"));
   if (target != base) {   // the other slot becomes a copy of the base first (behind whatever still reads it, see leave_slot)
     for (size_t o = 0; o < c->p.slot_bytes; o += (size_t)1 << 30) {
@@ -360,7 +360,7 @@ int echo_load_policy_begin(echo_ctx *c, int64_t version, size_t nbytes) {
   c->load.q8 = false;
   lk.unlock();
   auto undo = [&](int rc) { lk.lock(); c->load.open = false; if (target == c->active) { c->active = -1; c->st.active_version = -1; } return rc; };
-  if (hipSetDevice(c->device) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipSetDevice failed"));
+  if (use_device(c) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipSetDevice failed"));
   if (!running && hipStreamSynchronize(c->cs) != hipSuccess) return undo(fail(c, ECHO_EHIP, "hipStreamSynchronize failed"));
   c->load.segs = blob_segments(c, target);
   // (A rollout that has just switched away from the target slot may still have decode steps queued that read it; the
@@ -379,7 +379,7 @@ int echo_load_policy_chunk(echo_ctx *c, const void *data, size_t nbytes) {
     if (nbytes > c->load.total - c->load.received)
       return fail(c, ECHO_EINVAL, "%zu bytes after %zu overrun the blob of %zu", nbytes, c->load.received, c->load.total);
   }
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   int rc = c->load.q8 ? feed_q8(c, (const char *)data, nbytes) : feed_segments(c, c->load.segs, (const char *)data, c->load.received, nbytes);
   if (rc) return rc;
   HIPCHK(c, hipStreamSynchronize(c->ks));  // the piece may be freed when this call returns
@@ -394,7 +394,7 @@ int echo_load_policy_commit(echo_ctx *c) {
     if (!c->load.open) return fail(c, ECHO_ESTATE, "no snapshot is being loaded");
     if (c->load.received != c->load.total) return fail(c, ECHO_ESTATE, "%zu of %zu bytes have arrived", c->load.received, c->load.total);
   }
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   return commit_slot(c, c->load.target, c->load.version);
 }
 

@@ -52,7 +52,7 @@ extern "C" int echo_grpo_tensors_static(echo_ctx *c, const int32_t *tokens, int3
     base = c->device < MAX_DEVICES ? g_scratch_ptr[c->device] : nullptr;
   }
   if (!base) return fail(c, ECHO_ESTATE, "the static scratch of device %d was not resolved at echo_init", c->device);
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   hipStream_t st = c->cs;
   int32_t *d_tok = (int32_t *)base;
   float *d_at = (float *)(base + up16(cells * 4));

@@ -188,7 +188,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   RolloutGuard guard(c);
   if ((rc = guard.begin())) return rc;
 
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   const Plan &p = c->p;
   hipStream_t st = c->cs;
   auto t0 = std::chrono::steady_clock::now();
@@ -444,7 +444,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   if ((rc = guard.begin())) return rc;
   c->max_keys = max_pl + max_new;
 
-  HIPCHK(c, hipSetDevice(c->device));
+  HIPCHK(c, use_device(c));
   if ((rc = ensure_pinned(c))) return rc;
   const Plan &p = c->p;
   hipStream_t st = c->cs;

@@ -1,7 +1,7 @@
-"""What the host does when the HIP runtime refuses a call in the middle of a continuous rollout: a refused launch of one of its
-hand-over kernels is an error of the call (it would otherwise return the bytes of an earlier hand-over); where there is no pinned
-memory the call does without.  Each case is a process of
-its own, whose calls of the runtime go through hip_refusals.c; nothing that is refused reaches the GPU."""
+"""What the host does when the HIP runtime refuses a call in the middle of a rollout: a refused launch is an error of the call (it
+would otherwise return the bytes of an earlier one); where there is no pinned memory a continuous rollout does without; an error
+that somebody else has left behind is no error of the call.  Each case is a process of its own, whose calls of the runtime go through
+hip_refusals.c; nothing that is refused reaches the GPU."""
 import os
 import subprocess
 import sys
@@ -110,4 +110,38 @@ assert not shim.hip_refused()      # (it has its memory by now)
 want = ref_ctx.rollout(prompts, lens, G, new, 1.0, 4, eos_id=int(ref["tokens"][0, 0]), continuous=True)
 assert all(np.array_equal(free[k], want[k]) for k in ("tokens", "logprobs", "lens", "versions"))
 print("as expected")
+""")
+
+
+def test_an_error_of_the_callers_own_is_not_the_calls(child):
+    """The runtime keeps the last error of a thread until it is read.  One that the caller's own HIP code has left there is none
+    of the library's."""
+    child("""
+hip = ctypes.CDLL(next(l.split()[-1] for l in open("/proc/self/maps") if "libamdhip64" in l))
+plain = make_ctx(shape, P * G, 9 + new, blob)
+refilled = make_ctx(shape, 4, 9 + new, blob)
+tokens = np.random.default_rng(5).integers(0, shape.vocab, (4, 15)).astype(np.int32)
+tlens, rewards = np.array([15, 1, 7, 12], np.int32), np.array([1, 0, 0, 1], np.float32)
+version = iter(range(1, 100))
+calls = dict(
+    rollout=lambda: plain.rollout(prompts, lens, G, new, 1.0, 4, stop_lens=stop, forced=forced)["tokens"],
+    one_token=lambda: plain.rollout(prompts, lens, G, 1, 1.0, 4)["tokens"],
+    continuous=lambda: run(refilled)["tokens"],
+    scores=lambda: plain.logprobs(tokens, tlens),
+    grpo=lambda: plain.grpo_tensors(tokens, tlens, 2, 3, rewards)[2],
+    grpo_static=lambda: plain.grpo_tensors(tokens, tlens, 2, 3, rewards, static_scratch=True)[2],
+    draws=lambda: plain.draw_bits(1, 2, 3, 0, 9),
+    install=lambda: plain.load_policy(next(version), blob),
+)
+failed = []
+for name, call in calls.items():
+    want = call()
+    assert hip.hipSetDevice(4096) != 0 and hip.hipPeekAtLastError() != 0
+    try:
+        got = call()
+        assert np.array_equal(got, want) or want is None, name
+    except echo.EchoError as e:
+        failed.append((name, str(e)))
+    hip.hipGetLastError()
+print(failed or "as expected")
 """)
