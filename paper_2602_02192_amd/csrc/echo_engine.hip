@@ -100,6 +100,7 @@ int echo_logprobs(echo_ctx *c, const int32_t *tokens, int32_t stride, const int3
     for (int i = 0; i < M; ++i) tgt[i] = tokens[(int64_t)rows[i].slot * stride + rows[i].pos + 1];
     HIPCHK(c, hipMemcpyAsync(c->d_target, tgt.data(), M * 4, hipMemcpyHostToDevice, st));
     sample_rows(c, S, M, temperature, 0, false, c->d_target);
+    HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(lp.data(), c->d_target_lp, M * 4, hipMemcpyDeviceToHost, st));
     HIPCHK(c, hipStreamSynchronize(st));
     for (int i = 0; i < M; ++i) out[(int64_t)rows[i].slot * stride + rows[i].pos + 1] = lp[i];
@@ -164,6 +165,7 @@ int echo_debug_draw_bits(echo_ctx *c, uint64_t seed, uint32_t n, uint32_t s, uin
   HIPCHK(c, use_device(c));
   uint32_t *buf = at<uint32_t>(c, c->p.o_logits);
   launch_draw_bits(buf, seed, n, s, i0, count, c->cs);
+  HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipMemcpyAsync(out_bits, buf, (size_t)count * 4, hipMemcpyDeviceToHost, c->cs));
   HIPCHK(c, hipStreamSynchronize(c->cs));
   return ECHO_OK;

@@ -524,6 +524,7 @@ int run_chunk_seqs(echo_ctx *c, const Slot &S, const std::vector<ChunkSeq> &seqs
     }
     HIPCHK(c, hipStreamSynchronize(c->cs));  // the host vectors are reused by the next chunk
     forward_layers(c, S, M, splitk, false, (int)blocks.size());
+    HIPCHK(c, hipGetLastError());   // (a launch that was refused, of the pass or of what the caller prepared it with)
     int rc = after(&all[a], M);
     if (rc) return rc;
   }

@@ -15,6 +15,7 @@ int stage_rows(echo_ctx *c, const BlobSeg &g, const char *src, int64_t r0, int64
     c->stage_flip ^= 1;
     HIPCHK(c, hipMemcpyAsync(stg, src + r * row_bytes, (size_t)(n * row_bytes), hipMemcpyHostToDevice, c->ks));
     fast_pack_weight(g.dst, stg, g.dst_row0 + (r0 + r) * g.stride, g.stride, n, g.K, Kp, Np, c->ks);
+    HIPCHK(c, hipGetLastError());   // (a launch that was refused)
   }
   return 0;
 }
@@ -112,6 +113,7 @@ int patch_segments(echo_ctx *c, std::vector<BlobSeg> &segs, const char *data, si
       c->stage_flip ^= 1;
       HIPCHK(c, hipMemcpyAsync(stg, data + (o - lo), len, hipMemcpyHostToDevice, c->ks));
       fast_pack_span(g.dst, stg, (int64_t)((o - g.off) / elt), (int64_t)(len / elt), g.dst_row0, g.stride, g.K, Kp, Np, c->ks);
+      HIPCHK(c, hipGetLastError());
     }
   }
   return 0;
@@ -133,6 +135,7 @@ int feed_device(echo_ctx *c, std::vector<BlobSeg> &segs, const char *dev, size_t
     if ((a - g.off) % row_bytes || (b - a) % row_bytes) return fail(c, ECHO_EINVAL, "internal: a device piece cuts a matrix row");
     const int Np = (int)round_up(g.rows * g.stride, 32), Kp = (int)round_up(g.K, GEMM_K_PAD);
     fast_pack_weight(g.dst, src, g.dst_row0 + (int64_t)((a - g.off) / row_bytes) * g.stride, g.stride, (int64_t)((b - a) / row_bytes), g.K, Kp, Np, c->ks);
+    HIPCHK(c, hipGetLastError());   // (also of what made the bytes at `dev`)
   }
   return 0;
 }

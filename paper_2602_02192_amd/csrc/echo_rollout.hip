@@ -289,6 +289,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
   bool cut = !share_prefix;
   for (int q = 0; q < P; ++q) cut = cut || prompt_lens[q] % 32 != 0;
   if (cut) launch_kv_replicate(c->kv, c->d_plen_p, P, G, share_prefix ? 1 : 0, st);
+  HIPCHK(c, hipGetLastError());   // (of the gathers, of the first token, of the replication)
   HIPCHK(c, hipStreamSynchronize(st));
   auto t1 = std::chrono::steady_clock::now();
 

@@ -145,3 +145,82 @@ for name, call in calls.items():
     hip.hipGetLastError()
 print(failed or "as expected")
 """)
+
+
+@pytest.mark.parametrize("call,kernel", [("one_token", "dbg_embed_kernel"), ("one_token", "dbg_gemm_kernel"), ("one_token", "gather_rows_kernel"),
+                                         ("one_token", "dbg_sample_kernel"), ("one_token", "kv_replicate_kernel"),
+                                         ("scores", "dbg_gemm_kernel"), ("scores", "dbg_target_logprob_kernel"), ("draws", "draw_bits_kernel")])
+def test_a_refused_launch_outside_the_steps_is_an_error(child, call, kernel):
+    """The first launch, one in the middle and the last one of a rollout that ends with its first token, of a scoring pass, of a read-out
+    of the generator."""
+    child(f"""
+ctx = make_ctx(shape, P * G, 9 + new, blob)
+tokens = np.random.default_rng(5).integers(0, shape.vocab, (4, 15)).astype(np.int32)
+go = dict(one_token=lambda: ctx.rollout(prompts, lens, G, 1, 1.0, 4)["tokens"],
+          scores=lambda: ctx.logprobs(tokens, np.array([15, 2, 7, 12], np.int32)),
+          draws=lambda: ctx.draw_bits(1, 2, 3, 0, 9))["{call}"]
+shim.hip_refuse(b"{kernel}", 1 << 30)
+want = go()
+n = shim.hip_seen()
+assert n > 0
+for after in sorted({{0, n // 2, n - 1}}):
+    shim.hip_refuse(b"{kernel}", after)
+    try:
+        go()
+    except echo.EchoError as e:
+        assert e.code == echo.ECHO_EHIP and shim.hip_refused(), e
+    else:
+        raise SystemExit(f"succeeded with launch {{after}} of {{n}} refused")
+    assert np.array_equal(go(), want)
+print("as expected")
+""")
+
+
+@pytest.mark.parametrize("form,kernel", [("whole", "pack_weight_kernel"), ("q8", "pack_weight_kernel"), ("q8", "dequant_q8_kernel"),
+                                         ("delta", "pack_span_kernel")])
+def test_a_refused_launch_of_an_install_leaves_no_snapshot(child, form, kernel):
+    """The first and the last launch; a load from the start afterwards is as good as ever."""
+    child(f"""
+shape = synth.ModelShape(1, 64, 2, 1, 64, 96, 200)
+blob, q8 = synth.make_weights(shape, 1), synth.make_q8_weights(shape, 1)
+tokens, tlens = np.random.default_rng(5).integers(0, shape.vocab, (2, 15)).astype(np.int32), np.array([15, 7], np.int32)
+off = synth.blob_offsets(shape)["layers.0.w_gate"][0] * 2
+data = np.random.default_rng(6).integers(0, 60, 200, dtype=np.uint8)
+version = 0
+
+def install(ctx):
+    global version
+    if "{form}" == "delta":
+        ctx.load_policy(version + 1, blob)
+        ctx.load_policy_delta(version + 1, version + 2, [off, off + 1000], [80, 120], data)
+    elif "{form}" == "q8":
+        ctx.load_policy_q8(version + 1, q8)
+    else:
+        ctx.load_policy(version + 1, blob)
+
+ctx = make_ctx(shape, 2, 16)
+shim.hip_refuse(b"{kernel}", 1 << 30)
+install(ctx)
+n = shim.hip_seen()
+want = ctx.logprobs(tokens, tlens)
+assert n > 0
+for after in sorted({{0, n - 1}}):
+    version += 10
+    shim.hip_refuse(b"{kernel}", after)
+    try:
+        install(ctx)
+    except echo.EchoError as e:
+        assert e.code == echo.ECHO_EHIP and shim.hip_refused(), e
+    else:
+        raise SystemExit(f"succeeded with launch {{after}} of {{n}} refused")
+    try:
+        ctx.logprobs(tokens, tlens)
+    except echo.EchoError as e:
+        assert e.code == echo.ECHO_ESTATE, e
+    else:
+        raise SystemExit("a snapshot is there")
+    version += 10
+    install(ctx)
+    assert np.array_equal(ctx.logprobs(tokens, tlens), want)
+print("as expected")
+""")
