@@ -204,7 +204,7 @@ int echo_rollout(echo_ctx *c, const int32_t *prompt_tokens, int32_t prompt_strid
     plen_seq[n] = prompt_lens[n / G];
     limit[n] = o.stop_lens ? std::max(1, std::min(max_new, o.stop_lens[n])) : max_new;
     steps = std::max(steps, limit[n]);
-    c->max_keys = std::max(c->max_keys, plen_seq[n] + limit[n]);
+    c->max_keys = std::max(c->max_keys, plen_seq[n] + limit[n] - 1);   // (the last token drawn is no key)
   }
   HIPCHK(c, hipMemcpyAsync(c->d_prompt_len_seq, plen_seq.data(), N * 4, hipMemcpyHostToDevice, st));
   HIPCHK(c, hipMemcpyAsync(c->d_limit, limit.data(), N * 4, hipMemcpyHostToDevice, st));
@@ -443,7 +443,7 @@ int echo_rollout_continuous(echo_ctx *c, const int32_t *prompt_tokens, int32_t p
   for (int p = 0; p < P; ++p) max_pl = std::max(max_pl, prompt_lens[p]);
   RolloutGuard guard(c);
   if ((rc = guard.begin())) return rc;
-  c->max_keys = max_pl + max_new;
+  c->max_keys = max_pl + max_new - 1;
 
   HIPCHK(c, use_device(c));
   if ((rc = ensure_pinned(c))) return rc;

@@ -7,17 +7,18 @@ import pytest
 from paper_2602_02192_amd import synth
 
 from gpu_util import BF16_LOGIT_TOL, make_ctx, oracle_rollout
+from test_gpu_refused_calls import child  # noqa: F401  (a fixture)
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kv,hd,prompts,G,plen,new", [
     (2, 64, 1, 1, 1, 40),         # from one key on
-    (2, 128, 1, 1, 1017, 7),      # 1024 keys: alone
-    (2, 128, 1, 1, 1018, 7),      # 1025: split
-    (8, 64, 4, 2, 1020, 5),       # 10 splits by the batch, 1025 keys
-    (8, 64, 4, 4, 2040, 8),       # 5 splits by the batch, 2048 keys: alone
-    (8, 64, 4, 4, 2043, 8),       # 2051: split
+    (2, 128, 1, 1, 1018, 7),      # 1024 keys: alone
+    (2, 128, 1, 1, 1019, 7),      # 1025: split
+    (8, 64, 4, 2, 1021, 5),       # 10 splits by the batch, 1025 keys
+    (8, 64, 4, 4, 2041, 8),       # 5 splits by the batch, 2048 keys: alone
+    (8, 64, 4, 4, 2042, 8),       # 2049: split
     (8, 128, 4, 8, 70, 5),        # 32 rows, two splits by the batch: alone whatever the keys
     (8, 64, 20, 2, 33, 5),        # 40 rows
     (8, 64, 41, 1, 33, 5),        # 41 rows fill the chip
@@ -36,3 +37,24 @@ def test_keys_and_batches_around_the_lines(kv, hd, prompts, G, plen, new):
         ref = oracle_rollout(shape, synth.widen_to_f32(blob), toks[p:p + 1], lens[p:p + 1], G=G, max_new=new, temperature=1.0, seed=6, forced=forced[rows],
                              want_logits=True)
         assert np.abs(out["logits"][rows] - ref["logits"]).max() < BF16_LOGIT_TOL, p
+
+
+def test_how_many_workgroups_take_a_row(child):
+    """Rows of as many keys as the longest one comes to (the last drawn token is no key): 1024 and 1025 with ten splits and more by the
+    batch, 2048 and 2049 with five."""
+    child("""
+def splits(kv, rows, keys, continuous):
+    s = synth.ModelShape(1, 64, kv, kv, 64, 64, 300)
+    ctx = make_ctx(s, rows, keys + 8, synth.make_weights(s, 3))
+    p, l = synth.make_prompts(s.vocab, 1, keys - 1, seed=2)
+    shim.hip_refuse(b"attn_splitk_kernel", 1 << 30)
+    ctx.rollout(p, l, rows, 2, 1.0, 6, continuous=continuous)
+    assert shim.hip_seen() > 0
+    ctx.close()
+    return shim.hip_seen_grid()
+
+want = {(2, 1): [(2, 1), (1024, 1), (1025, 32)], (8, 8): [(1024, 1), (1025, 10)], (8, 16): [(1025, 1), (2048, 1), (2049, 5)], (8, 32): [(3000, 1)]}
+wrong = [(kv, rows, keys, n, got, continuous) for (kv, rows), lines in want.items() for keys, n in lines for continuous in (False, True)
+         for got in [splits(kv, rows, keys, continuous)] if got != n]
+print(wrong or "as expected")
+""")
