@@ -161,9 +161,9 @@ constexpr int GEMM_K_PAD = 128;   // packed weights and K8 activations pad K to 
 void fast_gemm(void *out, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, GemmEpilogue epi,
                hipStream_t st);
 int fast_gemm_even_split(int Kp, int nsplit);
-// The QKV projection with fast_qkv_post's work in its epilogue, for launch shapes that fit (the ring forms without a split over K):
+// The QKV projection with fast_qkv_post's work in its epilogue, for launch shapes that fit (the ring forms without a split over K, from 48 tiles on):
 // q_h16, and keys and values of the rows that are active, are written; there are no partials.
-bool fast_gemm_qkv_fits(GemmShape g);
+bool fast_gemm_qkv_fits(GemmShape g, int Mp, int Np);
 void fast_gemm_qkv(void *q_h16, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, const void *q_gain, const void *k_gain, int qk_norm,
                    float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv, hipStream_t st);
 void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g);

@@ -592,16 +592,17 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
                      (const h16x8 *)Wp, Mp, Np, Kp, gps, strips);
 }
 
-// ---- QKV projection of long passes: per-head norm, rotary embedding and KV append in the epilogue ---------------------------------
-// The ring tile for a projection that is not split over K (passes of about a thousand rows and more).  A wavefront holds the two
+// ---- QKV projection of large passes: per-head norm, rotary embedding and KV append in the epilogue --------------------------------
+// The ring tile for a projection that is not split over K and has tiles enough (fast_gemm_qkv_fits).  A wavefront holds the two
 // weight blocks whose dims are each other's rotation partners -- of a head of 128 blocks 0 and 2 or 1 and 3 (APART = 2), of a head of
 // 64 both.  32 rows at a time it transposes its two 32 x 32 tiles through LDS, rotates four neighbouring dims and their partners per
 // lane and stores q or the key tile; the per-head norm of a head of 128 adds the neighbouring wavefront's squares from its tiles.  A
 // value unit holds eight keys of one dim, so there a lane takes a dim and gathers the eight rows of a unit (rows of a pass are runs of
-// consecutive positions; the ends of a run, and rows in any other order, are stored one by one).
+// consecutive positions; the ends of a run, and rows in any other order -- a decode step's, each of another sequence -- are stored one by one).
 // What it saves is the fp32 plane of the projection, written and read once: same products, same order, so q and the cache are
 // bit-identical to qkv_post_wide_kernel's.  4096 rows, both kernels before against this one: 4B width 132 + 43 -> 138 us, 8B 208 + 46 ->
 // 215, 32B 383 + 64 -> 404; whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
+// Rollouts of 1000 rows, two layers, 31 steps: 4B width 27.7 -> 27.3 ms, 8B 39.4 -> 38.9.
 struct QkvOut {
   uint16_t *q;              // half [M][Hq][hd]
   const float2 *rope;       // [M][hd / 2] (cos, sin)
@@ -755,7 +756,15 @@ static void gemm_ring_qkv_launch(const QkvOut &out, const void *Xp, const void *
                      Kp, strips);
 }
 
-bool fast_gemm_qkv_fits(GemmShape g) { return g.form != GEMM_STREAM && g.nsplit == 1; }
+// A tile's epilogue is as long as its 256 rows, however few tiles there are, where the kernel of its own deals the rows to the whole
+// chip: below 48 tiles (narrow models, whose K is too short to be split) that one is the better.  This epilogue against it: rollouts of 48 steps,
+// 10 tiles (200 rows, hidden 896) 33.7 / 31.2 ms, 24 tiles (256 rows, hidden 512) 15.8 / 15.0, 32 tiles (130 rows, hidden 1008) 33.2 / 33.1, 48
+// tiles (512 rows, hidden 512) 18.7 / 18.7, 96 tiles (1000 rows) 24.0 / 24.8; scoring passes, 10 tiles 781 / 766 us, 24 tiles 660 / 656, 48 tiles
+// 744 / 756, 96 tiles 783 / 826.
+bool fast_gemm_qkv_fits(GemmShape g, int Mp, int Np) {
+  if (g.form == GEMM_STREAM || g.nsplit != 1) return false;
+  return g.form == GEMM_RING_256X256 || (Np / 32 + 3) / 4 * (Mp / 256) >= 48;   // (256 x 256 tiles: 128 or more, see fast_gemm_pick)
+}
 
 void fast_gemm_qkv(void *q_h16, const void *Xp, const void *Wp, int Mp, int Np, int Kp, GemmShape g, const void *q_gain, const void *k_gain, int qk_norm,
                    float eps, const float *rope_cs, RowState rows, KvGeom kv, int layer, int M, int Hq, int Hkv, hipStream_t st) {
