@@ -27,6 +27,11 @@ def oracle_rollout(shape, blob_f32, prompts, lens, **kw):
     return orc.rollout(oracle.desc_from_shape(shape), blob_f32, prompts, lens, **kw)
 
 
+def row_error(got, ref):
+    """The largest relative error of a row of logits: 2-norm of the difference over the 2-norm of the row."""
+    return float((np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)).max())
+
+
 def valid_mask(lens, max_new):
     return np.arange(max_new)[None, :] < np.asarray(lens)[:, None]
 

@@ -16,9 +16,8 @@ MID = synth.ModelShape(2, 512, 8, 2, 128, 1024, 2048, dtype="bf16")
 
 
 # the last two cases leave more than 32 rows in flight when the prompts run out, so the draining batch is compacted
-@pytest.mark.parametrize("P,G,max_seqs,no_graph", [(7, 2, 4, False), (5, 3, 8, True), (3, 4, 4, False), (2, 2, 16, False),
-                                                   (30, 2, 40, False), (12, 5, 70, True), (6, 1, 4, False)])
-def test_fp32_free_running_matches_the_oracle_sequence_by_sequence(P, G, max_seqs, no_graph):
+@pytest.mark.parametrize("P,G,max_seqs", [(7, 2, 4), (5, 3, 8), (3, 4, 4), (2, 2, 16), (6, 1, 4), (30, 2, 40), (12, 5, 70)])
+def test_fp32_free_running_matches_the_oracle_sequence_by_sequence(P, G, max_seqs):
     shape = synth.TINY
     blob = synth.make_weights(shape, 0)
     blob32 = synth.widen_to_f32(blob)
@@ -31,7 +30,7 @@ def test_fp32_free_running_matches_the_oracle_sequence_by_sequence(P, G, max_seq
     stop = synth.make_stop_lens(P * G, 1, max_new, seed=3)
     ref = oracle_rollout(shape, blob32, prompts, lens, G=G, max_new=max_new, temperature=1.0, seed=2, stop_lens=stop)
     ctx = make_ctx(shape, max_seqs, 64, blob)
-    out = ctx.rollout(prompts, lens, G, max_new, 1.0, 2, stop_lens=stop, continuous=True, no_graph=no_graph)
+    out = ctx.rollout(prompts, lens, G, max_new, 1.0, 2, stop_lens=stop, continuous=True)
     assert np.array_equal(out["lens"], ref["lens"]) and np.array_equal(out["lens"], stop)
     m = valid_mask(ref["lens"], max_new)
     if check_tokens_fp32_sampler(out["tokens"], ref) == 0:

@@ -75,7 +75,7 @@ def test_decode_prefill_and_scoring_at_workload_width_and_depth(name, rows):
         worst = max(worst, err)
         assert err < BF16_LOGIT_TOL, (name, rows, n, err)
         check_argmax(tf["logits"][n:n + 1], refs[p]["logits"], np.ones((1, NEW), bool), BF16_LOGIT_TOL, f"{name}-{rows}-seq{n}")
-    # the fused sampler in graph replay: sequence 0 has the oracle's stream id, so tokens and log-probs compare
+    # the fused sampler: sequence 0 has the oracle's stream id, so tokens and log-probs compare
     out = ctx.rollout(prompts, lens, G, NEW, 1.0, 2, forced=forced)
     assert np.array_equal(out["tokens"], tf["tokens"])
     same = out["tokens"][0] == refs[0]["tokens"][0]
@@ -240,7 +240,7 @@ def test_snapshots_installed_back_to_back_while_the_rollout_switches(dtype, mode
     """Three snapshots: B is staged while the rollout decodes under A; the moment the rollout has switched to B the next
     install starts into the slot A has just left, while decode steps of A may still be queued on the GPU.  Every step's
     result must be that of the snapshot its version tag names (oracle with the same switch steps).  "pinned": switches at
-    fixed steps, graph replay, the host queues steps ahead of the GPU; "pinned-logits": the same step by step with the
+    fixed steps, the host queues steps ahead of the GPU; "pinned-logits": the same step by step with the
     logits returned; "continuous": the rollout switches whenever a snapshot has been staged."""
     continuous = mode == "continuous"
     shape = synth.TINY.replace(dtype=dtype)
