@@ -9,14 +9,14 @@ namespace echo {
 constexpr int ATT_TILE = 32;     // keys per tile
 constexpr int ATT_ROWS_MAX = 8;            // rows per workgroup at most
 constexpr int ATT_ROWS_WAVES = 8;
-constexpr int ATT_ROWS_BATCH_MAX = 1024;   // rows of a batch that the plan kernel (one workgroup) deals
+constexpr int ATT_ROWS_BATCH_MAX = 1024;   // rows of a batch that attn_rows_plan (one workgroup) deals
 constexpr int ATT_SEG_MAX = 24;            // runs of rows with a common prompt (<= R/2) + two segments per row
 constexpr int ATT_SEG_INTS = 8;            // cache slot, first tile, first and end position in the workgroup's tile list, first and end column, valid keys
 constexpr int ATT_HDR_INTS = 16;           // number of rows, tiles in all, the rows
 constexpr int ATT_PLAN_INTS = ATT_HDR_INTS + ATT_SEG_MAX * ATT_SEG_INTS;
 
-// One workgroup of ATT_ROWS_BATCH_MAX threads, thread m for row m; NG row sets, each of at most R rows (NG * R >= M).
-__device__ __forceinline__ void attn_rows_plan(int32_t *__restrict__ plan, const RowState &rows, int M, int grp, int NG, int R) {
+// One workgroup of ATT_ROWS_BATCH_MAX threads, thread m for row m; NG row sets, each of at most ceil(M / NG) rows.
+__device__ __forceinline__ void attn_rows_plan(int32_t *__restrict__ plan, const RowState &rows, int M, int grp, int NG) {
   __shared__ int32_t f[ATT_ROWS_BATCH_MAX][4];   // prompt slot, whole prompt tiles, keys, slot
   __shared__ int32_t order[ATT_ROWS_BATCH_MAX];  // the rows that are generating, in row order
   __shared__ int32_t wtot[ATT_ROWS_BATCH_MAX / 64 + 1];
@@ -30,7 +30,7 @@ __device__ __forceinline__ void attn_rows_plan(int32_t *__restrict__ plan, const
   for (int i = 0; i < ATT_ROWS_BATCH_MAX / 64; ++i) { if (i < w) rank += wtot[i]; n_act += wtot[i]; }
   if (val) order[rank] = t;
   __syncthreads();
-  // set t takes the generating rows of rank ceil(t n / NG) .. ceil((t + 1) n / NG) - 1: at most ceil(n / NG) <= R of them
+  // set t takes the generating rows of rank ceil(t n / NG) .. ceil((t + 1) n / NG) - 1: at most ceil(n / NG) of them
   const int first = (int)(((int64_t)t * n_act + NG - 1) / NG), end = (int)(((int64_t)(t + 1) * n_act + NG - 1) / NG), nr = t < NG ? end - first : 0;
   // The sets go into the list longest first (by tiles, shared ones counted per row): workgroups start in list order, so
   // when a launch has more workgroups than the chip holds at once the short ones fill in behind the long ones.

@@ -90,7 +90,6 @@ int main(int argc, char **argv) {
   echo_rollout_opts o;
   memset(&o, 0, sizeof o);
   o.eos_id = -1; o.top_p = 1.0f;
-  o.no_graph = getenv("ECHO_CLIENT_NO_GRAPH") ? 1 : 0;
   auto t0 = std::chrono::steady_clock::now();
   rc = echo_rollout(ctx, prompts.data(), plen, lens.data(), P, G, max_new, 1.0f, 2, &o, toks.data(), lps.data(), out_lens.data(), nullptr);
   double s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -390,7 +390,7 @@ void forward_layers(echo_ctx *c, const Slot &S, int M, bool use_splitk_attn, boo
   // decode attention over several rows per workgroup: the tile lists are the same for every layer
   const int att_rows = n_prefill_blocks == 0 && use_splitk_attn && c->px.n_jobs == 0 ? fast_attention_rows_per_group(M, Hq, Hkv, c->attn_mode) : 1;
   if (n_prefill_blocks == 0 && use_splitk_attn) { c->st.attn_rows_per_workgroup = att_rows; c->st.attn_prefix_jobs = c->px.n_jobs; }
-  const RowsPlan plan = att_rows > 1 ? fast_attention_rows_plan(at<int32_t>(c, p.o_aplan), M, Hq, Hkv, c->attn_mode) : RowsPlan{nullptr, 0, 0};
+  const RowsPlan plan = att_rows > 1 ? fast_attention_rows_plan(at<int32_t>(c, p.o_aplan), M, Hq, Hkv, c->attn_mode) : RowsPlan{nullptr, 0};
   fast_step_begin(h, S.embed, c->rows, xa, S.layers[0].attn_norm, M, Mp, H, d.rms_eps, table, plan, Hq / Hkv, st);
   const GemmShape g_qkv = gemm_shape(c, Mp, p.Np_qkv, p.Kp_d, EPI_PARTIAL);
   const bool qkv_whole = fast_gemm_qkv_fits(g_qkv, Mp, p.Np_qkv);   // (large passes) norm, rotation and KV append in the projection's epilogue

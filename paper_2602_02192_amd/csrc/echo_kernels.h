@@ -71,7 +71,7 @@ struct StepBook {
 // The rotary table of a pass (cs [M][hd/2][2] from pos), written by the kernel that begins it.
 struct RopeTable { float *cs; const int32_t *pos; float base; int32_t hd; };
 // The tile lists of the several-rows decode attention (fast_attention_rows_plan), written by the kernel that begins a decode step; plan null: none.
-struct RowsPlan { int32_t *plan; int32_t sets, rows_per_set; };
+struct RowsPlan { int32_t *plan; int32_t sets; };
 // cut_only (tiled cache): only the tile that a prompt fills in part; for batches whose rows read the whole prompt tiles from slot p*G.
 void launch_kv_replicate(KvGeom kv, const int32_t *prompt_len /*[P]*/, int P, int G, int cut_only, hipStream_t st);
 // Row state and records of a continuous rollout between the device and pinned host memory (host pointers below are pinned and

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void attn_splitk_kernel(f
   // the compiler's wait counts assume it was not issued, and the waits that follow would drain the queue
   for (; tile + NW < ntiles; tile += NW) step(std::true_type{});
   if (tile < ntiles) step(std::false_type{});
-  // ---- the two lanes of a column add their sums; then the four wavefronts are folded in wavefront order
+  // ---- the two lanes of a column add their sums; then the wavefronts are folded in wavefront order
   l_run += __shfl_xor(l_run, 32, 64);
   {
     float *mo = (float *)(lds + w * L::MERGE_PER_WAVE);      // [8][HD] then m[8], l[8]
@@ -668,8 +668,7 @@ int fast_attention_rows_per_group(int M, int Hq, int Hkv, int mode) {
 size_t fast_attention_plan_ints(int max_rows) { return (size_t)(max_rows < ATT_ROWS_BATCH_MAX ? max_rows : ATT_ROWS_BATCH_MAX) * ATT_PLAN_INTS; }
 
 RowsPlan fast_attention_rows_plan(int32_t *plan, int M, int Hq, int Hkv, int mode) {
-  const int NG = attention_row_sets(M, Hq, Hkv, mode);
-  return RowsPlan{plan, NG, (M + NG - 1) / NG};
+  return RowsPlan{plan, attention_row_sets(M, Hq, Hkv, mode)};
 }
 
 template <int HD>

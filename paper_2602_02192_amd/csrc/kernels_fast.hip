@@ -108,7 +108,7 @@ __global__ __launch_bounds__(RN_THREADS) void step_begin_kernel(float *__restric
                                                                 RowsPlan plan, int grp) {
   const int extra = (int)blockIdx.x - M, planners = plan.plan ? 1 : 0;
   if (extra < 0) resid_norm_row<0, CH, true>(xcd_row(M), lanes, h, embed, rows.token, nullptr, 0, Xp, gain, Mp, d, eps);
-  else if (extra < planners) attn_rows_plan(plan.plan, rows, M, grp, plan.sets, plan.rows_per_set);
+  else if (extra < planners) attn_rows_plan(plan.plan, rows, M, grp, plan.sets);
   else rope_entry((float2 *)rope.cs, rope.pos, (extra - planners) * blockDim.x + threadIdx.x, M, rope.hd / 2, rope.base);
 }
 

@@ -833,7 +833,8 @@ void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
     // 229 workgroups, 81 us -- width 3 (534 workgroups, three rounds) took 109 us there, width 4 (two rounds) 90.
     // At 128 rows the activations that every workgroup reads, as much as four blocks, are counted, and widths of five and six spill
     // registers (seven and eight do not, with half as many operands read ahead): 1600 blocks width 7, 92 us (width 4: 121); two layers of the 32B width
-    // with 1100 blocks, 24 steps, width 7 14.1 ms (width 3: 15.7), 2040 blocks width 8 17.6 (width 4: 18.9).
+    // with 1100 blocks, 24 steps, width 7 14.1 ms (width 3: 15.7), 2040 blocks width 8 17.6 (width 4: 18.9); two layers of hidden 2560, 40 steps, 1030
+    // to 1793 blocks 5 to 8 % faster than the best of widths three and four, up to 900 blocks the same form.
     int best = 3, best_cost = 1 << 30;
     for (int wn = 3; wn <= 8; ++wn) {
       if (Mp > 64 && (wn == 5 || wn == 6)) continue;
@@ -1232,9 +1233,11 @@ static void lmhead_launch(const void *Xp, const void *Wp, int Mp, int Np, int Kp
 }
 
 // 128 rows of logits: every workgroup reads all activations, 4 of its WN + 4 blocks' worth of loads per k-step, and a compute unit holds
-// one workgroup, so a launch takes rounds x (WN + 4).  Seven wavefronts (two per SIMD, inside 256 registers with two chunks of
-// weights and half as many operands in flight; nothing spilled, where the form of four wavefronts spills 35) where that is less: 151936 entries at hidden 4096
-// 3 x 11 against 5 x 8, 277.7 -> 256.7 us; a vocabulary of 32000 fits one round of four.
+// one workgroup.  Seven wavefronts (two per SIMD, inside 256 registers with two chunks of weights and half as many operands in flight; nothing
+// spilled, where the form of four wavefronts spills 35) where rounds x (WN + 4) is less.  That count only orders the two forms: 151936 entries at hidden
+// 4096, 3 x 11 against 5 x 8, take 256.7 us for 277.7 (4.8 TB/s of weights; a unit drains and fills again between its rounds).  Decode steps with
+// nucleus sampling at hidden 2560 and 4096, wherever it takes seven: 1025 to 1280 blocks 8 % faster, 2049 blocks 1 to 2 %, 3073 blocks 8 to 10 %;
+// at 1793 and 4096 blocks it stays with four.
 static bool logits128_wide(int Np) {
   auto cost = [&](int wn) { return ((Np / 32 + wn - 1) / wn + 255) / 256 * (wn + 4); };
   return cost(7) < cost(LM_WN);
