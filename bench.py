@@ -21,12 +21,12 @@ HBM_PEAK_GBS = 8000.0
 # counters on a plain 256 MiB copy: KiB fetched + written per launch over the KiB of the K/V tiles the launch touches
 # (shared prompt tiles once per group, a sequence's last tile whole).  Taken at the same kernel and grid on a 2-layer
 # model generating 64 tokens (the profiler crashes on the 36-layer process); set to None whenever attn_rows_kernel changes.
-ATTN_TRAFFIC_OVER_TILE_BYTES = (29520.6 + 512.0) / (28608.0 + 512.0)
+ATTN_TRAFFIC_OVER_TILE_BYTES = (29533.4 + 512.0) / (28608.0 + 512.0)
 # The same kernel timed by rocprofv3 --kernel-trace in this very command (config 2), in microseconds
 # per launch (profiles/kernel_trace_dense4b-64x512+1024.md): the HIP events of the timed run bracket single launches
 # and include the launch gap, so both figures go into the line.  None for any other workload, and whenever the
 # kernel changes.
-ATTN_KERNEL_TRACE_US = {"dense4b-64x512+1024": 31.96}
+ATTN_KERNEL_TRACE_US = {"dense4b-64x512+1024": 31.88}
 
 
 def attn_kv_bytes_per_launch(shape, gen_lens, prompt_len, group, steps, whole_tiles, shared_elsewhere=False):

@@ -7,7 +7,8 @@ namespace {
 // One generation step over the N rows of the batch, launched kernel by kernel.  (A captured graph per step, which this was, leaves the GPU
 // idle for some 8 us between two replays, and for the capture, 5 us a launch, wherever the rows or the snapshot change; the host
 // enqueues a step in a quarter to a half of the time that the GPU takes for it.  Tiny fp32 model 2.30 -> 2.10 ms, one row of four 4B layers 18.97 ->
-// 18.50, 32B shape at 64 rows 28.0 -> 27.9.)
+// 18.50, 32B shape at 64 rows 28.0 -> 27.9; level where another thread installs snapshots meanwhile: 8B, 128 rows, seven installs in 2047 steps, 14.9 - 15.0 k
+// tokens/s replayed, 15.0 - 15.1 k so.)
 int launch_step(echo_ctx *c, const Slot &S, int N, int max_new, float temperature, uint64_t seed, bool unfused, const int32_t *forced, int eos,
                 float top_p, int per_row) {
   forward_layers(c, S, N, !c->attn_plain, true);
