@@ -84,8 +84,6 @@ void fast_dequant_q8(void *out_bf16, const void *codes, const void *scales, int6
                      (const float *)scales, n, K);
 }
 
-__device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
-
 // ---- weight-streaming GEMM with the activations staged through LDS -----------------------------------------
 // Measured on MI355X: a compute unit sustains about 48 GB/s of vector-memory reads whether they come from HBM
 // (weights) or from L2 (activations), so activation re-reads cost as much as weight bytes.  Here the WN wavefronts
@@ -96,6 +94,19 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x));
 // order, so waiting for them (to copy them into LDS) leaves every younger weight load in flight.
 // grid (ceil(Np/32 / WN), nsplit); 32*MB batch rows, up to 128; block 64*WN; chunks_per_split chunks of KC k-steps per grid split.
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+
+// The SwiGLU products of a 32 x 32 accumulator tile whose weight rows alternate gate_f, up_f: 16 features, of which a lane gets the eight of K8
+// group `half` of its batch row.  (It holds features 4g + 2 half + {0, 1}: the two lanes of a row exchange what the other's group needs.)
+// With the matrix cores idle this is time on top of the main loop, 2121 vector instructions per wavefront of a 256 x 256 ring tile while it was
+// expf, a division and shuffles through LDS, 1060 now.  4096 rows, gate/up of the 4B / 8B / 32B shapes: 345 / 651 / 1699 -> 332 / 634 / 1663 us (1.18 /
+// 1.27 / 1.26 -> 1.23 / 1.30 / 1.29 PFLOP/s), 1024 rows of the 4B shape 120.4 -> 114.2.
+__device__ __forceinline__ u32x4v swiglu_unit(const f32x16 &acc) {
+  uint32_t pk[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) pk[g] = f32_to_h16_pair(swiglu(acc[4 * g], acc[4 * g + 1]), swiglu(acc[4 * g + 2], acc[4 * g + 3]));
+  const auto x0 = __builtin_amdgcn_permlane32_swap(pk[0], pk[2], false, false), x1 = __builtin_amdgcn_permlane32_swap(pk[1], pk[3], false, false);
+  return u32x4v{x0[0], x0[1], x1[0], x1[1]};
+}
 
 constexpr int GEMM_KC = 8;   // k-steps per chunk
 template <int MB, int WN> struct GemmLds {
@@ -374,23 +385,8 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
     }
   } else {  // EPI_SWIGLU: weight rows alternate gate_f, up_f; a block of 32 rows yields 16 features = two K8 groups
     if (nb_own >= nblocks) return;
-    uint32_t *O = (uint32_t *)out;
 #pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      uint32_t pk[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {   // features 4g + 2*half + {0,1} of the block
-        float v0 = silu_f(acc[j][4 * g] * W_UNSCALE) * (acc[j][4 * g + 1] * W_UNSCALE);
-        float v1 = silu_f(acc[j][4 * g + 2] * W_UNSCALE) * (acc[j][4 * g + 3] * W_UNSCALE);
-        pk[g] = (uint32_t)f32_to_h16_bits(v0) | ((uint32_t)f32_to_h16_bits(v1) << 16);
-      }
-      // lane (half 0) assembles K8 group 0 (features 0..7), its partner (half 1) group 1 (features 8..15)
-      uint32_t give0 = half ? pk[0] : pk[2], give1 = half ? pk[1] : pk[3];
-      uint32_t got0 = __shfl_xor(give0, 32, 64), got1 = __shfl_xor(give1, 32, 64);
-      u32x4v o = half ? u32x4v{got0, pk[2], got1, pk[3]} : u32x4v{pk[0], got0, pk[1], got1};
-      int m = j * 32 + col;
-      *(u32x4v *)(O + (((int64_t)(nb * 2 + half) * Mp + m) * 4)) = o;
-    }
+    for (int j = 0; j < MB; ++j) *((u32x4v *)out + (int64_t)(nb * 2 + half) * Mp + j * 32 + col) = swiglu_unit(acc[j]);
   }
 }
 
@@ -556,26 +552,12 @@ __global__ __launch_bounds__(L::T) void gemm_ring_kernel(void *out, const u32x4v
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
     }
-  } else {  // EPI_SWIGLU, as in the kernels above
-    uint32_t *O = (uint32_t *)out;
+  } else {  // EPI_SWIGLU
 #pragma unroll
     for (int n = 0; n < NBW; ++n) {
       if (nb0 + n >= nblocks) break;
 #pragma unroll
-      for (int j = 0; j < MB; ++j) {
-        uint32_t pk[4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float v0 = silu_f(acc[n][j][4 * g] * W_UNSCALE) * (acc[n][j][4 * g + 1] * W_UNSCALE);
-          float v1 = silu_f(acc[n][j][4 * g + 2] * W_UNSCALE) * (acc[n][j][4 * g + 3] * W_UNSCALE);
-          pk[g] = (uint32_t)f32_to_h16_bits(v0) | ((uint32_t)f32_to_h16_bits(v1) << 16);
-        }
-        uint32_t give0 = half ? pk[0] : pk[2], give1 = half ? pk[1] : pk[3];
-        uint32_t got0 = __shfl_xor(give0, 32, 64), got1 = __shfl_xor(give1, 32, 64);
-        u32x4v o = half ? u32x4v{got0, pk[2], got1, pk[3]} : u32x4v{pk[0], got0, pk[1], got1};
-        int m = mrow0 + wrow + j * 32 + col;
-        *(u32x4v *)(O + (((int64_t)((nb0 + n) * 2 + half) * Mp + m) * 4)) = o;
-      }
+      for (int j = 0; j < MB; ++j) *((u32x4v *)out + (int64_t)((nb0 + n) * 2 + half) * Mp + mrow0 + wrow + j * 32 + col) = swiglu_unit(acc[n][j]);
     }
   }
 }
