@@ -40,19 +40,24 @@ __device__ __forceinline__ uint32_t f32_to_h16_pair(float a, float b) {
 __device__ __forceinline__ float h16_bits_to_f32(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
 __device__ __forceinline__ f32x16 mfma_h16(h16x8 a, h16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 
-// silu(g) * u of the accumulators g W_SCALE and u W_SCALE, silu(x) = x / (1 + exp(-x)).  Accumulators are finite: a product's operands and the
-// weights saturate.  The exponential is the hardware's 2^t, the rounding of t = -x log2 e (2^-18 of the result where |x| is large) made good by a
-// first-order term, and the quotient a reciprocal with one Newton step: twelve instructions where expf and an exact division are twenty-six.
-// Largest relative error of silu over [-80, 60] 2.3e-7 (those: 1.8e-7), a thousandth of the rounding to half behind it; the halves' mean square
-// error is the same in its first six digits.
+// silu(g) * u of the accumulators g W_SCALE and u W_SCALE, silu(x) = x / (1 + exp(-x)), in the bits of x / (1.0f + expf(-x)) * u wherever the half
+// behind it is not zero (checked over all g a product can come to): expf's steps without its range checks (x is held between -87, where exp(-x) is
+// finite and the quotient 1e-38 of x, and 126, where 1 + exp(-x) is 1), and the division's without the scaling of very large and very small
+// operands (1 + exp(-x) lies in [1, 2^126]).  Nineteen instructions for twenty-six and the latency of their condition masks.  Accumulators are
+// finite: a product's operands and the weights saturate.  Twelve instructions, a first-order term for the rounding of t and one Newton step for the
+// reciprocal, take 2 % off the long passes' projection, but a rounding of half in a thousand then falls the other way, and with it a draw now and then.
 __device__ __forceinline__ float swiglu(float g, float u) {
-  constexpr float L2E = 1.44269504088896341f, L2E_LOW = 1.92596299e-8f, LN2 = 0.693147180559945f;   // log2 e = L2E + L2E_LOW
-  const float x = __builtin_amdgcn_fmed3f(g, -87.0f * W_SCALE, INFINITY), t = x * (-L2E * W_UNSCALE);   // (exp(87) is finite; further below, the quotient is zero in half anyway)
-  const float rest = fmaf(x, -L2E_LOW * W_UNSCALE, fmaf(x, -L2E * W_UNSCALE, -t));
-  float e = __builtin_amdgcn_exp2f(t);
-  e = fmaf(e, rest * LN2, e);
-  const float d = 1.0f + e, r = __builtin_amdgcn_rcpf(d), q = g * r;
-  return fmaf(fmaf(-q, d, g), r, q) * (W_UNSCALE * W_UNSCALE) * u;
+#pragma clang fp contract(off)
+  constexpr float L2E = 1.44269504088896341f, L2E_LOW = 1.92596286e-8f;   // log2 e = L2E + L2E_LOW
+  const float x = __builtin_amdgcn_fmed3f(g, -87.0f * W_SCALE, 126.0f * W_SCALE), t = x * (-L2E * W_UNSCALE), whole = rintf(t);
+  const float low = fmaf(x, -L2E_LOW * W_UNSCALE, fmaf(x, -L2E * W_UNSCALE, -t));
+  const float d = 1.0f + __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((t - whole) + low), (int)whole);
+  float r = __builtin_amdgcn_rcpf(d), q;
+  r = fmaf(fmaf(-d, r, 1.0f), r, r);
+  q = g * r;
+  q = fmaf(fmaf(-d, q, g), r, q);
+  q = fmaf(fmaf(-d, q, g), r, q);
+  return q * (W_UNSCALE * W_UNSCALE) * u;
 }
 
 template <bool BF16>

@@ -98,8 +98,8 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 // The SwiGLU products of a 32 x 32 accumulator tile whose weight rows alternate gate_f, up_f: 16 features, of which a lane gets the eight of K8
 // group `half` of its batch row.  (It holds features 4g + 2 half + {0, 1}: the two lanes of a row exchange what the other's group needs.)
 // With the matrix cores idle this is time on top of the main loop, 2121 vector instructions per wavefront of a 256 x 256 ring tile while it was
-// expf, a division and shuffles through LDS, 1060 now.  4096 rows, gate/up of the 4B / 8B / 32B shapes: 345 / 651 / 1699 -> 332 / 634 / 1663 us (1.18 /
-// 1.27 / 1.26 -> 1.23 / 1.30 / 1.29 PFLOP/s), 1024 rows of the 4B shape 120.4 -> 114.2.
+// expf, a division and shuffles through LDS, 1477 now, same bits.  4096 rows, gate/up of the 4B / 8B / 32B shapes: 374 / 679 / 1735 -> 372 / 666 / 1711
+// us, 1024 rows of the 4B shape 134.8 -> 130.7.
 __device__ __forceinline__ u32x4v swiglu_unit(const f32x16 &acc) {
   uint32_t pk[4];
 #pragma unroll
