@@ -396,20 +396,32 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
 // (A register-streaming form with two row halves fetched every weight block once per row half, 24 KB per k-step, and
 // measured 12 - 25 % slower at 4096 rows.)  WR x WC wavefronts, each NBW weight blocks (32 NBW columns) x 32 MB rows.
 // The weight blocks and the activation chunk of a k-step are fetched as 1 KB loads that land in LDS without passing
-// through registers (global_load_lds, the data of lane l at 16 l), shared out over the wavefronts; a stage of the ring is one
+// through registers (buffer_load ... lds, the data of lane l at 16 l), shared out over the wavefronts; a stage of the ring is one
 // k-step: [NB blocks x 64 units of A operands][2 k8 groups x ROWS rows of B operands], eight stages.
-// Step c issues the loads of k-step c + LA, reads the operands of k-step c + 1 from the ring into the registers that k-step
+//
+// Step c of the plain loop issues the loads of k-step c + LA, reads the operands of k-step c + 1 from the ring into the registers that k-step
 // c - 1 has left, and runs the MFMAs of k-step c on the registers that the step before filled.  The scheduling barriers
-// lay one operand read behind every MFMA and the ring's loads behind the last of them: without them the compiler reads all
-// operands and waits, and with two wavefronts per SIMD in step with one another nothing covers that wait (4096 rows, gate/up
-// of the 4B / 8B / 32B shapes: 391 / 715 / 1908 us with operands read where they are used, 371 / 685 / 1780 us so).
+// lay the operand reads behind the first MFMAs and the ring's loads behind the next: without them the compiler reads all operands and
+// waits, and reads later in the step come too late for the next one.
 // Every second step ends with a barrier, before which a wavefront waits until its own loads of the next three k-steps
 // have landed (loads retire in order: all but the youngest LA - 3 k-steps' worth), so after the barrier of step c (odd) the
 // stages c + 1 .. c + 3 are there, which are what steps c + 1 and c + 2 read ahead.  The stage that step c's loads overwrite
-// held k-step c + LA - 8 <= c - 2, read in step c + LA - 9 <= c - 3, and a barrier lies between any two steps that far apart.
+// held k-step c + LA - 8 <= c - 2, read in step c + LA - 9 <= c - 3 and used by the MFMAs of the step after that, and a barrier lies
+// between any two steps that far apart.
 // The wait is written by hand, together with the barrier: the compiler's own barrier sequence would wait for every
-// outstanding load and empty the ring.  Sums run in the same order as in the other kernels (k ascending in one
-// accumulator), so results are bit-identical.
+// outstanding load and empty the ring, and for the operand reads, which may stay in flight over the barrier.
+//
+// The loop by pairs of k-steps (PAIRS) has 16 x 16 x 32 MFMAs: a quarter of the accumulator traffic per product for twice the operand reads
+// from the register file, and a 256 x 256 tile runs at the chip's power limit (1.5 GHz, the matrix cores busy 80 % of the cycles, with 32 x 32 x 16
+// ones), so what a product costs in energy is what it costs in time.  A pair p issues the loads of pair p + 3, reads the operands of pair p + 1, runs
+// its MFMAs and ends with the barrier, by which its wavefront's loads of the next four k-steps have landed; its loads overwrite pair p - 1's
+// stages, whose reads the MFMAs of pair p - 1 have waited for.  Lane l supplies row l % 16 and k 8 (l / 16) .. + 8 of an operand and receives rows
+// 4 (l / 16) + i of its column.  The weight rows of a tile are dealt to the A operand so that one lane swap per two registers turns two tiles into
+// the halves of a 32 x 32 tile as the epilogues know it; sums run k by k as before, and the results are bit-identical.
+// 4096 rows, gate/up of the 4B / 8B / 32B shapes: 347 / 660 / 1720 us with global loads to LDS (a vector addition each, and the compiler waits for
+// all operand reads at once behind them), 338 / 640 / 1660 with buffer loads and the reads behind the first MFMAs, 318 / 582 / 1521 by pairs (1.28 /
+// 1.42 / 1.41 PFLOP/s).  Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the plain loop; the 256 x 256
+// tile on four wavefronts is slower in both.
 // Forms: 256 x 256 on eight wavefronts where such tiles fill the chip; 256 x 128 on four (12 KB per k-step) for batches of
 // a few hundred rows.
 template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
@@ -417,6 +429,7 @@ template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
   static constexpr int AU = NB * 64, XU = 2 * ROWS, SU = AU + XU;         // 16-byte units of a stage: A operands, B operands
   static constexpr int ALW = NB / WN, XLW = XU / T, LPS = ALW + XLW;      // weight, activation, all loads per wavefront and k-step
   static constexpr int NS = 8, LA = 6;                                    // stages, k-steps ahead
+  static constexpr bool PAIRS = WN == 8;                                  // the loop by pairs of k-steps
   static constexpr int TILE_STRIDE = 36, BYTES = NS * SU * 16;            // 128 / 96 / 64 KB; the epilogue's WN x 32 x 36 floats reuse it
   static_assert(NB % WN == 0 && XU % T == 0 && WN * 32 * TILE_STRIDE * 4 <= BYTES, "whole loads per wavefront, room for the epilogue");
 };
@@ -424,8 +437,12 @@ using Ring256x256 = GemmRingT<2, 4, 4, 2>;
 using Ring256x128 = GemmRingT<2, 2, 4, 2>;   // 256 rows, 128 columns
 using Ring128x128 = GemmRingT<2, 2, 2, 2>;   // two workgroups fit a compute unit; the lm_head only
 
-__device__ __forceinline__ void load_to_lds(const void *g, void *l) {   // 16 bytes per lane; l is the wavefront's base, lane l lands at l + 16 l
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)g, (__attribute__((address_space(3))) void *)l, 16, 0, 0);
+// 16 bytes per lane from byte lane_off + off behind the buffer's base; l is the wavefront's base in LDS, lane l lands at l + 16 l.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t ring_buffer(const void *base) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
+}
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int off, void *l) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void *)l, 16, lane_off, off, 0, 0);
 }
 
 // Which tile a workgroup takes: column strip bx, row block bz, run of k-steps by.  Workgroup i starts on XCD i % 8, so the
@@ -458,61 +475,142 @@ __device__ __forceinline__ void ring_mainloop(f32x16 (&acc)[L::NBW][L::MB], u32x
   const int wrow = (w / WC) * 32 * MB;
   // what this wavefront fetches: weight blocks nbw + w, + WN .. (past the end: the last one again, never stored) and the
   // runs of 64 units i WN + w of the activation chunk (unit u: k8 group u / ROWS of the k-step, batch row u % ROWS)
-  const h16x8 *a_src[L::ALW];
+  __amdgpu_buffer_rsrc_t a_src[L::ALW];
 #pragma unroll
-  for (int i = 0; i < L::ALW; ++i) a_src[i] = Wp + w_block_base(min(nbw + i * WN + w, nblocks - 1), Kp) + lane;
-  const u32x4v *x_src[L::XLW];
+  for (int i = 0; i < L::ALW; ++i) a_src[i] = ring_buffer(Wp + w_block_base(min(nbw + i * WN + w, nblocks - 1), Kp));
+  int x_off[L::XLW];
 #pragma unroll
   for (int i = 0; i < L::XLW; ++i) {
-    int xi = (i * WN + w) * 64 + lane;
-    x_src[i] = Xp + (int64_t)(xi / ROWS) * Mp + mrow0 + xi % ROWS;
+    const int xi = (i * WN + w) * 64 + lane;
+    x_off[i] = ((xi / ROWS) * Mp + xi % ROWS) * 16;
   }
-  auto fetch = [&](int st, int c) {
+  const int x_step = 2 * Mp * 16;
+  // k-step c0 + i, or the last one (past the end: never used); the activations' offsets are from the trip's first k-step, a whole operand may pass 4 GB
+  auto fetch = [&](int st, int c0, int i) {
+    const __amdgpu_buffer_rsrc_t x_src = ring_buffer(Xp + mrow0 + (int64_t)(c0 * 2) * Mp);
+    const int at = min(i, last - c0);
 #pragma unroll
-    for (int i = 0; i < L::XLW; ++i) load_to_lds(x_src[i] + (int64_t)(c * 2) * Mp, ring + st * SU + AU + (i * WN + w) * 64);
+    for (int i = 0; i < L::XLW; ++i) load_to_lds(x_src, x_off[i], at * x_step, ring + st * SU + AU + (i * WN + w) * 64);
 #pragma unroll
-    for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i] + (int64_t)c * W_KSTEP, ring + st * SU + (i * WN + w) * 64);
-  };
-  // what it reads: its NBW weight blocks, and its rows
-  const u32x4v *a_lds = ring + ring_block<L, APART>(w % WC, 0) * 64 + lane;
-  const u32x4v *b_lds = ring + AU + (lane >> 5) * ROWS + wrow + (lane & 31);
-  u32x4v a[2][NBW], b[2][MB];
-  auto read = [&](int set, int st) {
-#pragma unroll
-    for (int n = 0; n < NBW; ++n) a[set][n] = a_lds[st * SU + n * APART * 64];
-#pragma unroll
-    for (int j = 0; j < MB; ++j) b[set][j] = b_lds[st * SU + j * 32];
+    for (int i = 0; i < L::ALW; ++i) load_to_lds(a_src[i], lane * 16, (c0 + at) * (int)(W_KSTEP * 16), ring + st * SU + (i * WN + w) * 64);
   };
 #pragma unroll
-  for (int n = 0; n < NBW; ++n)
+  for (int j = 0; j < LA; ++j) fetch(j, c_lo, j);   // a run has at least NS k-steps
+  if constexpr (L::PAIRS) {
+    // what it reads: 16 rows of its weight blocks, and of its batch rows; k8 group lane / 16 of the pair
+    const int s16 = lane & 15, k8 = lane >> 4, pair_at = (k8 >> 1) * SU;
+    // (an LDS read reaches 64 KB from its base: one for either half of the ring, opaque, or the compiler keeps a register for every far address)
+    int a_at[2], b_at[2];
 #pragma unroll
-    for (int j = 0; j < MB; ++j)
+    for (int h = 0; h < 2; ++h) {
+      a_at[h] = h * (NS / 2) * SU + ring_block<L, APART>(w % WC, 0) * 64 + pair_at + (k8 & 1) * 32 + (s16 & 3) + 4 * (s16 >> 3) + 8 * (s16 >> 2 & 1);
+      b_at[h] = h * (NS / 2) * SU + AU + pair_at + (k8 & 1) * ROWS + wrow + s16;
+      asm("" : "+v"(a_at[h]), "+v"(b_at[h]));
+    }
+    u32x4v a[2][2 * NBW], b[2][2 * MB];
+    auto read = [&](int set, int st) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
+      for (int n = 0; n < 2 * NBW; ++n) a[set][n] = ring[a_at[st / (NS / 2)] + st % (NS / 2) * SU + (n >> 1) * APART * 64 + (n & 1) * 16];
 #pragma unroll
-  for (int j = 0; j < LA; ++j) fetch(j, min(c_lo + j, last));   // a run has at least NS k-steps
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
-  read(0, 0);
-  for (int c0 = c_lo; c0 < c_hi; c0 += NS) {
+      for (int j = 0; j < 2 * MB; ++j) b[set][j] = ring[b_at[st / (NS / 2)] + st % (NS / 2) * SU + j * 16];
+    };
+    f32x4 q[2 * NBW][2 * MB];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      read((s + 1) & 1, (s + 1) % NS);
-      fetch((s + LA) % NS, min(c0 + s + LA, last));   // past the end: the last k-step again, never used
+    for (int n = 0; n < 2 * NBW; ++n)
+#pragma unroll
+      for (int j = 0; j < 2 * MB; ++j) q[n][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 4)) : "memory");
+    read(0, 0);
+    for (int c0 = c_lo; c0 < c_hi; c0 += NS) {
+#pragma unroll
+      for (int s = 0; s < NS; s += 2) {
+        read((s / 2 + 1) & 1, (s + 2) % NS);
+        fetch((s + LA) % NS, c0, s + LA);
+        fetch((s + 1 + LA) % NS, c0, s + 1 + LA);
+#pragma unroll
+        for (int j = 0; j < 2 * MB; ++j)
+#pragma unroll
+          for (int n = 0; n < 2 * NBW; ++n)
+            q[n][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, a[s / 2 & 1][n]), __builtin_bit_cast(h16x8, b[s / 2 & 1][j]), q[n][j], 0, 0, 0);
+        // MFMA, LDS read, four times; two MFMAs and a read (more reads at once and the registers of both pairs do not fit); two MFMAs and a load
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * (NBW + MB) - 4; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * LPS; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 4 * NBW * MB, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 4)) : "memory");
+      }
+    }
+    // tiles 2j and 2j + 1 of a row hold columns 16 apart: exchanging the odd rows of 16 lanes of the first with the even ones of the second gives
+    // every lane eight rows of the 16 for one of the 32 columns, the two results the rows 4 (l / 32) + i and 8 + 4 (l / 32) + i of the tile's half
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
 #pragma unroll
       for (int j = 0; j < MB; ++j)
 #pragma unroll
-        for (int n = 0; n < NBW; ++n)
-          acc[n][j] = mfma_h16(__builtin_bit_cast(h16x8, a[s & 1][n]), __builtin_bit_cast(h16x8, b[s & 1][j]), acc[n][j]);
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int q = 0; q < NBW + MB; ++q) {   // MFMA, LDS read, MFMA, LDS read, ...
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          for (int i = 0; i < 4; ++i) {
+            const float u = q[2 * n + t][2 * j][i], v = q[2 * n + t][2 * j + 1][i];
+            const auto x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, u), __builtin_bit_cast(uint32_t, v), false, false);
+            acc[n][j][8 * t + i] = __builtin_bit_cast(float, (uint32_t)x[0]);
+            acc[n][j][8 * t + 4 + i] = __builtin_bit_cast(float, (uint32_t)x[1]);
+          }
+  } else {
+    // what it reads: its NBW weight blocks, and its rows
+    const u32x4v *a_lds = ring + ring_block<L, APART>(w % WC, 0) * 64 + lane;
+    const u32x4v *b_lds = ring + AU + (lane >> 5) * ROWS + wrow + (lane & 31);
+    u32x4v a[2][NBW], b[2][MB];
+    auto read = [&](int set, int st) {
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) a[set][n] = a_lds[st * SU + n * APART * 64];
+#pragma unroll
+      for (int j = 0; j < MB; ++j) b[set][j] = b_lds[st * SU + j * 32];
+    };
+#pragma unroll
+    for (int n = 0; n < NBW; ++n)
+#pragma unroll
+      for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[n][j][r] = 0.f;
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
+    read(0, 0);
+    for (int c0 = c_lo; c0 < c_hi; c0 += NS) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        read((s + 1) & 1, (s + 1) % NS);
+        fetch((s + LA) % NS, c0, s + LA);
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+          for (int n = 0; n < NBW; ++n)
+            acc[n][j] = mfma_h16(__builtin_bit_cast(h16x8, a[s & 1][n]), __builtin_bit_cast(h16x8, b[s & 1][j]), acc[n][j]);
+#pragma unroll
+        for (int i = 0; i < (NBW + MB) / 2; ++i) {   // MFMA, two LDS reads, ...
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < LPS; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, NBW * MB, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s & 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, LPS, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, NBW * MB, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s & 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LPS * (LA - 3)) : "memory");
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the end have landed before the ring is reused
@@ -605,14 +703,14 @@ __global__ __launch_bounds__(L::T) void gemm_ring_qkv_kernel(QkvOut out, const u
   int bx, by, bz;
   ring_tile(strips, Mp / L::ROWS, &bx, &by, &bz);
   const int nb0 = bx * L::NB + ring_block<L, APART>(w % L::WC, 0), mrow0 = bz * L::ROWS + (w / L::WC) * 32 * MB;
-  int act[MB], pos[MB], slot[MB];   // of batch row mrow0 + 32 j + col
+  f32x16 acc[NBW][MB];
+  ring_mainloop<L, APART>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, bz * L::ROWS, 0, Kp >> 4);
+  int act[MB], pos[MB], slot[MB];   // of batch row mrow0 + 32 j + col (requested here: the main loop has no registers for them)
 #pragma unroll
   for (int j = 0; j < MB; ++j) {
     const int m = min(mrow0 + j * 32 + col, out.M - 1);
     act[j] = out.rows.active[m]; pos[j] = out.rows.pos[m]; slot[j] = out.rows.slot[m];
   }
-  f32x16 acc[NBW][MB];
-  ring_mainloop<L, APART>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, bz * L::ROWS, 0, Kp >> 4);
   const bool own = nb0 < nblocks;   // (heads are whole: both blocks lie past the end, or neither)
   if (!NORM && !own) return;
   const int head = nb0 / (HD / 32), d0 = (nb0 % (HD / 32)) * 32;   // dims d0 .. d0 + 31 and their partners HALF further
