@@ -519,6 +519,8 @@ int run_chunk_seqs(echo_ctx *c, const Slot &S, const std::vector<ChunkSeq> &seqs
                       blocks.back().pos0 + blocks.back().nrows == pos[i];
         if (extend) ++blocks.back().nrows; else blocks.push_back({i, 1, slot[i], pos[i]});
       }
+      // (the kernel takes them from the end: those with the most keys first, whichever sequence they belong to)
+      std::stable_sort(blocks.begin(), blocks.end(), [](const PrefillBlock &a, const PrefillBlock &b) { return a.pos0 + a.nrows < b.pos0 + b.nrows; });
       HIPCHK(c, hipMemcpyAsync(at<PrefillBlock>(c, c->p.o_blocks), blocks.data(), blocks.size() * sizeof(PrefillBlock),
                                hipMemcpyHostToDevice, c->cs));
     }
