@@ -418,10 +418,10 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
 // stages, whose reads the MFMAs of pair p - 1 have waited for.  Lane l supplies row l % 16 and k 8 (l / 16) .. + 8 of an operand and receives rows
 // 4 (l / 16) + i of its column.  The weight rows of a tile are dealt to the A operand so that one lane swap per two registers turns two tiles into
 // the halves of a 32 x 32 tile as the epilogues know it; sums run k by k as before, and the results are bit-identical.
-// 4096 rows, gate/up of the 4B / 8B / 32B shapes: 347 / 660 / 1720 us with global loads to LDS (a vector addition each, and the compiler waits for
-// all operand reads at once behind them), 338 / 640 / 1660 with buffer loads and the reads behind the first MFMAs, 318 / 582 / 1521 by pairs (1.28 /
-// 1.42 / 1.41 PFLOP/s).  Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the plain loop; the 256 x 256
-// tile on four wavefronts is slower in both.
+// 4096 rows, gate/up of the 4B / 8B / 32B shapes: 347 / 669 / 1736 us with global loads to LDS (a vector addition each, and the compiler waits for
+// all operand reads at once behind them), 336 / 646 / 1675 with buffer loads and the reads behind the first MFMAs; on another box 344 / 654 / 1691 so,
+// 329 / 605 / 1575 by pairs (1.24 / 1.36 / 1.36 PFLOP/s).  Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the
+// plain loop; a 256 x 256 tile on four wavefronts is level in the plain loop and slower by pairs.
 // Forms: 256 x 256 on eight wavefronts where such tiles fill the chip; 256 x 128 on four (12 KB per k-step) for batches of
 // a few hundred rows.
 template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
@@ -681,7 +681,7 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
 // consecutive positions; the ends of a run, and rows in any other order -- a decode step's, each of another sequence -- are stored one by one).
 // What it saves is the fp32 plane of the projection, written and read once: same products, same order, so q and the cache are
 // bit-identical to qkv_post_wide_kernel's.  4096 rows, both kernels before against this one: 4B width 132 + 43 -> 138 us, 8B 208 + 46 ->
-// 215, 32B 383 + 64 -> 404; whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
+// 215, 32B 383 + 64 -> 404 (129 / 190 / 358 with the loop by pairs); whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
 // Rollouts of 1000 rows, two layers, 31 steps: 4B width 27.7 -> 27.3 ms, 8B 39.4 -> 38.9.
 struct QkvOut {
   uint16_t *q;              // half [M][Hq][hd]
@@ -1200,9 +1200,9 @@ __global__ __launch_bounds__(WN * 64, lm_wgs_per_cu<MB>()) void lmhead_kernel(co
 // ---- lm_head on the tiles of the LDS ring (128 rows and more) ----------------------------------------------------------------
 // A wavefront holds 64 vocabulary entries of 32 MB batch rows; lanes l and l^32 hold the same rows.  One partial per (row, strip
 // of 32 NB entries): max z, sum exp, best score, its z, its index (sample_part_store); scoring (SCORE) writes the first two and target_z.
-// Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.75 ms at hidden 2560 (1.16
-// PFLOP/s), 5.17 ms at 5120 (1.23), where the register-streaming tile it replaced (24 KB per k-step, accumulators parked in
-// LDS for the epilogue) took 3.91 and 6.83.  Sampling takes 128 x 128 tiles: its epilogue keeps the vector unit busy for as long
+// Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.40 ms at hidden 2560 (1.33
+// PFLOP/s), 4.54 ms at 5120 (1.40; 2.63 and 5.10 before the loop by pairs), where the register-streaming tile it replaced (24 KB per k-step,
+// accumulators parked in LDS for the epilogue) took 3.91 and 6.83.  Sampling takes 128 x 128 tiles: its epilogue keeps the vector unit busy for as long
 // as the main loop keeps the loads and the matrix cores, and two workgroups per compute unit let one's epilogue run under the
 // other's main loop: 256 rows 275 us (256 x 256 tiles, one workgroup per unit: 344; 256 x 128: 336; the register-streaming tile
 // with the full evaluation of every entry: 517), 128 rows 181 us (280).
