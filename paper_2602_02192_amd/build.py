@@ -12,6 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libecho_hip.so")
 CLIENT = os.path.join(HERE, "echo_client")   # the C-ABI client without Python (csrc/echo_client.cpp)
+TESTS = os.path.join(HERE, "..", "tests")
+SWEEP = os.path.join(TESTS, "_build", "swiglu_sweep")   # the program of tests/test_gpu_swiglu_bits.py
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -32,16 +34,20 @@ def _stale(obj, src):
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def _hipcc(args):
+    r = subprocess.run(["hipcc", *FLAGS, *args], capture_output=True, text=True)
+    err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc failed on {' '.join(args)}:\n{err}")
+    if err.strip():
+        print(err, file=sys.stderr)
+
+
 def _compile(name, force):
     src = os.path.join(CSRC, name)
     obj = os.path.join(OBJ, name[:-4] + ".o")
     if force or _stale(obj, src):
-        r = subprocess.run(["hipcc", *FLAGS, "-c", src, "-o", obj], capture_output=True, text=True)
-        err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
-        if r.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {name}:\n{err}")
-        if err.strip():
-            print(err, file=sys.stderr)
+        _hipcc(["-c", src, "-o", obj])
     return obj
 
 
@@ -52,6 +58,9 @@ def build(force: bool = True) -> str:
     subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     subprocess.check_call(["hipcc", "-O2", "-std=c++17", "-fopenmp", "-Wno-unused-result", os.path.join(CSRC, "echo_client.cpp"), "-o", CLIENT,
                            "-L" + HERE, "-lecho_hip", "-Wl,-rpath,$ORIGIN"])
+    if os.path.isdir(TESTS):
+        os.makedirs(os.path.dirname(SWEEP), exist_ok=True)
+        _hipcc([os.path.join(TESTS, "swiglu_sweep.hip"), "-o", SWEEP])
     return LIB
 
 

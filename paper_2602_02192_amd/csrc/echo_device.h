@@ -41,14 +41,17 @@ __device__ __forceinline__ float h16_bits_to_f32(uint16_t b) { return (float)__b
 __device__ __forceinline__ f32x16 mfma_h16(h16x8 a, h16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 
 // silu(g) * u of the accumulators g W_SCALE and u W_SCALE, silu(x) = x / (1 + exp(-x)), in the bits of x / (1.0f + expf(-x)) * u wherever the half
-// behind it is not zero (checked over all g a product can come to): expf's steps without its range checks (x is held between -87, where exp(-x) is
-// finite and the quotient 1e-38 of x, and 126, where 1 + exp(-x) is 1), and the division's without the scaling of very large and very small
+// behind it is not zero (tests/test_gpu_swiglu_bits.py sweeps every g that a product can come to; bits of the compiler and device library that this is built
+// with).  The steps are theirs without what the range makes idle.  exp(-x): the device library's expf (ROCm-Device-Libs, ocml, open source), a two-part log2 e
+// multiplied out with fmas, 2^fraction by v_exp_f32, ldexp; without range checks (x is held between -87, where exp(-x) is finite and the
+// quotient 1e-38 of x, and 126, where 1 + exp(-x) is 1).  The quotient: LLVM's AMDGPU expansion of the fp32 division, a Newton step on v_rcp_f32 and two
+// corrections of the quotient by its residual (Markstein, IBM J. Res. Dev. 34, 1990); without the scaling of very large and very small
 // operands (1 + exp(-x) lies in [1, 2^126]).  Nineteen instructions for twenty-six and the latency of their condition masks.  Accumulators are
 // finite: a product's operands and the weights saturate.  Twelve instructions, a first-order term for the rounding of t and one Newton step for the
 // reciprocal, take 2 % off the long passes' projection, but a rounding of half in a thousand then falls the other way, and with it a draw now and then.
 __device__ __forceinline__ float swiglu(float g, float u) {
 #pragma clang fp contract(off)
-  constexpr float L2E = 1.44269504088896341f, L2E_LOW = 1.92596286e-8f;   // log2 e = L2E + L2E_LOW
+  constexpr float L2E = 1.44269504088896341f, L2E_LOW = 1.92596286e-8f;   // log2 e = L2E + L2E_LOW + 1.4e-15 (expf's; the nearest float is one ulp up)
   const float x = __builtin_amdgcn_fmed3f(g, -87.0f * W_SCALE, 126.0f * W_SCALE), t = x * (-L2E * W_UNSCALE), whole = rintf(t);
   const float low = fmaf(x, -L2E_LOW * W_UNSCALE, fmaf(x, -L2E * W_UNSCALE, -t));
   const float d = 1.0f + __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((t - whole) + low), (int)whole);
