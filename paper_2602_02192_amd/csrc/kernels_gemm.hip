@@ -411,19 +411,21 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
 // The wait is written by hand, together with the barrier: the compiler's own barrier sequence would wait for every
 // outstanding load and empty the ring, and for the operand reads, which may stay in flight over the barrier.
 //
-// The loop by pairs of k-steps (PAIRS) has 16 x 16 x 32 MFMAs: a quarter of the accumulator traffic per product for twice the operand reads
-// from the register file, and a 256 x 256 tile runs at the chip's power limit (1.5 GHz, the matrix cores busy 80 % of the cycles, with 32 x 32 x 16
+// The loop by pairs of k-steps (PAIRS) has 16 x 16 x 32 MFMAs: half of the accumulator traffic per product for twice the operand reads
+// from the register file (256 accumulators and 1024 operand halves for 8192 products, 1024 and 1024 for 16384 with 32 x 32 x 16 ones), and a
+// 256 x 256 tile runs at the chip's power limit (1.5 GHz, the matrix cores busy 80 % of the cycles, with 32 x 32 x 16
 // ones), so what a product costs in energy is what it costs in time.  A pair p issues the loads of pair p + 3, reads the operands of pair p + 1, runs
 // its MFMAs and ends with the barrier, by which its wavefront's loads of the next four k-steps have landed; its loads overwrite pair p - 1's
 // stages, whose reads the MFMAs of pair p - 1 have waited for.  Lane l supplies row l % 16 and k 8 (l / 16) .. + 8 of an operand and receives rows
 // 4 (l / 16) + i of its column.  The weight rows of a tile are dealt to the A operand so that one lane swap per two registers turns two tiles into
-// the halves of a 32 x 32 tile as the epilogues know it; sums run k by k as before, and the results are bit-identical.
-// 4096 rows, gate/up of the 4B / 8B / 32B shapes: 347 / 669 / 1736 us with global loads to LDS (a vector addition each, and the compiler waits for
-// all operand reads at once behind them), 336 / 646 / 1675 with buffer loads and the reads behind the first MFMAs; on another box 344 / 654 / 1691 so,
-// 329 / 605 / 1575 by pairs (1.24 / 1.36 / 1.36 PFLOP/s).  Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the
-// plain loop; a 256 x 256 tile on four wavefronts is level in the plain loop and slower by pairs.
-// Forms: 256 x 256 on eight wavefronts where such tiles fill the chip; 256 x 128 on four (12 KB per k-step) for batches of
-// a few hundred rows.
+// the halves of a 32 x 32 tile as the epilogues know it.  That one MFMA over 32 k sums in the bits of two over 16 is what the chip was seen to do, not
+// something that its documents promise: tests/test_gpu_ring_forms.py holds the two loops against each other.
+// 4096 rows, gate/up of the 4B / 8B / 32B shapes, launches back to back: 347 / 669 / 1736 us with global loads to LDS (a vector addition each, and the
+// compiler waits for all operand reads at once behind them), 336 / 646 / 1675 with buffer loads and the reads behind the first MFMAs; on another box
+// 344 / 654 / 1691 so, 329 / 605 / 1575 by pairs (1.24 / 1.36 / 1.36 PFLOP/s; inside scoring and prompt passes 320 - 327 / 596 - 633 / 1529 - 1570).
+// Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the plain loop; a 256 x 256 tile on four wavefronts is level in
+// the plain loop and slower by pairs.
+// Forms: 256 x 256 on eight wavefronts from 128 tiles on; 256 x 128 on four (12 KB per k-step) for batches of a few hundred rows (see fast_gemm_pick).
 template <int WRv, int WCv, int MBv, int NBWv> struct GemmRingT {
   static constexpr int WR = WRv, WC = WCv, WN = WR * WC, MB = MBv, NBW = NBWv, NB = WC * NBW, ROWS = 32 * WR * MB, T = WN * 64;
   static constexpr int AU = NB * 64, XU = 2 * ROWS, SU = AU + XU;         // 16-byte units of a stage: A operands, B operands
@@ -681,7 +683,7 @@ static void gemm_ring_launch(void *out, const void *Xp, const void *Wp, int Mp, 
 // consecutive positions; the ends of a run, and rows in any other order -- a decode step's, each of another sequence -- are stored one by one).
 // What it saves is the fp32 plane of the projection, written and read once: same products, same order, so q and the cache are
 // bit-identical to qkv_post_wide_kernel's.  4096 rows, both kernels before against this one: 4B width 132 + 43 -> 138 us, 8B 208 + 46 ->
-// 215, 32B 383 + 64 -> 404 (129 / 190 / 358 with the loop by pairs); whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
+// 215, 32B 383 + 64 -> 404 (126 - 131 / 189 - 199 / 353 - 358 with the loop by pairs); whole scoring passes of 900 to 4096 rows 1 to 5 % faster at the three widths, none slower.
 // Rollouts of 1000 rows, two layers, 31 steps: 4B width 27.7 -> 27.3 ms, 8B 39.4 -> 38.9.
 struct QkvOut {
   uint16_t *q;              // half [M][Hq][hd]
@@ -705,7 +707,9 @@ __global__ __launch_bounds__(L::T) void gemm_ring_qkv_kernel(QkvOut out, const u
   const int nb0 = bx * L::NB + ring_block<L, APART>(w % L::WC, 0), mrow0 = bz * L::ROWS + (w / L::WC) * 32 * MB;
   f32x16 acc[NBW][MB];
   ring_mainloop<L, APART>(acc, (u32x4v *)lds_raw, Xp, Wp, Mp, Kp, nblocks, bx * L::NB, bz * L::ROWS, 0, Kp >> 4);
-  int act[MB], pos[MB], slot[MB];   // of batch row mrow0 + 32 j + col (requested here: the main loop has no registers for them)
+  // of batch row mrow0 + 32 j + col; requested here: held through the loop by pairs they spill 8 to 12 registers (4096 rows of the 4B / 8B / 32B shapes, kernel
+  // medians 134 / 200 / 362 us, 131 / 199 / 358 so)
+  int act[MB], pos[MB], slot[MB];
 #pragma unroll
   for (int j = 0; j < MB; ++j) {
     const int m = min(mrow0 + j * 32 + col, out.M - 1);
@@ -875,17 +879,21 @@ int fast_gemm_even_split(int Kp, int nsplit) {
 // grid split over K that brings the launch to about one workgroup per compute unit (partials cost HBM writes, so
 // no more than that); a GEMM whose epilogue needs the whole K (SwiGLU) is not split and takes the workgroup width
 // (three to eight blocks) that needs the fewest rounds of the chip.  Batches that are a multiple of 256 rows take the
-// LDS-ring kernel (256 x 256 tiles when those fill the chip, 256 x 128 tiles with a split over K otherwise).  K is padded to
+// LDS-ring kernel (256 x 256 tiles from 128 of them on, 256 x 128 tiles with a split over K otherwise).  K is padded to
 // GEMM_K_PAD and the rows to 32, 64, 128 or a multiple of 256, so there are no other shapes.
 void fast_gemm_pick(int Np, int Kp, int Mp, int full_k, GemmShape *g) {
   const int nblocks = Np / 32, ksteps = Kp / 16;
-  if (Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {   // 256 x 256 tiles fill the chip
+  // 256 x 256 tiles against 256 x 128 at 512, 1024 and 4096 rows, no split, us: 112 tiles (224 of the smaller) 54 - 57 / 38 - 42 at K 2560, 80 - 89 / 57 - 63 at
+  // K 4096, 183 - 196 / 128 - 136 at K 9728; 144 tiles (288: a second round) 57 - 60 / 64 - 79, 86 - 92 / 99 - 120, 188 - 197 / 240 - 252.  At 128 tiles exactly
+  // the smaller ones are one round still and would be the better: 56 - 59 / 42 - 46, 83 - 92 / 63 - 70, 190 - 200 / 142 - 150.
+  if (Mp % 256 == 0 && (nblocks + 7) / 8 * (Mp / 256) >= 128) {
     g->form = GEMM_RING_256X256; g->waves_n = 0; g->nsplit = 1;
     // One tile per compute unit at a time, so a tile count just above a multiple of 256 leaves most of the chip idle in
     // the last round (320 tiles take two rounds).  Splitting K in two runs makes the units of work half as long and the
     // rounds fill up (320 tiles: 1.5 rounds' worth), at the price of a second plane of fp32 partials written and read
-    // again -- which pays once K is long (measured at 4096 rows: N 5120, K 8192: 411 -> 340 us, K 25600: 1228 -> 1011 us,
-    // for about 34 us of extra plane traffic; at K 4096 the plane costs more than the split saves).
+    // again -- which pays once K is long.  4096 rows, the product with the norm that reads its planes, whole / in two runs, us: 320 tiles (N 5120) K 4096
+    // 245 / 254, 5120 286 / 287, 6144 327 / 321, 8192 408 / 385 (344 / 297 the product alone), 25600 1100 / 950 (1036 / 875); 288 tiles K 4096 235 / 234,
+    // 6144 317 / 303, 8192 397 / 367; 384 tiles K 4096 264 / 288, 6144 351 / 354, 8192 435 / 427.
     if (!full_k && Kp >= 6144) {
       const int tiles = (nblocks + 7) / 8 * (Mp / 256);
       if ((2 * tiles + 255) / 256 * 0.5 <= 0.8 * ((tiles + 255) / 256)) g->nsplit = 2;
@@ -1200,12 +1208,13 @@ __global__ __launch_bounds__(WN * 64, lm_wgs_per_cu<MB>()) void lmhead_kernel(co
 // ---- lm_head on the tiles of the LDS ring (128 rows and more) ----------------------------------------------------------------
 // A wavefront holds 64 vocabulary entries of 32 MB batch rows; lanes l and l^32 hold the same rows.  One partial per (row, strip
 // of 32 NB entries): max z, sum exp, best score, its z, its index (sample_part_store); scoring (SCORE) writes the first two and target_z.
-// Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.40 ms at hidden 2560 (1.33
-// PFLOP/s), 4.54 ms at 5120 (1.40; 2.63 and 5.10 before the loop by pairs), where the register-streaming tile it replaced (24 KB per k-step,
+// Scoring passes take 256 x 256 tiles, bound by the matrix cores: 4096 rows, vocabulary 151936: 2.32 - 2.47 ms at hidden 2560 (1.29 - 1.37
+// PFLOP/s), 4.41 - 4.60 ms at 5120 (1.39 - 1.44; 2.63 and 5.10 before the loop by pairs), where the register-streaming tile it replaced (24 KB per k-step,
 // accumulators parked in LDS for the epilogue) took 3.91 and 6.83.  Sampling takes 128 x 128 tiles: its epilogue keeps the vector unit busy for as long
 // as the main loop keeps the loads and the matrix cores, and two workgroups per compute unit let one's epilogue run under the
-// other's main loop: 256 rows 275 us (256 x 256 tiles, one workgroup per unit: 344; 256 x 128: 336; the register-streaming tile
-// with the full evaluation of every entry: 517), 128 rows 181 us (280).
+// other's main loop: hidden 2560, 256 rows 267 us (256 x 256 tiles, one workgroup per unit: 298, 344 before the loop by pairs; 256 x 128: 338; the
+// register-streaming tile with the full evaluation of every entry: 517), 128 rows 181 us (280).  The longer K, the less the epilogue counts: 128 x 128 against
+// 256 x 256 tiles 408 / 427 us at hidden 4096, 504 / 485 at 5120; at 512 rows 457 / 489, 702 / 677, 873 / 793.
 template <class L, bool SCORE>
 __global__ __launch_bounds__(L::T) void lmhead_ring_kernel(const u32x4v *__restrict__ Xp, const h16x8 *__restrict__ Wp, int Mp, int Np, int Kp, int V,
                                                            float temperature, uint64_t seed, DrawIds ids, const int32_t *__restrict__ target,
@@ -1360,8 +1369,8 @@ void fast_sample_combine(int32_t *tok, float *lp, const float *part, int n_parts
 }
 
 void fast_lmhead_logits(float *logits, const void *Xp, const void *Wp, int Mp, int Np, int Kp, int V, hipStream_t st) {
-  // 256 rows, vocabulary 151936, hidden 2560: 236 us on 256 x 256 ring tiles (128 x 128: 278, the LDS-staged kernel: 296); 128 rows are
-  // level (186 us on 128 x 128 tiles and by workgroups of four blocks; see logits128_wide for those of seven).
+  // 256 rows, vocabulary 151936, hidden 2560 / 4096 / 5120: 235 / 352 / 421 us on 256 x 256 ring tiles (256 x 128: 239 / 363 / 445, 128 x 128: 279 / 428 / 532, the
+  // LDS-staged kernel at 2560: 296).  128 rows: 173 / 259 / 316 us by workgroups of seven blocks (see logits128_wide), 189 / 288 / 345 on 128 x 128 ring tiles.
   if (Mp % 256 == 0) { gemm_ring_launch<Ring256x256, EPI_PARTIAL>(logits, Xp, Wp, Mp, Np, Kp, 1, st); return; }
   lmhead_dispatch<true>(Xp, Wp, Mp, Np, Kp, V, 1.0f, 0, DrawIds{nullptr, nullptr, nullptr}, nullptr, nullptr, nullptr, logits, Np, st);
 }
