@@ -421,7 +421,7 @@ __global__ __launch_bounds__(WN * 64, (gemm_lds_min_wgs<MB, WN, NSTAGE>())) void
 // the halves of a 32 x 32 tile as the epilogues know it.  That one MFMA over 32 k sums in the bits of two over 16 is what the chip was seen to do, not
 // something that its documents promise: tests/test_gpu_ring_forms.py holds the two loops against each other.
 // 4096 rows, gate/up of the 4B / 8B / 32B shapes, launches back to back: 347 / 669 / 1736 us with global loads to LDS (a vector addition each, and the
-// compiler waits for all operand reads at once behind them), 336 / 646 / 1675 with buffer loads and the reads behind the first MFMAs; on another box
+// compiler waits for all operand reads at once behind them), 336 / 646 / 1675 with buffer loads and the reads behind the first MFMAs; on another card
 // 344 / 654 / 1691 so, 329 / 605 / 1575 by pairs (1.24 / 1.36 / 1.36 PFLOP/s; inside scoring and prompt passes 320 - 327 / 596 - 633 / 1529 - 1570).
 // Tiles of four wavefronts, bound by their loads, are 5 to 10 % slower by pairs and keep the plain loop; a 256 x 256 tile on four wavefronts is level in
 // the plain loop and slower by pairs.
