@@ -59,9 +59,13 @@ def build(force: bool = True) -> str:
     subprocess.check_call(["hipcc", "-O2", "-std=c++17", "-fopenmp", "-Wno-unused-result", os.path.join(CSRC, "echo_client.cpp"), "-o", CLIENT,
                            "-L" + HERE, "-lecho_hip", "-Wl,-rpath,$ORIGIN"])
     if os.path.isdir(TESTS):
-        os.makedirs(os.path.dirname(SWEEP), exist_ok=True)
-        _hipcc([os.path.join(TESTS, "swiglu_sweep.hip"), "-o", SWEEP])
+        build_sweep()
     return LIB
+
+
+def build_sweep():
+    os.makedirs(os.path.dirname(SWEEP), exist_ok=True)
+    _hipcc([os.path.join(TESTS, "swiglu_sweep.hip"), "-o", SWEEP])
 
 
 if __name__ == "__main__":

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 def test_every_gate():
     if not os.path.exists(build.SWEEP):
-        build.build(force=False)
+        build.build_sweep()
     r = subprocess.run([build.SWEEP], capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr
     lines = [[float(v) for v in l.split()] for l in r.stdout.splitlines()]
